@@ -69,6 +69,9 @@ def _gram_keep_workspace(ctx, X, Y, lam1, lam2, flags):
     M, L2 = Y.shape[0], Y.shape[1]
     if not sk.keeps_forward(N, L1, L2, d, lam1, lam2, flags, sk._dt(X), gram_M=M):
         return None
+    # (the backward sweep with four pairs per wavefront makes its own forward sweep, and is faster than the kept form)
+    if " pairs_per_wave=4" in sk.sigkernel_describe(sk.SK_OP_GRAM_BWD, N, M, L1, L2, d, lam1, lam2, flags, sk._dt(X)):
+        return None
     need = sk.sigkernel_workspace_bytes(sk.SK_OP_GRAM, N, M, L1, L2, d, lam1, lam2, flags | sk.SK_FLAG_KEEP_FORWARD,
                                         sk._dt(X))
     if need > _KEEP_LIMIT:

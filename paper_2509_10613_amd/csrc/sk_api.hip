@@ -189,7 +189,10 @@ int run(const Layout& lay, bool backward, const void* x, const void* y, void* k,
     a.coop_ring_stride = (unsigned)p.coop_ring_stride;
     a.solo = p.solo;
     a.tile = p.tile;
-    a.quad = p.quad; a.qd_nquads = p.nquads;
+    a.quad = p.quad; a.qd_nquads = p.nquads; a.qd_even = p.qd_even;
+    a.fv_ck = p.fv_ck; a.fv_bands = p.fv_bands;
+    a.fv_gx = p.fv_gx_slot ? reinterpret_cast<double*>(base + p.off_fvgx) : nullptr;
+    a.fv_gx_slot = p.fv_gx_slot;
     a.band = p.band; a.bd_nbands = p.bd_nbands;
     a.bd_off_y = (unsigned)p.bd_off_y; a.bd_off_gy = (unsigned)p.bd_off_gy; a.bd_off_rings = (unsigned)p.bd_off_rings;
     a.bd_flags = reinterpret_cast<int*>(base + p.off_flags);
@@ -274,6 +277,7 @@ int run(const Layout& lay, bool backward, const void* x, const void* y, void* k,
     if (p.band) SK_CHECK(launch_sweep_band(phase ? phase + 1 : (backward ? 1 : 0), p.BL, p.DT, a, p.grid, p.lds_bytes, st));
     else if (p.lock) SK_CHECK(launch_sweep_lockstep(backward, p.BL, p.DT, a, p.grid, p.lds_bytes, st));
     else if (p.quad) SK_CHECK(launch_sweep_quad(p.BL, p.DT, a, p.grid, p.lds_bytes, st));
+    else if (p.four) SK_CHECK(launch_sweep_four(p.BL, p.DT, a, p.grid, p.lds_bytes, st));
     else if (p.tile) SK_CHECK(launch_sweep_tile(backward, p.DT, a, p.grid, p.lds_bytes, st));
     else if (p.solo) SK_CHECK(launch_sweep_solo(backward, p.BL, p.DT, a, p.grid, p.lds_bytes, st));
     else SK_CHECK(launch_sweep(backward, p.BL, p.DT, a, p.grid, p.lds_bytes, st));
@@ -735,6 +739,11 @@ int sigkernel_describe(int op, int64_t B_or_N, int64_t M, int64_t L1, int64_t L2
         if (backward) std::snprintf(kern, sizeof(kern), "tile_bwd_kernel<%d, %s>", p.DT / 4, p.nb + 1 < sk::kTileCols - 1 ? "true" : "false");
         else std::snprintf(kern, sizeof(kern), "tile_fwd_kernel<%d>", p.DT / 4);
         threads = sk::kWavesPerWG * sk::kWave;
+    } else if (p.four) {
+        mode = "solo";
+        std::snprintf(kern, sizeof(kern), "solo_bwd_kernel<%d, %d, %d, 0, 0, %d>", p.BL, p.DT, p.lk_M,
+                      sk::four_occupancy(p.BL, p.DT));
+        threads = sk::kWave;
     } else if (p.solo) {
         mode = "solo";
         if (backward || phase)
@@ -759,11 +768,12 @@ int sigkernel_describe(int op, int64_t B_or_N, int64_t M, int64_t L1, int64_t L2
     std::snprintf(out, out_bytes,
                   "mode=%s kernel=%s grid=%d threads=%d lds_bytes=%zu strips=%d rows_per_lane=%d fused=%d "
                   "kept_sweep_half=%d lead_lag_form=%s second_launch_lds_bytes=%zu workspace_bytes=%zu "
-                  "drifted_pairs_counter_at=%zu",
+                  "drifted_pairs_counter_at=%zu pairs_per_wave=%d",
                   mode, kern, p.grid, threads, p.lds_bytes, (p.lock || p.solo || p.tile || p.quad || p.band) ? p.lk_ns : p.ns,
                   (p.lock || p.solo || p.tile || p.quad || p.band) ? p.lk_M : 1,
                   fused ? 1 : 0, phase, lay.ll ? "checkerboard" : "none",
-                  (lay.has_sc && backward && phase != 1) ? lay.sc.lds_bytes : (size_t)0, lay.total, p.off_badlist != 0 ? p.off_badcnt : (size_t)0);
+                  (lay.has_sc && backward && phase != 1) ? lay.sc.lds_bytes : (size_t)0, lay.total, p.off_badlist != 0 ? p.off_badcnt : (size_t)0,
+                  (p.four || p.quad) ? sk::kQuadPairs : 1);
     return SK_OK;
 }
 

@@ -92,7 +92,12 @@ struct SweepArgs {
     int tile;            // 1: tile kernels (one wave per pair, increment Gram matrix in LDS, contractions by MFMA; uses
                          // lk_NT, lk_padb, lk_off_krows / lk_off_dump as offsets inside a wave's LDS)
     int quad;            // 1: quad kernel (forward Gram calls: four pairs per wave; uses lk_M, lk_padb)
+    long qd_even;        // four pairs per wave: quads handed out in equal shares; the rest by the counter bd_flags[0]
     long qd_nquads;      // groups of four pairs of one Gram row in the launch's sequence
+    int fv_bands;        // solo kernel with four pairs per wave: bands of 16 lanes per pair,
+    int fv_ck;           // macro-steps between checkpoints (nseg: places per band),
+    real* fv_gx;         // per slot the x-side sums of the bands of the pairs in work (several bands only)
+    long fv_gx_slot;
     // lock-step mode on a batch of pairs of double paths: the kernels read the caller's points and write the
     // caller's gradients themselves (no preparation and finalisation launches, no global accumulators)
     int fused;
@@ -149,6 +154,8 @@ hipError_t launch_second_chance_reset(real* g1, long n1, real* g2, long n2, cons
 hipError_t launch_sweep_solo(bool backward, int BL, int DT, const SweepArgs& a, int grid, size_t lds, hipStream_t st);
 // the one-wave builds of the solo backward kernels (sk_solo_one.hip), called by launch_sweep_solo
 hipError_t launch_sweep_solo_one(bool backward, int BL, int DT, const SweepArgs& a, int grid, size_t lds, hipStream_t st);
+// solo mode with four pairs per wave (backward Gram calls), defined in sk_four.hip
+hipError_t launch_sweep_four(int BL, int DT, const SweepArgs& a, int grid, size_t lds, hipStream_t st);
 // tile mode (a.tile != 0), defined in sk_tile.hip
 hipError_t launch_sweep_tile(bool backward, int DT, const SweepArgs& a, int grid, size_t lds, hipStream_t st);
 // quad mode (a.quad != 0; forward only), defined in sk_quad.hip

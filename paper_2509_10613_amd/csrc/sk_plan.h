@@ -73,6 +73,12 @@ struct Plan {
     int tile = 0;   // one wave per pair, at most 64 x 64 cells, contractions on the matrix cores (sk_tile.hip)
     int quad = 0;   // four pairs per wave, forward Gram calls on the tile kernels' shapes (sk_quad.hip)
     int64_t nquads = 0;   // groups of four pairs of one Gram row the quad launch works through
+    int64_t qd_even = 0;  // quads of a four-pair launch that are handed out in equal shares (the rest by a counter)
+    int four = 0;         // solo mode with four pairs per wave (backward Gram calls, sk_four.hip)
+    int fv_bands = 0;     // bands of 16 lanes per pair
+    int fv_ck = 0;        // macro-steps between its checkpoints
+    int64_t fv_gx_slot = 0;
+    size_t off_fvgx = 0;  // x-side sums of the strips of the pairs in work (several strips only)
     int solo = 0;   // one wave per pair, a single strip of 64 * lk_M block rows (many pairs of short paths)
     int lock = 0, lk_M = 0, lk_ns = 0, lk_NT = 0, lk_padb = 0, lk_rowlen = 0;
     size_t lk_off_y = 0, lk_off_gy = 0, lk_off_cring = 0, lk_off_gp = 0, lk_off_krows = 0, lk_off_arows = 0,
@@ -136,6 +142,30 @@ constexpr int quad_max_rows(int BL, int DT)
 // Row stride of the y copy in LDS (doubles): for an even channel count a multiple of 16 bytes that spreads the
 // 16-byte reads of lanes at consecutive rows over the banks; an odd count does that by itself.
 constexpr int quad_y_stride(int DT) { return DT % 2 ? DT : (DT == 6 ? 10 : DT + 2); }
+// Four-pair mode (backward Gram calls, sk_four.hip): block rows per lane, doubles per lane of a checkpoint, doubles
+// between the groups' rings of finished y-side sums, wavefronts per SIMD the kernel is built for (0: no such kernel).
+constexpr int four_rows(int BL, int DT) { return (BL == 2 || DT >= 8) ? 2 : 4; }
+constexpr int four_ckpt_values(int BL, int DT) { return (four_rows(BL, DT) << BL) + 1 + (1 << BL); }
+constexpr int four_gring_stride(int DT) { return 16 * DT + 2; }
+constexpr int four_occupancy(int BL, int DT)
+{
+    return DT < 2 || DT > 16 ? 0 : (DT >= 16 || (BL == 2 && DT >= 12)) ? 1 : 2;
+}
+// Channel count of the four-pair kernel for d channels (16 is far from most counts above 8).
+constexpr int four_channels(int DT, int d) { return DT == 16 && d <= 12 ? 12 : DT; }
+// Quads of a four-pair launch that are handed out in equal shares: all of them unless every wavefront has work for about
+// 0.5 ms (`instr`: vector instructions per quad, at ten clocks each), and then half.
+inline int64_t four_even_share(int64_t nquads, int64_t nwaves, int64_t instr)
+{
+    return nquads < 3 * nwaves || nquads / nwaves * instr < 100000 ? nquads : nquads / 2 / nwaves * nwaves;
+}
+constexpr int kFourCkpt = 32;                 // macro-steps between checkpoints
+// Quads of pairs from which the four-pair kernel is taken.  A wavefront needs three to four times as long for its quad as
+// the one-pair kernels for a pair, so it takes about a wavefront per SIMD to pay: steps of Gram n x n with n = 48 / 64 / 128
+// (576, 1024, 4096 quads), one-pair and four-pair: L = 128, order 1, d = 3: 317 / 415 / 1700 against 376 / 433 / 1316 us;
+// L = 60, order 1, d = 12: 498 / 755 against 319 / 404 us (sixteen channels in the one-pair kernel, twelve here); L = 220,
+// d = 4 (wave-per-pair kernels): 1248 / 1538 against 973 / 1139 us.
+constexpr int64_t four_min_quads(bool solo, int DT) { return solo && DT <= 6 ? 1100 : 512; }
 constexpr int kTileRowPad = 8;     // backward: node columns kept left of column 0 in the pair's bottom row (all 1)
 constexpr int kTileCkChunks = 8;   // backward: chunks of 8 macro-steps between two checkpoints (kept in LDS)
 
@@ -411,6 +441,35 @@ inline Plan make_plan(bool backward, bool gram, bool symmetric, int64_t nx, int6
         p.nseg = NT / kLockS;
     }
 
+    // Four-pair mode: backward calls for Gram matrices with enough quads of pairs to fill the chip.
+    bool four = false;
+    if (backward && gram && p.uncompute && !keep && !second_chance && !lead_lag && !p.tile && p.DT >= 2 &&
+        ny * ((nx + kQuadPairs - 1) / kQuadPairs) >= four_min_quads(p.solo != 0, p.DT)) {
+        const int DT = four_channels(p.DT, p.d), band = kWave / kQuadPairs * four_rows(p.BL, DT);
+        const int bands = (p.mb + band - 1) / band;
+        size_t used = 0;
+        auto lds_take = [&](size_t bytes) { size_t o = used; used = align_up(used + bytes, 256); return o; };
+        const size_t o_y = lds_take((size_t)(p.q + 1) * quad_y_stride(DT) * elem);
+        const size_t o_gyp = lds_take((size_t)p.q * DT * elem);
+        const size_t o_gring = lds_take((size_t)kQuadPairs * four_gring_stride(DT) * elem);
+        const size_t o_ring = lds_take((size_t)(bands > 1 ? 3 : 1) * kWave * C * elem);
+        if (four_occupancy(p.BL, DT) > 0 && used <= kLdsPerCU / 4) {
+            four = true;
+            p.lock = 0; p.coop = 0; p.solo = 1; p.four = 1;
+            p.DT = DT;
+            p.lk_M = bands > 1 ? 2 : 1;
+            p.fv_bands = bands; p.lk_padb = bands * band - p.mb;
+            p.lk_ns = (p.mb + kWave * p.lk_M - 1) / (kWave * p.lk_M);
+            p.lk_NT = p.nb + kWave / kQuadPairs - 1;
+            p.lk_off_y = o_y; p.lk_off_gyp = o_gyp; p.lk_off_gp = o_gring; p.lk_off_krows = o_ring;
+            p.y_lds = 1;
+            p.lds_wave = used;
+            p.lds_bytes = used;                  // one wavefront per workgroup
+            p.fv_ck = kFourCkpt;
+            p.nseg = (p.lk_NT - 1) / p.fv_ck + 1;   // checkpoint places per band
+        }
+    }
+
     // Symmetric Gram matrix: k(x, y) = k(y, x) bit for bit, so the solo and tile kernels solve the pairs n <= m
     // only, write both entries of K, and use the sum of the two upstream gradients.  Eq. (1) is symmetric under
     // a swap of the paths together with their dyadic orders, so this holds for equal orders only; with unequal
@@ -421,6 +480,24 @@ inline Plan make_plan(bool backward, bool gram, bool symmetric, int64_t nx, int6
         const int64_t want = (p.npairs + kWavesPerWG - 1) / kWavesPerWG;
         if (want < p.grid) p.grid = (int)want;
         p.nslots = (int64_t)p.grid * kWavesPerWG;
+    }
+    // The sequence of quads: rows of the Gram matrix in groups of four x paths (symmetric: the pairs n <= m of row m).
+    if (p.tri) {
+        const int64_t J = nx / kQuadPairs, e = nx % kQuadPairs;
+        p.nquads = 2 * J * (J + 1) + e * (J + 1);
+    } else if (gram) {
+        p.nquads = ny * ((nx + kQuadPairs - 1) / kQuadPairs);
+    }
+    if (four) {
+        int waves = (int)(kLdsPerCU / p.lds_bytes);                      // per compute unit
+        const int regs = 4 * four_occupancy(p.BL, p.DT);
+        if (waves > regs) waves = regs;
+        const int64_t cap = (int64_t)kNumCU * waves;
+        p.grid = (int)(p.nquads < cap ? p.nquads : cap);
+        p.nslots = p.grid;
+        p.qd_even = four_even_share(p.nquads, p.nslots, (int64_t)p.fv_bands * p.lk_NT * four_rows(p.BL, p.DT) *
+                                                            (C * C * 11 + 15 + 5 * p.DT));
+        p.nflags = 1;   // the launch's counter
     }
 
     // Quad mode: forward calls for Gram matrices (the four pairs of a wavefront share the y path) on the shapes of the
@@ -433,12 +510,6 @@ inline Plan make_plan(bool backward, bool gram, bool symmetric, int64_t nx, int6
         const size_t ycopy = align_up((size_t)(p.nb + 1) * quad_y_stride(p.DT) * elem, 256);   // the y copy and a row of zeros
         if (M <= quad_max_rows(p.BL, p.DT) && p.mb <= M * lanes && ycopy * kWavesPerWG <= kLdsPerCU) {
             p.tile = 0; p.solo = 0; p.quad = 1;
-            if (p.tri) {
-                const int64_t J = nx / kQuadPairs, e = nx % kQuadPairs;
-                p.nquads = 2 * J * (J + 1) + e * (J + 1);
-            } else {
-                p.nquads = ny * ((nx + kQuadPairs - 1) / kQuadPairs);
-            }
             p.lk_M = M; p.lk_ns = 1; p.lk_NT = p.nb + lanes - 1; p.lk_padb = M * lanes - p.mb;
             p.y_lds = 1;
             p.lds_wave = ycopy;
@@ -491,7 +562,7 @@ inline Plan make_plan(bool backward, bool gram, bool symmetric, int64_t nx, int6
         p.off_dxT = take((size_t)nx * p.xstride * elem);
         p.off_dyT = symmetric ? p.off_dxT : take((size_t)ny * p.ystride * elem);
     }
-    p.rows_slot = (int64_t)p.ns * p.rowlen;
+    p.rows_slot = p.four ? (int64_t)p.fv_bands * kQuadPairs * p.rowlen : (int64_t)p.ns * p.rowlen;
     p.off_rows = take((size_t)p.nslots * p.rows_slot * elem);
     if (backward) {
         if (!second_chance) {
@@ -504,6 +575,11 @@ inline Plan make_plan(bool backward, bool gram, bool symmetric, int64_t nx, int6
         const bool lean = p.lock || p.solo || p.tile || p.band;
         const int NVC = lean ? p.lk_M * R + C + 2 : R + C + 2;
         p.ckpt_slot = p.tile ? 0 : (int64_t)(lean ? p.lk_ns : p.ns) * (p.nseg + 1) * NVC * kWave;
+        if (p.four) {
+            p.ckpt_slot = (int64_t)p.fv_bands * p.nseg * four_ckpt_values(p.BL, p.DT) * kWave;
+            p.fv_gx_slot = p.fv_bands > 1 ? (int64_t)p.fv_bands * four_rows(p.BL, p.DT) * p.DT * kWave : 0;
+            p.off_fvgx = take((size_t)p.nslots * p.fv_gx_slot * elem);
+        }
         p.keep_solo = (keep && p.solo) ? 1 : 0;
         p.off_ckpt = take((size_t)(p.keep_solo ? p.npairs : p.nslots) * p.ckpt_slot * elem);
         if (p.keep_solo) {

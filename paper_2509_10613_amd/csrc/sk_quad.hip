@@ -26,51 +26,9 @@
 #include "sk_dev.h"
 #include "sk_kernels.h"
 #include "sk_lane.h"
+#include "sk_quad.h"
 
 namespace sk {
-
-// lane i of a row of 16 lanes receives v of lane i - 1; the row's first lane receives edge (its own lane's value)
-__device__ __forceinline__ real row_from_above_or(real v, real edge)
-{
-    int lo = __double2loint(v), hi = __double2hiint(v);
-    int elo = __double2loint(edge), ehi = __double2hiint(edge);
-    lo = __builtin_amdgcn_update_dpp(elo, lo, 0x111, 0xf, 0xf, false);
-    hi = __builtin_amdgcn_update_dpp(ehi, hi, 0x111, 0xf, 0xf, false);
-    return __hiloint2double(hi, lo);
-}
-
-// Quad q of the sequence a launch works through: row yi of the Gram matrix in groups of four x paths, rows in
-// ascending order.  A row has N pairs, or, for a symmetric Gram matrix K(X, X), the yi + 1 pairs n <= yi.
-struct QuadCursor {
-    long yi, xi0, npr;
-    __device__ __forceinline__ void locate(const SweepArgs& a, long u)
-    {
-        if (!a.tri) {
-            const long per_row = (a.gramN + kQuadPairs - 1) / kQuadPairs;
-            yi = u / per_row;
-            xi0 = (u - yi * per_row) * kQuadPairs;
-            npr = a.gramN;
-        } else {
-            // rows 4 j .. 4 j + 3 hold j + 1 quads each: 2 j (j + 1) quads lie before row 4 j
-            long j = (long)((sqrt(2.0 * (double)u + 1.0) - 1.0) * 0.5);
-            while (2 * (j + 1) * (j + 2) <= u) ++j;
-            while (2 * j * (j + 1) > u) --j;
-            const long rest = u - 2 * j * (j + 1);
-            yi = 4 * j + rest / (j + 1);
-            xi0 = (rest % (j + 1)) * kQuadPairs;
-            npr = yi + 1;
-        }
-    }
-    __device__ __forceinline__ void next(const SweepArgs& a)
-    {
-        xi0 += kQuadPairs;
-        if (xi0 >= npr) {
-            xi0 = 0;
-            ++yi;
-            if (a.tri) npr = yi + 1;
-        }
-    }
-};
 
 template <int BL, int D, int M>
 __global__ __launch_bounds__(kWavesPerWG* kWave, 2) void quad_fwd_kernel(SweepArgs a)

@@ -1,0 +1,77 @@
+"""The backward sweep of Gram matrices with four path pairs per wavefront (sk_four.hip) against the oracle: one and
+several strips, rows above the grid, rows of the Gram matrix that are no multiple of four, refinement inside and above the
+blocks, the time channel, float arrays, K(X, X), and pairs that drift and are taken out of their quad."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2509_10613_amd import binding as sk
+from paper_2509_10613_amd import workloads
+from tests.test_gpu_parity import check_grads, check_rows, check_values, dev, host, rounded
+
+pytestmark = pytest.mark.gpu
+
+
+def paths(seed, n, L, d, var):
+    rng = np.random.default_rng(seed)
+    return np.cumsum(rng.normal(0.0, var ** 0.5, (n, L, d)), axis=1)
+
+
+@pytest.mark.parametrize("nx,ny,L1,L2,d,lam1,lam2,flags,sym,dtype", [
+    (70, 66, 65, 64, 3, 0, 0, 0, False, torch.float64),      # one strip, every lane's rows inside the grid
+    (65, 72, 66, 12, 2, 0, 0, 1, False, torch.float64),      # 65 block rows: two rows per lane more than needed
+    (70, 68, 129, 5, 3, 0, 0, 1, False, torch.float32),      # the largest single strip of eight rows per lane
+    (67, 66, 130, 40, 3, 1, 1, 0, False, torch.float64),     # two strips
+    (65, 66, 70, 30, 8, 1, 1, 1, False, torch.float64),      # two strips of four rows per lane
+    (130, 35, 20, 40, 5, 2, 2, 1, False, torch.float64),     # blocks of 4 x 4 cells
+    (90, 54, 9, 10, 4, 3, 3, 0, False, torch.float64),       # refinement above the blocks
+    (80, 61, 24, 20, 6, 0, 2, 1, False, torch.float64),      # unequal orders
+    (93, 0, 33, 33, 3, 1, 1, 1, True, torch.float64),        # K(X, X): rows of the triangle
+    (91, 0, 70, 70, 4, 0, 0, 0, True, torch.float32),
+    (70, 0, 18, 18, 2, 0, 1, 0, True, torch.float64),        # K(X, X) with unequal orders: every pair
+    (90, 50, 35, 30, 12, 0, 0, 1, False, torch.float64),      # twelve channels, two bands
+    (70, 40, 20, 34, 14, 2, 2, 0, False, torch.float64),      # sixteen channels, blocks of 4 x 4 cells
+    (4600, 1, 6, 200, 2, 0, 0, 0, False, torch.float64),     # fewer rows than lanes, one y path
+])
+def test_four_pairs_per_wave(nx, ny, L1, L2, d, lam1, lam2, flags, sym, dtype):
+    X = paths(1300 + nx + d, nx, L1, d, 1.0 / (d * L1))
+    Y = X if sym else paths(1400 + ny, ny, L2, d, 1.0 / (d * L2))
+    ny = nx if sym else ny
+    sdt = sk.SK_F64 if dtype == torch.float64 else sk.SK_F32
+    desc = sk.sigkernel_describe(sk.SK_OP_GRAM_BWD, nx, ny, L1, Y.shape[1], d, lam1, lam2, flags, sdt)
+    assert "pairs_per_wave=4" in desc, desc
+    W = workloads.upstream_weights(88, (nx, ny))
+    x = dev(X, dtype)
+    K, gX, gY = sk.sigkernel_gram(x, x if sym else dev(Y, dtype), dev(W, dtype), lam1, lam2, flags)
+    torch.cuda.synchronize()
+    Xr = rounded(X, dtype)
+    Kr, gXr, gYr = oracle.gram(Xr, Xr if sym else rounded(Y, dtype), rounded(W, dtype), lam1, lam2, flags)
+    check_values(host(K), Kr, dtype, "K")
+    check_grads(host(gX), gXr, dtype, "grad_X")
+    if not sym:
+        check_grads(host(gY), gYr, dtype, "grad_Y")
+
+
+@pytest.mark.parametrize("L1,L2,d,lam", [(40, 40, 3, 1), (150, 30, 4, 0)])
+def test_four_pairs_per_wave_with_pairs_that_drift(L1, L2, d, lam):
+    # one path of either side with increments of order one: its pairs leave their quads, the others stay
+    nx, ny = 72, 66
+    X, Y = paths(1500, nx, L1, d, 1.0 / (d * L1)), paths(1501, ny, L2, d, 1.0 / (d * L2))
+    rng = np.random.default_rng(1502)
+    X[7, 1:] = np.cumsum(rng.choice([-1.0, 1.0], size=(L1 - 1, d)) * (1.6 / d ** 0.5), axis=0)
+    Y[3, 1:] = np.cumsum(rng.choice([-1.0, 1.0], size=(L2 - 1, d)) * (1.6 / d ** 0.5), axis=0)
+    W = workloads.upstream_weights(89, (nx, ny))
+    need = sk.sigkernel_workspace_bytes(sk.SK_OP_GRAM_BWD, nx, ny, L1, L2, d, lam, lam, 0, sk.SK_F64)
+    ws = torch.empty(need, dtype=torch.uint8, device="cuda")
+    desc = sk.sigkernel_describe(sk.SK_OP_GRAM_BWD, nx, ny, L1, L2, d, lam, lam, 0, sk.SK_F64)
+    assert "pairs_per_wave=4" in desc, desc
+    K, gX, gY = sk.sigkernel_gram(dev(X), dev(Y), dev(W), lam, lam, 0, ws=ws)
+    torch.cuda.synchronize()
+    at = int(desc.split("drifted_pairs_counter_at=", 1)[1].split()[0])
+    n = int(ws[at:at + 4].view(torch.int32)[0])
+    assert 0 < n <= nx + ny - 1
+    Kr, gXr, gYr = oracle.gram(X, Y, W, lam, lam, 0)
+    check_values(host(K), Kr, torch.float64, "K")
+    check_rows(host(gX), gXr, torch.float64, "grad_X")
+    check_rows(host(gY), gYr, torch.float64, "grad_Y")
