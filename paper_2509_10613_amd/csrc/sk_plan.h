@@ -129,15 +129,18 @@ constexpr bool solo_bwd_shares_simd(int BL, int M, int DT, size_t lds)
 // kTileStride (even, not a multiple of 4: row-contiguous, skewed and transposed accesses all stay at most
 // two-way bank conflicted), kTileCols columns (-1 .. 64: a zero guard column on either side).
 constexpr int kTileStride = 66, kTileCols = 66;
-// Quad mode: a wavefront works on four pairs that share the y path, 16 lanes with four or eight block rows each.
+// Quad mode: a wavefront works on four pairs that share the y path, 16 lanes with four to eight block rows each.
 constexpr int kQuadPairs = 4;
 // Block rows per lane the quad kernel is built for (0: none): blocks of at most 2 x 2 cells, and the increments of a
-// lane's rows in at most 128 registers.
+// lane's rows in at most 128 registers (eight channels: Gram 500 x 123, 99 x 76 cells, 702 us in the solo kernel, 378
+// with seven rows per lane; Gram 256 x 256, 127 rows, order 1, where the kernel keeps 104 bytes per lane in scratch, 1461
+// against 998 us).
+constexpr int kQuadMinRows = 4;
 constexpr int quad_max_rows(int BL, int DT)
 {
     if (BL > 1 || DT == 0) return 0;
     if (DT == 16) return BL == 0 ? 4 : 0;
-    return DT == 8 ? 4 : 8;
+    return 8;
 }
 // Row stride of the y copy in LDS (doubles): for an even channel count a multiple of 16 bytes that spreads the
 // 16-byte reads of lanes at consecutive rows over the banks; an odd count does that by itself.
@@ -506,7 +509,11 @@ inline Plan make_plan(bool backward, bool gram, bool symmetric, int64_t nx, int6
     // only.  Two workgroups of four waves per compute unit.
     if ((p.tile || p.solo) && !backward && gram && !lead_lag && p.rs1 == 0 && p.rs2 == 0) {
         const int lanes = kWave / kQuadPairs;
-        const int M = p.mb <= 4 * lanes ? 4 : 8;
+        // As few rows per lane as hold the pair: a row above the grid costs what any other does.  Gram 256 x 256, 94 block
+        // rows, d = 6, order 1, eight rows and six: 676 and 506 us; d = 2, 79 block rows, order 0, eight and five: 311
+        // and 213 us.  (Kernels of fewer than four rows are not built.)
+        int M = (p.mb + lanes - 1) / lanes;
+        if (M < kQuadMinRows) M = kQuadMinRows;
         const size_t ycopy = align_up((size_t)(p.nb + 1) * quad_y_stride(p.DT) * elem, 256);   // the y copy and a row of zeros
         if (M <= quad_max_rows(p.BL, p.DT) && p.mb <= M * lanes && ycopy * kWavesPerWG <= kLdsPerCU) {
             p.tile = 0; p.solo = 0; p.quad = 1;

@@ -3,7 +3,7 @@
 //
 // A wavefront that gives one lane to every block row of one pair walks 64 lanes over the pair's columns: the skew of
 // the anti-diagonal sweep (Section 3.3) leaves 63 of its macro-steps per lane outside the grid, half of them all for
-// 63 columns.  Here a pair has 16 lanes, each with M = 4 or 8 consecutive block rows, and the wavefront's four groups
+// 63 columns.  Here a pair has 16 lanes, each with M = 4 to 8 consecutive block rows, and the wavefront's four groups
 // of 16 lanes work on four pairs at once, in lock-step, so that a sweep takes nb + 15 macro-steps of M blocks per lane
 // instead of nb + 63 of one or two:
 //
@@ -226,7 +226,10 @@ template <int BL, int D>
 static hipError_t launch_quad_fwd_m(const SweepArgs& a, int grid, size_t lds, hipStream_t st)
 {
     if (a.lk_M == 4) return launch_quad_fwd_t<BL, D, 4>(a, grid, lds, st);
-    if constexpr (quad_max_rows(BL, D) >= 8) {
+    if constexpr (quad_max_rows(BL, D) == 8) {
+        if (a.lk_M == 5) return launch_quad_fwd_t<BL, D, 5>(a, grid, lds, st);
+        if (a.lk_M == 6) return launch_quad_fwd_t<BL, D, 6>(a, grid, lds, st);
+        if (a.lk_M == 7) return launch_quad_fwd_t<BL, D, 7>(a, grid, lds, st);
         if (a.lk_M == 8) return launch_quad_fwd_t<BL, D, 8>(a, grid, lds, st);
     }
     return hipErrorInvalidValue;
