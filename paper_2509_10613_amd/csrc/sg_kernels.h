@@ -39,6 +39,8 @@ struct BwdArgs {
 
 hipError_t launch_horner(int DT, int M, int S, const Args& a, long grid, hipStream_t st);
 hipError_t launch_horner_bwd(int DT, int M, int S, const BwdArgs& a, long grid, size_t lds_bytes, hipStream_t st);
+// a.Q = N - 2, a.WP and a.NW in wavefronts of this kernel; a.NB, a.LP, a.PW, a.lds_wave and a.leadlag are not read
+hipError_t launch_horner_bwd_matrix(const BwdArgs& a, int S, long grid, hipStream_t st);
 
 template <typename TO>
 hipError_t launch_point_gradients(const double* gz, TO* gx, long B, long L, int d, int Dpad, int P, long Lc, long np,

@@ -53,6 +53,40 @@ constexpr Variant kVariants[] = {SG_VARIANTS(SG_ROW)};
 constexpr Variant kBwdVariants[] = {SG_BWD_VARIANTS(SG_ROW)};
 #undef SG_ROW
 
+// Backward with the top level's sum over words on the matrix cores (sg_horner_bwd_matrix.hip): lanes of one or two words of
+// N - 1 letters, the last letter over 4, 8 or 16 lanes, sixteen segments at a time.
+constexpr int kMatrixMinD = 5, kMatrixMaxQ = 3, kMatrixSteps = 16, kMatrixFlush = 4;
+constexpr int matrix_lanes(int D, int S)                           // per prefix, S last letters each
+{
+    int l = kMatrixFlush;
+    while (l * S < D) l *= 2;
+    return l;
+}
+constexpr int matrix_lds_doubles(int S) { return kMatrixSteps * 16 + kMatrixFlush * kWave + S * kMatrixSteps * kWave; }   // per wave
+inline int64_t matrix_waves(int64_t D, int Q, int S)               // per path
+{
+    int64_t prefixes = 1;
+    for (int i = 0; i < Q; ++i) prefixes *= D;
+    const int64_t per_wave = kWave / matrix_lanes((int)D, S);
+    return (prefixes + per_wave - 1) / per_wave;
+}
+// Two words per lane once one word each gives more than a wavefront per SIMD: they share the arithmetic of their prefix, but
+// are half as many wavefronts.  signature_bwd, one and two words (B, L, D, N): (128, 512, 8, 4) 200 and 249 us, (128, 512,
+// 16, 3) 191 and 199; (128, 512, 12, 4) 529 and 489, (128, 1024, 16, 4) 1832 and 1476.
+inline int matrix_words(int64_t VB, int64_t D, int Q) { return VB * matrix_waves(D, Q, 1) > kSimds ? 2 : 1; }
+// Where the matrix kernel is taken.  From eleven channels and words of at most three letters on always: (1000, 65, 11, 4)
+// 357 us by the other kernel, 322 by this one, (1000, 65, 14, 4) 848 and 555, (4000, 65, 12, 3) 254 and 176, (8000, 17, 16,
+// 3) 206 and 184.  Below, the matrix instruction's sixteen columns are half empty, and four letters leave most of the time
+// in the chains over the prefix, which the other kernel spreads over more words of a lane: there only while the chip is not
+// full and a segment's latency counts, up to two wavefronts per SIMD: (500, 65, 8, 4) 67 and 60, (128, 256, 7, 4) 203 and
+// 109, (128, 256, 5, 5) 220 and 197; but (2000, 65, 8, 4) 164 and 195, (4000, 65, 5, 3) 99 and 138, (128, 512, 8, 5) 552 and
+// 741.
+inline bool matrix_pays(int64_t VB, int64_t D, int N, int64_t segments)
+{
+    if (D < kMatrixMinD || D > 16 || N < 3 || N - 2 > kMatrixMaxQ || segments < kMatrixSteps) return false;
+    return (D >= 11 && N <= 4) || VB * matrix_waves(D, N - 2, matrix_words(VB, D, N - 2)) <= 2 * kSimds;
+}
+
 inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
 struct Plan {
@@ -84,6 +118,9 @@ struct Plan {
     size_t lds_wave = 0;      // doubles of LDS per wave
     size_t lds_bytes = 0;
     size_t off_gz = 0, off_sig = 0, off_gout = 0;
+    bool matrix = false;             // the top level on the matrix cores; launch shape of that kernel:
+    int matrix_Q = 0, matrix_S = 1;
+    int64_t matrix_WP = 0, matrix_waves = 0, matrix_grid = 0;
 };
 
 // entries of levels 0..N over D channels; 0 if that does not fit in 2^40
@@ -186,6 +223,7 @@ inline Plan make_plan(int64_t B, int64_t L, int64_t d, int N, bool time_aug, boo
         return true;
     };
     if (!choose(B)) return p;
+    const bool may_matrix = backward && force_M < 0 && force_S == 0 && force_W == 0;   // (no kernel of the others asked for)
     // Few long paths leave most SIMDs without a wave: cut every path into P pieces of Lc segments, let the Horner
     // kernel treat the pieces as paths, and multiply the signatures of the pieces pairwise afterwards (Chen's identity,
     // Proposition 2.2).  Backward: the same products, then their adjoints pair by pair back down to the pieces, then
@@ -196,7 +234,8 @@ inline Plan make_plan(int64_t B, int64_t L, int64_t d, int N, bool time_aug, boo
             P = force_P;
         } else if (B > 0 && p.n >= 2 * kMinPiece && p.sig_len < ((int64_t)1 << 31)) {
             // backward, the products and their adjoints cost several launches: only when the chip is mostly empty
-            const int64_t w1 = p.PW > 1 ? (B + p.PW - 1) / p.PW : B * p.WP;
+            const int64_t w1 = may_matrix && matrix_pays(B, D, N, p.n) ? B * matrix_waves(D, N - 2, 1)
+                               : p.PW > 1 ? (B + p.PW - 1) / p.PW : B * p.WP;
             const int64_t few = backward ? kSimds / 2 : kSimds, want = backward ? kSimds : 2 * kSimds;
             if (w1 < few)
                 while (P < kMaxPieces && w1 * P < want && p.n / (2 * P) >= kMinPiece) P *= 2;
@@ -231,6 +270,14 @@ inline Plan make_plan(int64_t B, int64_t L, int64_t d, int N, bool time_aug, boo
         }
     } else {
         if (p.DT == 0 && D > kBwdMaxRuntimeD) { p.why = "backward: more than 1024 channels"; return p; }
+        if (may_matrix && matrix_pays(p.VB, D, N, p.Lc)) {
+            p.matrix_Q = N - 2;
+            p.matrix_S = matrix_words(p.VB, D, p.matrix_Q);
+            p.matrix_WP = matrix_waves(D, p.matrix_Q, p.matrix_S);
+            p.matrix_waves = p.VB * p.matrix_WP;
+            p.matrix_grid = (p.matrix_waves + kWavesPerWG - 1) / kWavesPerWG;
+            p.matrix = p.matrix_grid <= 0x7fffffffLL;
+        }
         const bool uniform = p.DT > 0 && p.M > 0;
         p.lds_wave = (size_t)p.Dpad + (uniform ? (size_t)kWave * (size_t)(D | 1) : 0);
         p.lds_bytes = (size_t)kWavesPerWG * p.lds_wave * sizeof(double);

@@ -933,7 +933,12 @@ int run_signature_bwd(const sg::Plan& p, const sg::Plan& pf, const void* x, cons
     a.LP = p.LP; a.WP = p.WP; a.sig_len = p.sig_len; a.lds_wave = p.lds_wave; a.PW = p.PW; a.NW = p.waves;
     a.leadlag = (flags & SK_FLAG_LEAD_LAG) ? 1 : 0;
     if (timed && p.P == 1) SK_CHECK(ev.begin(1, ttag, st));
-    SK_CHECK(sg::launch_horner_bwd(p.DT, p.M, p.S, a, p.grid, p.lds_bytes, st));
+    if (p.matrix) {
+        a.Q = p.matrix_Q; a.WP = p.matrix_WP; a.NW = p.matrix_waves;
+        SK_CHECK(sg::launch_horner_bwd_matrix(a, p.matrix_S, p.matrix_grid, st));
+    } else {
+        SK_CHECK(sg::launch_horner_bwd(p.DT, p.M, p.S, a, p.grid, p.lds_bytes, st));
+    }
     if (timed) SK_CHECK(ev.end(st));
     SK_CHECK(sg::launch_point_gradients<T>(gz, static_cast<T*>(grad_x), p.B, p.L, p.d, p.Dpad, p.P, p.Lc, p.np,
                                            (flags & SK_FLAG_LEAD_LAG) ? 1 : 0, st));
@@ -1013,14 +1018,17 @@ int signature_bwd_describe(int64_t B, int64_t L, int64_t d, int N, int flags, sk
     sg::Plan p;
     int rc = sig_validate(B, L, d, N, flags, (int)dt, &p, true, true);
     if (rc != SK_OK) return rc;
+    char matrix[64] = "none";
+    if (p.matrix) std::snprintf(matrix, sizeof(matrix), "horner_bwd_matrix_kernel<%d, %d, %d>", p.D, p.matrix_Q, p.matrix_S);
     std::snprintf(out, out_bytes,
                   "kernel=horner_bwd_kernel<%d, %d, %d, %d, %s, %s> channels=%d prefix_letters=%d letter_blocks=%d "
                   "lanes_per_path=%lld waves_per_path=%lld paths_per_wave=%d pieces_per_path=%d segments_per_piece=%lld "
-                  "grid=%lld threads=%d lds_bytes=%zu entries_per_path=%lld workspace_bytes=%zu",
+                  "grid=%lld threads=%d lds_bytes=%zu entries_per_path=%lld workspace_bytes=%zu matrix_kernel=%s "
+                  "matrix_grid=%lld",
                   p.DT, p.M, p.S, p.Q <= sg::kQExact ? p.Q : sg::kQMax, p.PW > 1 ? "true" : "false",
                   ((flags & SK_FLAG_LEAD_LAG) && p.DT >= 4 && p.M >= 1) ? "true" : "false", p.D, p.Q, p.NB,
                   (long long)p.LP, (long long)p.WP, p.PW, p.P, (long long)p.Lc, (long long)p.grid, sg::kWave * sg::kWavesPerWG, p.lds_bytes, (long long)p.sig_len,
-                  B == 0 ? (size_t)0 : p.total);
+                  B == 0 ? (size_t)0 : p.total, matrix, (long long)p.matrix_grid);
     return SK_OK;
 }
 
