@@ -315,20 +315,24 @@ __global__ __launch_bounds__(kWave * kWavesPerWG) void horner_bwd_kernel(const B
 // dF/dx from dF/dz (one row per segment of the transformed path): a point gains what the segment before it gives and
 // loses what the segment after it gives.  Lead-lag: segment 2k moves the lead half by x[k+1] - x[k], segment 2k + 1
 // the lag half by the same difference.  The time channel has no gradient.
-template <typename TO>
-__global__ __launch_bounds__(256) void point_gradients_kernel(const double* __restrict__ gz, TO* __restrict__ gx, long B,
+// I: type of the entries' numbers, as in increments_kernel.
+template <typename TO, typename I>
+__global__ __launch_bounds__(256) void point_gradients_kernel(const double* __restrict__ gz, TO* __restrict__ gx, I total,
                                                               long L, int d, int Dpad, int P, long Lc, long np,
                                                               int lead_lag)
 {
-    const long total = B * L * d;
-    for (long i = (long)blockIdx.x * blockDim.x + threadIdx.x; i < total; i += (long)gridDim.x * blockDim.x) {
-        const int ch = (int)(i % d);
-        const long bp = i / d;
-        const long pt = bp % L;
-        const long b = bp / L;
+    for (I i = (I)blockIdx.x * blockDim.x + threadIdx.x; i < total; i += (I)gridDim.x * blockDim.x) {
+        const int ch = (int)(i % (I)d);
+        const I bp = i / (I)d;
+        const long pt = bp % (I)L;
+        const long b = bp / (I)L;
         const double* g = gz + b * P * np * Dpad;
         // row of segment s of the transformed path: piece s / Lc, row s % Lc of that piece
-        auto row = [&](long s, int c) { return g[((s / Lc) * np + s % Lc) * Dpad + c]; };
+        auto row = [&](long s, int c) {
+            if (P == 1) return g[s * Dpad + c];
+            const long piece = (I)s / (I)Lc;
+            return g[(piece * np + (s - piece * Lc)) * Dpad + c];
+        };
         auto seg = [&](long k) { return lead_lag ? row(2 * k, ch) + row(2 * k + 1, d + ch) : row(k, ch); };
         double v = 0.0;
         if (pt > 0) v += seg(pt - 1);
@@ -463,8 +467,12 @@ hipError_t launch_point_gradients(const double* gz, TO* gx, long B, long L, int 
     if (P < 1 || (Lc < 1 && L > 1) || np < Lc) return hipErrorInvalidValue;
     long grid = (total + 255) / 256;
     if (grid > 65536) grid = 65536;
-    hipLaunchKernelGGL((point_gradients_kernel<TO>), dim3((unsigned)grid), dim3(256), 0, st, gz, gx, B, L, d, Dpad, P, Lc,
-                       np, lead_lag);
+    if (total < (1L << 30))       // (a step of the loop adds at most 2^24, a lead-lag path has twice the segments)
+        hipLaunchKernelGGL((point_gradients_kernel<TO, unsigned>), dim3((unsigned)grid), dim3(256), 0, st, gz, gx, (unsigned)total,
+                           L, d, Dpad, P, Lc, np, lead_lag);
+    else
+        hipLaunchKernelGGL((point_gradients_kernel<TO, unsigned long>), dim3((unsigned)grid), dim3(256), 0, st, gz, gx,
+                           (unsigned long)total, L, d, Dpad, P, Lc, np, lead_lag);
     return hipGetLastError();
 }
 

@@ -111,24 +111,26 @@ struct PathSet {
 // (inc[path][a][c] = x[path][a+1][c] - x[path][a][c] for a < L-1, c < d: first line of the paper's
 // forward listing), the gradient accumulators cleared, and the error flag cleared.
 // (Lead-lag paths, Section 4, need nothing here: the sweeps work on the increments of the original paths.)
-template <typename TI>
+// I: type of the entries' numbers.  Two divisions per entry: for 2 x 1024 paths of 64 points, 16 channels, 14.2 us in 64 bits
+// and 12.5 us in 32.
+template <typename TI, typename I>
 __global__ void prepare_kernel(PathSet<TI> px, PathSet<TI> py, int d, int DS, int* err, int nclear)
 {
-    const long nx = px.inc ? px.npaths * (long)px.rows * DS : 0;
-    const long ny = py.inc ? py.npaths * (long)py.rows * DS : 0;
-    long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    const long st = (long)gridDim.x * blockDim.x;
+    const I nx = px.inc ? (I)(px.npaths * (long)px.rows * DS) : 0;
+    const I ny = py.inc ? (I)(py.npaths * (long)py.rows * DS) : 0;
+    I i = (I)blockIdx.x * blockDim.x + threadIdx.x;
+    const I st = (I)gridDim.x * blockDim.x;
     if (err) {   // the error flag and the nclear - 1 ints behind it (progress counters)
-        for (long t = i; t < nclear; t += st) err[t] = 0;
+        for (I t = i; t < (I)nclear; t += st) err[t] = 0;
     }
     for (; i < nx + ny; i += st) {
         const bool second = i >= nx;
         const PathSet<TI>& p = second ? py : px;
-        const long j = second ? i - nx : i;
-        const int c = (int)(j % DS);
-        const long t = j / DS;
-        const int a = (int)(t % p.rows);
-        const long pth = t / p.rows;
+        const I j = second ? i - nx : i;
+        const int c = (int)(j % (I)DS);
+        const I t = j / (I)DS;
+        const int a = (int)(t % (I)p.rows);
+        const long pth = t / (I)p.rows;
         real v = 0.0;
         if (a < p.L - 1 && c < d) {
             const TI* xp = p.x + (pth * p.L + a) * (long)d + c;
@@ -142,24 +144,25 @@ __global__ void prepare_kernel(PathSet<TI> px, PathSet<TI> py, int d, int DS, in
 // Finalisation, one launch per backward call: grad[path][i][c] = g[path][i-1][c] - g[path][i][c]
 // (out-of-range terms zero).  The increments are differences of consecutive points, so the gradient of
 // a point collects the two increments it touches.
-template <typename TO>
+// I: as in prepare_kernel.
+template <typename TO, typename I>
 __global__ void finalize_kernel(PathSet<TO> px, PathSet<TO> py, int d, int DS, const int* err)
 {
     // a bounded wait ran out (1) or the workspace held another call's forward sweep (3); 2 means that every pair was
     // solved once more by the replay kernel, whose results the accumulators then hold
     const bool bad = err != nullptr && *err != 0 && *err != 2;
-    const long nx = px.grad ? px.npaths * (long)px.L * d : 0;
-    const long ny = py.grad ? py.npaths * (long)py.L * d : 0;
-    long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    const long st = (long)gridDim.x * blockDim.x;
+    const I nx = px.grad ? (I)(px.npaths * (long)px.L * d) : 0;
+    const I ny = py.grad ? (I)(py.npaths * (long)py.L * d) : 0;
+    I i = (I)blockIdx.x * blockDim.x + threadIdx.x;
+    const I st = (I)gridDim.x * blockDim.x;
     for (; i < nx + ny; i += st) {
         const bool second = i >= nx;
         const PathSet<TO>& p = second ? py : px;
-        const long j = second ? i - nx : i;
-        const int c = (int)(j % d);
-        const long t = j / d;
-        const int pt = (int)(t % p.L);
-        const long pth = t / p.L;
+        const I j = second ? i - nx : i;
+        const int c = (int)(j % (I)d);
+        const I t = j / (I)d;
+        const int pt = (int)(t % (I)p.L);
+        const long pth = t / (I)p.L;
         const real* gp = p.ginc + (pth * p.rows) * (long)DS + c;
         const real hi = pt >= 1 ? gp[(long)(pt - 1) * DS] : 0.0;
         const real lo = pt < p.L - 1 ? gp[(long)pt * DS] : 0.0;
@@ -2037,7 +2040,10 @@ hipError_t launch_prepare(const T* x, real* dx, real* gdx, long nx, int L1, int 
     if (total <= 0) total = 1;
     long blocks = (total + 255) / 256;
     if (blocks > 8192) blocks = 8192;
-    hipLaunchKernelGGL(prepare_kernel<T>, dim3((unsigned)blocks), dim3(256), 0, st, px, py, d, DS, err, nclear);
+    if (total < (1L << 31))       // (a step of the loops adds at most 2^21)
+        hipLaunchKernelGGL((prepare_kernel<T, unsigned>), dim3((unsigned)blocks), dim3(256), 0, st, px, py, d, DS, err, nclear);
+    else
+        hipLaunchKernelGGL((prepare_kernel<T, unsigned long>), dim3((unsigned)blocks), dim3(256), 0, st, px, py, d, DS, err, nclear);
     return hipGetLastError();
 }
 
@@ -2051,7 +2057,10 @@ hipError_t launch_finalize(const real* gdx, T* grad_x, long nx, int L1, int rpad
     if (total <= 0) return hipSuccess;
     long blocks = (total + 255) / 256;
     if (blocks > 8192) blocks = 8192;
-    hipLaunchKernelGGL(finalize_kernel<T>, dim3((unsigned)blocks), dim3(256), 0, st, px, py, d, DS, err);
+    if (total < (1L << 31))
+        hipLaunchKernelGGL((finalize_kernel<T, unsigned>), dim3((unsigned)blocks), dim3(256), 0, st, px, py, d, DS, err);
+    else
+        hipLaunchKernelGGL((finalize_kernel<T, unsigned long>), dim3((unsigned)blocks), dim3(256), 0, st, px, py, d, DS, err);
     return hipGetLastError();
 }
 
