@@ -63,9 +63,21 @@ __global__ __launch_bounds__(1024) void mmd2_reduce_kernel(const T* __restrict__
     __shared__ real part[1024];
     real acc = 0.0;
     const real wxx = 1.0 / (real)nxx, wxy = -2.0 / (real)nxy, wyy = 1.0 / (real)nyy;
-    for (long i = threadIdx.x; i < nxx; i += blockDim.x) acc += wxx * (real)Kxx[i];
-    for (long i = threadIdx.x; i < nxy; i += blockDim.x) acc += wxy * (real)Kxy[i];
-    for (long i = threadIdx.x; i < nyy; i += blockDim.x) acc += wyy * (real)Kyy[i];
+    // Sixteen loads before the first is waited for (a load's way to HBM is what one workgroup is bound by), added in the
+    // order of a plain loop: 58 k entries 17.3 -> MMDUS us.
+    auto add = [&](const T* __restrict__ K, long n, real w) {
+        for (long i = threadIdx.x; i < n; i += 16 * 1024) {
+            T v[16];
+#pragma unroll
+            for (int u = 0; u < 16; ++u) v[u] = K[min(i + u * 1024, n - 1)];
+#pragma unroll
+            for (int u = 0; u < 16; ++u)
+                if (i + u * 1024 < n) acc += w * (real)v[u];
+        }
+    };
+    add(Kxx, nxx, wxx);
+    add(Kxy, nxy, wxy);
+    add(Kyy, nyy, wyy);
     part[threadIdx.x] = acc;
     __syncthreads();
     for (int s = blockDim.x / 2; s > 0; s >>= 1) {
