@@ -190,7 +190,7 @@ int run(const Layout& lay, bool backward, const void* x, const void* y, void* k,
     a.solo = p.solo;
     a.tile = p.tile;
     a.quad = p.quad; a.qd_nquads = p.nquads; a.qd_even = p.qd_even;
-    a.fv_ck = p.fv_ck; a.fv_bands = p.fv_bands;
+    a.fv_bands = p.fv_bands;
     a.fv_gx = p.fv_gx_slot ? reinterpret_cast<double*>(base + p.off_fvgx) : nullptr;
     a.fv_gx_slot = p.fv_gx_slot;
     a.band = p.band; a.bd_nbands = p.bd_nbands;
@@ -438,10 +438,15 @@ size_t sigkernel_workspace_bytes(int op, int64_t B_or_N, int64_t M, int64_t L1, 
     if (op < SK_OP_FWD || op > SK_OP_GRAM_BWD) return 0;
     const int64_t ny = gram ? M : B_or_N;
     if (validate(B_or_N, ny, L1, L2, d, lam1, lam2, flags, (int)dt) != SK_OK) return 0;
-    // The symmetric Gram case needs no more than the general one, so the query does not distinguish them.
-    const Layout l = make_layout(backward, gram, false, B_or_N, ny, L1, L2, d, lam1, lam2, flags, dt == SK_F64 ? 8 : 4,
-                                 !(flags & SK_FLAG_BWD_REPLAY), kept);
-    return l.p.valid ? l.total : 0;
+    auto total = [&](bool symmetric) {
+        const Layout l = make_layout(backward, gram, symmetric, B_or_N, ny, L1, L2, d, lam1, lam2, flags, dt == SK_F64 ? 8 : 4,
+                                     !(flags & SK_FLAG_BWD_REPLAY), kept);
+        return l.p.valid ? l.total : (size_t)0;
+    };
+    const size_t need = total(false);
+    // K(X, X) is the same query.  It needs no more, unless the two take different launch modes.
+    const size_t sym = gram && backward && B_or_N == ny && L1 == L2 ? total(true) : 0;
+    return need > sym ? need : sym;
 }
 
 int sigkernel_fwd(const void* x, const void* y, void* k, int64_t B, int64_t L1, int64_t L2, int64_t d, int lam1,

@@ -14,13 +14,27 @@
 //    p = 0, i.e. A = B = 1, and adds zeros (its travelling sum belongs to no column and is dropped);
 //  * rows above the grid fill the first band from the top; macro-steps in which only they would work are skipped.
 //
-// The reverse sweep inverts Eq. (1) between checkpoints of the lane state and is checked against them as everywhere
-// (sk_lane.h).  A pair that drifts is listed for the replay kernel, replaced by zeros, and the quad's reverse sweep is
-// run again for the other three: the sums of a quad are never split by pair.
+// The reverse sweep inverts Eq. (1) between checkpoints of the lane state and is checked against them (sk_lane.h).  A pair
+// that drifts is listed for the replay kernel, replaced by zeros, and the quad is swept again for the other three: the sums
+// of a quad are never split by pair, so a drifted pair costs more than in the one-pair kernels and has to be rarer.  What
+// decides is how far an error travels between two checkpoints, and a lane's four block rows take it twice as far per
+// macro-step as two.  Pairs that drift of Gram 256 x 256, L = 128, order 1, d = 3, and milliseconds, by the squared length
+// of the paths' increments (one-pair kernel: a checkpoint every 8 macro-steps):
 //
-// Bound by fp64 issue: Gram 256 x 256, L = 128, order 1, d = 3 takes 25 k vector instructions per pair where the one-pair
-// kernel takes 39 k, 6.2 -> 3.6 ms; K(X, X) of 300 paths, L = 100, order 1, d = 5: 4.9 -> 2.2 ms; Gram 192 x 192, L = 100,
-// order 0, d = 12 (built for twelve channels, the one-pair kernel for sixteen): 9.3 -> 4.4 ms.  Four block rows per lane
+//    spacing       squared length 4      10           20             30            50
+//    one-pair        0    6.1        0   6.2      0    6.2      192   7.4    28850   167
+//    32              0    3.8      345   6.3  12682   76.7    46700   267    65494   371
+//    8               0    4.2        0   4.2     37    4.8     1682  15.4    24725   146
+//    4               0    4.8        0   4.8      0    4.9        6   5.5     1132    13
+//    8 / 4 by band   0    4.2        0   4.3      0    4.9      100   6.3     3884    29   (as built)
+//
+// Checkpoints are what the kernel moves through memory, so a band takes 8 where no block of it can have a large increment
+// product and 4 elsewhere (kFourSteady), with the guard at kFourDriftTol.  1 / B has a term more than in the other kernels:
+// theirs is what drifts first on unrefined paths (L = 60, order 0, d = 5, squared length 10: 8315 pairs in the one-pair
+// kernel, 12671 here without the term, 15 with it; no time is seen).
+//
+// Bound by fp64 issue: Gram 256 x 256, L = 128, order 1, d = 3: 6.1 -> 4.2 ms; K(X, X) of 300 paths, L = 100, order 1,
+// d = 5: 4.6 -> 2.7 ms; Gram 128 x 128, L = 100, order 0, d = 16: 4.0 -> 2.7 ms.  Four block rows per lane
 // up to six channels, two from eight on and for blocks of 4 x 4 cells: with more the lane state does not fit the 256
 // registers of a wavefront that shares its SIMD (eight rows, d = 3: 1 KB of it in scratch, 22 ms), and a lone wavefront
 // is slower (4.7 ms).  Sixteen channels, and twelve with 4 x 4 blocks, do not fit either way and run alone on their SIMD
@@ -38,6 +52,13 @@ namespace sk {
 namespace four {
 
 constexpr real kSqrt3 = 1.7320508075688772, kRsqrt12 = 0.28867513459481287;
+
+__device__ __forceinline__ real wave_max(real v)
+{
+#pragma unroll
+    for (int s = 32; s > 0; s >>= 1) v = fmax(v, __shfl_xor(v, s));
+    return __hiloint2double(__builtin_amdgcn_readfirstlane(__double2hiint(v)), __builtin_amdgcn_readfirstlane(__double2loint(v)));
+}
 
 // M: 1 = the block rows of a pair fit one band of 16 lanes, 2 = several bands; TC: whether there is a time channel.
 template <int BL, int D, int M, bool TC>
@@ -69,7 +90,6 @@ __device__ __forceinline__ void backward(const SweepArgs& a)
     const int nb = a.nb, q = a.q;
     const int ns = M == 1 ? 1 : a.fv_bands;
     const int NT = nb + LP - 1;
-    const int ckS = a.fv_ck;                                      // macro-steps between checkpoints
     const int nck = a.nseg;                                       // checkpoint places per band, the last for the band's end
     // Scratch of this wavefront.  rows[band][group]: the band's bottom row, node column n at [2 C - 1 + n] (1 up to
     // node column 0); adj[group]: the adjoints that enter a band from below, column J at [J C ...].
@@ -84,6 +104,7 @@ __device__ __forceinline__ void backward(const SweepArgs& a)
     for (int t = lane; t < q * D; t += kWave) gyp[t] = 0.0;
 
     long cur_y = -1;
+    real ylen2 = 0.0;   // largest squared length of a y increment
     QuadQueue queue(a, slot, gridDim.x);
     unsigned out = 0;   // groups of the quad whose pairs drifted
     while (queue.more()) {
@@ -96,6 +117,14 @@ __device__ __forceinline__ void backward(const SweepArgs& a)
                 ylds[b * YS + c] = dyg[(long)b * a.DS + c];
             }
             cur_y = yi;
+            ylen2 = 0.0;
+            for (int b = lane; b < q; b += kWave) {
+                real t = 0.0;
+#pragma unroll
+                for (int c = 0; c < D; ++c) t = fma(ylds[b * YS + c], ylds[b * YS + c], t);
+                ylen2 = fmax(ylen2, t);
+            }
+            ylen2 = wave_max(ylen2);
         }
         // a group beyond the row's end, or whose pair has drifted: zero increments, no outputs
         const bool inrow = cur.xi0 + g < cur.npr, valid = inrow && ((out >> g) & 1u) == 0;
@@ -105,7 +134,8 @@ __device__ __forceinline__ void backward(const SweepArgs& a)
 
         const real gxs = a.sc * (1.0 / kSqrt3);   // of the x-side sums; the y-side sums hold sc / 2 (through dxr)
         real dxr[RL][D];
-        // increments of the lane's block rows in band s (zeros above the grid)
+        // Increments of the lane's block rows in band s (zeros above the grid).  Returns log2 of the macro-steps between the
+        // band's checkpoints: 8 where no block of the band can have an increment product above kFourSteady, else 4.
         auto load_x = [&](int s) __attribute__((always_inline)) {
             const real* const dxp = a.dx + xi * a.xstride;
             const int I0 = (s * LP + r) * RL - a.lk_padb;
@@ -122,6 +152,17 @@ __device__ __forceinline__ void backward(const SweepArgs& a)
 #pragma unroll
                 for (int c = 0; c < D; ++c) dxr[m][c] *= sc;
             }
+            real xlen2 = 0.0;
+#pragma unroll
+            for (int m = 0; m < RL; ++m) {
+                real t = 0.0;
+#pragma unroll
+                for (int c = 0; c < D; ++c) t = fma(dxr[m][c], dxr[m][c], t);
+                xlen2 = fmax(xlen2, t);
+            }
+            // (|dx| |dy| per cell, times the cells of a block)
+            const real most = kFourSteady * kRsqrt12 / (C * C);
+            return wave_max(xlen2) * ylen2 <= most * most ? 3 : 2;
         };
         // the D increments of the block column the lane is at in macro-step T
         auto fetch = [&](int T, real (&y)[D]) __attribute__((always_inline)) {
@@ -154,9 +195,10 @@ __device__ __forceinline__ void backward(const SweepArgs& a)
             else return 0.0;
         };
 
-        // ---- forward, a checkpoint every ckS macro-steps, every band's bottom row into global scratch ----
+        // ---- forward, a checkpoint every 2^ckL macro-steps, every band's bottom row into global scratch ----
+        int ckL = 0;   // of the band in work (the last band's serves both sweeps, as its increments do)
         for (int s = 0; s < ns; ++s) {
-            load_x(s);
+            ckL = load_x(s);
             const int nabove = a.lk_padb - (s * LP + r) * RL;
             const int Ts = s == 0 ? a.lk_padb / RL : 0;
             real left[RR + 1], bot[C], blc = 1.0;
@@ -196,9 +238,9 @@ __device__ __forceinline__ void backward(const SweepArgs& a)
                 next_edge(0);
             }
             fetch(Ts, y);
-            for (int k = Ts / ckS; k * ckS < NT; ++k) {
-                if (k * ckS > Ts) store(k - 1);
-                const int T0 = max(Ts, k * ckS), T1 = min(NT, (k + 1) * ckS);
+            for (int k = Ts >> ckL; k << ckL < NT; ++k) {
+                if (k << ckL > Ts) store(k - 1);
+                const int T0 = max(Ts, k << ckL), T1 = min(NT, (k + 1) << ckL);
                 for (int T = T0; T < T1; ++T) {
                     const real tcj = tc_at(T);
                     real p[RL];
@@ -255,7 +297,7 @@ __device__ __forceinline__ void backward(const SweepArgs& a)
         bool drift = false;
         const real gk = valid ? gram_weight(a, pid, pid2) : 0.0;   // dF/dk[m, n]: enters under the last lane
         for (int s = ns - 1; s >= 0; --s) {
-            if (s < ns - 1) load_x(s);
+            if (s < ns - 1) ckL = load_x(s);
             const int nabove = a.lk_padb - (s * LP + r) * RL;
             const int Ts = s == 0 ? a.lk_padb / RL : 0;
             real kR[RR + 1], accL[RR + 1], ktop[C], up[C], corner = 0.0, kscale = 1.0;
@@ -285,7 +327,7 @@ __device__ __forceinline__ void backward(const SweepArgs& a)
                 if (check) {
 #pragma unroll
                     for (int i = 0; i <= RR; ++i)   // written so that a NaN counts as drift
-                        if (!(fabs(kR[i] - v[i]) <= kDriftTol * kscale)) drift = true;
+                        if (!(fabs(kR[i] - v[i]) <= kFourDriftTol * kscale)) drift = true;
                 }
 #pragma unroll
                 for (int i = 0; i <= RR; ++i) kR[i] = v[i];
@@ -329,8 +371,8 @@ __device__ __forceinline__ void backward(const SweepArgs& a)
             next_edge(NT - 1);
             if (s == ns - 1) ea[C - 1] = gk;
             fetch(NT - 1, y);
-            for (int k = (NT - 1) / ckS; k * ckS + ckS > Ts; --k) {
-                const int T0 = max(Ts, k * ckS), T1 = min(NT, (k + 1) * ckS);
+            for (int k = (NT - 1) >> ckL; (k + 1) << ckL > Ts; --k) {
+                const int T0 = max(Ts, k << ckL), T1 = min(NT, (k + 1) << ckL);
                 restore(T1 == NT ? nck - 1 : k, T1 != NT);
                 for (int T = T1 - 1; T >= T0; --T) {
                     real yn[D];
@@ -353,7 +395,8 @@ __device__ __forceinline__ void backward(const SweepArgs& a)
                         __builtin_amdgcn_sched_barrier(0);   // block by block: the lane state leaves no room
                         const real p = inner(m, nabove, tcj, y);
                         const real Bc = fma(-p, p, 1.0), r0 = fma(p, p, 1.0), Ac = fma(p, kSqrt3, r0);
-                        const real ee = fma(-Bc, r0, 1.0), iB = fma(fma(ee, ee, ee), r0, r0);   // 1 / B as in sk_lane.h
+                        const real ee = fma(-Bc, r0, 1.0), r1 = fma(ee, r0, r0);
+                        const real iB = fma(ee * ee, r1, r1);   // 1 / B = r0 (1 + ee) (1 + ee^2 ...), see coef_rev in sk_lane.h
                         real gs = 0.0, gq = 0.0;
 #pragma unroll
                         for (int rb = R - 1; rb >= 0; --rb) {
@@ -419,7 +462,7 @@ __device__ __forceinline__ void backward(const SweepArgs& a)
             // the left end: the sweep started from the boundary value 1 in every lane
 #pragma unroll
             for (int i = 0; i <= RR; ++i)
-                if (!(fabs(kR[i] - 1.0) <= kDriftTol * kscale)) drift = true;
+                if (!(fabs(kR[i] - 1.0) <= kFourDriftTol * kscale)) drift = true;
             // the x-side sums wait for the verdict on the whole pair: in registers if this is the only band
             if constexpr (M > 1) {
                 real* gsp = a.fv_gx + slot * a.fv_gx_slot + (long)s * RL * D * kWave;
@@ -542,8 +585,8 @@ hipError_t launch_sweep_four(int BL, int DT, const SweepArgs& a, int grid, size_
     const size_t rings = (size_t)(a.lk_M == 1 ? 1 : 3) * kWave * C * sizeof(real);
     if (!a.gramM || !a.bd_flags || a.qd_even < 0 || a.ll != 0 || a.lk_phase != 0 || bands < 1 || a.lk_M != (bands == 1 ? 1 : 2) || a.mb < 1 || a.nb < 1 ||
         a.lk_padb != bands * 16 * lanerows - a.mb || a.lk_padb < 0 || a.lk_padb >= 16 * lanerows || a.DS < DT || a.d > DT ||
-        a.qd_nquads < 1 || a.nb != a.q << a.rs2 || a.mb != a.r << a.rs1 || a.fv_ck < 1 ||
-        a.nseg < (a.nb + 14) / a.fv_ck + 1 || a.rowlen < (a.nb + 2) * C || !a.bad_list || !a.bad_count ||
+        a.qd_nquads < 1 || a.nb != a.q << a.rs2 || a.mb != a.r << a.rs1 ||
+        a.nseg < (a.nb + 14) / kFourCkpt + 1 || a.rowlen < (a.nb + 2) * C || !a.bad_list || !a.bad_count ||
         a.rows_slot < (long)bands * kQuadPairs * a.rowlen || a.adj_slot < (long)kQuadPairs * a.rowlen ||
         a.ckpt_slot < (long)bands * a.nseg * four_ckpt_values(BL, DT) * kWave ||
         (bands > 1 && (!a.fv_gx || a.fv_gx_slot < (long)bands * lanerows * DT * kWave)) ||

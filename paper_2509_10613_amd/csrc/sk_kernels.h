@@ -94,8 +94,7 @@ struct SweepArgs {
     int quad;            // 1: quad kernel (forward Gram calls: four pairs per wave; uses lk_M, lk_padb)
     long qd_even;        // four pairs per wave: quads handed out in equal shares; the rest by the counter bd_flags[0]
     long qd_nquads;      // groups of four pairs of one Gram row in the launch's sequence
-    int fv_bands;        // solo kernel with four pairs per wave: bands of 16 lanes per pair,
-    int fv_ck;           // macro-steps between checkpoints (nseg: places per band),
+    int fv_bands;        // four pairs per wave, backward: bands of 16 lanes per pair (nseg: checkpoint places per band),
     real* fv_gx;         // per slot the x-side sums of the bands of the pairs in work (several bands only)
     long fv_gx_slot;
     // lock-step mode on a batch of pairs of double paths: the kernels read the caller's points and write the

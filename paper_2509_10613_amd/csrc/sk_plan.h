@@ -76,7 +76,6 @@ struct Plan {
     int64_t qd_even = 0;  // quads of a four-pair launch that are handed out in equal shares (the rest by a counter)
     int four = 0;         // solo mode with four pairs per wave (backward Gram calls, sk_four.hip)
     int fv_bands = 0;     // bands of 16 lanes per pair
-    int fv_ck = 0;        // macro-steps between its checkpoints
     int64_t fv_gx_slot = 0;
     size_t off_fvgx = 0;  // x-side sums of the strips of the pairs in work (several strips only)
     int solo = 0;   // one wave per pair, a single strip of 64 * lk_M block rows (many pairs of short paths)
@@ -162,7 +161,16 @@ inline int64_t four_even_share(int64_t nquads, int64_t nwaves, int64_t instr)
 {
     return nquads < 3 * nwaves || nquads / nwaves * instr < 100000 ? nquads : nquads / 2 / nwaves * nwaves;
 }
-constexpr int kFourCkpt = 32;                 // macro-steps between checkpoints
+// Macro-steps between its checkpoints: kFourCkpt, or twice as many in a band whose largest increment product of a block,
+// |dx| |dy|, is at most kFourSteady (sk_four.hip has the pairs that drift with either; with 8 the first ones do at 0.55).
+constexpr int kFourCkpt = 4;
+constexpr double kFourSteady = 0.5;
+// Its drift guard (kDriftTol elsewhere).  With its short spacing and its 1 / B recovered values stay closer, so the guard can:
+// L = 60, order 0, d = 5, squared length 20, largest gradient error of the pairs that pass 2.8e-12 (1.1e-11 with 1e-11).
+constexpr double kFourDriftTol = 3e-12;
+// Scratch that mode may take where the one-pair kernels need less: its checkpoints are many for long paths of high order
+// (722 x 43 paths of 890 and 415 points, order 3: 101 GiB against 16 in the wave-per-pair kernel).
+constexpr size_t kFourScratch = (size_t)4 << 30;
 // Quads of pairs from which the four-pair kernel is taken.  A wavefront needs three to four times as long for its quad as
 // the one-pair kernels for a pair, so it takes about a wavefront per SIMD to pay: steps of Gram n x n with n = 48 / 64 / 128
 // (576, 1024, 4096 quads), one-pair and four-pair: L = 128, order 1, d = 3: 317 / 415 / 1700 against 376 / 433 / 1316 us;
@@ -192,7 +200,7 @@ constexpr double kDriftTol = 1e-11;
 
 inline Plan make_plan(bool backward, bool gram, bool symmetric, int64_t nx, int64_t ny, int64_t L1, int64_t L2,
                       int64_t d, int lam1, int lam2, int io_elem, bool uncompute = true, bool keep = false,
-                      bool second_chance = false, bool lead_lag = false)
+                      bool second_chance = false, bool lead_lag = false, bool may_four = true)
 {
     // lead_lag: the sweep of two lead-lag paths (Section 4) on the grid of the original increments; lam1 and lam2 then
     // count the lead-lag level as one more dyadic level (the caller's orders plus one), L1, L2 and d are the caller's.
@@ -446,7 +454,7 @@ inline Plan make_plan(bool backward, bool gram, bool symmetric, int64_t nx, int6
 
     // Four-pair mode: backward calls for Gram matrices with enough quads of pairs to fill the chip.
     bool four = false;
-    if (backward && gram && p.uncompute && !keep && !second_chance && !lead_lag && !p.tile && p.DT >= 2 &&
+    if (may_four && backward && gram && p.uncompute && !keep && !second_chance && !lead_lag && !p.tile && p.DT >= 2 &&
         ny * ((nx + kQuadPairs - 1) / kQuadPairs) >= four_min_quads(p.solo != 0, p.DT)) {
         const int DT = four_channels(p.DT, p.d), band = kWave / kQuadPairs * four_rows(p.BL, DT);
         const int bands = (p.mb + band - 1) / band;
@@ -468,8 +476,7 @@ inline Plan make_plan(bool backward, bool gram, bool symmetric, int64_t nx, int6
             p.y_lds = 1;
             p.lds_wave = used;
             p.lds_bytes = used;                  // one wavefront per workgroup
-            p.fv_ck = kFourCkpt;
-            p.nseg = (p.lk_NT - 1) / p.fv_ck + 1;   // checkpoint places per band
+            p.nseg = (p.lk_NT - 1) / kFourCkpt + 1;   // checkpoint places per band
         }
     }
 
@@ -605,6 +612,11 @@ inline Plan make_plan(bool backward, bool gram, bool symmetric, int64_t nx, int6
     if (backward && p.uncompute && !second_chance) p.off_badlist = take((size_t)p.kcount * sizeof(long long));
     p.total = off;
     p.valid = true;
+    if (p.four && p.total > kFourScratch) {
+        const Plan one = make_plan(backward, gram, symmetric, nx, ny, L1, L2, d, lam1, lam2, io_elem, uncompute, keep,
+                                   second_chance, lead_lag, false);
+        if (one.total < p.total) return one;
+    }
     return p;
 }
 

@@ -53,6 +53,28 @@ def test_four_pairs_per_wave(nx, ny, L1, L2, d, lam1, lam2, flags, sym, dtype):
         check_grads(host(gY), gYr, dtype, "grad_Y")
 
 
+@pytest.mark.parametrize("L,d,lam,squared", [(100, 5, 1, 20.0), (100, 3, 1, 10.0), (60, 5, 0, 10.0), (40, 3, 2, 20.0)])
+def test_four_pairs_per_wave_on_larger_increments(L, d, lam, squared):
+    # The inverse recurrence holds on paths on which the one-pair kernels' does (they list 0, 0, 513 and 8 pairs of these
+    # four, with gradients within 7e-14, 2e-13, 4e-12 and 7e-13 of their largest entry).  Bounds: one pair in 500, and what
+    # the drift guard lets pass of forward values (3e-12).
+    nx, ny = 96, 48
+    X, Y = paths(1600 + L + d, nx, L, d, squared / (d * (L - 1))), paths(1601 + L + d, ny, L, d, squared / (d * (L - 1)))
+    W = workloads.upstream_weights(90, (nx, ny))
+    desc = sk.sigkernel_describe(sk.SK_OP_GRAM_BWD, nx, ny, L, L, d, lam, lam, 0, sk.SK_F64)
+    assert "pairs_per_wave=4" in desc, desc
+    ws = torch.empty(sk.sigkernel_workspace_bytes(sk.SK_OP_GRAM_BWD, nx, ny, L, L, d, lam, lam, 0, sk.SK_F64),
+                     dtype=torch.uint8, device="cuda")
+    K, gX, gY = sk.sigkernel_gram(dev(X), dev(Y), dev(W), lam, lam, 0, ws=ws)
+    torch.cuda.synchronize()
+    at = int(desc.split("drifted_pairs_counter_at=", 1)[1].split()[0])
+    assert int(ws[at:at + 4].view(torch.int32)[0]) <= nx * ny // 500
+    _, gXr, gYr = oracle.gram(X, Y, W, lam, lam, 0, dtype=np.longdouble)
+    for got, ref in ((host(gX), np.asarray(gXr, np.float64)), (host(gY), np.asarray(gYr, np.float64))):
+        err = np.max(np.abs(got - ref), axis=(1, 2)) / np.max(np.abs(ref), axis=(1, 2))
+        assert np.max(err) <= 3e-12, np.max(err)
+
+
 @pytest.mark.parametrize("L1,L2,d,lam", [(40, 40, 3, 1), (150, 30, 4, 0)])
 def test_four_pairs_per_wave_with_pairs_that_drift(L1, L2, d, lam):
     # one path of either side with increments of order one: its pairs leave their quads, the others stay

@@ -123,6 +123,11 @@ def test_launch_plan_of_the_five_configurations(lib):
     # strip (127 block rows at two per lane)
     p = _plan(binding.SK_OP_GRAM_BWD, 256, 256, 128, 128, 3, 1, 1, 0, f64)
     assert p["mode"] == "solo" and p["kernel"] == "solo_bwd_kernel<1, 3, 2, 0, 0, 2>" and p["strips"] == "1"
+    # ... whose checkpoints stay within 4 GiB, or within what the other kernels need (722 x 43 long paths of order 3: 16 GiB)
+    assert "pairs_per_wave=4" in binding.sigkernel_describe(binding.SK_OP_GRAM_BWD, 256, 256, 128, 128, 3, 2, 2, 0, f64)
+    assert q(binding.SK_OP_GRAM_BWD, 256, 256, 128, 128, 3, 2, 2, 0, f64) < 4 << 30
+    assert "pairs_per_wave=1" in binding.sigkernel_describe(binding.SK_OP_GRAM_BWD, 722, 43, 890, 415, 2, 3, 3, 0, f64)
+    assert q(binding.SK_OP_GRAM_BWD, 722, 43, 890, 415, 2, 3, 3, 0, f64) < 17 << 30
     # c5 (1048576 pairs, 63 x 63 unrefined cells, 16 channels).  Forward: quad mode, four pairs of a Gram row per
     # wave (16 lanes with four grid rows each per pair), two workgroups per compute unit; a pair batch of that shape
     # has no shared y path and takes the tile kernel.  Backward: the channel contraction dominates -> tile mode,
