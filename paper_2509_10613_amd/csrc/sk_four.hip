@@ -489,6 +489,10 @@ __device__ __forceinline__ void backward(const SweepArgs& a)
             if (r == 0 && ((bad >> (16 * g)) & 0xffffull) != 0ull) list_drifted(a, pid, pid2);
             for (int i = 0; i < kQuadPairs; ++i) out |= ((bad >> (16 * i)) & 0xffffull) != 0ull ? 1u << i : 0u;
             for (int t = lane; t < q * D; t += kWave) gyp[t] = 0.0;
+            if (__ballot(inrow && ((out >> g) & 1u) == 0) == 0ull) {   // no pair of the quad is left: nothing to sweep again
+                out = 0;
+                queue.next(a);
+            }
             continue;
         }
         if (M > 1 && a.want_gx && valid) {

@@ -97,3 +97,26 @@ def test_four_pairs_per_wave_with_pairs_that_drift(L1, L2, d, lam):
     check_values(host(K), Kr, torch.float64, "K")
     check_rows(host(gX), gXr, torch.float64, "grad_X")
     check_rows(host(gY), gYr, torch.float64, "grad_Y")
+
+
+@pytest.mark.parametrize("L1,L2,d,lam,flags", [(40, 40, 3, 1, 0), (150, 30, 4, 0, 0), (70, 24, 11, 0, 1)])
+def test_quads_whose_pairs_all_drift_and_the_quads_after_them(L1, L2, d, lam, flags):
+    # four neighbouring x paths with increments of order one: one quad of every Gram row has no pair left, and the wavefronts
+    # go on with further quads
+    nx, ny = 132, 72
+    X, Y = paths(1510, nx, L1, d, 1.0 / (d * L1)), paths(1511, ny, L2, d, 1.0 / (d * L2))
+    rng = np.random.default_rng(1512)
+    X[4:8, 1:] = np.cumsum(rng.choice([-1.0, 1.0], size=(4, L1 - 1, d)) * ((12.0 if lam else 6.0) / d ** 0.5), axis=1)
+    W = workloads.upstream_weights(91, (nx, ny))
+    desc = sk.sigkernel_describe(sk.SK_OP_GRAM_BWD, nx, ny, L1, L2, d, lam, lam, flags, sk.SK_F64)
+    assert "pairs_per_wave=4" in desc and int(desc.split(" grid=")[1].split()[0]) < ny * nx // 4, desc
+    ws = torch.empty(sk.sigkernel_workspace_bytes(sk.SK_OP_GRAM_BWD, nx, ny, L1, L2, d, lam, lam, flags, sk.SK_F64),
+                     dtype=torch.uint8, device="cuda")
+    K, gX, gY = sk.sigkernel_gram(dev(X), dev(Y), dev(W), lam, lam, flags, ws=ws)
+    torch.cuda.synchronize()
+    at = int(desc.split("drifted_pairs_counter_at=", 1)[1].split()[0])
+    assert int(ws[at:at + 4].view(torch.int32)[0]) == 4 * ny
+    Kr, gXr, gYr = oracle.gram(X, Y, W, lam, lam, flags)
+    check_values(host(K), Kr, torch.float64, "K")
+    check_rows(host(gX), gXr, torch.float64, "grad_X")
+    check_rows(host(gY), gYr, torch.float64, "grad_Y")
