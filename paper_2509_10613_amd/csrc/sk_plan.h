@@ -171,12 +171,47 @@ constexpr double kFourDriftTol = 3e-12;
 // Scratch that mode may take where the one-pair kernels need less: its checkpoints are many for long paths of high order
 // (722 x 43 paths of 890 and 415 points, order 3: 101 GiB against 16 in the wave-per-pair kernel).
 constexpr size_t kFourScratch = (size_t)4 << 30;
-// Quads of pairs from which the four-pair kernel is taken.  A wavefront needs three to four times as long for its quad as
-// the one-pair kernels for a pair, so it takes about a wavefront per SIMD to pay: steps of Gram n x n with n = 48 / 64 / 128
-// (576, 1024, 4096 quads), one-pair and four-pair: L = 128, order 1, d = 3: 317 / 415 / 1700 against 376 / 433 / 1316 us;
-// L = 60, order 1, d = 12: 498 / 755 against 319 / 404 us (sixteen channels in the one-pair kernel, twelve here); L = 220,
-// d = 4 (wave-per-pair kernels): 1248 / 1538 against 973 / 1139 us.
-constexpr int64_t four_min_quads(bool solo, int DT) { return solo && DT <= 6 ? 1100 : 512; }
+// Groups of four pairs of one row of the Gram matrix in a launch's sequence (tri: rows of the pairs n <= m).
+inline int64_t gram_quads(bool tri, int64_t nx, int64_t ny)
+{
+    if (!tri) return ny * ((nx + kQuadPairs - 1) / kQuadPairs);
+    const int64_t J = nx / kQuadPairs, e = nx % kQuadPairs;
+    return 2 * J * (J + 1) + e * (J + 1);
+}
+// One side of the choice between one pair and four per wavefront: what its launch has to do, and how many wavefronts of
+// it the chip holds.
+struct SweepLoad {
+    int64_t items;    // pairs or quads
+    int64_t slots;    // wavefronts resident at once
+    double steps;     // block rows a lane goes through per item
+    int64_t even;     // items handed out in equal shares
+};
+// Whether the four-pair kernel is the faster one.  Either launch takes rounds of `slots` items, a nearly empty round as long
+// as a full one (unless the last items are handed out one by one), and a round about as long as its steps.  step: a step of
+// the four-pair kernel next to one of the other; lone: where few quads leave its wavefronts alone on their SIMDs, next to
+// where they share them.
+// One-pair and four-pair, us per call (n x n; (n): K(X, X)):
+//   L = 128, order 1, d = 3: 64 / 80 / 96 / 128: 377 / 613 / 819 / 1393 and 406 / 527 / 944 / 1156
+//                            (72) / (84) / (112) / (128): 342 / 347 / 613 / 784 and 351 / 369 / 523 / 942
+//   L = 64, order 0, d = 4:  (60) / (72) / (112), 64, 128: 80 / 133 / 233, 141, 490 and 86 / 96 / 146, 118, 361
+//   L = 120, order 1, d = 8 (alone): 64 / 80 / 160 / 256: 711 / 1082 / 3641 / 8982 and 766 / 1343 / 3307 / 7420
+//   L = 128, order 2, d = 3 (alone): 64 / 80 / 96 / 128: 929 / 1580 / 2110 / 3931 and 878 / 1298 / 2569 / 2857
+//   L = 200, order 0, d = 4 (chained): 40 / 48 / 64 / 128: 597 / 967 / 1173 / 4584 and 677 / 722 / 860 / 2267
+inline bool four_pays(const SweepLoad& one, const SweepLoad& four, double step, double lone)
+{
+    auto rounds = [](const SweepLoad& l) {
+        return l.even < l.items ? (double)l.items / (double)l.slots + 0.3 : (double)((l.items + l.slots - 1) / l.slots);
+    };
+    if ((four.items < four.slots ? four.items : four.slots) <= 4 * kNumCU) step *= lone;
+    return rounds(four) * four.steps * step < rounds(one) * one.steps;
+}
+// The fewest x paths for it next to the solo kernels: with fewer the quads are half empty and do not pay however many there
+// are (n x m, L = 64, order 0, d = 4: 1 x 8192 / 2 x 8192 / 5 x 4000 / 7 x 1000: 804 / 1050 / 677 / 261 us and 1248 / 1305 /
+// 787 / 219; L = 100, order 1, d = 5: 3 x 4000 / 5 x 4000: 1403 / 2057 and 1401 / 1773; L = 40, order 2, d = 5: 5 x 1000 /
+// 6 x 3000: 435 / 1243 and 490 / 1021).
+// Nor is it taken below kFourMinQuads, counted as for K(X, Y): half a wavefront per SIMD.
+constexpr int64_t kFourMinQuads = 512;
+constexpr int four_min_paths(int BL) { return BL == 0 ? 7 : (BL == 1 ? 5 : 6); }
 constexpr int kTileRowPad = 8;     // backward: node columns kept left of column 0 in the pair's bottom row (all 1)
 constexpr int kTileCkChunks = 8;   // backward: chunks of 8 macro-steps between two checkpoints (kept in LDS)
 
@@ -248,6 +283,7 @@ inline Plan make_plan(bool backward, bool gram, bool symmetric, int64_t nx, int6
     p.xstride = (int64_t)p.DP * p.rpad;
     p.ystride = (int64_t)p.DP * p.qpad;
 
+    int64_t slots = 1;           // wavefronts of a launch with one pair each that the chip holds at once
     const int NVR = R + C + 1;   // block input edges kept per macro-step in the ring
     const size_t ring_step = (size_t)kWave * NVR * elem;
     p.coop = (p.ns >= 2 && p.npairs <= kCoopMaxPairs && !second_chance) ? 1 : 0;
@@ -335,6 +371,7 @@ inline Plan make_plan(bool backward, bool gram, bool symmetric, int64_t nx, int6
         int64_t want = (p.npairs + kWavesPerWG - 1) / kWavesPerWG;
         int64_t cap = (int64_t)kNumCU * wg_per_cu;
         if (second_chance && cap > kNumCU) cap = kNumCU;
+        slots = cap * kWavesPerWG;
         p.grid = (int)(want < cap ? want : cap);
         p.nslots = (int64_t)p.grid * kWavesPerWG;
     }
@@ -419,6 +456,7 @@ inline Plan make_plan(bool backward, bool gram, bool symmetric, int64_t nx, int6
             if (wgpc > maxwg) wgpc = maxwg;
             const int64_t want = (p.npairs + kWavesPerWG - 1) / kWavesPerWG;
             const int64_t cap = (int64_t)kNumCU * wgpc;
+            slots = cap * kWavesPerWG;
             p.grid = (int)(want < cap ? want : cap);
             p.nslots = (int64_t)p.grid * kWavesPerWG;
             p.S = kLockS;
@@ -452,10 +490,17 @@ inline Plan make_plan(bool backward, bool gram, bool symmetric, int64_t nx, int6
         p.nseg = NT / kLockS;
     }
 
-    // Four-pair mode: backward calls for Gram matrices with enough quads of pairs to fill the chip.
+    // Symmetric Gram matrix: k(x, y) = k(y, x) bit for bit, so the solo, four-pair and tile kernels solve the pairs n <= m
+    // only, write both entries of K, and use the sum of the two upstream gradients.  Eq. (1) is symmetric under
+    // a swap of the paths together with their dyadic orders, so this holds for equal orders only; with unequal
+    // orders K(X, X) is not a symmetric matrix and all N^2 pairs are solved over the shared increment buffer.
+    const bool may_tri = symmetric && gram && nx == ny && lam1 == lam2;
+
+    // Four-pair mode: backward calls for Gram matrices, where it pays (four_pays).
     bool four = false;
-    if (may_four && backward && gram && p.uncompute && !keep && !second_chance && !lead_lag && !p.tile && p.DT >= 2 &&
-        ny * ((nx + kQuadPairs - 1) / kQuadPairs) >= four_min_quads(p.solo != 0, p.DT)) {
+    int64_t four_slots = 0;
+    if (may_four && backward && gram && p.uncompute && !keep && !second_chance && !lead_lag && !p.tile && !p.lock && !p.coop &&
+        p.DT >= 2 && gram_quads(false, nx, ny) >= kFourMinQuads && (!p.solo || nx >= four_min_paths(p.BL))) {
         const int DT = four_channels(p.DT, p.d), band = kWave / kQuadPairs * four_rows(p.BL, DT);
         const int bands = (p.mb + band - 1) / band;
         size_t used = 0;
@@ -464,8 +509,26 @@ inline Plan make_plan(bool backward, bool gram, bool symmetric, int64_t nx, int6
         const size_t o_gyp = lds_take((size_t)p.q * DT * elem);
         const size_t o_gring = lds_take((size_t)kQuadPairs * four_gring_stride(DT) * elem);
         const size_t o_ring = lds_take((size_t)(bands > 1 ? 3 : 1) * kWave * C * elem);
-        if (four_occupancy(p.BL, DT) > 0 && used <= kLdsPerCU / 4) {
-            four = true;
+        const int occupancy = four_occupancy(p.BL, DT);
+        int waves = used ? (int)(kLdsPerCU / used) : 0;                  // per compute unit
+        if (waves > 4 * occupancy) waves = 4 * occupancy;
+        if (waves >= 4) {
+            const SweepLoad one = {may_tri && p.solo ? nx * (nx + 1) / 2 : nx * ny, slots,
+                                   p.solo ? (double)p.lk_M * p.lk_NT : (double)p.ns * (p.nb + kWave - 1), p.npairs};
+            const int64_t steps = (int64_t)bands * four_rows(p.BL, DT) * (p.nb + kWave / kQuadPairs - 1);
+            SweepLoad quads = {gram_quads(may_tri, nx, ny), (int64_t)kNumCU * waves, (double)steps, 0};
+            quads.even = four_even_share(quads.items, quads.items < quads.slots ? quads.items : quads.slots,
+                                         steps * (C * C * 11 + 15 + 5 * DT));
+            // (Eight channels and few columns, chained: the x-side sums, which both add to memory, are most of the time.
+            // 64 x 64 paths of 200 and 30 points, order 0: 596 us and 690.)
+            const bool sums = !p.solo && p.DT == 8 && p.nb < kWave;
+            const bool alone = p.solo && occupancy == 2 && solo_bwd_waves_per_simd(p.BL, p.lk_M, p.DT) == 1;
+            const double step = !p.solo ? 0.65 : (alone ? 1.75 : (p.lk_M == 2 && p.DT >= 5 ? 0.88 : 1.0));
+            four = !sums && four_pays(one, quads, step, alone && p.DT >= 8 ? 0.85 : 0.73);
+            four_slots = quads.slots;
+            if (four) p.qd_even = quads.even;
+        }
+        if (four) {
             p.lock = 0; p.coop = 0; p.solo = 1; p.four = 1;
             p.DT = DT;
             p.lk_M = bands > 1 ? 2 : 1;
@@ -480,11 +543,7 @@ inline Plan make_plan(bool backward, bool gram, bool symmetric, int64_t nx, int6
         }
     }
 
-    // Symmetric Gram matrix: k(x, y) = k(y, x) bit for bit, so the solo and tile kernels solve the pairs n <= m
-    // only, write both entries of K, and use the sum of the two upstream gradients.  Eq. (1) is symmetric under
-    // a swap of the paths together with their dyadic orders, so this holds for equal orders only; with unequal
-    // orders K(X, X) is not a symmetric matrix and all N^2 pairs are solved over the shared increment buffer.
-    if (symmetric && gram && nx == ny && lam1 == lam2 && (p.solo || p.tile)) {
+    if (may_tri && (p.solo || p.tile)) {
         p.tri = 1;
         p.npairs = nx * (nx + 1) / 2;
         const int64_t want = (p.npairs + kWavesPerWG - 1) / kWavesPerWG;
@@ -492,23 +551,14 @@ inline Plan make_plan(bool backward, bool gram, bool symmetric, int64_t nx, int6
         p.nslots = (int64_t)p.grid * kWavesPerWG;
     }
     // The sequence of quads: rows of the Gram matrix in groups of four x paths (symmetric: the pairs n <= m of row m).
-    if (p.tri) {
-        const int64_t J = nx / kQuadPairs, e = nx % kQuadPairs;
-        p.nquads = 2 * J * (J + 1) + e * (J + 1);
-    } else if (gram) {
-        p.nquads = ny * ((nx + kQuadPairs - 1) / kQuadPairs);
-    }
+    if (gram) p.nquads = gram_quads(p.tri != 0, nx, ny);
     if (four) {
-        int waves = (int)(kLdsPerCU / p.lds_bytes);                      // per compute unit
-        const int regs = 4 * four_occupancy(p.BL, p.DT);
-        if (waves > regs) waves = regs;
-        const int64_t cap = (int64_t)kNumCU * waves;
-        p.grid = (int)(p.nquads < cap ? p.nquads : cap);
+        p.grid = (int)(p.nquads < four_slots ? p.nquads : four_slots);
         p.nslots = p.grid;
-        p.qd_even = four_even_share(p.nquads, p.nslots, (int64_t)p.fv_bands * p.lk_NT * four_rows(p.BL, p.DT) *
-                                                            (C * C * 11 + 15 + 5 * p.DT));
-        p.nflags = 1;   // the launch's counter
     }
+    // The four-pair launch's counter (bd_flags[0]); the other kernels of a backward Gram call leave its place free, so that
+    // what follows it does not move with the launch mode.
+    if (backward && gram && !keep) p.nflags = 1;
 
     // Quad mode: forward calls for Gram matrices (the four pairs of a wavefront share the y path) on the shapes of the
     // tile kernels and on those of the solo kernels whose blocks hold all of the refinement.  The sequence is the Gram

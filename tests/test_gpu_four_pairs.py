@@ -32,7 +32,7 @@ def paths(seed, n, L, d, var):
     (70, 0, 18, 18, 2, 0, 1, 0, True, torch.float64),        # K(X, X) with unequal orders: every pair
     (90, 50, 35, 30, 12, 0, 0, 1, False, torch.float64),      # twelve channels, two bands
     (70, 40, 20, 34, 14, 2, 2, 0, False, torch.float64),      # sixteen channels, blocks of 4 x 4 cells
-    (4600, 1, 6, 200, 2, 0, 0, 0, False, torch.float64),     # fewer rows than lanes, one y path
+    (4600, 1, 6, 20, 2, 0, 0, 0, False, torch.float64),      # fewer rows than lanes, one y path
 ])
 def test_four_pairs_per_wave(nx, ny, L1, L2, d, lam1, lam2, flags, sym, dtype):
     X = paths(1300 + nx + d, nx, L1, d, 1.0 / (d * L1))

@@ -177,6 +177,27 @@ def test_launch_plan_of_the_five_configurations(lib):
     assert p["mode"] == "cooperative" and p["kernel"].startswith("sweep_bwd_coop_kernel")
 
 
+def test_where_backward_gram_calls_take_four_pairs_per_wave(lib):
+    # rounds of the chip's wavefronts, a quad of pairs taking two to three times as long as a pair: (N, M, L, d, order)
+    four = lambda N, M, L1, L2, d, lam: "pairs_per_wave=4" in binding.sigkernel_describe(  # noqa: E731
+        binding.SK_OP_GRAM_BWD, N, M, L1, L2, d, lam, lam, 0, binding.SK_F64)
+    for N, expected in ((40, False), (64, False), (80, True), (96, False), (128, True), (256, True)):
+        assert four(N, N, 128, 128, 3, 1) == expected, N     # 96: 2304 quads are two rounds, the second nearly empty
+    for N, expected in ((40, False), (48, True), (96, True), (256, True)):
+        assert four(N, N, 100, 100, 5, 1) == expected, N
+    for N, expected in ((40, False), (48, True), (128, True)):
+        assert four(N, N, 200, 200, 4, 0) == expected, N     # next to kernels that chain strips
+    # quads that are half empty or worse
+    for N in (1, 2, 3):
+        for M in (600, 2048, 8192):
+            assert not four(N, M, 64, 64, 4, 0) and not four(N, M, 20, 20, 3, 0) and not four(N, M, 40, 40, 5, 2), (N, M)
+    assert not four(1, 8192, 200, 200, 4, 0) and four(13, 1500, 64, 64, 4, 0)
+    # few pairs, and none at all
+    assert not four(8, 8, 64, 64, 4, 0) and not four(1, 1, 5, 5, 2, 0) and not four(16, 32, 20, 20, 3, 0)
+    # shapes whose y copy leaves no room for four wavefronts per compute unit
+    assert not four(100, 100, 60, 900, 16, 0) and not four(100, 100, 30, 3000, 4, 1)
+
+
 def test_launch_plan_stays_inside_the_hardware_limits(lib):
     f64 = binding.SK_F64
     for op in (binding.SK_OP_FWD, binding.SK_OP_BWD):
