@@ -141,6 +141,18 @@ constexpr int quad_max_rows(int BL, int DT)
     if (DT == 16) return BL == 0 ? 4 : 0;
     return 8;
 }
+// Whether the quad kernel with eight channels and M = 5 to 8 rows per lane is faster than the solo kernel it replaces, in
+// rounds of block rows as in four_pays; a wavefront alone on its SIMD goes through them in 0.5 (quad) and 0.8 (solo) of the
+// time it takes where it shares it.  Solo and quad, us per call: L = 128, order 0, d = 8: 32 x 32 / 24 x 100 / 1 x 2000 /
+// 2 x 1000 / 128 x 128: 35 / 62 / 55 / 51 / 266 and 50 / 50 / 91 / 56 / 164; L = 70: 25 / 44 / 41 / 37 / 178 and 25 / 25 / 45 /
+// 29 / 67.  (Up to four rows, and up to six channels, the kernel is always taken.)
+inline bool quad_pays(int64_t pairs, int64_t slots1, double steps1, int64_t quads, int64_t slots4, double steps4)
+{
+    constexpr int64_t kSimds = 4 * kNumCU;
+    if (slots1 > 2 * kSimds) slots1 = 2 * kSimds;
+    const double r1 = (double)((pairs + slots1 - 1) / slots1), r4 = (double)((quads + slots4 - 1) / slots4);
+    return r4 * steps4 * (quads <= kSimds ? 0.5 : 0.85) < r1 * steps1 * (pairs <= kSimds ? 0.8 : 1.0);
+}
 // Row stride of the y copy in LDS (doubles): for an even channel count a multiple of 16 bytes that spreads the
 // 16-byte reads of lanes at consecutive rows over the banks; an odd count does that by itself.
 constexpr int quad_y_stride(int DT) { return DT % 2 ? DT : (DT == 6 ? 10 : DT + 2); }
@@ -572,7 +584,10 @@ inline Plan make_plan(bool backward, bool gram, bool symmetric, int64_t nx, int6
         int M = (p.mb + lanes - 1) / lanes;
         if (M < kQuadMinRows) M = kQuadMinRows;
         const size_t ycopy = align_up((size_t)(p.nb + 1) * quad_y_stride(p.DT) * elem, 256);   // the y copy and a row of zeros
-        if (M <= quad_max_rows(p.BL, p.DT) && p.mb <= M * lanes && ycopy * kWavesPerWG <= kLdsPerCU) {
+        const int64_t quad_slots = 4 * kNumCU * (2 * ycopy * kWavesPerWG <= kLdsPerCU ? 2 : 1);
+        const bool pays = !p.solo || p.DT < 8 || M <= 4 ||
+                          quad_pays(p.npairs, slots, (double)p.lk_M * p.lk_NT, p.nquads, quad_slots, (double)M * (p.nb + lanes - 1));
+        if (M <= quad_max_rows(p.BL, p.DT) && p.mb <= M * lanes && ycopy * kWavesPerWG <= kLdsPerCU && pays) {
             p.tile = 0; p.solo = 0; p.quad = 1;
             p.lk_M = M; p.lk_ns = 1; p.lk_NT = p.nb + lanes - 1; p.lk_padb = M * lanes - p.mb;
             p.y_lds = 1;

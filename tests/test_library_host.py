@@ -198,6 +198,17 @@ def test_where_backward_gram_calls_take_four_pairs_per_wave(lib):
     assert not four(100, 100, 60, 900, 16, 0) and not four(100, 100, 30, 3000, 4, 1)
 
 
+def test_where_forward_gram_calls_with_eight_channels_take_the_quad_kernel(lib):
+    mode = lambda N, M, L1, L2, d, lam: _plan(binding.SK_OP_GRAM, N, M, L1, L2, d, lam, lam, 0, binding.SK_F64)["mode"]  # noqa: E731
+    for N, M, expected in ((32, 32, "solo"), (40, 40, "solo"), (1, 2000, "solo"), (2, 1000, "solo"), (1, 8192, "solo"),
+                           (24, 100, "quad"), (64, 64, "quad"), (500, 123, "quad")):
+        assert mode(N, M, 128, 128, 8, 0) == expected, (N, M)
+        assert mode(N, M, 127, 127, 7, 1) == expected, (N, M)
+    assert mode(32, 32, 100, 77, 7, 0) == "solo" and mode(500, 123, 100, 77, 7, 0) == "quad"
+    assert mode(32, 32, 70, 70, 8, 0) == "quad" and mode(1, 2000, 70, 70, 8, 0) == "solo"
+    assert mode(32, 32, 128, 128, 6, 0) == "quad" and mode(40, 40, 60, 60, 8, 1) == "quad"    # up to six channels, or four rows
+
+
 def test_launch_plan_stays_inside_the_hardware_limits(lib):
     f64 = binding.SK_F64
     for op in (binding.SK_OP_FWD, binding.SK_OP_BWD):
