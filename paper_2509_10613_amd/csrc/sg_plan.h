@@ -80,12 +80,24 @@ inline int matrix_words(int64_t VB, int64_t D, int Q) { return VB * matrix_waves
 // in the chains over the prefix, which the other kernel spreads over more words of a lane: there only while the chip is not
 // full and a segment's latency counts, up to two wavefronts per SIMD: (500, 65, 8, 4) 67 and 60, (128, 256, 7, 4) 203 and
 // 109, (128, 256, 5, 5) 220 and 197; but (2000, 65, 8, 4) 164 and 195, (4000, 65, 5, 3) 99 and 138, (128, 512, 8, 5) 552 and
-// 741.
-inline bool matrix_pays(int64_t VB, int64_t D, int N, int64_t segments)
+// 741.  Lead-lag paths, where the other kernel leaves out the half that stands still (L points, twice the segments): (128,
+// 512, 8, 4) 1904 and 1398, (128, 256, 4, 4) 280 and 199, (500, 65, 3, 4) 115 and 89, (16, 300, 5, 5) 638 and 462; only with
+// eight channels and five levels, where its waves come out even, it stays ahead of more than one wavefront per SIMD: (28,
+// 300, 4, 5) 451 and 290, (37, 300, 4, 5) 436 and 456, (64, 300, 4, 5) 437 and 458.
+inline bool matrix_pays(int64_t VB, int64_t D, int N, int64_t segments, bool lead_lag)
 {
     if (D < kMatrixMinD || D > 16 || N < 3 || N - 2 > kMatrixMaxQ || segments < kMatrixSteps) return false;
-    return (D >= 11 && N <= 4) || VB * matrix_waves(D, N - 2, matrix_words(VB, D, N - 2)) <= 2 * kSimds;
+    if (D >= 11 && N <= 4) return true;
+    const int64_t most = lead_lag && D == 8 && N == 5 ? kSimds : 2 * kSimds;
+    return VB * matrix_waves(D, N - 2, matrix_words(VB, D, N - 2)) <= most;
 }
+// Pieces of long paths for the matrix kernel (make_plan): segments from which a path is long, the least of a piece, and the
+// entries of a signature up to which more pieces are worth their products.  (B, L, D, N) by the matrix kernel's waves, and
+// as cut by this rule: (128, 1024, 5, 4) 350 and 196, (32, 1024, 10, 4) 367 and 297, (128, 1024, 10, 3) 236 and 194;
+// lead-lag, D channels in all: (16, 1024, 12, 4) 730 and 455, (32, 1024, 10, 4) 722 and 490, (8, 1024, 16, 4) 735 and 511;
+// but (1, 1024, 10, 5) lead-lag, 111111 entries, 411 and 455, (64, 300, 6, 5) 144 and 204, and lead-lag (450, 300, 10, 3), 598
+// segments, 251 and 288.
+constexpr int64_t kMatrixLong = 768, kMatrixPiece = 120, kMatrixPieceEntries = 100000;
 
 inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
@@ -234,11 +246,23 @@ inline Plan make_plan(int64_t B, int64_t L, int64_t d, int N, bool time_aug, boo
             P = force_P;
         } else if (B > 0 && p.n >= 2 * kMinPiece && p.sig_len < ((int64_t)1 << 31)) {
             // backward, the products and their adjoints cost several launches: only when the chip is mostly empty
-            const int64_t w1 = may_matrix && matrix_pays(B, D, N, p.n) ? B * matrix_waves(D, N - 2, 1)
-                               : p.PW > 1 ? (B + p.PW - 1) / p.PW : B * p.WP;
             const int64_t few = backward ? kSimds / 2 : kSimds, want = backward ? kSimds : 2 * kSimds;
-            if (w1 < few)
-                while (P < kMaxPieces && w1 * P < want && p.n / (2 * P) >= kMinPiece) P *= 2;
+            auto pieces = [&](int64_t w1, int64_t least) {
+                int q = 1;
+                if (w1 < few)
+                    while (q < kMaxPieces && w1 * q < want && p.n / (2 * q) >= least) q *= 2;
+                return q;
+            };
+            const int64_t w1 = p.PW > 1 ? (B + p.PW - 1) / p.PW : B * p.WP;
+            if (may_matrix && matrix_pays(B, D, N, p.n, lead_lag)) {
+                // The matrix kernel has more waves for the same words, and cuts paths less.  Long paths go by the other
+                // kernel's waves down to pieces of kMatrixPiece segments: the time of a segment counts there, not the waves.
+                P = pieces(B * matrix_waves(D, N - 2, 1), kMinPiece);
+                const int q = p.n >= kMatrixLong && p.sig_len < kMatrixPieceEntries ? pieces(w1, kMatrixPiece) : 1;
+                if (q > P) P = q;
+            } else {
+                P = pieces(w1, kMinPiece);
+            }
         }
         if (P > 1) {
             if ((P & (P - 1)) != 0 || P > kMaxPieces) { p.why = "the number of pieces must be a power of two up to 1024"; return p; }
@@ -270,7 +294,7 @@ inline Plan make_plan(int64_t B, int64_t L, int64_t d, int N, bool time_aug, boo
         }
     } else {
         if (p.DT == 0 && D > kBwdMaxRuntimeD) { p.why = "backward: more than 1024 channels"; return p; }
-        if (may_matrix && matrix_pays(p.VB, D, N, p.Lc)) {
+        if (may_matrix && matrix_pays(p.VB, D, N, p.Lc, lead_lag)) {
             p.matrix_Q = N - 2;
             p.matrix_S = matrix_words(p.VB, D, p.matrix_Q);
             p.matrix_WP = matrix_waves(D, p.matrix_Q, p.matrix_S);

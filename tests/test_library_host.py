@@ -198,6 +198,23 @@ def test_where_backward_gram_calls_take_four_pairs_per_wave(lib):
     assert not four(100, 100, 60, 900, 16, 0) and not four(100, 100, 30, 3000, 4, 1)
 
 
+def test_where_signature_gradients_take_the_matrix_kernel_and_how_paths_are_cut(lib):
+    LL = binding.SK_FLAG_LEAD_LAG
+
+    def plan(B, L, d, N, flags=0):
+        text = binding.signature_bwd_describe(B, L, d, N, flags, binding.SK_F64)
+        return "matrix_kernel=horner" in text, int(re.search(r"pieces_per_path=(\d+)", text).group(1))
+    # eight channels and five levels, lead-lag: one wavefront per SIMD and no more
+    assert plan(28, 300, 4, 5, LL)[0] and not plan(37, 300, 4, 5, LL)[0] and not plan(64, 60, 4, 5, LL)[0]
+    assert plan(64, 60, 8, 5)[0] and plan(128, 512, 8, 4, LL)[0] and plan(128, 256, 4, 4, LL)[0]
+    # long paths are cut by the other kernel's wavefronts, into pieces of at least 120 segments ...
+    assert plan(128, 1024, 5, 4) == (True, 4) and plan(32, 1024, 10, 4) == (True, 4) and plan(128, 1024, 10, 3) == (True, 8)
+    assert plan(16, 1024, 6, 4, LL) == (True, 8) and plan(8, 1024, 8, 4, LL) == (True, 4)
+    # ... others, and those with many entries, by the matrix kernel's
+    assert plan(64, 300, 6, 5) == (True, 1) and plan(450, 300, 5, 3, LL) == (True, 1) and plan(1, 1024, 12, 5) == (True, 4)
+    assert plan(32, 1024, 5, 4, binding.SK_FLAG_TIME_AUG)[1] == plan(32, 1024, 6, 4)[1]
+
+
 def test_where_forward_gram_calls_with_eight_channels_take_the_quad_kernel(lib):
     mode = lambda N, M, L1, L2, d, lam: _plan(binding.SK_OP_GRAM, N, M, L1, L2, d, lam, lam, 0, binding.SK_F64)["mode"]  # noqa: E731
     for N, M, expected in ((32, 32, "solo"), (40, 40, "solo"), (1, 2000, "solo"), (2, 1000, "solo"), (1, 8192, "solo"),
