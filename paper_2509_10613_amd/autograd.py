@@ -16,15 +16,61 @@ library's flag takes t_i = i/(L-1)) is an ordinary channel: ``with_times(x, t)``
 
 The gradients are first-order only (the backward pass is not itself differentiable).
 """
+import threading
+import weakref
+
 import torch
 
 from . import binding as sk
 
 
-# Bytes of workspace a forward call may hold on to for its backward call: a small part of the card's 288 GB.  The sweep
-# of 32 pairs of 2048 points (order 2) takes 1.6 GiB; without it the backward call sweeps forward once more (6.49 ms a
-# training step against 5.14 ms).
-_KEEP_LIMIT = 1 << 32
+# Bytes of workspace a forward call may hold on to for its backward call, as long as its graph lives.  A sweep that takes
+# more is kept while all such sweeps of the live graphs together take at most _KEEP_LARGE bytes on their device, and its
+# workspace is given back by the first backward call.  Training steps without and with it: 32 pairs of 2048 points, order 2
+# (1.6 GiB) 6.54 and 5.20 ms; lead-lag Grams of 128 x 128 paths of 101 points, d = 4 (1.5 GiB) 1.77 and 1.61 ms, K(X, X) of the
+# same 0.99 and 0.92 ms.
+_KEEP_LIMIT = 1 << 30
+_KEEP_LARGE = 1 << 32
+
+_large_lock = threading.RLock()   # (taken again if a tensor is collected while it is held)
+_large_held = {}                  # device: bytes of the live workspaces above _KEEP_LIMIT
+
+
+def _give_back(device, nbytes):
+    with _large_lock:
+        _large_held[device] -= nbytes
+
+
+def _keep_workspace(nbytes, device):
+    """A workspace of `nbytes` to keep for the backward call, or None: it exceeds what may be kept, or the device has no room
+    for it (the calls go on without one)."""
+    nbytes = max(int(nbytes), 256)
+    if nbytes <= _KEEP_LIMIT:
+        try:
+            return torch.empty(nbytes, dtype=torch.uint8, device=device)
+        except torch.OutOfMemoryError:
+            return None
+    key = str(device)
+    with _large_lock:
+        if _large_held.get(key, 0) + nbytes > _KEEP_LARGE:
+            return None
+        _large_held[key] = _large_held.get(key, 0) + nbytes
+    try:
+        ws = torch.empty(nbytes, dtype=torch.uint8, device=device)
+    except torch.OutOfMemoryError:
+        _give_back(key, nbytes)
+        return None
+    weakref.finalize(ws, _give_back, key, nbytes).atexit = False
+    return ws
+
+
+def _take_workspace(ctx):
+    """The workspace the forward call kept, or None.  A large one is taken out of the graph: a further backward call through
+    it sweeps forward itself."""
+    ws = ctx.ws
+    if ws is not None and ws.numel() > _KEEP_LIMIT:
+        ctx.ws = None
+    return ws
 
 
 class _PairKernel(torch.autograd.Function):
@@ -36,15 +82,14 @@ class _PairKernel(torch.autograd.Function):
         ctx.args = (lam1, lam2, flags)
         ctx.ws = None
         # Where the launch mode can hand its forward sweep to the backward call, this call keeps it in a workspace of
-        # its own, which lives until the graph is freed (the grid the paper's backward pass takes over from its
-        # forward pass, here as checkpoints).
+        # its own (the grid the paper's backward pass takes over from its forward pass, here as checkpoints).
         B, L1, d = x.shape
         if (ctx.needs_input_grad[0] or ctx.needs_input_grad[1]) and sk.keeps_forward(B, L1, y.shape[1], d, lam1, lam2,
                                                                                      flags, sk._dt(x)):
             need = sk.sigkernel_workspace_bytes(sk.SK_OP_FWD, B, 0, L1, y.shape[1], d, lam1, lam2,
                                                 flags | sk.SK_FLAG_KEEP_FORWARD, sk._dt(x))
-            if need <= _KEEP_LIMIT:    # large batches of pairs would pin gigabytes per live graph: they sweep twice
-                ctx.ws = torch.empty(max(int(need), 256), dtype=torch.uint8, device=x.device)
+            ctx.ws = _keep_workspace(need, x.device)
+            if ctx.ws is not None:
                 return sk.sigkernel_fwd(x, y, lam1, lam2, flags | sk.SK_FLAG_KEEP_FORWARD, ws=ctx.ws)
         return sk.sigkernel_fwd(x, y, lam1, lam2, flags)
 
@@ -55,9 +100,10 @@ class _PairKernel(torch.autograd.Function):
         want_x, want_y = ctx.needs_input_grad[0], ctx.needs_input_grad[1]
         if not (want_x or want_y):
             return None, None, None, None, None
-        if ctx.ws is not None:
+        ws = _take_workspace(ctx)
+        if ws is not None:
             _, gx, gy = sk.sigkernel_bwd(x, y, grad_k.contiguous(), lam1, lam2, flags | sk.SK_FLAG_HAVE_FORWARD,
-                                         want_x=want_x, want_y=want_y, ws=ctx.ws)
+                                         want_x=want_x, want_y=want_y, ws=ws)
         else:
             _, gx, gy = sk.sigkernel_bwd(x, y, grad_k.contiguous(), lam1, lam2, flags, want_x=want_x, want_y=want_y)
         return gx, gy, None, None, None
@@ -65,7 +111,7 @@ class _PairKernel(torch.autograd.Function):
 
 def _gram_keep_workspace(ctx, X, Y, lam1, lam2, flags):
     """A workspace of this call's own if it wants gradients, the launch mode can keep the forward sweep of a Gram matrix
-    for its backward call, and that costs no more than _KEEP_LIMIT bytes; else None."""
+    for its backward call, and that much may be kept; else None."""
     if not any(ctx.needs_input_grad[:2]):
         return None
     N, L1, d = X.shape
@@ -77,9 +123,7 @@ def _gram_keep_workspace(ctx, X, Y, lam1, lam2, flags):
         return None
     need = sk.sigkernel_workspace_bytes(sk.SK_OP_GRAM, N, M, L1, L2, d, lam1, lam2, flags | sk.SK_FLAG_KEEP_FORWARD,
                                         sk._dt(X))
-    if need > _KEEP_LIMIT:
-        return None
-    return torch.empty(max(int(need), 256), dtype=torch.uint8, device=X.device)
+    return _keep_workspace(need, X.device)
 
 
 class _GramKernel(torch.autograd.Function):
@@ -98,8 +142,9 @@ class _GramKernel(torch.autograd.Function):
     def backward(ctx, grad_K):
         X, Y = ctx.saved_tensors
         lam1, lam2, flags = ctx.args
-        if ctx.ws is not None:
-            _, gX, gY = sk.sigkernel_gram(X, Y, grad_K.contiguous(), lam1, lam2, flags | sk.SK_FLAG_HAVE_FORWARD, ws=ctx.ws)
+        ws = _take_workspace(ctx)
+        if ws is not None:
+            _, gX, gY = sk.sigkernel_gram(X, Y, grad_K.contiguous(), lam1, lam2, flags | sk.SK_FLAG_HAVE_FORWARD, ws=ws)
         else:
             _, gX, gY = sk.sigkernel_gram(X, Y, grad_K.contiguous(), lam1, lam2, flags)
         return (gX if ctx.needs_input_grad[0] else None), (gY if ctx.needs_input_grad[1] else None), None, None, None
@@ -120,8 +165,9 @@ class _GramKernelSym(torch.autograd.Function):
     def backward(ctx, grad_K):
         (X,) = ctx.saved_tensors
         lam1, lam2, flags = ctx.args
-        keep = sk.SK_FLAG_HAVE_FORWARD if ctx.ws is not None else 0
-        _, gX, _ = sk.sigkernel_gram(X, X, grad_K.contiguous(), lam1, lam2, flags | keep, ws=ctx.ws)   # total derivative
+        ws = _take_workspace(ctx)
+        keep = sk.SK_FLAG_HAVE_FORWARD if ws is not None else 0
+        _, gX, _ = sk.sigkernel_gram(X, X, grad_K.contiguous(), lam1, lam2, flags | keep, ws=ws)   # total derivative
         return gX, None, None, None
 
 
