@@ -101,11 +101,12 @@ int sigkernel_fwd(const void* x, const void* y, void* k, int64_t B, int64_t L1, 
  *   grad_x[B,L1,d] = dF/dx,  grad_y[B,L2,d] = dF/dy   (either may be NULL = not wanted)
  * and, if k_out != NULL, k_out[B] = k(x[b], y[b]) (the forward values are recomputed inside).
  * By default the reverse sweep recovers the forward values it needs by inverting Eq. (1) between exact
- * checkpoints eight block steps apart (32 in one launch mode), and checks the recovered state against every
- * checkpoint and, at the left end of the grid, against the boundary value 1.  Increment inner products of order one
- * make the inverse recurrence ill-conditioned (it divides by B(p)): where the recovered state differs from the exact
- * one by more than 1e-11 of the largest forward value met along the row, the pair is left out of the gradient sums
- * and solved once more, in the same call, by the variant that replays forward segments, which has no such limit.
+ * checkpoints eight block steps apart (64 in one launch mode, four or eight in another), and checks the recovered state
+ * against every checkpoint and, at the left end of the grid, against the boundary value 1.  Increment inner products of
+ * order one make the inverse recurrence ill-conditioned (it divides by B(p)): where the recovered state differs from the
+ * exact one by more than 1e-11 (3e-12 in the latter mode) of the largest forward value met along the row, the pair is left
+ * out of the gradient sums and solved once more, in the same call, by the variant that replays forward segments, which has
+ * no such limit.
  * The gradients are therefore the exact ones of the scheme for any input (Section 3.4); such pairs only cost more
  * time (a few launch modes cannot tell which pair drifted and then solve every pair of the call again).
  * SK_FLAG_BWD_REPLAY selects the replaying variant for the whole call from the start: the choice for data sets
@@ -206,7 +207,9 @@ int sigkernel_event_timing_read(double* fwd_ms, int* fwd_launches, double* bwd_m
  * the backward pass, kept for the backward call; 2: its reverse half; 0: neither); lead_lag_form (none, or
  * checkerboard: the grid of the caller's increments swept with one more level of refinement whose off-diagonal
  * quadrants carry no increment product); second_launch_lds_bytes (backward calls: LDS per workgroup of the launch
- * that solves drifted pairs once more).  Same arguments as sigkernel_workspace_bytes.
+ * that solves drifted pairs once more); drifted_pairs_counter_at (where in the workspace the call counts those pairs);
+ * pairs_per_wave; for Gram calls with N == M and L1 == L2 also symmetric_mode and symmetric_grid, of the call with Y == X.
+ * Same arguments as sigkernel_workspace_bytes.
  * Pure host arithmetic: no GPU call.  Returns SK_OK or a negative error code.
  */
 int sigkernel_describe(int op, int64_t B_or_N, int64_t M, int64_t L1, int64_t L2, int64_t d, int lam1, int lam2,

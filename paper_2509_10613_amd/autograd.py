@@ -109,7 +109,7 @@ class _PairKernel(torch.autograd.Function):
         return gx, gy, None, None, None
 
 
-def _gram_keep_workspace(ctx, X, Y, lam1, lam2, flags):
+def _gram_keep_workspace(ctx, X, Y, lam1, lam2, flags, symmetric=False):
     """A workspace of this call's own if it wants gradients, the launch mode can keep the forward sweep of a Gram matrix
     for its backward call, and that much may be kept; else None."""
     if not any(ctx.needs_input_grad[:2]):
@@ -119,7 +119,8 @@ def _gram_keep_workspace(ctx, X, Y, lam1, lam2, flags):
     if not sk.keeps_forward(N, L1, L2, d, lam1, lam2, flags, sk._dt(X), gram_M=M):
         return None
     # (the backward sweep with four pairs per wavefront makes its own forward sweep, and is faster than the kept form)
-    if " pairs_per_wave=4" in sk.sigkernel_describe(sk.SK_OP_GRAM_BWD, N, M, L1, L2, d, lam1, lam2, flags, sk._dt(X)):
+    desc = sk.sigkernel_describe(sk.SK_OP_GRAM_BWD, N, M, L1, L2, d, lam1, lam2, flags, sk._dt(X))
+    if (" symmetric_mode=four " in desc) if symmetric else desc.startswith("mode=four "):
         return None
     need = sk.sigkernel_workspace_bytes(sk.SK_OP_GRAM, N, M, L1, L2, d, lam1, lam2, flags | sk.SK_FLAG_KEEP_FORWARD,
                                         sk._dt(X))
@@ -156,7 +157,7 @@ class _GramKernelSym(torch.autograd.Function):
         X = X.contiguous()
         ctx.save_for_backward(X)
         ctx.args = (lam1, lam2, flags)
-        ctx.ws = _gram_keep_workspace(ctx, X, X, lam1, lam2, flags)
+        ctx.ws = _gram_keep_workspace(ctx, X, X, lam1, lam2, flags, symmetric=True)
         if ctx.ws is not None:
             return sk.sigkernel_gram(X, X, None, lam1, lam2, flags | sk.SK_FLAG_KEEP_FORWARD, ws=ctx.ws)
         return sk.sigkernel_gram(X, X, None, lam1, lam2, flags)

@@ -142,7 +142,7 @@ def sigkernel_workspace_bytes(op, B_or_N, M, L1, L2, d, lam1, lam2, flags, dt):
 
 def sigkernel_describe(op, B_or_N, M, L1, L2, d, lam1, lam2, flags, dt):
     """The launch the library would make for this operation and shape, as 'key=value' text (no GPU call)."""
-    buf = C.create_string_buffer(512)
+    buf = C.create_string_buffer(1024)
     _check(load().sigkernel_describe(op, B_or_N, M, L1, L2, d, lam1, lam2, flags, dt, buf, len(buf)))
     return buf.value.decode()
 
@@ -300,7 +300,7 @@ def signature_workspace_bytes(B, L, d, N, flags, dt):
 
 
 def signature_describe(B, L, d, N, flags, dt):
-    buf = C.create_string_buffer(512)
+    buf = C.create_string_buffer(1024)
     _check(load().signature_describe(B, L, d, N, flags, dt, buf, len(buf)))
     return buf.value.decode()
 
@@ -321,7 +321,7 @@ def signature_fwd(x, N, flags=0, ws=None, out=None):
 
 
 def signature_bwd_describe(B, L, d, N, flags, dt):
-    buf = C.create_string_buffer(512)
+    buf = C.create_string_buffer(1024)
     _check(load().signature_bwd_describe(B, L, d, N, flags, dt, buf, len(buf)))
     return buf.value.decode()
 

@@ -305,7 +305,7 @@ int run(const Layout& lay, bool backward, const void* x, const void* y, void* k,
         b.ring_off = (unsigned)q.ring_off;
         b.coop = 0; b.uncompute = 0; b.lock = 0; b.solo = 0; b.tile = 0; b.band = 0;
         b.lk_phase = 0; b.keep_tag = nullptr;
-        if (!(p.lock || p.solo || p.tile))
+        if (!(p.lock || p.solo || p.tile || p.four))
             SK_CHECK(launch_second_chance_reset(a.want_gx ? a.gdx : nullptr, (long)(p.nx * p.xstride),
                                                 (a.want_gy && !p.symmetric) ? a.gdy : nullptr,
                                                 (long)(p.ny * p.ystride), a.err, st));
@@ -532,6 +532,69 @@ extern "C" int sigkernel_bwd_static(const void* x, const void* y, const void* gr
 // Layout of the scratch of sigkernel_mmd2: the three Gram matrices, their constant upstream weights, the second
 // halves of the two gradients (all in the caller's element type), then the scratch of the Gram calls.
 namespace {
+// What a description says about the sweep launch of a plan (phase: as in run).
+struct LaunchNames {
+    const char* mode;
+    char kernel[128];
+    int threads, strips, rows;   // strips (four-pair mode: bands of 16 lanes) per pair, block rows per lane
+};
+LaunchNames launch_names(const sk::Plan& p, bool backward, int phase, bool time)
+{
+    LaunchNames l;
+    const bool lean = p.lock || p.solo || p.tile || p.quad || p.band;
+    l.strips = lean ? p.lk_ns : p.ns;
+    l.rows = lean ? p.lk_M : 1;
+    if (p.band) {
+        l.mode = "band";
+        // backward: two launches, the forward sweep with checkpoints and then the reverse sweep (the larger one)
+        if (phase == 1) std::snprintf(l.kernel, sizeof(l.kernel), "band_fwd_kernel<%d, %d, true, %d>", p.BL, p.DT, p.ll);
+        else if (phase == 2) std::snprintf(l.kernel, sizeof(l.kernel), "band_rev_kernel<%d, %d, %d>", p.BL, p.DT, p.ll);
+        else if (backward)
+            std::snprintf(l.kernel, sizeof(l.kernel), "band_fwd_kernel<%d, %d, true, %d>+band_rev_kernel<%d, %d, %d>", p.BL, p.DT,
+                          p.ll, p.BL, p.DT, p.ll);
+        else
+            std::snprintf(l.kernel, sizeof(l.kernel), "band_fwd_kernel<%d, %d, false, %d>", p.BL, p.DT, p.ll);
+        l.threads = (sk::kBandStrips + 1) * sk::kWave;
+    } else if (p.quad) {
+        l.mode = "quad";
+        std::snprintf(l.kernel, sizeof(l.kernel), "quad_fwd_kernel<%d, %d, %d>", p.BL, p.DT, p.lk_M);
+        l.threads = sk::kWavesPerWG * sk::kWave;
+    } else if (p.tile) {
+        l.mode = "tile";
+        // (backward: the second argument says whether the sweeps move two columns per LDS instruction, sk_tile_bwd.hip)
+        if (backward) std::snprintf(l.kernel, sizeof(l.kernel), "tile_bwd_kernel<%d, %s>", p.DT / 4, p.nb + 1 < sk::kTileCols - 1 ? "true" : "false");
+        else std::snprintf(l.kernel, sizeof(l.kernel), "tile_fwd_kernel<%d>", p.DT / 4);
+        l.threads = sk::kWavesPerWG * sk::kWave;
+    } else if (p.four) {
+        l.mode = "four";
+        std::snprintf(l.kernel, sizeof(l.kernel), "four_bwd_kernel<%d, %d, %d, %s, %d>", p.BL, p.DT, p.lk_M, time ? "true" : "false",
+                      sk::four_occupancy(p.BL, p.DT));
+        l.threads = sk::kWave;
+        l.strips = p.fv_bands;
+        l.rows = sk::four_rows(p.BL, p.DT);
+    } else if (p.solo) {
+        l.mode = "solo";
+        if (backward || phase)
+            std::snprintf(l.kernel, sizeof(l.kernel), "solo_bwd_kernel<%d, %d, %d, %d, %d, %d>", p.BL, p.DT, p.lk_M, phase, p.ll,
+                          sk::solo_bwd_shares_simd(p.BL, p.lk_M, p.DT, p.lds_bytes) ? 2 : 1);
+        else std::snprintf(l.kernel, sizeof(l.kernel), "solo_fwd_kernel<%d, %d, %d, %d>", p.BL, p.DT, p.lk_M, p.ll);
+        l.threads = sk::kWavesPerWG * sk::kWave;
+    } else if (p.lock) {
+        l.mode = "lock-step";
+        if (backward || phase)
+            std::snprintf(l.kernel, sizeof(l.kernel), "lock_bwd_kernel<%d, %d, %d, %d, %d>", p.BL, p.DT, p.lk_M, phase, p.ll);
+        else std::snprintf(l.kernel, sizeof(l.kernel), "lock_fwd_kernel<%d, %d, %d, %d>", p.BL, p.DT, p.lk_M, p.ll);
+        l.threads = (p.lk_ns == 1 ? 3 : (p.lk_ns == 2 ? 8 : 12)) * sk::kWave;
+    } else {
+        const char* base = !backward ? "sweep_fwd" : (p.uncompute ? "sweep_bwdu" : "sweep_bwd");
+        l.mode = p.coop ? "cooperative" : "wave-per-pair";
+        std::snprintf(l.kernel, sizeof(l.kernel), "%s%s_kernel<%d, %d, %s>", base, p.coop ? "_coop" : "", p.BL, p.DT,
+                      (p.y_lds && p.DT) ? "true" : "false");
+        l.threads = (p.coop ? p.nw : sk::kWavesPerWG) * sk::kWave;
+    }
+    return l;
+}
+
 struct MmdLayout {
     size_t kxx, kxy, kyy, wxx, wxy, wyy, gx2, gy2, sub, sub_bytes, total;
 };
@@ -720,65 +783,24 @@ int sigkernel_describe(int op, int64_t B_or_N, int64_t M, int64_t L1, int64_t L2
         }
     }
     const sk::Plan& p = lay.p;
-    char kern[128];
-    int threads;
-    const char* mode;
-    if (p.band) {
-        mode = "band";
-        // backward: two launches, the forward sweep with checkpoints and then the reverse sweep (the larger one)
-        if (phase == 1) std::snprintf(kern, sizeof(kern), "band_fwd_kernel<%d, %d, true, %d>", p.BL, p.DT, p.ll);
-        else if (phase == 2) std::snprintf(kern, sizeof(kern), "band_rev_kernel<%d, %d, %d>", p.BL, p.DT, p.ll);
-        else if (backward)
-            std::snprintf(kern, sizeof(kern), "band_fwd_kernel<%d, %d, true, %d>+band_rev_kernel<%d, %d, %d>", p.BL, p.DT,
-                          p.ll, p.BL, p.DT, p.ll);
-        else
-            std::snprintf(kern, sizeof(kern), "band_fwd_kernel<%d, %d, false, %d>", p.BL, p.DT, p.ll);
-        threads = (sk::kBandStrips + 1) * sk::kWave;
-    } else if (p.quad) {
-        mode = "quad";
-        std::snprintf(kern, sizeof(kern), "quad_fwd_kernel<%d, %d, %d>", p.BL, p.DT, p.lk_M);
-        threads = sk::kWavesPerWG * sk::kWave;
-    } else if (p.tile) {
-        mode = "tile";
-        // (backward: the second argument says whether the sweeps move two columns per LDS instruction, sk_tile_bwd.hip)
-        if (backward) std::snprintf(kern, sizeof(kern), "tile_bwd_kernel<%d, %s>", p.DT / 4, p.nb + 1 < sk::kTileCols - 1 ? "true" : "false");
-        else std::snprintf(kern, sizeof(kern), "tile_fwd_kernel<%d>", p.DT / 4);
-        threads = sk::kWavesPerWG * sk::kWave;
-    } else if (p.four) {
-        mode = "solo";
-        std::snprintf(kern, sizeof(kern), "solo_bwd_kernel<%d, %d, %d, 0, 0, %d>", p.BL, p.DT, p.lk_M,
-                      sk::four_occupancy(p.BL, p.DT));
-        threads = sk::kWave;
-    } else if (p.solo) {
-        mode = "solo";
-        if (backward || phase)
-            std::snprintf(kern, sizeof(kern), "solo_bwd_kernel<%d, %d, %d, %d, %d, %d>", p.BL, p.DT, p.lk_M, phase, p.ll,
-                          sk::solo_bwd_shares_simd(p.BL, p.lk_M, p.DT, p.lds_bytes) ? 2 : 1);
-        else std::snprintf(kern, sizeof(kern), "solo_fwd_kernel<%d, %d, %d, %d>", p.BL, p.DT, p.lk_M, p.ll);
-        threads = sk::kWavesPerWG * sk::kWave;
-    } else if (p.lock) {
-        mode = "lock-step";
-        if (backward || phase)
-            std::snprintf(kern, sizeof(kern), "lock_bwd_kernel<%d, %d, %d, %d, %d>", p.BL, p.DT, p.lk_M, phase, p.ll);
-        else std::snprintf(kern, sizeof(kern), "lock_fwd_kernel<%d, %d, %d, %d>", p.BL, p.DT, p.lk_M, p.ll);
-        threads = (p.lk_ns == 1 ? 3 : (p.lk_ns == 2 ? 8 : 12)) * sk::kWave;
-    } else {
-        const char* base = !backward ? "sweep_fwd" : (p.uncompute ? "sweep_bwdu" : "sweep_bwd");
-        mode = p.coop ? "cooperative" : "wave-per-pair";
-        std::snprintf(kern, sizeof(kern), "%s%s_kernel<%d, %d, %s>", base, p.coop ? "_coop" : "", p.BL, p.DT,
-                      (p.y_lds && p.DT) ? "true" : "false");
-        threads = (p.coop ? p.nw : sk::kWavesPerWG) * sk::kWave;
-    }
+    const bool time = (flags & SK_FLAG_TIME_AUG) != 0;
+    const LaunchNames l = launch_names(p, backward, phase, time);
     const bool fused = p.lock && !gram && dt == SK_F64;
     std::snprintf(out, out_bytes,
                   "mode=%s kernel=%s grid=%d threads=%d lds_bytes=%zu strips=%d rows_per_lane=%d fused=%d "
                   "kept_sweep_half=%d lead_lag_form=%s second_launch_lds_bytes=%zu workspace_bytes=%zu "
                   "drifted_pairs_counter_at=%zu pairs_per_wave=%d",
-                  mode, kern, p.grid, threads, p.lds_bytes, (p.lock || p.solo || p.tile || p.quad || p.band) ? p.lk_ns : p.ns,
-                  (p.lock || p.solo || p.tile || p.quad || p.band) ? p.lk_M : 1,
-                  fused ? 1 : 0, phase, lay.ll ? "checkerboard" : "none",
-                  (lay.has_sc && backward && phase != 1) ? lay.sc.lds_bytes : (size_t)0, lay.total, p.off_badlist != 0 ? p.off_badcnt : (size_t)0,
-                  (p.four || p.quad) ? sk::kQuadPairs : 1);
+                  l.mode, l.kernel, p.grid, l.threads, p.lds_bytes, l.strips, l.rows, fused ? 1 : 0, phase,
+                  lay.ll ? "checkerboard" : "none", (lay.has_sc && backward && phase != 1) ? lay.sc.lds_bytes : (size_t)0,
+                  lay.total, p.off_badlist != 0 ? p.off_badcnt : (size_t)0, (p.four || p.quad) ? sk::kQuadPairs : 1);
+    if (gram && B_or_N == ny && L1 == L2) {
+        // the call with Y == X, which may be launched in another way
+        const Layout ls = make_layout(backward || phase != 0, true, true, B_or_N, ny, L1, L2, d, lam1, lam2, flags,
+                                      dt == SK_F64 ? 8 : 4, !(flags & SK_FLAG_BWD_REPLAY), phase != 0);
+        const LaunchNames n = launch_names(ls.p, backward, phase, time);
+        const size_t used = std::strlen(out);
+        std::snprintf(out + used, out_bytes - used, " symmetric_mode=%s symmetric_grid=%d", n.mode, ls.p.grid);
+    }
     return SK_OK;
 }
 
@@ -1023,17 +1045,24 @@ int signature_bwd_describe(int64_t B, int64_t L, int64_t d, int N, int flags, sk
     sg::Plan p;
     int rc = sig_validate(B, L, d, N, flags, (int)dt, &p, true, true);
     if (rc != SK_OK) return rc;
-    char matrix[64] = "none";
-    if (p.matrix) std::snprintf(matrix, sizeof(matrix), "horner_bwd_matrix_kernel<%d, %d, %d>", p.D, p.matrix_Q, p.matrix_S);
+    char kern[96];
+    if (p.matrix)
+        std::snprintf(kern, sizeof(kern), "horner_bwd_matrix_kernel<%d, %d, %d>", p.D, p.matrix_Q, p.matrix_S);
+    else
+        std::snprintf(kern, sizeof(kern), "horner_bwd_kernel<%d, %d, %d, %d, %s, %s>", p.DT, p.M, p.S,
+                      p.Q <= sg::kQExact ? p.Q : sg::kQMax, p.PW > 1 ? "true" : "false",
+                      ((flags & SK_FLAG_LEAD_LAG) && p.DT >= 4 && p.M >= 1) ? "true" : "false");
+    const int lanes = p.matrix ? sg::matrix_lanes(p.D, p.matrix_S) : 0;   // per prefix of the matrix kernel
     std::snprintf(out, out_bytes,
-                  "kernel=horner_bwd_kernel<%d, %d, %d, %d, %s, %s> channels=%d prefix_letters=%d letter_blocks=%d "
+                  "kernel=%s channels=%d prefix_letters=%d letter_blocks=%d "
                   "lanes_per_path=%lld waves_per_path=%lld paths_per_wave=%d pieces_per_path=%d segments_per_piece=%lld "
-                  "grid=%lld threads=%d lds_bytes=%zu entries_per_path=%lld workspace_bytes=%zu matrix_kernel=%s "
-                  "matrix_grid=%lld",
-                  p.DT, p.M, p.S, p.Q <= sg::kQExact ? p.Q : sg::kQMax, p.PW > 1 ? "true" : "false",
-                  ((flags & SK_FLAG_LEAD_LAG) && p.DT >= 4 && p.M >= 1) ? "true" : "false", p.D, p.Q, p.NB,
-                  (long long)p.LP, (long long)p.WP, p.PW, p.P, (long long)p.Lc, (long long)p.grid, sg::kWave * sg::kWavesPerWG, p.lds_bytes, (long long)p.sig_len,
-                  B == 0 ? (size_t)0 : p.total, matrix, (long long)p.matrix_grid);
+                  "grid=%lld threads=%d lds_bytes=%zu entries_per_path=%lld workspace_bytes=%zu",
+                  kern, p.D, p.matrix ? p.matrix_Q : p.Q, p.matrix ? lanes : p.NB,
+                  (long long)(p.matrix ? p.matrix_WP * sg::kWave : p.LP), (long long)(p.matrix ? p.matrix_WP : p.WP),
+                  p.matrix ? 1 : p.PW, p.P, (long long)p.Lc, (long long)(p.matrix ? p.matrix_grid : p.grid),
+                  sg::kWave * sg::kWavesPerWG,
+                  p.matrix ? (size_t)sg::kWavesPerWG * sg::matrix_lds_doubles(p.matrix_S) * sizeof(double) : p.lds_bytes,
+                  (long long)p.sig_len, B == 0 ? (size_t)0 : p.total);
     return SK_OK;
 }
 

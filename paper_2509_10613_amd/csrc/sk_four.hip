@@ -525,20 +525,12 @@ __device__ __forceinline__ void backward(const SweepArgs& a)
     }
 }
 
-// The kernel's name and arguments follow those of the one-pair kernel (PHASE and LL always 0); OCC: wavefronts per SIMD
-// the registers are allotted for.  A second kernel for calls with a time channel: together in one kernel the two
-// copies of the sweep cost each other registers.
-template <int BL, int D, int M, int PHASE, int LL, int OCC>
-__global__ __launch_bounds__(kWave, OCC) void solo_bwd_kernel(SweepArgs a)
+// OCC: wavefronts per SIMD the registers are allotted for.  Calls with a time channel have kernels of their own: together in
+// one kernel the two copies of the sweep cost each other registers.
+template <int BL, int D, int M, bool TC, int OCC>
+__global__ __launch_bounds__(kWave, OCC) void four_bwd_kernel(SweepArgs a)
 {
-    static_assert(PHASE == 0 && LL == 0, "one form only");
-    backward<BL, D, M, false>(a);
-}
-template <int BL, int D, int M, int PHASE, int LL, int OCC>
-__global__ __launch_bounds__(kWave, OCC) void solo_bwd_time_kernel(SweepArgs a)
-{
-    static_assert(PHASE == 0 && LL == 0, "one form only");
-    backward<BL, D, M, true>(a);
+    backward<BL, D, M, TC>(a);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -548,8 +540,8 @@ template <int BL, int D, int M>
 static hipError_t launch_t(const SweepArgs& a, int grid, size_t lds, hipStream_t st)
 {
     if constexpr (four_occupancy(BL, D) > 0) {
-        auto kernel = a.tc != 0.0 ? &solo_bwd_time_kernel<BL, D, M, 0, 0, four_occupancy(BL, D)>
-                                  : &solo_bwd_kernel<BL, D, M, 0, 0, four_occupancy(BL, D)>;
+        auto kernel = a.tc != 0.0 ? &four_bwd_kernel<BL, D, M, true, four_occupancy(BL, D)>
+                                  : &four_bwd_kernel<BL, D, M, false, four_occupancy(BL, D)>;
         if (hipError_t e = allow_full_lds(reinterpret_cast<const void*>(kernel)); e != hipSuccess) return e;
         hipLaunchKernelGGL(kernel, dim3(grid), dim3(kWave), lds, st, a);
         return hipGetLastError();

@@ -74,7 +74,7 @@ struct Plan {
     int quad = 0;   // four pairs per wave, forward Gram calls on the tile kernels' shapes (sk_quad.hip)
     int64_t nquads = 0;   // groups of four pairs of one Gram row the quad launch works through
     int64_t qd_even = 0;  // quads of a four-pair launch that are handed out in equal shares (the rest by a counter)
-    int four = 0;         // solo mode with four pairs per wave (backward Gram calls, sk_four.hip)
+    int four = 0;         // four pairs per wave, backward Gram calls (sk_four.hip); lk_M: 1 = one band, 2 = several
     int fv_bands = 0;     // bands of 16 lanes per pair
     int64_t fv_gx_slot = 0;
     size_t off_fvgx = 0;  // x-side sums of the strips of the pairs in work (several strips only)
@@ -541,11 +541,11 @@ inline Plan make_plan(bool backward, bool gram, bool symmetric, int64_t nx, int6
             if (four) p.qd_even = quads.even;
         }
         if (four) {
-            p.lock = 0; p.coop = 0; p.solo = 1; p.four = 1;
+            p.lock = 0; p.coop = 0; p.solo = 0; p.four = 1;
             p.DT = DT;
             p.lk_M = bands > 1 ? 2 : 1;
             p.fv_bands = bands; p.lk_padb = bands * band - p.mb;
-            p.lk_ns = (p.mb + kWave * p.lk_M - 1) / (kWave * p.lk_M);
+            p.lk_ns = 0;
             p.lk_NT = p.nb + kWave / kQuadPairs - 1;
             p.lk_off_y = o_y; p.lk_off_gyp = o_gyp; p.lk_off_gp = o_gring; p.lk_off_krows = o_ring;
             p.y_lds = 1;
@@ -555,7 +555,7 @@ inline Plan make_plan(bool backward, bool gram, bool symmetric, int64_t nx, int6
         }
     }
 
-    if (may_tri && (p.solo || p.tile)) {
+    if (may_tri && (p.solo || p.tile || p.four)) {
         p.tri = 1;
         p.npairs = nx * (nx + 1) / 2;
         const int64_t want = (p.npairs + kWavesPerWG - 1) / kWavesPerWG;
@@ -602,7 +602,7 @@ inline Plan make_plan(bool backward, bool gram, bool symmetric, int64_t nx, int6
 
     // Band mode: few pairs of long paths.  The strips of a pair are spread over workgroups (bands of kBandStrips
     // strips) that all run at once; chosen when that fills more of the chip than one workgroup per pair does.
-    if (!p.lock && !p.tile && !p.solo && (!backward || p.uncompute) && p.DT >= 2 && p.DT <= 8 && p.ns > kBandMinStrips &&
+    if (!p.lock && !p.tile && !p.solo && !p.four && (!backward || p.uncompute) && p.DT >= 2 && p.DT <= 8 && p.ns > kBandMinStrips &&
         !second_chance) {
         const int nbands = (p.ns + kBandStrips - 1) / kBandStrips;
         if (p.npairs * nbands <= kNumCU) {
@@ -651,7 +651,7 @@ inline Plan make_plan(bool backward, bool gram, bool symmetric, int64_t nx, int6
         p.adj_slot = (p.band && p.bd_nbands > 4 ? p.bd_nbands : 4) * (int64_t)p.rowlen;   // two rows of 2C values per block column; band mode: one row per band
         p.off_adj = take((size_t)p.nslots * p.adj_slot * elem);
         // lane state kept per checkpoint: right edge, bottom edge, bottom-left corner
-        const bool lean = p.lock || p.solo || p.tile || p.band;
+        const bool lean = p.lock || p.solo || p.tile || p.band || p.four;
         const int NVC = lean ? p.lk_M * R + C + 2 : R + C + 2;
         p.ckpt_slot = p.tile ? 0 : (int64_t)(lean ? p.lk_ns : p.ns) * (p.nseg + 1) * NVC * kWave;
         if (p.four) {

@@ -261,8 +261,8 @@ def test_tile_mode_pair_batch():
 
 
 def test_short_paths_with_many_channels_stay_solo():
-    # 16 channels but fewer than 33 cells per side: the solo kernels (channel contraction on the vector units)
-    nx, ny, L, d = 70, 60, 30, 16
+    # 16 channels but fewer than 33 cells per side, few x paths: the solo kernels (channel contraction on the vector units)
+    nx, ny, L, d = 6, 700, 30, 16
     rng = np.random.default_rng(78)
     X = np.cumsum(rng.normal(0.0, (1.0 / (d * L)) ** 0.5, (nx, L, d)), axis=1)
     Y = np.cumsum(rng.normal(0.0, (1.0 / (d * L)) ** 0.5, (ny, L, d)), axis=1)
@@ -914,9 +914,9 @@ def test_c5_full_size_gram_sampled_rows_and_columns():
 
 def test_symmetric_gram_with_unequal_dyadic_orders():
     # k with orders (l1, l2) of (y, x) equals k with orders (l2, l1) of (x, y), not k with (l1, l2): for unequal orders
-    # K(X, X) is not a symmetric matrix and every pair has to be solved (solo kernels, shared increment buffer)
+    # K(X, X) is not a symmetric matrix and every pair has to be solved (four pairs per wave, shared increment buffer)
     N, L, d, lam1, lam2 = 300, 20, 3, 0, 1
-    assert "mode=solo" in sk.sigkernel_describe(sk.SK_OP_GRAM_BWD, N, N, L, L, d, lam1, lam2, 0, sk.SK_F64)
+    assert " symmetric_mode=four " in sk.sigkernel_describe(sk.SK_OP_GRAM_BWD, N, N, L, L, d, lam1, lam2, 0, sk.SK_F64)
     X = rand_paths(8700, N, L, d, 0.25)
     W = workloads.upstream_weights(87, (N, N))
     x = dev(X)
@@ -1313,7 +1313,7 @@ def drifted_pairs(op, B_or_N, M, L1, L2, d, lam1, lam2, flags, dtype, ws):
     torch.cuda.synchronize()
     n = int(ws[at:at + 4].view(torch.int32)[0])
     mode = desc.split("mode=", 1)[1].split()[0]
-    return n if mode in ("lock-step", "solo", "tile") else -1
+    return n if mode in ("lock-step", "solo", "tile", "four") else -1
 
 
 def pairs_backward_with_ws(X, Y, gk, lam1, lam2, flags, dtype=torch.float64):

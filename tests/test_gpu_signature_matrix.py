@@ -12,7 +12,7 @@ pytestmark = pytest.mark.gpu
 
 
 def matrix_kernel(B, L, d, N, flags=0):
-    return sk.signature_bwd_describe(B, L, d, N, flags, sk.SK_F64).split("matrix_kernel=")[1]
+    return sk.signature_bwd_describe(B, L, d, N, flags, sk.SK_F64).split("kernel=")[1]
 
 
 @pytest.mark.parametrize("L", [17, 18, 32, 34])          # 16, 17, 31 and 33 segments

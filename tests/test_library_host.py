@@ -119,10 +119,21 @@ def test_launch_plan_of_the_five_configurations(lib):
     # c1: tiny, one strip: stencil, coefficient and auxiliary wave
     p = _plan(binding.SK_OP_FWD, 8, 0, 32, 32, 2, 0, 0, 0, f64)
     assert p["mode"] == "lock-step" and p["threads"] == "192" and p["strips"] == "1"
-    # c3 (Gram matrix with 65536 pairs of short paths): one wave per pair fills the chip, and a pair is a single
-    # strip (127 block rows at two per lane)
+    # c3 (Gram matrix with 65536 pairs of short paths): four pairs of a Gram row per wave, one wave per workgroup; the 127
+    # block rows of a pair are two bands of 16 lanes with four rows each.  Two waves per SIMD: 2048 for 16384 quads
     p = _plan(binding.SK_OP_GRAM_BWD, 256, 256, 128, 128, 3, 1, 1, 0, f64)
-    assert p["mode"] == "solo" and p["kernel"] == "solo_bwd_kernel<1, 3, 2, 0, 0, 2>" and p["strips"] == "1"
+    assert p["mode"] == "four" and p["kernel"] == "four_bwd_kernel<1, 3, 2, false, 2>" and p["pairs_per_wave"] == "4"
+    assert (p["strips"], p["rows_per_lane"], p["grid"], p["threads"]) == ("2", "4", "2048", "64")
+    # ... with a time channel the kernel's other form; K(X, X) of 96 paths, and a few pairs, one wave per pair, a single
+    # strip of 127 block rows at two per lane
+    assert _plan(binding.SK_OP_GRAM_BWD, 256, 256, 128, 128, 3, 1, 1, 1, f64)["kernel"] == "four_bwd_kernel<1, 3, 2, true, 2>"
+    p = _plan(binding.SK_OP_GRAM_BWD, 256, 256, 128, 128, 3, 1, 1, 0, f64)
+    assert p["symmetric_mode"] == "four" and p["symmetric_grid"] == "2048"
+    p = _plan(binding.SK_OP_GRAM_BWD, 128, 128, 128, 128, 3, 1, 1, 0, f64)
+    assert p["mode"] == "four" and p["symmetric_mode"] == "solo"
+    p = _plan(binding.SK_OP_GRAM_BWD, 48, 40, 128, 128, 3, 1, 1, 0, f64)
+    assert p["mode"] == "solo" and p["kernel"] == "solo_bwd_kernel<1, 3, 2, 0, 0, 2>" and p["pairs_per_wave"] == "1"
+    assert p["strips"] == "1" and p["rows_per_lane"] == "2" and "symmetric_mode" not in p
     # ... whose checkpoints stay within 4 GiB, or within what the other kernels need (722 x 43 long paths of order 3: 16 GiB)
     assert "pairs_per_wave=4" in binding.sigkernel_describe(binding.SK_OP_GRAM_BWD, 256, 256, 128, 128, 3, 2, 2, 0, f64)
     assert q(binding.SK_OP_GRAM_BWD, 256, 256, 128, 128, 3, 2, 2, 0, f64) < 4 << 30
@@ -141,10 +152,13 @@ def test_launch_plan_of_the_five_configurations(lib):
     assert _plan(binding.SK_OP_GRAM_BWD, 1024, 1024, 64, 64, 7, 0, 0, 1, f64)["kernel"] == "tile_bwd_kernel<2, true>"
     # 64 columns leave no zero column behind the zero column: the sweeps move one column per LDS instruction
     assert _plan(binding.SK_OP_GRAM_BWD, 1024, 1024, 64, 65, 16, 0, 0, 0, f64)["kernel"] == "tile_bwd_kernel<4, false>"
-    # the same shape with few channels, with dyadic refinement, or with very short paths stays with the solo kernels
-    assert _plan(binding.SK_OP_GRAM_BWD, 1024, 1024, 64, 64, 3, 0, 0, 0, f64)["mode"] == "solo"
-    assert _plan(binding.SK_OP_GRAM_BWD, 1024, 1024, 64, 64, 16, 1, 1, 0, f64)["mode"] == "solo"
-    assert _plan(binding.SK_OP_GRAM_BWD, 1024, 1024, 30, 64, 16, 0, 0, 0, f64)["mode"] == "solo"
+    # the same shape with few channels, with dyadic refinement, or with very short paths: four pairs per wave on the vector
+    # units; pair batches and lead-lag paths stay with the solo kernels
+    assert _plan(binding.SK_OP_GRAM_BWD, 1024, 1024, 64, 64, 3, 0, 0, 0, f64)["mode"] == "four"
+    assert _plan(binding.SK_OP_GRAM_BWD, 1024, 1024, 64, 64, 16, 1, 1, 0, f64)["mode"] == "four"
+    assert _plan(binding.SK_OP_GRAM_BWD, 1024, 1024, 30, 64, 16, 0, 0, 0, f64)["mode"] == "four"
+    assert _plan(binding.SK_OP_BWD, 5000, 0, 64, 64, 3, 0, 0, 0, f64)["mode"] == "solo"
+    assert _plan(binding.SK_OP_GRAM_BWD, 1024, 1024, 64, 64, 3, 0, 0, binding.SK_FLAG_LEAD_LAG, f64)["mode"] == "solo"
     # ... whose forward Gram calls take the quad kernel where its lanes can hold the rows' increments (four or eight
     # block rows per lane, blocks of at most 2 x 2 cells that hold all of the refinement)
     assert _plan(binding.SK_OP_GRAM, 1024, 1024, 64, 64, 3, 0, 0, 0, f64)["kernel"] == "quad_fwd_kernel<0, 3, 4>"
@@ -203,7 +217,7 @@ def test_where_signature_gradients_take_the_matrix_kernel_and_how_paths_are_cut(
 
     def plan(B, L, d, N, flags=0):
         text = binding.signature_bwd_describe(B, L, d, N, flags, binding.SK_F64)
-        return "matrix_kernel=horner" in text, int(re.search(r"pieces_per_path=(\d+)", text).group(1))
+        return "kernel=horner_bwd_matrix_kernel" in text, int(re.search(r"pieces_per_path=(\d+)", text).group(1))
     # eight channels and five levels, lead-lag: one wavefront per SIMD and no more
     assert plan(28, 300, 4, 5, LL)[0] and not plan(37, 300, 4, 5, LL)[0] and not plan(64, 60, 4, 5, LL)[0]
     assert plan(64, 60, 8, 5)[0] and plan(128, 512, 8, 4, LL)[0] and plan(128, 256, 4, 4, LL)[0]
@@ -344,15 +358,21 @@ def test_signature_backward_host_side(lib):
     w2 = lib.signature_bwd_workspace_bytes(4, 8, 3, 3, 0, 0, 1)
     assert base <= w0 < base + 1024 and w1 >= w0 + 4 * n * 8 and w2 >= w0 + 2 * 4 * n * 8
     # launch plans: the backward variants hold entries and adjoints, so the subtrees are smaller than the forward's
-    text = binding.signature_bwd_describe(128, 1024, 16, 4, 0, binding.SK_F64)
-    assert "horner_bwd_kernel<16, 1, 2, 2, false, false>" in text and "lanes_per_path=2048" in text and "grid=1024" in text
-    assert "horner_bwd_kernel<8, 1, 4, 3, false, false>" in binding.signature_bwd_describe(128, 512, 8, 5, 0, binding.SK_F64)
+    other = binding.SK_SIG_ONE_PATH_PER_WAVE       # a form of the kernel that sums over the words lane by lane
+    text = binding.signature_bwd_describe(128, 1024, 16, 4, other, binding.SK_F64)
+    assert "kernel=horner_bwd_kernel<16, 1, 2, 2, false, false>" in text and "lanes_per_path=2048" in text and "grid=1024" in text
+    assert "kernel=horner_bwd_kernel<8, 1, 4, 3, false, false>" in binding.signature_bwd_describe(128, 512, 8, 5, 0, binding.SK_F64)
     assert "horner_bwd_kernel<0, 0, 1, 2, false, false>" in binding.signature_bwd_describe(4, 9, 20, 3, 0, binding.SK_F64)
     lds = int(re.search(r"lds_bytes=(\d+)", text).group(1))
     assert lds == 4 * (16 + 64 * 17) * 8
+    # ... and the one that is launched there, with the top level's sum on the matrix cores: two words per lane, eight lanes
+    # per prefix, 32 waves per path
+    text = binding.signature_bwd_describe(128, 1024, 16, 4, 0, binding.SK_F64)
+    assert "kernel=horner_bwd_matrix_kernel<16, 2, 2> " in text and " waves_per_path=32 " in text and " grid=1024 " in text
+    assert int(re.search(r"lds_bytes=(\d+)", text).group(1)) == 4 * (16 * 16 + 4 * 64 + 2 * 16 * 64) * 8
     # lead-lag paths take the kernels that leave out the half of the channels a segment does not move
     assert "horner_bwd_kernel<16, 1, 2, 2, false, true>" in binding.signature_bwd_describe(
-        128, 512, 8, 4, binding.SK_FLAG_LEAD_LAG, binding.SK_F64)
+        128, 512, 8, 4, binding.SK_FLAG_LEAD_LAG | other, binding.SK_F64)
     assert "horner_kernel<16, 1, 4, 2, false, true>" in binding.signature_describe(
         128, 512, 8, 4, binding.SK_FLAG_LEAD_LAG, binding.SK_F64)
     assert "horner_kernel<2, 3, 1, 2, true, false>" in binding.signature_describe(    # two channels: no such form
