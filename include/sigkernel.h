@@ -208,7 +208,9 @@ int sigkernel_event_timing_read(double* fwd_ms, int* fwd_launches, double* bwd_m
  * checkerboard: the grid of the caller's increments swept with one more level of refinement whose off-diagonal
  * quadrants carry no increment product); second_launch_lds_bytes (backward calls: LDS per workgroup of the launch
  * that solves drifted pairs once more); drifted_pairs_counter_at (where in the workspace the call counts those pairs);
- * pairs_per_wave; for Gram calls with N == M and L1 == L2 also symmetric_mode and symmetric_grid, of the call with Y == X.
+ * pairs_per_wave; over_kept_sweep (1: a backward Gram call that sweeps forward itself in a mode that is estimated to be
+ * faster than a reverse sweep that takes over a kept one); for Gram calls with N == M and L1 == L2 also symmetric_mode,
+ * symmetric_grid and symmetric_over_kept_sweep, of the call with Y == X.
  * Same arguments as sigkernel_workspace_bytes.
  * Pure host arithmetic: no GPU call.  Returns SK_OK or a negative error code.
  */

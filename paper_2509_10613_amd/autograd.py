@@ -118,9 +118,9 @@ def _gram_keep_workspace(ctx, X, Y, lam1, lam2, flags, symmetric=False):
     M, L2 = Y.shape[0], Y.shape[1]
     if not sk.keeps_forward(N, L1, L2, d, lam1, lam2, flags, sk._dt(X), gram_M=M):
         return None
-    # (the backward sweep with four pairs per wavefront makes its own forward sweep, and is faster than the kept form)
+    # (the backward sweep with four pairs per wavefront makes its own forward sweep, and is mostly faster than the kept form)
     desc = sk.sigkernel_describe(sk.SK_OP_GRAM_BWD, N, M, L1, L2, d, lam1, lam2, flags, sk._dt(X))
-    if (" symmetric_mode=four " in desc) if symmetric else desc.startswith("mode=four "):
+    if (" symmetric_over_kept_sweep=1" if symmetric else " over_kept_sweep=1") in desc:
         return None
     need = sk.sigkernel_workspace_bytes(sk.SK_OP_GRAM, N, M, L1, L2, d, lam1, lam2, flags | sk.SK_FLAG_KEEP_FORWARD,
                                         sk._dt(X))

@@ -789,17 +789,19 @@ int sigkernel_describe(int op, int64_t B_or_N, int64_t M, int64_t L1, int64_t L2
     std::snprintf(out, out_bytes,
                   "mode=%s kernel=%s grid=%d threads=%d lds_bytes=%zu strips=%d rows_per_lane=%d fused=%d "
                   "kept_sweep_half=%d lead_lag_form=%s second_launch_lds_bytes=%zu workspace_bytes=%zu "
-                  "drifted_pairs_counter_at=%zu pairs_per_wave=%d",
+                  "drifted_pairs_counter_at=%zu pairs_per_wave=%d over_kept_sweep=%d",
                   l.mode, l.kernel, p.grid, l.threads, p.lds_bytes, l.strips, l.rows, fused ? 1 : 0, phase,
                   lay.ll ? "checkerboard" : "none", (lay.has_sc && backward && phase != 1) ? lay.sc.lds_bytes : (size_t)0,
-                  lay.total, p.off_badlist != 0 ? p.off_badcnt : (size_t)0, (p.four || p.quad) ? sk::kQuadPairs : 1);
+                  lay.total, p.off_badlist != 0 ? p.off_badcnt : (size_t)0, (p.four || p.quad) ? sk::kQuadPairs : 1,
+                  p.four_over_kept ? 1 : 0);
     if (gram && B_or_N == ny && L1 == L2) {
         // the call with Y == X, which may be launched in another way
         const Layout ls = make_layout(backward || phase != 0, true, true, B_or_N, ny, L1, L2, d, lam1, lam2, flags,
                                       dt == SK_F64 ? 8 : 4, !(flags & SK_FLAG_BWD_REPLAY), phase != 0);
         const LaunchNames n = launch_names(ls.p, backward, phase, time);
         const size_t used = std::strlen(out);
-        std::snprintf(out + used, out_bytes - used, " symmetric_mode=%s symmetric_grid=%d", n.mode, ls.p.grid);
+        std::snprintf(out + used, out_bytes - used, " symmetric_mode=%s symmetric_grid=%d symmetric_over_kept_sweep=%d", n.mode, ls.p.grid,
+                      ls.p.four_over_kept ? 1 : 0);
     }
     return SK_OK;
 }

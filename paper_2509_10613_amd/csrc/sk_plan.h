@@ -75,6 +75,7 @@ struct Plan {
     int64_t nquads = 0;   // groups of four pairs of one Gram row the quad launch works through
     int64_t qd_even = 0;  // quads of a four-pair launch that are handed out in equal shares (the rest by a counter)
     int four = 0;         // four pairs per wave, backward Gram calls (sk_four.hip); lk_M: 1 = one band, 2 = several
+    bool four_over_kept = false;   // faster than a one-pair reverse sweep that takes over the forward call's sweep, too
     int fv_bands = 0;     // bands of 16 lanes per pair
     int64_t fv_gx_slot = 0;
     size_t off_fvgx = 0;  // x-side sums of the strips of the pairs in work (several strips only)
@@ -142,7 +143,7 @@ constexpr int quad_max_rows(int BL, int DT)
     return 8;
 }
 // Whether the quad kernel with eight channels and M = 5 to 8 rows per lane is faster than the solo kernel it replaces, in
-// rounds of block rows as in four_pays; a wavefront alone on its SIMD goes through them in 0.5 (quad) and 0.8 (solo) of the
+// rounds of block rows as in four_gain; a wavefront alone on its SIMD goes through them in 0.5 (quad) and 0.8 (solo) of the
 // time it takes where it shares it.  Solo and quad, us per call: L = 128, order 0, d = 8: 32 x 32 / 24 x 100 / 1 x 2000 /
 // 2 x 1000 / 128 x 128: 35 / 62 / 55 / 51 / 266 and 50 / 50 / 91 / 56 / 164; L = 70: 25 / 44 / 41 / 37 / 178 and 25 / 25 / 45 /
 // 29 / 67.  (Up to four rows, and up to six channels, the kernel is always taken.)
@@ -198,7 +199,7 @@ struct SweepLoad {
     double steps;     // block rows a lane goes through per item
     int64_t even;     // items handed out in equal shares
 };
-// Whether the four-pair kernel is the faster one.  Either launch takes rounds of `slots` items, a nearly empty round as long
+// How much faster the four-pair kernel is.  Either launch takes rounds of `slots` items, a nearly empty round as long
 // as a full one (unless the last items are handed out one by one), and a round about as long as its steps.  step: a step of
 // the four-pair kernel next to one of the other; lone: where few quads leave its wavefronts alone on their SIMDs, next to
 // where they share them.
@@ -209,13 +210,13 @@ struct SweepLoad {
 //   L = 120, order 1, d = 8 (alone): 64 / 80 / 160 / 256: 711 / 1082 / 3641 / 8982 and 766 / 1343 / 3307 / 7420
 //   L = 128, order 2, d = 3 (alone): 64 / 80 / 96 / 128: 929 / 1580 / 2110 / 3931 and 878 / 1298 / 2569 / 2857
 //   L = 200, order 0, d = 4 (chained): 40 / 48 / 64 / 128: 597 / 967 / 1173 / 4584 and 677 / 722 / 860 / 2267
-inline bool four_pays(const SweepLoad& one, const SweepLoad& four, double step, double lone)
+inline double four_gain(const SweepLoad& one, const SweepLoad& four, double step, double lone)
 {
     auto rounds = [](const SweepLoad& l) {
         return l.even < l.items ? (double)l.items / (double)l.slots + 0.3 : (double)((l.items + l.slots - 1) / l.slots);
     };
     if ((four.items < four.slots ? four.items : four.slots) <= 4 * kNumCU) step *= lone;
-    return rounds(four) * four.steps * step < rounds(one) * one.steps;
+    return rounds(one) * one.steps / (rounds(four) * four.steps * step);
 }
 // The fewest x paths for it next to the solo kernels: with fewer the quads are half empty and do not pay however many there
 // are (n x m, L = 64, order 0, d = 4: 1 x 8192 / 2 x 8192 / 5 x 4000 / 7 x 1000: 804 / 1050 / 677 / 261 us and 1248 / 1305 /
@@ -508,7 +509,7 @@ inline Plan make_plan(bool backward, bool gram, bool symmetric, int64_t nx, int6
     // orders K(X, X) is not a symmetric matrix and all N^2 pairs are solved over the shared increment buffer.
     const bool may_tri = symmetric && gram && nx == ny && lam1 == lam2;
 
-    // Four-pair mode: backward calls for Gram matrices, where it pays (four_pays).
+    // Four-pair mode: backward calls for Gram matrices, where it pays (four_gain).
     bool four = false;
     int64_t four_slots = 0;
     if (may_four && backward && gram && p.uncompute && !keep && !second_chance && !lead_lag && !p.tile && !p.lock && !p.coop &&
@@ -536,7 +537,13 @@ inline Plan make_plan(bool backward, bool gram, bool symmetric, int64_t nx, int6
             const bool sums = !p.solo && p.DT == 8 && p.nb < kWave;
             const bool alone = p.solo && occupancy == 2 && solo_bwd_waves_per_simd(p.BL, p.lk_M, p.DT) == 1;
             const double step = !p.solo ? 0.65 : (alone ? 1.75 : (p.lk_M == 2 && p.DT >= 5 ? 0.88 : 1.0));
-            four = !sums && four_pays(one, quads, step, alone && p.DT >= 8 ? 0.85 : 0.73);
+            const double gain = four_gain(one, quads, step, alone && p.DT >= 8 ? 0.85 : 0.73);
+            four = !sums && gain > 1.0;
+            // A step with a kept sweep and one without (K(X, X) of n paths): two block rows per lane of few channels, L = 128,
+            // order 1, d = 3, n = 92 / 112: 500 / 673 us and 595 / 611; order 2, n = 80 / 112: 973 / 1686 and 1015 / 1628;
+            // L = 120, order 0, d = 3, n = 92 / 112: 310 / 401 and 383 / 400.  Elsewhere small gains are enough: L = 64, order 0,
+            // d = 4, n = 128: 388 and 271; L = 100, order 1, d = 5, n = 128: 1240 and 1021.
+            p.four_over_kept = four && gain >= (p.solo && p.lk_M == 2 && p.DT <= 4 ? 1.2 : 1.0);
             four_slots = quads.slots;
             if (four) p.qd_even = quads.even;
         }

@@ -131,6 +131,11 @@ def test_launch_plan_of_the_five_configurations(lib):
     assert p["symmetric_mode"] == "four" and p["symmetric_grid"] == "2048"
     p = _plan(binding.SK_OP_GRAM_BWD, 128, 128, 128, 128, 3, 1, 1, 0, f64)
     assert p["mode"] == "four" and p["symmetric_mode"] == "solo"
+    assert p["over_kept_sweep"] == "1" and p["symmetric_over_kept_sweep"] == "0"
+    p = _plan(binding.SK_OP_GRAM_BWD, 92, 92, 128, 128, 3, 1, 1, 0, f64)      # K(X, X): a little faster, but not than a kept sweep
+    assert p["symmetric_mode"] == "four" and p["symmetric_over_kept_sweep"] == "0"
+    p = _plan(binding.SK_OP_GRAM_BWD, 92, 92, 64, 64, 4, 0, 0, 0, f64)
+    assert p["symmetric_mode"] == "four" and p["symmetric_over_kept_sweep"] == "1" and p["over_kept_sweep"] == "1"
     p = _plan(binding.SK_OP_GRAM_BWD, 48, 40, 128, 128, 3, 1, 1, 0, f64)
     assert p["mode"] == "solo" and p["kernel"] == "solo_bwd_kernel<1, 3, 2, 0, 0, 2>" and p["pairs_per_wave"] == "1"
     assert p["strips"] == "1" and p["rows_per_lane"] == "2" and "symmetric_mode" not in p
