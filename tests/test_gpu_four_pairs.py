@@ -1,5 +1,5 @@
 """The backward sweep of Gram matrices with four path pairs per wavefront (sk_four.hip) against the oracle: one and
-several strips, rows above the grid, rows of the Gram matrix that are no multiple of four, refinement inside and above the
+several bands, rows above the grid, rows of the Gram matrix that are no multiple of four, refinement inside and above the
 blocks, the time channel, float arrays, K(X, X), and pairs that drift and are taken out of their quad."""
 import numpy as np
 import pytest
@@ -18,20 +18,21 @@ def paths(seed, n, L, d, var):
     return np.cumsum(rng.normal(0.0, var ** 0.5, (n, L, d)), axis=1)
 
 
+# (Sixteen lanes with four block rows each, two from eight channels on and for blocks of 4 x 4 cells, are a band.)
 @pytest.mark.parametrize("nx,ny,L1,L2,d,lam1,lam2,flags,sym,dtype", [
-    (70, 66, 65, 64, 3, 0, 0, 0, False, torch.float64),      # one strip, every lane's rows inside the grid
-    (65, 72, 66, 12, 2, 0, 0, 1, False, torch.float64),      # 65 block rows: two rows per lane more than needed
-    (70, 68, 129, 5, 3, 0, 0, 1, False, torch.float32),      # the largest single strip of eight rows per lane
-    (67, 66, 130, 40, 3, 1, 1, 0, False, torch.float64),     # two strips
-    (65, 66, 70, 30, 8, 1, 1, 1, False, torch.float64),      # two strips of four rows per lane
+    (70, 66, 65, 64, 3, 0, 0, 0, False, torch.float64),      # one band, every row of every lane inside the grid
+    (65, 72, 66, 12, 2, 0, 0, 1, False, torch.float64),      # 65 block rows: a second band for one of them
+    (70, 68, 129, 5, 3, 0, 0, 1, False, torch.float32),      # two full bands, fewer columns than lanes
+    (67, 66, 130, 40, 3, 1, 1, 0, False, torch.float64),     # three bands of 2 x 2 cells
+    (65, 66, 70, 30, 8, 1, 1, 1, False, torch.float64),      # three bands of two rows per lane
     (130, 35, 20, 40, 5, 2, 2, 1, False, torch.float64),     # blocks of 4 x 4 cells
     (90, 54, 9, 10, 4, 3, 3, 0, False, torch.float64),       # refinement above the blocks
     (80, 61, 24, 20, 6, 0, 2, 1, False, torch.float64),      # unequal orders
     (93, 0, 33, 33, 3, 1, 1, 1, True, torch.float64),        # K(X, X): rows of the triangle
     (91, 0, 70, 70, 4, 0, 0, 0, True, torch.float32),
     (70, 0, 18, 18, 2, 0, 1, 0, True, torch.float64),        # K(X, X) with unequal orders: every pair
-    (90, 50, 35, 30, 12, 0, 0, 1, False, torch.float64),      # twelve channels, two bands
-    (70, 40, 20, 34, 14, 2, 2, 0, False, torch.float64),      # sixteen channels, blocks of 4 x 4 cells
+    (90, 50, 35, 30, 12, 0, 0, 1, False, torch.float64),     # twelve channels, two bands
+    (70, 40, 20, 34, 14, 2, 2, 0, False, torch.float64),     # sixteen channels, blocks of 4 x 4 cells
     (4600, 1, 6, 20, 2, 0, 0, 0, False, torch.float64),      # fewer rows than lanes, one y path
 ])
 def test_four_pairs_per_wave(nx, ny, L1, L2, d, lam1, lam2, flags, sym, dtype):
@@ -40,7 +41,7 @@ def test_four_pairs_per_wave(nx, ny, L1, L2, d, lam1, lam2, flags, sym, dtype):
     ny = nx if sym else ny
     sdt = sk.SK_F64 if dtype == torch.float64 else sk.SK_F32
     desc = sk.sigkernel_describe(sk.SK_OP_GRAM_BWD, nx, ny, L1, Y.shape[1], d, lam1, lam2, flags, sdt)
-    assert "pairs_per_wave=4" in desc, desc
+    assert (" symmetric_mode=four " in desc) if sym else desc.startswith("mode=four "), desc
     W = workloads.upstream_weights(88, (nx, ny))
     x = dev(X, dtype)
     K, gX, gY = sk.sigkernel_gram(x, x if sym else dev(Y, dtype), dev(W, dtype), lam1, lam2, flags)
@@ -51,6 +52,69 @@ def test_four_pairs_per_wave(nx, ny, L1, L2, d, lam1, lam2, flags, sym, dtype):
     check_grads(host(gX), gXr, dtype, "grad_X")
     if not sym:
         check_grads(host(gY), gYr, dtype, "grad_Y")
+
+
+def run_with_counters(X, Y, W, lam, flags, dtype):
+    """K, gradients, the pairs that drifted, and how often a wavefront asked the launch's counter for a quad."""
+    sym = Y is None
+    nx, L1, d = X.shape
+    ny, L2 = (nx, L1) if sym else Y.shape[:2]
+    sdt = sk.SK_F64 if dtype == torch.float64 else sk.SK_F32
+    desc = sk.sigkernel_describe(sk.SK_OP_GRAM_BWD, nx, ny, L1, L2, d, lam, lam, flags, sdt)
+    assert (" symmetric_mode=four " in desc) if sym else desc.startswith("mode=four "), desc
+    grid = int(desc.split(" symmetric_grid=" if sym else " grid=")[1].split()[0])
+    quads = sum((m + 4) // 4 for m in range(nx)) if sym else ny * ((nx + 3) // 4)
+    assert grid < quads, desc                       # wavefronts go on with further quads
+    ws = torch.empty(sk.sigkernel_workspace_bytes(sk.SK_OP_GRAM_BWD, nx, ny, L1, L2, d, lam, lam, flags, sdt),
+                     dtype=torch.uint8, device="cuda")
+    x = dev(X, dtype)
+    out = sk.sigkernel_gram(x, x if sym else dev(Y, dtype), dev(W, dtype), lam, lam, flags, ws=ws)
+    torch.cuda.synchronize()
+    at = int(desc.split("drifted_pairs_counter_at=", 1)[1].split()[0])
+    return out, int(ws[at:at + 4].view(torch.int32)[0]), int(ws[at - 4:at].view(torch.int32)[0])
+
+
+@pytest.mark.parametrize("nx,ny,L1,L2,d,lam,flags,counted,dtype", [
+    (300, 0, 60, 60, 3, 1, 0, True, torch.float64),          # K(X, X), one band: the triangle's rows, the launch's counter
+    (300, 0, 70, 70, 3, 0, 1, True, torch.float64),          # ... several bands, the time channel
+    (260, 130, 70, 64, 11, 0, 1, True, torch.float64),       # twelve channels, three bands
+    (260, 250, 24, 20, 5, 2, 1, True, torch.float32),        # blocks of 4 x 4 cells
+    (131, 90, 20, 24, 2, 0, 0, False, torch.float64),        # short: equal shares only; a last quad of three pairs
+])
+def test_wavefronts_with_several_quads(nx, ny, L1, L2, d, lam, flags, counted, dtype):
+    X = paths(1700 + nx + d, nx, L1, d, 1.0 / (d * L1))
+    Y = paths(1701 + ny, ny, L2, d, 1.0 / (d * L2)) if ny else None
+    W = workloads.upstream_weights(92, (nx, ny or nx))
+    (K, gX, gY), drifted, asked = run_with_counters(X, Y, W, lam, flags, dtype)
+    assert drifted == 0 and (asked > 0) == counted
+    Xr = rounded(X, dtype)
+    Kr, gXr, gYr = oracle.gram(Xr, Xr if Y is None else rounded(Y, dtype), rounded(W, dtype), lam, lam, flags)
+    check_values(host(K), Kr, dtype, "K")
+    check_rows(host(gX), gXr, dtype, "grad_X")
+    if ny:
+        check_rows(host(gY), gYr, dtype, "grad_Y")
+
+
+@pytest.mark.parametrize("nx,ny,L1,L2,d,lam,flags", [(260, 140, 40, 36, 3, 1, 1), (300, 0, 50, 50, 3, 1, 0),
+                                                     (260, 0, 70, 70, 4, 0, 1), (250, 130, 40, 30, 12, 0, 0)])
+def test_pairs_that_drift_leave_their_quads_and_the_wavefronts_go_on(nx, ny, L1, L2, d, lam, flags):
+    X = paths(1710 + nx + d, nx, L1, d, 1.0 / (d * L1))
+    Y = paths(1711 + ny, ny, L2, d, 1.0 / (d * L2)) if ny else None
+    rng = np.random.default_rng(1712)
+    wild = 0
+    for P, rows in ((X, (7, 100, 201)), (Y, (3, 60))):
+        if P is not None:
+            for r in rows:
+                P[r, 1:] = np.cumsum(rng.choice([-1.0, 1.0], size=(P.shape[1] - 1, d)) * (1.6 / d ** 0.5), axis=0)
+            wild += len(rows)
+    W = workloads.upstream_weights(93, (nx, ny or nx))
+    (K, gX, gY), drifted, _ = run_with_counters(X, Y, W, lam, flags, torch.float64)
+    assert 3 <= drifted <= wild * max(nx, ny) * (1 if ny else 2)
+    Kr, gXr, gYr = oracle.gram(X, X if Y is None else Y, W, lam, lam, flags)
+    check_values(host(K), Kr, torch.float64, "K")
+    check_rows(host(gX), gXr, torch.float64, "grad_X")
+    if ny:
+        check_rows(host(gY), gYr, torch.float64, "grad_Y")
 
 
 @pytest.mark.parametrize("L,d,lam,squared", [(100, 5, 1, 20.0), (100, 3, 1, 10.0), (60, 5, 0, 10.0), (40, 3, 2, 20.0)])
