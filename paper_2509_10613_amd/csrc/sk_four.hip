@@ -26,15 +26,15 @@
 //    32              0    3.8      345   6.3  12682   76.7    46700   267    65494   371
 //    8               0    4.2        0   4.2     37    4.8     1682  15.4    24725   146
 //    4               0    4.8        0   4.8      0    4.9        6   5.5     1132    13
-//    8 / 4 by band   0    4.2        0   4.3      0    4.9      100   6.3     3884    29   (as built)
+//    by band         0    3.8        0   4.4      1    5.9      105   6.7     3884    29   (as built)
 //
-// Checkpoints are what the kernel moves through memory, so a band takes 8 where no block of it can have a large increment
-// product and 4 elsewhere (kFourSteady), with the guard at kFourDriftTol.  1 / B has a term more than in the other kernels:
-// theirs is what drifts first on unrefined paths (L = 60, order 0, d = 5, squared length 10: 8315 pairs in the one-pair
-// kernel, 12671 here without the term, 15 with it; no time is seen).
+// Checkpoints are what the kernel moves through memory, so a band takes 16, 8 or 4 by the largest increment product that
+// one of its blocks can have (kFourCalm, kFourSteady), with the guard at kFourDriftTol.  1 / B has a term more than in the
+// other kernels: theirs is what drifts first on unrefined paths (L = 60, order 0, d = 5, squared length 10: 8315 pairs in
+// the one-pair kernel, 12671 here without the term, 15 with it; no time is seen).
 //
-// Bound by fp64 issue: Gram 256 x 256, L = 128, order 1, d = 3: 6.1 -> 4.2 ms; K(X, X) of 300 paths, L = 100, order 1,
-// d = 5: 4.6 -> 2.7 ms; Gram 128 x 128, L = 100, order 0, d = 16: 4.0 -> 2.7 ms.  Four block rows per lane
+// Bound by fp64 issue: Gram 256 x 256, L = 128, order 1, d = 3: 5.9 -> 3.8 ms; K(X, X) of 300 paths, L = 100, order 1,
+// d = 5: 4.6 -> 2.5 ms; Gram 128 x 128, L = 100, order 0, d = 16: 4.0 -> 2.7 ms.  Four block rows per lane
 // up to six channels, two from eight on and for blocks of 4 x 4 cells: with more the lane state does not fit the 256
 // registers of a wavefront that shares its SIMD (eight rows, d = 3: 1 KB of it in scratch, 22 ms), and a lone wavefront
 // is slower (4.7 ms).  Sixteen channels, and twelve with 4 x 4 blocks, do not fit either way and run alone on their SIMD
@@ -135,7 +135,7 @@ __device__ __forceinline__ void backward(const SweepArgs& a)
         const real gxs = a.sc * (1.0 / kSqrt3);   // of the x-side sums; the y-side sums hold sc / 2 (through dxr)
         real dxr[RL][D];
         // Increments of the lane's block rows in band s (zeros above the grid).  Returns log2 of the macro-steps between the
-        // band's checkpoints: 8 where no block of the band can have an increment product above kFourSteady, else 4.
+        // band's checkpoints, by the largest increment product that a block of the band can have.
         auto load_x = [&](int s) __attribute__((always_inline)) {
             const real* const dxp = a.dx + xi * a.xstride;
             const int I0 = (s * LP + r) * RL - a.lk_padb;
@@ -160,9 +160,9 @@ __device__ __forceinline__ void backward(const SweepArgs& a)
                 for (int c = 0; c < D; ++c) t = fma(dxr[m][c], dxr[m][c], t);
                 xlen2 = fmax(xlen2, t);
             }
-            // (|dx| |dy| per cell, times the cells of a block)
-            const real most = kFourSteady * kRsqrt12 / (C * C);
-            return wave_max(xlen2) * ylen2 <= most * most ? 3 : 2;
+            const real unit = kRsqrt12 / (C * C);   // (the cells of a block share its product)
+            const real most2 = wave_max(xlen2) * ylen2;
+            return most2 <= (kFourCalm * unit) * (kFourCalm * unit) ? 4 : (most2 <= (kFourSteady * unit) * (kFourSteady * unit) ? 3 : 2);
         };
         // the D increments of the block column the lane is at in macro-step T
         auto fetch = [&](int T, real (&y)[D]) __attribute__((always_inline)) {

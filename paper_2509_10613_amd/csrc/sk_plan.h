@@ -174,10 +174,11 @@ inline int64_t four_even_share(int64_t nquads, int64_t nwaves, int64_t instr)
 {
     return nquads < 3 * nwaves || nquads / nwaves * instr < 100000 ? nquads : nquads / 2 / nwaves * nwaves;
 }
-// Macro-steps between its checkpoints: kFourCkpt, or twice as many in a band whose largest increment product of a block,
-// |dx| |dy|, is at most kFourSteady (sk_four.hip has the pairs that drift with either; with 8 the first ones do at 0.55).
+// Macro-steps between its checkpoints: kFourCkpt, or twice or four times as many in a band whose largest increment product
+// of a block, |dx| |dy|, is at most kFourSteady or kFourCalm (sk_four.hip has the pairs that drift; the first ones do with 8 at
+// products of 0.55 and with 16 at 0.2.  Gradient errors up to either bound are those of half the spacing to a tenth).
 constexpr int kFourCkpt = 4;
-constexpr double kFourSteady = 0.5;
+constexpr double kFourSteady = 0.5, kFourCalm = 0.16;
 // Its drift guard (kDriftTol elsewhere).  With its short spacing and its 1 / B recovered values stay closer, so the guard can:
 // L = 60, order 0, d = 5, squared length 20, largest gradient error of the pairs that pass 2.8e-12 (1.1e-11 with 1e-11).
 constexpr double kFourDriftTol = 3e-12;
