@@ -537,8 +537,10 @@ inline Plan make_plan(bool backward, bool gram, bool symmetric, int64_t nx, int6
             // 64 x 64 paths of 200 and 30 points, order 0: 596 us and 690.)
             const bool sums = !p.solo && p.DT == 8 && p.nb < kWave;
             const bool alone = p.solo && occupancy == 2 && solo_bwd_waves_per_simd(p.BL, p.lk_M, p.DT) == 1;
-            const double step = !p.solo ? 0.65 : (alone ? 1.75 : (p.lk_M == 2 && p.DT >= 5 ? 0.88 : 1.0));
-            const double gain = four_gain(one, quads, step, alone && p.DT >= 8 ? 0.85 : 0.73);
+            // (Nine to twelve channels are sixteen to the solo kernel: L = 34, order 1, d = 12, (54) / (89): 242 / 478 and 142 / 246.)
+            const bool twelve = alone && DT < p.DT;
+            const double step = !p.solo ? 0.65 : (twelve ? 1.1 : (alone ? 1.75 : (p.lk_M == 2 && p.DT >= 5 ? 0.88 : 1.0)));
+            const double gain = four_gain(one, quads, step, twelve ? 0.6 : (alone && p.DT >= 8 ? 0.85 : 0.73));
             four = !sums && gain > 1.0;
             // A step with a kept sweep and one without (K(X, X) of n paths): two block rows per lane of few channels, L = 128,
             // order 1, d = 3, n = 92 / 112: 500 / 673 us and 595 / 611; order 2, n = 80 / 112: 973 / 1686 and 1015 / 1628;

@@ -206,6 +206,10 @@ def test_where_backward_gram_calls_take_four_pairs_per_wave(lib):
         assert four(N, N, 100, 100, 5, 1) == expected, N
     for N, expected in ((40, False), (48, True), (128, True)):
         assert four(N, N, 200, 200, 4, 0) == expected, N     # next to kernels that chain strips
+    # nine to twelve channels, sixteen in the one-pair kernel: K(X, X) already where its quads leave half the SIMDs empty
+    for N, L, d in ((54, 34, 12), (60, 50, 9), (48, 64, 10)):
+        assert "symmetric_mode=four" in binding.sigkernel_describe(binding.SK_OP_GRAM_BWD, N, N, L, L, d, 1, 1, 0,
+                                                                   binding.SK_F64), (N, L, d)
     # quads that are half empty or worse
     for N in (1, 2, 3):
         for M in (600, 2048, 8192):
