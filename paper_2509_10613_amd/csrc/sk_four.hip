@@ -160,7 +160,7 @@ __device__ __forceinline__ void backward(const SweepArgs& a)
                 for (int c = 0; c < D; ++c) t = fma(dxr[m][c], dxr[m][c], t);
                 xlen2 = fmax(xlen2, t);
             }
-            const real unit = kRsqrt12 / (C * C);   // (the cells of a block share its product)
+            const real unit = kRsqrt12 / (C * C) * four_calm_scale(BL, D);   // (the cells of a block share its product)
             const real most2 = wave_max(xlen2) * ylen2;
             return most2 <= (kFourCalm * unit) * (kFourCalm * unit) ? 4 : (most2 <= (kFourSteady * unit) * (kFourSteady * unit) ? 3 : 2);
         };

@@ -179,6 +179,11 @@ inline int64_t four_even_share(int64_t nquads, int64_t nwaves, int64_t instr)
 // products of 0.55 and with 16 at 0.2.  Gradient errors up to either bound are those of half the spacing to a tenth).
 constexpr int kFourCkpt = 4;
 constexpr double kFourSteady = 0.5, kFourCalm = 0.16;
+// Both are for four block rows per lane and for two of 4 x 4 cells; with two of fewer cells an error goes half as far per
+// macro-step.  96 x 48 paths, gradient errors (mean, largest) and us, one-pair / bounds as above / twice those: L = 60, order 1,
+// d = 8, squared length 20: 1.3e-14, 3.9e-14, 379 / 1.4e-14, 4.2e-14, 306 / 1.4e-14, 4.0e-14, 296; L = 30, order 0, d = 16,
+// squared length 6: 3.6e-15, 2.2e-14, 510 / 3.3e-15, 6.1e-15, 212 / 3.2e-15, 6.2e-15, 185.
+constexpr double four_calm_scale(int BL, int DT) { return BL < 2 && four_rows(BL, DT) == 2 ? 2.0 : 1.0; }
 // Its drift guard (kDriftTol elsewhere).  With its short spacing and its 1 / B recovered values stay closer, so the guard can:
 // L = 60, order 0, d = 5, squared length 20, largest gradient error of the pairs that pass 2.8e-12 (1.1e-11 with 1e-11).
 constexpr double kFourDriftTol = 3e-12;

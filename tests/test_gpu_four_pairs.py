@@ -117,10 +117,12 @@ def test_pairs_that_drift_leave_their_quads_and_the_wavefronts_go_on(nx, ny, L1,
         check_rows(host(gY), gYr, torch.float64, "grad_Y")
 
 
-@pytest.mark.parametrize("L,d,lam,squared", [(100, 5, 1, 20.0), (100, 3, 1, 10.0), (60, 5, 0, 10.0), (40, 3, 2, 20.0)])
+@pytest.mark.parametrize("L,d,lam,squared", [(100, 5, 1, 20.0), (100, 3, 1, 10.0), (60, 5, 0, 10.0), (40, 3, 2, 20.0),
+                                             (60, 8, 1, 20.0), (40, 12, 1, 20.0), (30, 16, 0, 10.0)])
 def test_four_pairs_per_wave_on_larger_increments(L, d, lam, squared):
-    # The inverse recurrence holds on paths on which the one-pair kernels' does (they list 0, 0, 513 and 8 pairs of these
-    # four, with gradients within 7e-14, 2e-13, 4e-12 and 7e-13 of their largest entry).  Bounds: one pair in 500, and what
+    # The inverse recurrence holds on paths on which the one-pair kernels' does (they list 0, 0, 513 and 8 pairs of the first
+    # four, with gradients within 7e-14, 2e-13, 4e-12 and 7e-13 of their largest entry; of the last three, with two block rows
+    # per lane, 0, 0 and about 100, within 4e-14, 2e-14 and 2e-12).  Bounds: one pair in 500, and what
     # the drift guard lets pass of forward values (3e-12).
     nx, ny = 96, 48
     X, Y = paths(1600 + L + d, nx, L, d, squared / (d * (L - 1))), paths(1601 + L + d, ny, L, d, squared / (d * (L - 1)))
