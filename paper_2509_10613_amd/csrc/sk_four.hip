@@ -489,36 +489,34 @@ __device__ __forceinline__ void backward(const SweepArgs& a)
             if (r == 0 && ((bad >> (16 * g)) & 0xffffull) != 0ull) list_drifted(a, pid, pid2);
             for (int i = 0; i < kQuadPairs; ++i) out |= ((bad >> (16 * i)) & 0xffffull) != 0ull ? 1u << i : 0u;
             for (int t = lane; t < q * D; t += kWave) gyp[t] = 0.0;
-            if (__ballot(inrow && ((out >> g) & 1u) == 0) == 0ull) {   // no pair of the quad is left: nothing to sweep again
-                out = 0;
-                queue.next(a);
-            }
-            continue;
-        }
-        if (M > 1 && a.want_gx && valid) {
-            real* const gx = a.gdx + xi * a.xstride;
-            for (int s = 0; s < ns; ++s) {
-                const real* gsp = a.fv_gx + slot * a.fv_gx_slot + (long)s * RL * D * kWave;
+            if (__ballot(inrow && ((out >> g) & 1u) == 0) != 0ull) continue;
+            // (no pair of the quad is left: nothing to sweep again)
+        } else {
+            if (M > 1 && a.want_gx && valid) {
+                real* const gx = a.gdx + xi * a.xstride;
+                for (int s = 0; s < ns; ++s) {
+                    const real* gsp = a.fv_gx + slot * a.fv_gx_slot + (long)s * RL * D * kWave;
 #pragma unroll
-                for (int m = 0; m < RL; ++m) {
-                    const int I = (s * LP + r) * RL + m - a.lk_padb;
-                    if (I >= 0) {
+                    for (int m = 0; m < RL; ++m) {
+                        const int I = (s * LP + r) * RL + m - a.lk_padb;
+                        if (I >= 0) {
 #pragma unroll
-                        for (int c = 0; c < D; ++c)
-                            unsafeAtomicAdd(gx + (I >> a.rs1) * a.DS + c, ld_scratch(gsp + ((m * D + c) * kWave + lane)) * gxs);
+                            for (int c = 0; c < D; ++c)
+                                unsafeAtomicAdd(gx + (I >> a.rs1) * a.DS + c, ld_scratch(gsp + ((m * D + c) * kWave + lane)) * gxs);
+                        }
                     }
                 }
             }
-        }
-        if (a.want_gy) {
-            real* gdy = a.gdy + yi * a.ystride;
-            for (int t = lane; t < q * D; t += kWave) {
-                const int b = t / D, c = t - b * D;
-                unsafeAtomicAdd(&gdy[(long)b * a.DS + c], 2.0 * gyp[t]);
-                gyp[t] = 0.0;
+            if (a.want_gy) {
+                real* gdy = a.gdy + yi * a.ystride;
+                for (int t = lane; t < q * D; t += kWave) {
+                    const int b = t / D, c = t - b * D;
+                    unsafeAtomicAdd(&gdy[(long)b * a.DS + c], 2.0 * gyp[t]);
+                    gyp[t] = 0.0;
+                }
+            } else {
+                for (int t = lane; t < q * D; t += kWave) gyp[t] = 0.0;
             }
-        } else {
-            for (int t = lane; t < q * D; t += kWave) gyp[t] = 0.0;
         }
         out = 0;
         queue.next(a);
