@@ -469,8 +469,8 @@ def main():
                     help="the backward call sweeps forward again instead of taking over the sweep of the forward call "
                          "before it (SK_FLAG_KEEP_FORWARD / SK_FLAG_HAVE_FORWARD)")
     ap.add_argument("--keep-forward-any-size", action="store_true",
-                    help="keep the forward sweep whatever workspace that takes (c3: 7 GB of checkpoints per pair for a "
-                         "step that is 10 % shorter); by default only if it adds at most 1 GiB to the backward call's workspace")
+                    help="keep the forward sweep whatever workspace that takes (c3: 7 GB of checkpoints in the one-pair "
+                         "kernels); by default only if it adds at most 1 GiB to the backward call's workspace")
     ap.add_argument("--no-cpu-baseline", action="store_true")
     ap.add_argument("--no-parity", action="store_true", help="skip the comparison with the oracle after the timed region")
     ap.add_argument("--cpu-seconds", type=float, default=12.0)
