@@ -96,6 +96,9 @@ int validate(int64_t nx, int64_t ny, int64_t L1, int64_t L2, int64_t d, int lam1
     return SK_OK;
 }
 
+// Internal bit beside the caller's flags: the plan whose scratch stays small (no wide mode).
+constexpr int kSmallScratch = 1 << 20;
+
 // The scratch of a call: the launch plan's, then (backward calls whose reverse sweep inverts Eq. (1)) that of the
 // launch that solves drifted pairs once more with the replay kernel.
 struct Layout {
@@ -116,9 +119,10 @@ Layout make_layout(bool backward, bool gram, bool symmetric, int64_t nx, int64_t
     Layout l;
     l.ll = (flags & SK_FLAG_LEAD_LAG) != 0;
     if (l.ll) { lam1 += 1; lam2 += 1; }
-    l.p = sk::make_plan(backward, gram, symmetric, nx, ny, L1, L2, d, lam1, lam2, io_elem, uncompute, keep, false, l.ll);
+    l.p = sk::make_plan(backward, gram, symmetric, nx, ny, L1, L2, d, lam1, lam2, io_elem, uncompute, keep, false, l.ll, true,
+                        !(flags & kSmallScratch));
     l.total = l.p.total;
-    if (l.p.valid && backward && l.p.uncompute) {
+    if (l.p.valid && backward && l.p.uncompute && !l.p.wide) {   // (the wide kernels divide by nothing: no pair of theirs drifts)
         l.sc = sk::make_plan(true, gram, symmetric, nx, ny, L1, L2, d, lam1, lam2, io_elem, false, false, true, l.ll);
         l.has_sc = l.sc.valid;
         l.off_sc = l.p.total;
@@ -193,6 +197,8 @@ int run(const Layout& lay, bool backward, const void* x, const void* y, void* k,
     a.fv_bands = p.fv_bands;
     a.fv_gx = p.fv_gx_slot ? reinterpret_cast<double*>(base + p.off_fvgx) : nullptr;
     a.fv_gx_slot = p.fv_gx_slot;
+    a.wd_scratch = p.wide ? reinterpret_cast<double*>(base + p.off_wd) : nullptr;
+    a.wd_slot = p.wd_slot;
     a.band = p.band; a.bd_nbands = p.bd_nbands;
     a.bd_off_y = (unsigned)p.bd_off_y; a.bd_off_gy = (unsigned)p.bd_off_gy; a.bd_off_rings = (unsigned)p.bd_off_rings;
     a.bd_flags = reinterpret_cast<int*>(base + p.off_flags);
@@ -280,6 +286,7 @@ int run(const Layout& lay, bool backward, const void* x, const void* y, void* k,
     else if (p.four) SK_CHECK(launch_sweep_four(p.BL, p.DT, a, p.grid, p.lds_bytes, st));
     else if (p.tile) SK_CHECK(launch_sweep_tile(backward, p.DT, a, p.grid, p.lds_bytes, st));
     else if (p.solo) SK_CHECK(launch_sweep_solo(backward, p.BL, p.DT, a, p.grid, p.lds_bytes, st));
+    else if (p.wide) SK_CHECK(launch_sweep_wide(backward, p.BL, a, p.grid, st));
     else SK_CHECK(launch_sweep(backward, p.BL, p.DT, a, p.grid, p.lds_bytes, st));
     if (ttag) SK_CHECK(ev.end(st));
     // Pairs whose inverse recurrence drifted were left out of the gradient sums and listed: the replay kernel solves
@@ -372,7 +379,7 @@ int dispatch(bool backward, bool gram, const void* x, const void* y, void* k, co
              void* grad_y, int64_t nx, int64_t ny, int64_t L1, int64_t L2, int64_t d, int lam1, int lam2, int flags,
              sk_dtype dt, void* ws, size_t ws_bytes, void* stream)
 {
-    int rc = validate(nx, ny, L1, L2, d, lam1, lam2, flags, (int)dt);
+    int rc = validate(nx, ny, L1, L2, d, lam1, lam2, flags & ~kSmallScratch, (int)dt);
     if (rc != SK_OK) return rc;
     const int64_t npairs = gram ? nx * ny : nx;
     if (npairs == 0 && !(gram && backward)) return SK_OK;
@@ -515,7 +522,11 @@ extern "C" int sigkernel_bwd_static(const void* x, const void* y, const void* gr
                     "(its scratch is shared by every call on the device)");
     int rc = validate(B, B, L1, L2, d, lam1, lam2, flags, (int)dt);
     if (rc != SK_OK) return rc;
-    const size_t need = B > 0 ? sigkernel_workspace_bytes(SK_OP_BWD, B, 0, L1, L2, d, lam1, lam2, flags, dt) : 0;
+    size_t need = B > 0 ? sigkernel_workspace_bytes(SK_OP_BWD, B, 0, L1, L2, d, lam1, lam2, flags, dt) : 0;
+    if (need > kStaticScratchBytes) {
+        flags |= kSmallScratch;
+        need = make_layout(true, false, false, B, B, L1, L2, d, lam1, lam2, flags, dt == SK_F64 ? 8 : 4, !(flags & SK_FLAG_BWD_REPLAY)).total;
+    }
     if (need > kStaticScratchBytes)
         return fail(SK_ERR_WORKSPACE, "this shape needs %zu bytes of scratch, sigkernel_bwd_static holds %zu per device; "
                     "use sigkernel_bwd with a workspace of the caller's", need, kStaticScratchBytes);
@@ -541,7 +552,7 @@ struct LaunchNames {
 LaunchNames launch_names(const sk::Plan& p, bool backward, int phase, bool time)
 {
     LaunchNames l;
-    const bool lean = p.lock || p.solo || p.tile || p.quad || p.band;
+    const bool lean = p.lock || p.solo || p.tile || p.quad || p.band || p.wide;
     l.strips = lean ? p.lk_ns : p.ns;
     l.rows = lean ? p.lk_M : 1;
     if (p.band) {
@@ -565,6 +576,12 @@ LaunchNames launch_names(const sk::Plan& p, bool backward, int phase, bool time)
         if (backward) std::snprintf(l.kernel, sizeof(l.kernel), "tile_bwd_kernel<%d, %s>", p.DT / 4, p.nb + 1 < sk::kTileCols - 1 ? "true" : "false");
         else std::snprintf(l.kernel, sizeof(l.kernel), "tile_fwd_kernel<%d>", p.DT / 4);
         l.threads = sk::kWavesPerWG * sk::kWave;
+    } else if (p.wide) {
+        l.mode = p.nw > 1 ? "cooperative" : "wave-per-pair";
+        if (backward) std::snprintf(l.kernel, sizeof(l.kernel), "wide_bwd_kernel<%d, %d>", p.BL, p.ll == 1 ? 1 : 0);
+        else if (p.ll == 1) std::snprintf(l.kernel, sizeof(l.kernel), "wide_ll_fwd_kernel<%d>", p.BL);
+        else std::snprintf(l.kernel, sizeof(l.kernel), "sweep_fwd_kernel<%d, 0, false>", p.BL);
+        l.threads = p.nw * sk::kWave;
     } else if (p.four) {
         l.mode = "four";
         std::snprintf(l.kernel, sizeof(l.kernel), "four_bwd_kernel<%d, %d, %d, %s, %d>", p.BL, p.DT, p.lk_M, time ? "true" : "false",
@@ -588,7 +605,7 @@ LaunchNames launch_names(const sk::Plan& p, bool backward, int phase, bool time)
     } else {
         const char* base = !backward ? "sweep_fwd" : (p.uncompute ? "sweep_bwdu" : "sweep_bwd");
         l.mode = p.coop ? "cooperative" : "wave-per-pair";
-        std::snprintf(l.kernel, sizeof(l.kernel), "%s%s_kernel<%d, %d, %s>", base, p.coop ? "_coop" : "", p.BL, p.DT,
+        std::snprintf(l.kernel, sizeof(l.kernel), "%s%s_kernel<%d, %d, %s>", base, p.coop ? "_coop" : "", p.BL, p.DT ? p.DT : -1,
                       (p.y_lds && p.DT) ? "true" : "false");
         l.threads = (p.coop ? p.nw : sk::kWavesPerWG) * sk::kWave;
     }

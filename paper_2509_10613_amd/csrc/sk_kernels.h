@@ -97,6 +97,8 @@ struct SweepArgs {
     int fv_bands;        // four pairs per wave, backward: bands of 16 lanes per pair (nseg: checkpoint places per band),
     real* fv_gx;         // per slot the x-side sums of the bands of the pairs in work (several bands only)
     long fv_gx_slot;
+    real* wd_scratch;    // wide kernels (any channel count): per workgroup p of every block and, backward, the blocks' edges
+    long wd_slot;        // (uses lk_ns, lk_NT, lk_padb, nw)
     // lock-step mode on a batch of pairs of double paths: the kernels read the caller's points and write the
     // caller's gradients themselves (no preparation and finalisation launches, no global accumulators)
     int fused;
@@ -157,6 +159,8 @@ hipError_t launch_sweep_solo_one(bool backward, int BL, int DT, const SweepArgs&
 hipError_t launch_sweep_four(int BL, int DT, const SweepArgs& a, int grid, size_t lds, hipStream_t st);
 // tile mode (a.tile != 0), defined in sk_tile.hip
 hipError_t launch_sweep_tile(bool backward, int DT, const SweepArgs& a, int grid, size_t lds, hipStream_t st);
+// wide mode, defined in sk_wide.hip
+hipError_t launch_sweep_wide(bool backward, int BL, const SweepArgs& a, int grid, hipStream_t st);
 // quad mode (a.quad != 0; forward only), defined in sk_quad.hip
 hipError_t launch_sweep_quad(int BL, int DT, const SweepArgs& a, int grid, size_t lds, hipStream_t st);
 // lock-step mode (a.lock != 0), defined in sk_lockstep.hip

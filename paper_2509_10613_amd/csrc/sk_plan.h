@@ -18,7 +18,8 @@ constexpr size_t kLdsPerWave = kLdsPerCU / kWavesPerWG - 1024;
 constexpr int kNumCU = 256;
 constexpr int kMaxBL = 2;
 
-// Channel counts with a dedicated kernel instantiation (increments kept in registers).
+// Channel counts with a dedicated kernel instantiation (increments kept in registers).  (More: the wide kernels, or, where
+// their scratch is too much, the sweep kernels with a run-time loop over the channels, template argument -1.)
 constexpr int kTemplD[] = {2, 3, 4, 5, 6, 8, 16};
 
 inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
@@ -79,6 +80,9 @@ struct Plan {
     int fv_bands = 0;     // bands of 16 lanes per pair
     int64_t fv_gx_slot = 0;
     size_t off_fvgx = 0;  // x-side sums of the strips of the pairs in work (several strips only)
+    int wide = 0;         // p of every block in scratch, any channel count and any number of strips (sk_wide.hip)
+    int64_t wd_slot = 0;  // doubles of that scratch per workgroup
+    size_t off_wd = 0;
     int solo = 0;   // one wave per pair, a single strip of 64 * lk_M block rows (many pairs of short paths)
     int lock = 0, lk_M = 0, lk_ns = 0, lk_NT = 0, lk_padb = 0, lk_rowlen = 0;
     size_t lk_off_y = 0, lk_off_gy = 0, lk_off_cring = 0, lk_off_gp = 0, lk_off_krows = 0, lk_off_arows = 0,
@@ -234,6 +238,14 @@ constexpr int four_min_paths(int BL) { return BL == 0 ? 7 : (BL == 1 ? 5 : 6); }
 constexpr int kTileRowPad = 8;     // backward: node columns kept left of column 0 in the pair's bottom row (all 1)
 constexpr int kTileCkChunks = 8;   // backward: chunks of 8 macro-steps between two checkpoints (kept in LDS)
 
+// Wide mode: waves per workgroup at most, doubles per block of the stored edges (right edge, and bottom edge without the
+// corner they share), macro-steps per chunk (what a wave holds of the coming chunk stays in registers), and the scratch that
+// its resident workgroups may take together.
+constexpr int kWideMaxWaves = 8;
+constexpr int wide_edge_values(int BL) { return 2 * (1 << BL) - 1; }
+constexpr int wide_chunk(int BL) { return BL == 2 ? 4 : 8; }
+constexpr size_t kWideScratch = (size_t)8 << 30;
+
 // Band mode: strips per workgroup, block columns per hand-over ring, coarse y columns per y ring (powers of
 // two), chunks the data-moving wave works ahead, and the bound on its polls of another workgroup's counter.
 constexpr int kBandStrips = 4, kBandRing = 64, kBandYRing = 512, kBandLead = 2, kBandSpin = 1 << 22, kBandSlack = 8, kBandLeadRev = 3;
@@ -241,6 +253,25 @@ constexpr int kBandStrips = 4, kBandRing = 64, kBandYRing = 512, kBandLead = 2, 
 // Band mode takes over from three strips on (a single band then: measured a little ahead of the cooperative kernels).
 constexpr int kBandMinStrips = 2;
 constexpr int64_t kCoopMaxPairs = 1024;   // above this, one wave per pair already fills the chip
+
+// Whether the wide kernels take the place of the wave-per-pair or cooperative kernels that the plan has come to: above
+// sixteen channels always, backward also where those keep the y side out of LDS (their sums are then an atomic addition per
+// block and channel) and next to the cooperative kernels with sixteen channels.  us per call, those kernels and these
+// (d channels, order in brackets):
+//   Gram 66 x 593, L = 124, 76, d = 19 (1), forward: 39185 and 4711;  31 x 917, L = 16, d = 19 (1), step: 24879 and 2976
+//   64 pairs, L = 889, 460, d = 19 (0), step: 74602 and 2411;  96 pairs, L = 38, 68, d = 17 (1), forward: 215 and 39
+//   Gram 59 x 106, L = 232, 164, d = 10 (0), step: 185727 and 9105 (y in memory);  1500 pairs, L = 300, 700, backward, y in
+//   memory, d = 5 (0) / (1): 49543 / 49937 and 7085 / 9599;  d = 8: 119663 / 121405 and 7265 / 9784
+//   backward with sixteen channels, cooperative, (0) / (1) / (2): 8 pairs, L = 150: 279 / 416 / 500 and 168 / 217 / 357; 64 pairs,
+//   L = 300: 586 / 959 / 1420 and 393 / 485 / 835; 300 pairs, L = 200, 250: 873 / 905 / 1531 and 575 / 785 / 1306
+// Not elsewhere: forward with sixteen channels, 300 pairs, L = 200, 250: 150 / 180 / 248 and 195 / 206 / 288; backward, sixteen
+// channels, wave per pair, 1500 pairs, L = 90 (1) / (2): 624 / 894 and 763 / 1250; up to eight channels with y in LDS, 64 pairs,
+// L = 1500, d = 3 (1), backward: 5140 and 9668; forward with y in memory, 1500 pairs, L = 300, 700, d = 8 (0): 1468 and 2530.
+inline bool wide_pays(const Plan& p)
+{
+    if (p.lock || p.solo || p.tile || p.quad || p.four || p.band) return false;
+    return p.DT == 0 || (p.backward && (!p.y_lds || (p.coop && p.DT == 16)));
+}
 
 constexpr int kUncomputeS = 8;   // macro-steps between checkpoints when the reverse sweep inverts Eq. (1)
 constexpr size_t kSecondChanceBytes = (size_t)8 << 20;   // scratch of the launch that solves drifted pairs once more
@@ -254,7 +285,7 @@ constexpr double kDriftTol = 1e-11;
 
 inline Plan make_plan(bool backward, bool gram, bool symmetric, int64_t nx, int64_t ny, int64_t L1, int64_t L2,
                       int64_t d, int lam1, int lam2, int io_elem, bool uncompute = true, bool keep = false,
-                      bool second_chance = false, bool lead_lag = false, bool may_four = true)
+                      bool second_chance = false, bool lead_lag = false, bool may_four = true, bool may_wide = true)
 {
     // lead_lag: the sweep of two lead-lag paths (Section 4) on the grid of the original increments; lam1 and lam2 then
     // count the lead-lag level as one more dyadic level (the caller's orders plus one), L1, L2 and d are the caller's.
@@ -644,6 +675,36 @@ inline Plan make_plan(bool backward, bool gram, bool symmetric, int64_t nx, int6
         }
     }
 
+    // Wide mode takes over what is left to the wave-per-pair and the cooperative kernels with more channels than those hold
+    // in registers, or with y increments (and their sums) that do not fit in LDS.
+    if (may_wide && wide_pays(p) && (!backward || p.uncompute) && !second_chance) {
+        const int NT = (int)align_up((size_t)p.nb + kWave - 1, 8);
+        const int64_t pairs = may_tri ? nx * (nx + 1) / 2 : p.npairs;
+        const int64_t slot = (int64_t)p.ns * kWave * (NT + (backward ? (int64_t)(NT + 2) * wide_edge_values(p.BL) : 0));
+        // as many waves per pair as fill the chip: two wavefronts per SIMD by registers, forward four
+        const int64_t resident = (backward ? 8 : 16) * kNumCU;
+        int64_t nw = (resident + pairs - 1) / pairs;
+        if (nw > p.ns) nw = p.ns;
+        if (nw > kWideMaxWaves) nw = kWideMaxWaves;
+        int64_t grid = resident / nw;
+        if (grid > pairs) grid = pairs;
+        grid = (pairs + (pairs + grid - 1) / grid - 1) / ((pairs + grid - 1) / grid);   // the same rounds, evenly filled
+        const int64_t fit = (int64_t)(kWideScratch / ((size_t)slot * elem));
+        if (grid > fit) grid = fit;
+        if (grid >= (pairs < kNumCU / 8 ? pairs : kNumCU / 8)) {
+            p.wide = 1; p.coop = 0;
+            p.nw = (int)nw;
+            p.tri = may_tri ? 1 : 0;
+            p.npairs = pairs;
+            p.lk_M = 1; p.lk_ns = p.ns; p.lk_NT = NT; p.lk_padb = p.ns * kWave - p.mb;
+            p.wd_slot = slot;
+            p.y_lds = 0;
+            p.lds_wave = p.lds_bytes = 0;
+            p.grid = (int)grid;
+            p.nslots = grid;
+        }
+    }
+
     // Workspace layout (all offsets 256-byte aligned).
     size_t off = 0;
     auto take = [&](size_t bytes) { size_t o = off; off = align_up(off + bytes, 256); return o; };
@@ -656,6 +717,7 @@ inline Plan make_plan(bool backward, bool gram, bool symmetric, int64_t nx, int6
         p.off_dxT = take((size_t)nx * p.xstride * elem);
         p.off_dyT = symmetric ? p.off_dxT : take((size_t)ny * p.ystride * elem);
     }
+    if (p.wide) p.off_wd = take((size_t)p.nslots * p.wd_slot * elem);
     p.rows_slot = p.four ? (int64_t)p.fv_bands * kQuadPairs * p.rowlen : (int64_t)p.ns * p.rowlen;
     p.off_rows = take((size_t)p.nslots * p.rows_slot * elem);
     if (backward) {
@@ -663,12 +725,12 @@ inline Plan make_plan(bool backward, bool gram, bool symmetric, int64_t nx, int6
             p.off_gdxT = take((size_t)nx * p.xstride * elem);
             p.off_gdyT = symmetric ? p.off_gdxT : take((size_t)ny * p.ystride * elem);
         }
-        p.adj_slot = (p.band && p.bd_nbands > 4 ? p.bd_nbands : 4) * (int64_t)p.rowlen;   // two rows of 2C values per block column; band mode: one row per band
+        p.adj_slot = p.wide ? 0 : (p.band && p.bd_nbands > 4 ? p.bd_nbands : 4) * (int64_t)p.rowlen;   // two rows of 2C values per block column; band mode: one row per band
         p.off_adj = take((size_t)p.nslots * p.adj_slot * elem);
         // lane state kept per checkpoint: right edge, bottom edge, bottom-left corner
         const bool lean = p.lock || p.solo || p.tile || p.band || p.four;
         const int NVC = lean ? p.lk_M * R + C + 2 : R + C + 2;
-        p.ckpt_slot = p.tile ? 0 : (int64_t)(lean ? p.lk_ns : p.ns) * (p.nseg + 1) * NVC * kWave;
+        p.ckpt_slot = p.tile || p.wide ? 0 : (int64_t)(lean ? p.lk_ns : p.ns) * (p.nseg + 1) * NVC * kWave;
         if (p.four) {
             p.ckpt_slot = (int64_t)p.fv_bands * p.nseg * four_ckpt_values(p.BL, p.DT) * kWave;
             p.fv_gx_slot = p.fv_bands > 1 ? (int64_t)p.fv_bands * four_rows(p.BL, p.DT) * p.DT * kWave : 0;
@@ -694,7 +756,7 @@ inline Plan make_plan(bool backward, bool gram, bool symmetric, int64_t nx, int6
     p.valid = true;
     if (p.four && p.total > kFourScratch) {
         const Plan one = make_plan(backward, gram, symmetric, nx, ny, L1, L2, d, lam1, lam2, io_elem, uncompute, keep,
-                                   second_chance, lead_lag, false);
+                                   second_chance, lead_lag, false, may_wide);
         if (one.total < p.total) return one;
     }
     return p;
