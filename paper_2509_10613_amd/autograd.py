@@ -15,6 +15,11 @@ library's flag takes t_i = i/(L-1)) is an ordinary channel: ``with_times(x, t)``
 ``times=`` / ``times_x=, times_y=`` and do that for the caller.
 
 The gradients are first-order only (the backward pass is not itself differentiable).
+
+Each call goes to the same wrapper in native code first (csrc/sk_torch.cpp: the same library calls as nodes of PyTorch's
+graph; the classes below cost a short training pass 20 to 90 us of host time).  It leaves to the classes what is not the
+ordinary case: tracers and function transforms, forward gradients, kept workspaces above _KEEP_LIMIT, and everything that
+is an error.
 """
 import threading
 import weakref
@@ -22,6 +27,9 @@ import weakref
 import torch
 
 from . import binding as sk
+
+sk.load()
+from . import _native  # noqa: E402  (needs the library, and raises if it has not been built)
 
 
 # Bytes of workspace a forward call may hold on to for its backward call, as long as its graph lives.  A sweep that takes
@@ -213,7 +221,8 @@ def signature(x, N, flags=0, times=None):
     caller's own, appended as the last channel."""
     if times is not None:
         x = with_times(x, times)
-    return _Signature.apply(x, N, flags)
+    out = _native.signature(x, N, flags)
+    return _Signature.apply(x, N, flags) if out is None else out
 
 
 def with_times(x, t):
@@ -226,7 +235,8 @@ def with_times(x, t):
 def sig_mmd2(X, Y, lam1=0, lam2=0, flags=0):
     """mean K(X,X) - 2 mean K(X,Y) + mean K(Y,Y) for device tensors X[N,L1,d], Y[M,L2,d] (sigkernel_mmd2: value and
     gradients in one call, the upstream weights never leave the GPU); differentiable in X and Y."""
-    return _Mmd2.apply(X, Y, lam1, lam2, flags)
+    out = _native.mmd2(X, Y, lam1, lam2, flags)
+    return _Mmd2.apply(X, Y, lam1, lam2, flags) if out is None else out
 
 
 def sig_kernel(x, y, lam1=0, lam2=0, flags=0, times_x=None, times_y=None):
@@ -236,7 +246,8 @@ def sig_kernel(x, y, lam1=0, lam2=0, flags=0, times_x=None, times_y=None):
         raise ValueError("give time grids for both sides or for neither")
     if times_x is not None:
         x, y = with_times(x, times_x), with_times(y, times_y)
-    return _PairKernel.apply(x, y, lam1, lam2, flags)
+    out = _native.pair(x, y, lam1, lam2, flags, _KEEP_LIMIT)
+    return _PairKernel.apply(x, y, lam1, lam2, flags) if out is None else out
 
 
 def sig_kernel_gram(X, Y=None, lam1=0, lam2=0, flags=0, times_x=None, times_y=None):
@@ -250,6 +261,9 @@ def sig_kernel_gram(X, Y=None, lam1=0, lam2=0, flags=0, times_x=None, times_y=No
             Y = with_times(Y, times_y)
     elif times_y is not None:
         raise ValueError("give time grids for both sides or for neither")
+    out = _native.gram(X, Y, lam1, lam2, flags, _KEEP_LIMIT)
+    if out is not None:
+        return out
     if Y is None:
         return _GramKernelSym.apply(X, lam1, lam2, flags)
     return _GramKernel.apply(X, Y, lam1, lam2, flags)

@@ -1,13 +1,16 @@
 """Compile the HIP library (libsigkernel.so, gfx950) in-tree with hipcc."""
+import importlib.util
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libsigkernel.so")
+NATIVE = os.path.join(HERE, "_native.so")   # the autograd wrappers' host path (a Python module over the library)
 SOURCES = ["sk_api.hip", "sk_kernels.hip", "sk_lockstep.hip", "sk_solo.hip", "sk_solo_one.hip", "sk_tile.hip", "sk_tile_bwd.hip", "sk_quad.hip", "sk_four.hip", "sk_band.hip", "sk_wide.hip", "sg_horner.hip", "sg_horner_bwd.hip", "sg_horner_bwd_matrix.hip"]
 HEADERS = ["sk_plan.h", "sk_kernels.h", "sk_dev.h", "sk_lane.h", "sk_solo_impl.h", "sk_tile.h", "sk_quad.h", "sg_plan.h", "sg_kernels.h", "sg_dev.h"]
 PUBLIC = ["sigkernel.h", "signature.h"]
@@ -23,9 +26,27 @@ def _stale(target, deps):
     return (not os.path.exists(target)) or any(os.path.getmtime(target) < os.path.getmtime(d) for d in deps)
 
 
+def _build_native():
+    """csrc/sk_torch.cpp against the installed torch's headers and libraries and the library beside it."""
+    torch = os.path.dirname(importlib.util.find_spec("torch").origin)
+    rocm = os.environ.get("ROCM_PATH", "/opt/rocm")
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM", "-I", os.path.join(ROOT, "include")]
+    for inc in (os.path.join(torch, "include"), os.path.join(torch, "include", "torch", "csrc", "api", "include"),
+                os.path.join(rocm, "include"), sysconfig.get_paths()["include"]):
+        cmd += ["-isystem", inc]
+    cmd += [os.path.join(CSRC, "sk_torch.cpp"), "-o", NATIVE, "-L" + os.path.join(torch, "lib"), "-lc10", "-lc10_hip", "-ltorch_cpu",
+            "-ltorch_python", "-L" + HERE, "-lsigkernel", "-Wl,-rpath,$ORIGIN"]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError("g++ failed on sk_torch.cpp:\n" + r.stderr)
+
+
 def build(force: bool = False, verbose: bool = False, extra_flags=()) -> str:
     deps = [os.path.join(CSRC, f) for f in SOURCES + HEADERS] + [os.path.join(ROOT, "include", h) for h in PUBLIC]
+    native_deps = [os.path.join(CSRC, "sk_torch.cpp")] + [os.path.join(ROOT, "include", h) for h in PUBLIC]
     if not force and not _stale(LIB, deps):
+        if _stale(NATIVE, native_deps):
+            _build_native()
         return LIB
     objdir = os.path.join(HERE, "_build")
     os.makedirs(objdir, exist_ok=True)
@@ -51,6 +72,7 @@ def build(force: bool = False, verbose: bool = False, extra_flags=()) -> str:
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError("link failed:\n" + r.stderr)
+    _build_native()
     return LIB
 
 

@@ -1,0 +1,109 @@
+"""The wrappers' native host path (csrc/sk_torch.cpp) against the torch.autograd.Function classes it stands for: the same values
+and gradients, the same calls taken and refused."""
+import pytest
+import torch
+
+from paper_2509_10613_amd import _native
+from paper_2509_10613_amd import autograd as ska
+from paper_2509_10613_amd import binding as sk
+
+pytestmark = pytest.mark.gpu
+
+
+def paths(seed, n, L, d, dtype=torch.float64):
+    g = torch.Generator(device="cuda")
+    g.manual_seed(seed)
+    return ((torch.randn(n, L, d, generator=g, device="cuda", dtype=torch.float64) / (d * L) ** 0.5).cumsum(1)).to(dtype)
+
+
+# (name, the wrapper, the class)
+CALLS = [
+    ("pairs", lambda x, y: ska.sig_kernel(x, y, 1, 1), lambda x, y: ska._PairKernel.apply(x, y, 1, 1, 0)),
+    ("pairs of many strips", lambda x, y: ska.sig_kernel(x, y, 3, 3, 1), lambda x, y: ska._PairKernel.apply(x, y, 3, 3, 1)),
+    ("gram", lambda x, y: ska.sig_kernel_gram(x, y, 0, 1), lambda x, y: ska._GramKernel.apply(x, y, 0, 1, 0)),
+    ("gram, kept sweep", lambda x, y: ska.sig_kernel_gram(x, y, 1, 1, 8), lambda x, y: ska._GramKernel.apply(x, y, 1, 1, 8)),
+    ("gram of one set", lambda x, y: ska.sig_kernel_gram(x + y), lambda x, y: ska._GramKernelSym.apply(x + y, 0, 0, 0)),
+    ("mmd", lambda x, y: ska.sig_mmd2(x, y, 1, 1), lambda x, y: ska._Mmd2.apply(x, y, 1, 1, 0)),
+    ("signature", lambda x, y: ska.signature(x + y, 3, 1), lambda x, y: ska._Signature.apply(x + y, 3, 1)),
+]
+
+
+@pytest.mark.parametrize("name,wrapper,cls", CALLS, ids=[c[0] for c in CALLS])
+@pytest.mark.parametrize("dtype", [torch.float64, torch.float32])
+@pytest.mark.parametrize("wanted", ["both", "x", "y"])
+def test_values_and_gradients_are_those_of_the_classes(name, wrapper, cls, dtype, wanted):
+    got = []
+    for call in (wrapper, cls):
+        x, y = paths(1, 9, 24, 3, dtype), paths(2, 9, 24, 3, dtype)
+        leaves = [t.requires_grad_() for t, n in ((x, "x"), (y, "y")) if wanted in ("both", n)]
+        xs = x.transpose(1, 2).contiguous().transpose(1, 2)              # not contiguous
+        out = call(xs, y)
+        weight = torch.linspace(0.5, 1.5, out.numel(), device="cuda", dtype=dtype).reshape(out.shape)
+        first = torch.autograd.grad((out * weight).sum(), leaves, retain_graph=True)
+        second = torch.autograd.grad(out.sum(), leaves)                  # once more through the graph, an expanded gradient
+        got.append((out.detach(), *first, *second))
+        with torch.no_grad():
+            plain = call(x, y)
+        assert not plain.requires_grad and torch.equal(plain, out.detach())
+    # (gradient sums meet in atomic additions: equal to rounding)
+    tol = 1e-12 if dtype == torch.float64 else 1e-5
+    for a, b in zip(*got):
+        assert a.dtype == b.dtype and a.shape == b.shape
+        assert float((a - b).abs().max()) <= tol * max(1.0, float(b.abs().max()))
+
+
+def test_graph_rules_hold():
+    x, y = paths(3, 4, 20, 2).requires_grad_(), paths(4, 4, 20, 2)
+    loss = ska.sig_kernel(x, y).sum()
+    loss.backward()
+    with pytest.raises(RuntimeError, match="second time"):
+        loss.backward()
+    z = x * 1.0
+    loss = ska.sig_kernel(z, y).sum()
+    z.add_(1.0)                                                          # saved for the backward call, changed before it
+    with pytest.raises(RuntimeError, match="inplace"):
+        loss.backward()
+    packed = []
+    with torch.autograd.graph.saved_tensors_hooks(lambda t: packed.append(t) or t.cpu(), lambda t: t.cuda()):
+        out = ska.signature(x, 2)
+    assert len(packed) == 2
+    g = torch.autograd.grad(out.sum(), x)[0]
+    assert torch.allclose(g, torch.autograd.grad(ska.signature(x, 2).sum(), x)[0], rtol=0, atol=1e-12)
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        g2 = torch.autograd.grad(ska.signature(x, 2).sum(), x)[0]
+    torch.cuda.current_stream().wait_stream(side)
+    assert torch.allclose(g, g2, rtol=0, atol=1e-12)
+
+
+def test_what_is_left_to_the_classes_or_refused():
+    x, y = paths(5, 4, 20, 2), paths(6, 4, 20, 2)
+    take = lambda *a: _native.pair(*a, 1 << 30) is not None  # noqa: E731
+    assert take(x, y, 0, 0, 0)
+    assert not take(x.cpu(), y.cpu(), 0, 0, 0) and not take(x.half(), y.half(), 0, 0, 0) and not take(x, y.float(), 0, 0, 0)
+    assert not take(x, y[:3], 0, 0, 0) and not take(x, y[..., :1], 0, 0, 0) and not take(x[0], y[0], 0, 0, 0)
+    assert not take(x, y, 0.0, 0, 0) and not take(x, y, 21, 0, 0) and not take(x, y, 0, 0, 1 << 12)
+    assert not take(x, y, 0, 0, sk.SK_FLAG_KEEP_FORWARD) and not take(None, y, 0, 0, 0) and not take(x, y, 1 << 40, 0, 0)
+    assert _native.pair(x.requires_grad_(), y, 0, 0, 0, 0) is None       # a kept sweep above the limit
+    x = x.detach()
+    assert _native.gram(x, x, 0, 0, 0, 1 << 30) is None                  # one set given as two: the library's choice
+    with pytest.raises(ValueError):
+        ska.sig_kernel(x.cpu(), y.cpu())
+    with pytest.raises(AssertionError):
+        ska.sig_kernel(x, y[:3])
+    with pytest.raises(sk.SigKernelError):
+        ska.sig_kernel(x, y, 21, 0)
+    with pytest.raises(sk.SigKernelError):
+        ska.signature(x, 0)
+    with pytest.raises(sk.SigKernelError):
+        ska.sig_mmd2(x, x)
+    with pytest.raises(RuntimeError):
+        torch.func.vmap(lambda a, b: ska.sig_kernel(a, b))(x[None], y[None])
+    with pytest.raises(RuntimeError):
+        torch.func.grad(lambda a: ska.sig_kernel(a, y).sum())(x)
+    with pytest.raises(RuntimeError), torch.autograd.forward_ad.dual_level():
+        ska.sig_kernel(torch.autograd.forward_ad.make_dual(x, x), y)
+    e = torch.empty((0, 5, 2), dtype=torch.float64, device="cuda", requires_grad=True)
+    out = ska.sig_kernel(e, e.detach())
+    assert out.shape == (0,) and torch.autograd.grad(out.sum(), e)[0].shape == (0, 5, 2)
