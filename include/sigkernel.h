@@ -61,6 +61,10 @@ enum {
     SK_FLAG_KEEP_FORWARD = 16, /* forward calls: leave the forward sweep in the workspace for the backward call
                                   (Section 3.4: the backward pass works on the forward pass's grid); see sigkernel_bwd */
     SK_FLAG_HAVE_FORWARD = 32, /* backward calls: the workspace holds the forward sweep a forward call kept */
+    SK_FLAG_KEEP_SWEEPS = 256,  /* forward calls: sweep the adjoint recurrence (for the upstream gradient 1) beside the forward one
+                                  and leave both in the workspace, where the shape has such a form (few pairs);
+                                  ignored elsewhere.  See sigkernel_bwd */
+    SK_FLAG_HAVE_SWEEPS = 512, /* backward calls: the workspace holds both sweeps of a forward call with that flag */
     SK_FLAG_SHORT_WAITS = 4 /* diagnostic: a workgroup that waits for another one's progress gives up after a single
                                poll.  Exercises the path a wait that runs out takes: every kernel still ends normally
                                and the results of the call are NaN.  Only launches whose workgroups wait for each
@@ -129,6 +133,11 @@ int sigkernel_fwd(const void* x, const void* y, void* k, int64_t B, int64_t L1, 
  *    that workspace erases the signature (where it lays the workspace out in the same way); and a backward call
  *    whose own hash differs from the signature it finds returns NaN gradients.  Paths changed in place between the
  *    two calls, or another forward call on that workspace, are not noticed.
+ *  - SK_FLAG_KEEP_SWEEPS / SK_FLAG_HAVE_SWEEPS: the same, in the same way, for both recurrences.  The forward call also
+ *    sweeps the adjoint recurrence, which needs no forward values and runs beside the forward sweep on compute units
+ *    that a few pairs leave idle; the backward call then has no sweep left, multiplies by grad_k and maps to the paths.
+ *    Shapes that have no such form ignore these flags (sigkernel_describe says kept_sweeps=2 where they do not), and
+ *    then honour SK_FLAG_KEEP_FORWARD / SK_FLAG_HAVE_FORWARD if given.  No increment is too large for this form.
  *  - Launch modes without this form ignore both flags (the forward call runs as usual, the backward call sweeps
  *    forward itself), so results never depend on the flags; sigkernel_describe names the kernels either way.
  */
@@ -143,7 +152,7 @@ int sigkernel_bwd(const void* x, const void* y, const void* grad_k, void* grad_x
  * (one copy per GPU, held until the process ends).  The call allocates and frees nothing.
  *  - Shapes whose sigkernel_workspace_bytes(SK_OP_BWD, ...) exceeds SK_STATIC_SCRATCH_BYTES are refused with
  *    SK_ERR_WORKSPACE (configuration-2-sized batches fit: 128 pairs of 256 points at dyadic order 1).
- *  - SK_FLAG_KEEP_FORWARD / SK_FLAG_HAVE_FORWARD are refused (SK_ERR_DTYPE): the scratch belongs to no caller.
+ *  - The flags of kept sweeps are refused (SK_ERR_DTYPE): the scratch belongs to no caller.
  *  - Every call on a GPU uses that GPU's one array: calls that overlap on one GPU (two streams, two threads) race.
  *    Calls on one stream are ordered and safe; each call clears what it needs cleared.
  *  - The first call on a device looks the array's address up (hipGetSymbolAddress); make that call, like the first
@@ -176,7 +185,7 @@ int sigkernel_gram(const void* X, const void* Y, void* K, const void* grad_K, vo
  * Three Gram computations (two of them symmetric: half of their pairs are solved) with constant upstream
  * weights that are generated on the device, then one reduction.  Same conventions as the other entry points;
  * the workspace size comes from sigkernel_mmd2_workspace_bytes (with_grads != 0 if any gradient is wanted).
- * SK_FLAG_KEEP_FORWARD and SK_FLAG_HAVE_FORWARD do not apply here (one call computes everything) and are refused.
+ * The flags of kept sweeps do not apply here (one call computes everything) and are refused.
  */
 size_t sigkernel_mmd2_workspace_bytes(int64_t N, int64_t M, int64_t L1, int64_t L2, int64_t d, int lam1, int lam2,
                                       int flags, sk_dtype dt, int with_grads);

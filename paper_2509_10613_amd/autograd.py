@@ -72,6 +72,11 @@ def _keep_workspace(nbytes, device):
     return ws
 
 
+# Flags of the two forms in which a forward call leaves its sweeps for the backward call: forward and backward.
+_SWEEP = (sk.SK_FLAG_KEEP_FORWARD, sk.SK_FLAG_HAVE_FORWARD)
+_SWEEPS = (sk.SK_FLAG_KEEP_SWEEPS, sk.SK_FLAG_HAVE_SWEEPS)
+
+
 def _take_workspace(ctx):
     """The workspace the forward call kept, or None.  A large one is taken out of the graph: a further backward call through
     it sweeps forward itself."""
@@ -92,13 +97,16 @@ class _PairKernel(torch.autograd.Function):
         # Where the launch mode can hand its forward sweep to the backward call, this call keeps it in a workspace of
         # its own (the grid the paper's backward pass takes over from its forward pass, here as checkpoints).
         B, L1, d = x.shape
-        if (ctx.needs_input_grad[0] or ctx.needs_input_grad[1]) and sk.keeps_forward(B, L1, y.shape[1], d, lam1, lam2,
-                                                                                     flags, sk._dt(x)):
-            need = sk.sigkernel_workspace_bytes(sk.SK_OP_FWD, B, 0, L1, y.shape[1], d, lam1, lam2,
-                                                flags | sk.SK_FLAG_KEEP_FORWARD, sk._dt(x))
-            ctx.ws = _keep_workspace(need, x.device)
+        if ctx.needs_input_grad[0] or ctx.needs_input_grad[1]:
+            shape = (B, L1, y.shape[1], d, lam1, lam2, flags, sk._dt(x))
+            ctx.kept = _SWEEPS if sk.keeps_sweeps(*shape) else (_SWEEP if sk.keeps_forward(*shape) else None)
+            if ctx.kept is not None:
+                # (room for either form)
+                need = max(sk.sigkernel_workspace_bytes(sk.SK_OP_FWD, B, 0, L1, y.shape[1], d, lam1, lam2, flags | form, sk._dt(x))
+                           for form in (ctx.kept[0], sk.SK_FLAG_KEEP_FORWARD))
+                ctx.ws = _keep_workspace(need, x.device)
             if ctx.ws is not None:
-                return sk.sigkernel_fwd(x, y, lam1, lam2, flags | sk.SK_FLAG_KEEP_FORWARD, ws=ctx.ws)
+                return sk.sigkernel_fwd(x, y, lam1, lam2, flags | ctx.kept[0], ws=ctx.ws)
         return sk.sigkernel_fwd(x, y, lam1, lam2, flags)
 
     @staticmethod
@@ -110,7 +118,7 @@ class _PairKernel(torch.autograd.Function):
             return None, None, None, None, None
         ws = _take_workspace(ctx)
         if ws is not None:
-            _, gx, gy = sk.sigkernel_bwd(x, y, grad_k.contiguous(), lam1, lam2, flags | sk.SK_FLAG_HAVE_FORWARD,
+            _, gx, gy = sk.sigkernel_bwd(x, y, grad_k.contiguous(), lam1, lam2, flags | ctx.kept[1],
                                          want_x=want_x, want_y=want_y, ws=ws)
         else:
             _, gx, gy = sk.sigkernel_bwd(x, y, grad_k.contiguous(), lam1, lam2, flags, want_x=want_x, want_y=want_y)
@@ -118,12 +126,17 @@ class _PairKernel(torch.autograd.Function):
 
 
 def _gram_keep_workspace(ctx, X, Y, lam1, lam2, flags, symmetric=False):
-    """A workspace of this call's own if it wants gradients, the launch mode can keep the forward sweep of a Gram matrix
+    """A workspace of this call's own if it wants gradients, the launch mode can keep the sweeps of a Gram matrix
     for its backward call, and that much may be kept; else None."""
     if not any(ctx.needs_input_grad[:2]):
         return None
     N, L1, d = X.shape
     M, L2 = Y.shape[0], Y.shape[1]
+    if sk.keeps_sweeps(N, L1, L2, d, lam1, lam2, flags, sk._dt(X), gram_M=M):
+        ctx.kept = _SWEEPS
+        need = sk.sigkernel_workspace_bytes(sk.SK_OP_GRAM, N, M, L1, L2, d, lam1, lam2, flags | ctx.kept[0], sk._dt(X))
+        return _keep_workspace(need, X.device)
+    ctx.kept = _SWEEP
     if not sk.keeps_forward(N, L1, L2, d, lam1, lam2, flags, sk._dt(X), gram_M=M):
         return None
     # (the backward sweep with four pairs per wavefront makes its own forward sweep, and is mostly faster than the kept form)
@@ -144,7 +157,7 @@ class _GramKernel(torch.autograd.Function):
         ctx.args = (lam1, lam2, flags)
         ctx.ws = _gram_keep_workspace(ctx, X, Y, lam1, lam2, flags)
         if ctx.ws is not None:
-            return sk.sigkernel_gram(X, Y, None, lam1, lam2, flags | sk.SK_FLAG_KEEP_FORWARD, ws=ctx.ws)
+            return sk.sigkernel_gram(X, Y, None, lam1, lam2, flags | ctx.kept[0], ws=ctx.ws)
         return sk.sigkernel_gram(X, Y, None, lam1, lam2, flags)
 
     @staticmethod
@@ -153,7 +166,7 @@ class _GramKernel(torch.autograd.Function):
         lam1, lam2, flags = ctx.args
         ws = _take_workspace(ctx)
         if ws is not None:
-            _, gX, gY = sk.sigkernel_gram(X, Y, grad_K.contiguous(), lam1, lam2, flags | sk.SK_FLAG_HAVE_FORWARD, ws=ws)
+            _, gX, gY = sk.sigkernel_gram(X, Y, grad_K.contiguous(), lam1, lam2, flags | ctx.kept[1], ws=ws)
         else:
             _, gX, gY = sk.sigkernel_gram(X, Y, grad_K.contiguous(), lam1, lam2, flags)
         return (gX if ctx.needs_input_grad[0] else None), (gY if ctx.needs_input_grad[1] else None), None, None, None
@@ -167,7 +180,7 @@ class _GramKernelSym(torch.autograd.Function):
         ctx.args = (lam1, lam2, flags)
         ctx.ws = _gram_keep_workspace(ctx, X, X, lam1, lam2, flags, symmetric=True)
         if ctx.ws is not None:
-            return sk.sigkernel_gram(X, X, None, lam1, lam2, flags | sk.SK_FLAG_KEEP_FORWARD, ws=ctx.ws)
+            return sk.sigkernel_gram(X, X, None, lam1, lam2, flags | ctx.kept[0], ws=ctx.ws)
         return sk.sigkernel_gram(X, X, None, lam1, lam2, flags)
 
     @staticmethod
@@ -175,7 +188,7 @@ class _GramKernelSym(torch.autograd.Function):
         (X,) = ctx.saved_tensors
         lam1, lam2, flags = ctx.args
         ws = _take_workspace(ctx)
-        keep = sk.SK_FLAG_HAVE_FORWARD if ws is not None else 0
+        keep = ctx.kept[1] if ws is not None else 0
         _, gX, _ = sk.sigkernel_gram(X, X, grad_K.contiguous(), lam1, lam2, flags | keep, ws=ws)   # total derivative
         return gX, None, None, None
 

@@ -18,6 +18,8 @@ SK_FLAG_SHORT_WAITS = 4
 SK_FLAG_LEAD_LAG = 8
 SK_FLAG_KEEP_FORWARD = 16
 SK_FLAG_HAVE_FORWARD = 32
+SK_FLAG_KEEP_SWEEPS = 256
+SK_FLAG_HAVE_SWEEPS = 512
 SK_OP_FWD, SK_OP_BWD, SK_OP_GRAM, SK_OP_GRAM_BWD = 0, 1, 2, 3
 
 
@@ -186,6 +188,15 @@ def keeps_forward(B, L1, L2, d, lam1, lam2, flags, dt, gram_M=None):
     else:
         desc = sigkernel_describe(SK_OP_GRAM, B, gram_M, L1, L2, d, lam1, lam2, flags | SK_FLAG_KEEP_FORWARD, dt)
     return " kept_sweep_half=1 " in desc
+
+
+def keeps_sweeps(B, L1, L2, d, lam1, lam2, flags, dt, gram_M=None):
+    """Whether the forward call (as in keeps_forward) with SK_FLAG_KEEP_SWEEPS sweeps the adjoint recurrence beside the forward
+    one and leaves both for the backward call with SK_FLAG_HAVE_SWEEPS, or ignores the flag."""
+    if B < 1 or L1 < 2 or L2 < 2 or (gram_M is not None and gram_M < 1):
+        return False
+    op, M = (SK_OP_FWD, 0) if gram_M is None else (SK_OP_GRAM, gram_M)
+    return " kept_sweeps=2" in sigkernel_describe(op, B, M, L1, L2, d, lam1, lam2, flags | SK_FLAG_KEEP_SWEEPS, dt)
 
 
 def sigkernel_fwd(x, y, lam1=0, lam2=0, flags=0, k=None, ws=None):

@@ -78,7 +78,7 @@ int validate(int64_t nx, int64_t ny, int64_t L1, int64_t L2, int64_t d, int lam1
 {
     if (dt != SK_F32 && dt != SK_F64) return fail(SK_ERR_DTYPE, "dtype %d is neither SK_F32 nor SK_F64", dt);
     if (flags & ~(SK_FLAG_TIME_AUG | SK_FLAG_BWD_REPLAY | SK_FLAG_SHORT_WAITS | SK_FLAG_LEAD_LAG | SK_FLAG_KEEP_FORWARD |
-                  SK_FLAG_HAVE_FORWARD))
+                  SK_FLAG_HAVE_FORWARD | SK_FLAG_KEEP_SWEEPS | SK_FLAG_HAVE_SWEEPS))
         return fail(SK_ERR_DTYPE, "unknown flag bits 0x%x", flags);
     if (lam1 < 0 || lam2 < 0 || lam1 > 20 || lam2 > 20)
         return fail(SK_ERR_DYADIC, "dyadic orders (%d, %d) outside 0..20", lam1, lam2);
@@ -96,6 +96,7 @@ int validate(int64_t nx, int64_t ny, int64_t L1, int64_t L2, int64_t d, int lam1
     return SK_OK;
 }
 
+constexpr int kKeptFlags = SK_FLAG_KEEP_FORWARD | SK_FLAG_HAVE_FORWARD | SK_FLAG_KEEP_SWEEPS | SK_FLAG_HAVE_SWEEPS;
 // Internal bit beside the caller's flags: the plan whose scratch stays small (no wide mode).
 constexpr int kSmallScratch = 1 << 20;
 
@@ -114,15 +115,15 @@ struct Layout {
 
 // L1, L2, d, lam1, lam2 are the caller's.
 Layout make_layout(bool backward, bool gram, bool symmetric, int64_t nx, int64_t ny, int64_t L1, int64_t L2, int64_t d,
-                   int lam1, int lam2, int flags, int io_elem, bool uncompute, bool keep = false)
+                   int lam1, int lam2, int flags, int io_elem, bool uncompute, bool keep = false, bool split = false)
 {
     Layout l;
     l.ll = (flags & SK_FLAG_LEAD_LAG) != 0;
     if (l.ll) { lam1 += 1; lam2 += 1; }
     l.p = sk::make_plan(backward, gram, symmetric, nx, ny, L1, L2, d, lam1, lam2, io_elem, uncompute, keep, false, l.ll, true,
-                        !(flags & kSmallScratch));
+                        !(flags & kSmallScratch), split);
     l.total = l.p.total;
-    if (l.p.valid && backward && l.p.uncompute && !l.p.wide) {   // (the wide kernels divide by nothing: no pair of theirs drifts)
+    if (l.p.valid && backward && l.p.uncompute && !l.p.wide && !l.p.split) {   // (those divide by nothing: no pair of theirs drifts)
         l.sc = sk::make_plan(true, gram, symmetric, nx, ny, L1, L2, d, lam1, lam2, io_elem, false, false, true, l.ll);
         l.has_sc = l.sc.valid;
         l.off_sc = l.p.total;
@@ -228,7 +229,16 @@ int run(const Layout& lay, bool backward, const void* x, const void* y, void* k,
         a.bad_list = reinterpret_cast<long long*>(base + p.off_badlist);
     }
     // Lock-step mode on a batch of pairs of double paths works on the caller's arrays directly.
-    const bool fused = p.lock && p.gramM == 0 && kIsDouble;
+    // (split mode: the first of its two launches)
+    const bool fused = p.lock && p.gramM == 0 && kIsDouble && (!p.split || phase == 1);
+    if (p.split) {
+        a.lk_keep = p.lock ? reinterpret_cast<double*>(base + p.off_keep) : nullptr;
+        a.sp_arows = reinterpret_cast<double*>(base + p.off_sp_arows);
+        a.sp_ackpt = reinterpret_cast<double*>(base + p.off_sp_ackpt);
+        a.sp_ackpt_slot = p.sp_ackpt_slot;
+        a.sp_chunks = p.sp_chunks; a.sp_tasks = p.sp_tasks; a.sp_win = p.sp_win;
+        a.sp_off_gy = (unsigned)p.sp_off_gy; a.sp_off_feed = (unsigned)p.sp_off_feed;
+    }
     if (fused) {
         a.fused = 1;
         a.xraw = static_cast<const double*>(x);
@@ -242,14 +252,14 @@ int run(const Layout& lay, bool backward, const void* x, const void* y, void* k,
         a.lk_phase = phase;
         a.lk_keep = reinterpret_cast<double*>(base + p.off_keep);
         a.keep_len = p.keep_len;
-    } else if (phase != 0 && !p.band) {
+    } else if (phase != 0 && !p.band && !p.split) {
         return fail(SK_ERR_SHAPE, "internal: no split form of this launch");
     }
     // Band mode is two launches anyway (forward sweep with checkpoints and bottom rows in global memory, reverse
     // sweep); a kept forward sweep is the first of them, and its kernel values wait in the workspace.
-    double* keep_k = (p.band && phase != 0) ? reinterpret_cast<double*>(base + p.off_keep) : nullptr;
-    const bool own_tag_launch = p.band || p.keep_solo;   // these sign, erase and check in launches of their own
-    if (backward && ((p.gramM == 0 && (fused || p.band)) || p.keep_solo) && p.off_keep_tag != 0) {
+    double* keep_k = (p.band && phase != 0 && !p.split) ? reinterpret_cast<double*>(base + p.off_keep) : nullptr;
+    const bool own_tag_launch = (p.band && !p.split) || p.keep_solo;   // these sign, erase and check in launches of their own
+    if (backward && (p.split || (p.gramM == 0 && (fused || p.band)) || p.keep_solo) && p.off_keep_tag != 0) {
         a.keep_tag = reinterpret_cast<unsigned long long*>(base + p.off_keep_tag);
         // FNV-1a over what the kept sweep depends on
         unsigned long long h = 1469598103934665603ull;
@@ -266,11 +276,14 @@ int run(const Layout& lay, bool backward, const void* x, const void* y, void* k,
     // one preparation launch: increments of both sides, cleared gradient accumulators, cleared error flag
     // (the reverse sweep of a kept forward sweep: the same increments once more, cleared accumulators, and only the
     // reverse sweep's progress counters cleared - the error flag still says how the forward sweep went)
+    // (split mode: nothing is counted in the backward call, and the signature of what is kept stays)
+    int* clear = phase == 2 ? a.bd_flags + p.nflags / 2 : a.err;
+    if (p.split && phase == 2) clear = nullptr;
     if (!fused)
     SK_CHECK(launch_prepare<T>(static_cast<const T*>(x), dxT, (backward && a.want_gx) ? a.gdx : nullptr, p.nx, p.L1,
                                p.rpad, static_cast<const T*>(y), p.symmetric ? nullptr : dyT,
                                (backward && a.want_gy && !p.symmetric) ? a.gdy : nullptr, p.ny, p.L2, p.qpad, p.d,
-                               p.DP, phase == 2 ? a.bd_flags + p.nflags / 2 : a.err,
+                               p.DP, clear,
                                phase == 2 ? p.nflags / 2 + 1 : 1 + (int)((p.off_flags - p.off_err) / sizeof(int)) + p.nflags,
                                st));   // (both ranges end with the counter of drifted pairs, the int behind the flags)
     // the calls that work on the caller's arrays have no preparation launch: their counter of drifted pairs
@@ -280,7 +293,11 @@ int run(const Layout& lay, bool backward, const void* x, const void* y, void* k,
     const int ttag = timing_tag();
     EventPair ev;
     if (ttag) SK_CHECK(ev.begin((backward && phase != 1) ? 1 : 0, ttag, st));   // a kept forward sweep counts as a forward launch
-    if (p.band) SK_CHECK(launch_sweep_band(phase ? phase + 1 : (backward ? 1 : 0), p.BL, p.DT, a, p.grid, p.lds_bytes, st));
+    if (p.split) {
+        if (phase == 2) SK_CHECK(launch_split_seg(p.BL, p.DT, a, p.sp_lds, st));
+        else if (p.lock) SK_CHECK(launch_split_lock(p.BL, p.DT, a, p.lds_bytes, st));
+        else SK_CHECK(launch_split_band(p.BL, p.DT, a, p.lds_bytes, st));
+    } else if (p.band) SK_CHECK(launch_sweep_band(phase ? phase + 1 : (backward ? 1 : 0), p.BL, p.DT, a, p.grid, p.lds_bytes, st));
     else if (p.lock) SK_CHECK(launch_sweep_lockstep(backward, p.BL, p.DT, a, p.grid, p.lds_bytes, st));
     else if (p.quad) SK_CHECK(launch_sweep_quad(p.BL, p.DT, a, p.grid, p.lds_bytes, st));
     else if (p.four) SK_CHECK(launch_sweep_four(p.BL, p.DT, a, p.grid, p.lds_bytes, st));
@@ -406,7 +423,17 @@ int dispatch(bool backward, bool gram, const void* x, const void* y, void* k, co
     // A forward sweep kept for the backward call: the launch modes that have the two halves of the backward call as
     // launches of their own run the first half here and the second half there; the others ignore both flags.
     int phase = 0;
-    if (flags & (backward ? SK_FLAG_HAVE_FORWARD : SK_FLAG_KEEP_FORWARD)) {
+    if (flags & (backward ? SK_FLAG_HAVE_SWEEPS : SK_FLAG_KEEP_SWEEPS)) {
+        const Layout lb = make_layout(true, gram, symmetric, nx, ny, L1, L2, d, lam1, lam2, flags, elem,
+                                      !(flags & SK_FLAG_BWD_REPLAY), false, true);
+        if (lb.p.valid && lb.p.split) {
+            if (ws_bytes < lb.total)
+                return fail(SK_ERR_WORKSPACE, "workspace has %zu bytes, %zu needed (kept sweeps: asked for with the flag)", ws_bytes, lb.total);
+            phase = backward ? 2 : 1;
+            lay = lb;
+        }
+    }
+    if (phase == 0 && (flags & (backward ? SK_FLAG_HAVE_FORWARD : SK_FLAG_KEEP_FORWARD))) {
         const Layout lb = make_layout(true, gram, symmetric, nx, ny, L1, L2, d, lam1, lam2, flags, elem,
                                       !(flags & SK_FLAG_BWD_REPLAY), true);
         if (!lb.p.valid) return fail(SK_ERR_SHAPE, "internal: plan invalid");
@@ -446,13 +473,19 @@ size_t sigkernel_workspace_bytes(int op, int64_t B_or_N, int64_t M, int64_t L1, 
     const int64_t ny = gram ? M : B_or_N;
     if (validate(B_or_N, ny, L1, L2, d, lam1, lam2, flags, (int)dt) != SK_OK) return 0;
     auto total = [&](bool symmetric) {
+        if (flags & (fwd_op ? SK_FLAG_KEEP_SWEEPS : SK_FLAG_HAVE_SWEEPS)) {
+            const Layout l = make_layout(true, gram, symmetric, B_or_N, ny, L1, L2, d, lam1, lam2, flags, dt == SK_F64 ? 8 : 4,
+                                         !(flags & SK_FLAG_BWD_REPLAY), false, true);
+            if (l.p.valid && l.p.split) return l.total;
+        }
         const Layout l = make_layout(backward, gram, symmetric, B_or_N, ny, L1, L2, d, lam1, lam2, flags, dt == SK_F64 ? 8 : 4,
                                      !(flags & SK_FLAG_BWD_REPLAY), kept);
         return l.p.valid ? l.total : (size_t)0;
     };
     const size_t need = total(false);
     // K(X, X) is the same query.  It needs no more, unless the two take different launch modes.
-    const size_t sym = gram && backward && B_or_N == ny && L1 == L2 ? total(true) : 0;
+    const bool both = (flags & (fwd_op ? SK_FLAG_KEEP_SWEEPS : SK_FLAG_HAVE_SWEEPS)) != 0;
+    const size_t sym = gram && (backward || both) && B_or_N == ny && L1 == L2 ? total(true) : 0;
     return need > sym ? need : sym;
 }
 
@@ -517,8 +550,8 @@ extern "C" int sigkernel_bwd_static(const void* x, const void* y, const void* gr
                                     void* k_out, int64_t B, int64_t L1, int64_t L2, int64_t d, int lam1, int lam2,
                                     int flags, sk_dtype dt, void* stream)
 {
-    if (flags & (SK_FLAG_KEEP_FORWARD | SK_FLAG_HAVE_FORWARD))
-        return fail(SK_ERR_DTYPE, "SK_FLAG_KEEP_FORWARD / SK_FLAG_HAVE_FORWARD do not apply to sigkernel_bwd_static "
+    if (flags & kKeptFlags)
+        return fail(SK_ERR_DTYPE, "flags of kept sweeps do not apply to sigkernel_bwd_static "
                     "(its scratch is shared by every call on the device)");
     int rc = validate(B, B, L1, L2, d, lam1, lam2, flags, (int)dt);
     if (rc != SK_OK) return rc;
@@ -555,7 +588,15 @@ LaunchNames launch_names(const sk::Plan& p, bool backward, int phase, bool time)
     const bool lean = p.lock || p.solo || p.tile || p.quad || p.band || p.wide;
     l.strips = lean ? p.lk_ns : p.ns;
     l.rows = lean ? p.lk_M : 1;
-    if (p.band) {
+    if (p.split) {
+        // two launches: the forward call that keeps its sweeps makes the first, the backward call that takes them over the other
+        l.mode = p.lock ? "lock-step" : "band";
+        if (phase == 2) std::snprintf(l.kernel, sizeof(l.kernel), "seg_kernel<%d, %d, %d, %d>", p.BL, p.DT, p.lk_M, p.ll);
+        else if (p.lock) std::snprintf(l.kernel, sizeof(l.kernel), "lock_split_kernel<%d, %d, %d, %d>", p.BL, p.DT, p.lk_M, p.ll);
+        else std::snprintf(l.kernel, sizeof(l.kernel), "band_split_kernel<%d, %d, %d>", p.BL, p.DT, p.ll);
+        l.threads = phase == 2 ? sk::split_seg_waves(p.BL, p.DT, p.lk_M) * sk::kWave
+                               : p.lock ? (p.lk_ns == 1 ? 3 : (p.lk_ns == 2 ? 8 : 12)) * sk::kWave : (sk::kBandStrips + 1) * sk::kWave;
+    } else if (p.band) {
         l.mode = "band";
         // backward: two launches, the forward sweep with checkpoints and then the reverse sweep (the larger one)
         if (phase == 1) std::snprintf(l.kernel, sizeof(l.kernel), "band_fwd_kernel<%d, %d, true, %d>", p.BL, p.DT, p.ll);
@@ -698,7 +739,7 @@ extern "C" {
 size_t sigkernel_mmd2_workspace_bytes(int64_t N, int64_t M, int64_t L1, int64_t L2, int64_t d, int lam1, int lam2,
                                       int flags, sk_dtype dt, int with_grads)
 {
-    if (N < 1 || M < 1 || (flags & (SK_FLAG_KEEP_FORWARD | SK_FLAG_HAVE_FORWARD)) ||
+    if (N < 1 || M < 1 || (flags & kKeptFlags) ||
         validate(N, M, L1, L2, d, lam1, lam2, flags, (int)dt) != SK_OK)
         return 0;
     return mmd_layout(N, M, L1, L2, d, lam1, lam2, flags, dt, with_grads != 0).total;
@@ -709,8 +750,7 @@ int sigkernel_mmd2(const void* X, const void* Y, void* loss, void* grad_X, void*
                    size_t ws_bytes, void* stream)
 {
     // one call computes everything: there is no forward sweep to keep or to take over
-    if (flags & (SK_FLAG_KEEP_FORWARD | SK_FLAG_HAVE_FORWARD))
-        return fail(SK_ERR_DTYPE, "SK_FLAG_KEEP_FORWARD / SK_FLAG_HAVE_FORWARD do not apply to sigkernel_mmd2");
+    if (flags & kKeptFlags) return fail(SK_ERR_DTYPE, "flags of kept sweeps do not apply to sigkernel_mmd2");
     int rc = validate(N, M, L1, L2, d, lam1, lam2, flags, (int)dt);
     if (rc != SK_OK) return rc;
     if (N < 1 || M < 1) return fail(SK_ERR_SHAPE, "mmd2 needs at least one path on either side");
@@ -789,7 +829,15 @@ int sigkernel_describe(int op, int64_t B_or_N, int64_t M, int64_t L1, int64_t L2
     }
     // a kept forward sweep: the two halves of the backward call, where the launch mode has them
     int phase = 0;
-    if (flags & (backward ? SK_FLAG_HAVE_FORWARD : SK_FLAG_KEEP_FORWARD)) {
+    if (flags & (backward ? SK_FLAG_HAVE_SWEEPS : SK_FLAG_KEEP_SWEEPS)) {
+        const Layout lb = make_layout(true, gram, false, B_or_N, ny, L1, L2, d, lam1, lam2, flags, dt == SK_F64 ? 8 : 4,
+                                      !(flags & SK_FLAG_BWD_REPLAY), false, true);
+        if (lb.p.valid && lb.p.split) {
+            phase = backward ? 2 : 1;
+            lay = lb;
+        }
+    }
+    if (phase == 0 && (flags & (backward ? SK_FLAG_HAVE_FORWARD : SK_FLAG_KEEP_FORWARD))) {
         const Layout lb = make_layout(true, gram, false, B_or_N, ny, L1, L2, d, lam1, lam2, flags, dt == SK_F64 ? 8 : 4,
                                       !(flags & SK_FLAG_BWD_REPLAY), true);
         if (lb.p.valid && split_forward(lb.p, dt)) {
@@ -802,19 +850,23 @@ int sigkernel_describe(int op, int64_t B_or_N, int64_t M, int64_t L1, int64_t L2
     const sk::Plan& p = lay.p;
     const bool time = (flags & SK_FLAG_TIME_AUG) != 0;
     const LaunchNames l = launch_names(p, backward, phase, time);
-    const bool fused = p.lock && !gram && dt == SK_F64;
+    const bool fused = p.lock && !gram && dt == SK_F64 && (!p.split || phase == 1);
     std::snprintf(out, out_bytes,
                   "mode=%s kernel=%s grid=%d threads=%d lds_bytes=%zu strips=%d rows_per_lane=%d fused=%d "
                   "kept_sweep_half=%d lead_lag_form=%s second_launch_lds_bytes=%zu workspace_bytes=%zu "
                   "drifted_pairs_counter_at=%zu pairs_per_wave=%d over_kept_sweep=%d",
-                  l.mode, l.kernel, p.grid, l.threads, p.lds_bytes, l.strips, l.rows, fused ? 1 : 0, phase,
+                  l.mode, l.kernel, p.grid, l.threads, p.split && phase == 2 ? p.sp_lds : p.lds_bytes, l.strips, l.rows, fused ? 1 : 0, phase,
                   lay.ll ? "checkerboard" : "none", (lay.has_sc && backward && phase != 1) ? lay.sc.lds_bytes : (size_t)0,
                   lay.total, p.off_badlist != 0 ? p.off_badcnt : (size_t)0, (p.four || p.quad) ? sk::kQuadPairs : 1,
                   p.four_over_kept ? 1 : 0);
+    if (p.split) {
+        const size_t used = std::strlen(out);
+        std::snprintf(out + used, out_bytes - used, " kept_sweeps=2 chunks_per_task=%d tasks_per_strip=%d", p.sp_chunks, p.sp_tasks);
+    }
     if (gram && B_or_N == ny && L1 == L2) {
         // the call with Y == X, which may be launched in another way
         const Layout ls = make_layout(backward || phase != 0, true, true, B_or_N, ny, L1, L2, d, lam1, lam2, flags,
-                                      dt == SK_F64 ? 8 : 4, !(flags & SK_FLAG_BWD_REPLAY), phase != 0);
+                                      dt == SK_F64 ? 8 : 4, !(flags & SK_FLAG_BWD_REPLAY), phase != 0 && !p.split, p.split != 0);
         const LaunchNames n = launch_names(ls.p, backward, phase, time);
         const size_t used = std::strlen(out);
         std::snprintf(out + used, out_bytes - used, " symmetric_mode=%s symmetric_grid=%d symmetric_over_kept_sweep=%d", n.mode, ls.p.grid,

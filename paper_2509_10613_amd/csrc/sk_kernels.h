@@ -97,6 +97,13 @@ struct SweepArgs {
     int fv_bands;        // four pairs per wave, backward: bands of 16 lanes per pair (nseg: checkpoint places per band),
     real* fv_gx;         // per slot the x-side sums of the bands of the pairs in work (several bands only)
     long fv_gx_slot;
+    // split mode: what the adjoint sweep leaves (checkpoints of its lane state per strip and task, the rows between the strips),
+    // chunks per task, tasks per strip, columns of a wave's window, and the second launch's LDS offsets
+    real* sp_ackpt;
+    long sp_ackpt_slot;
+    real* sp_arows;
+    int sp_chunks, sp_tasks, sp_win;
+    unsigned sp_off_gy, sp_off_feed;
     real* wd_scratch;    // wide kernels (any channel count): per workgroup p of every block and, backward, the blocks' edges
     long wd_slot;        // (uses lk_ns, lk_NT, lk_padb, nw)
     // lock-step mode on a batch of pairs of double paths: the kernels read the caller's points and write the
@@ -159,6 +166,10 @@ hipError_t launch_sweep_solo_one(bool backward, int BL, int DT, const SweepArgs&
 hipError_t launch_sweep_four(int BL, int DT, const SweepArgs& a, int grid, size_t lds, hipStream_t st);
 // tile mode (a.tile != 0), defined in sk_tile.hip
 hipError_t launch_sweep_tile(bool backward, int DT, const SweepArgs& a, int grid, size_t lds, hipStream_t st);
+// split mode: the two sweeps side by side (sk_split_lock.hip, sk_split_band.hip), then the gradients (sk_split_seg.hip)
+hipError_t launch_split_lock(int BL, int DT, const SweepArgs& a, size_t lds, hipStream_t st);
+hipError_t launch_split_band(int BL, int DT, const SweepArgs& a, size_t lds, hipStream_t st);
+hipError_t launch_split_seg(int BL, int DT, const SweepArgs& a, size_t lds, hipStream_t st);
 // wide mode, defined in sk_wide.hip
 hipError_t launch_sweep_wide(bool backward, int BL, const SweepArgs& a, int grid, hipStream_t st);
 // quad mode (a.quad != 0; forward only), defined in sk_quad.hip

@@ -452,6 +452,80 @@ struct Lock {
         }
     };
 
+    // ---------------- stencil wave, the adjoint recurrence alone ----------------
+    // The first relation of Section 3.4 takes no forward values, so its sweep can run beside the forward sweep.
+    struct Adj {
+        static constexpr int NVA = RR + 1 + C;   // doubles per lane of a checkpoint
+        real accL[RR + 1];   // partial adjoints of the left edge nodes (index 0 unused)
+        real corner;         // partial adjoint of the top-left node
+        real up[C];          // adjoint contributions to the top edge nodes, handed to the lane above
+
+        __device__ __forceinline__ void init()
+        {
+#pragma unroll
+            for (int i = 0; i <= RR; ++i) accL[i] = 0.0;
+#pragma unroll
+            for (int i = 0; i < C; ++i) up[i] = 0.0;
+            corner = 0.0;
+        }
+        // A0, B0: coefficients of the off-diagonal quadrants (LL = 1; equal to the others otherwise)
+        __device__ __forceinline__ void step(const real (&recv)[C], const real (&Ac)[M], const real (&Bc)[M], const real (&A0)[M],
+                                             const real (&B0)[M])
+        {
+            real gn[RR + 1][C + 1];
+            begin(gn, recv);
+#pragma unroll
+            for (int rr = RR - 1; rr >= 0; --rr) {
+                const int m = rr >> BL;
+#pragma unroll
+                for (int cc = C - 1; cc >= 0; --cc) {
+                    const real Aq = cell_off(rr, cc) ? A0[m] : Ac[m], Bq = cell_off(rr, cc) ? B0[m] : Bc[m];
+                    const real go = gn[rr + 1][cc + 1];
+                    gn[rr + 1][cc] = fma(go, Aq, gn[rr + 1][cc]);
+                    gn[rr][cc + 1] = fma(go, Aq, gn[rr][cc + 1]);
+                    gn[rr][cc] = fma(-go, Bq, gn[rr][cc]);
+                }
+            }
+            finish(gn);
+        }
+        __device__ __forceinline__ void begin(real (&gn)[RR + 1][C + 1], const real (&recv)[C]) const
+        {
+#pragma unroll
+            for (int rr = 0; rr <= RR; ++rr)
+#pragma unroll
+                for (int cc = 0; cc <= C; ++cc) gn[rr][cc] = 0.0;
+#pragma unroll
+            for (int rr = 1; rr <= RR; ++rr) gn[rr][C] = accL[rr];
+#pragma unroll
+            for (int cc = 0; cc < C; ++cc) gn[RR][cc + 1] += recv[cc];
+            gn[0][C] = corner;
+        }
+        __device__ __forceinline__ void finish(const real (&gn)[RR + 1][C + 1])
+        {
+#pragma unroll
+            for (int cc = 0; cc < C; ++cc) up[cc] = gn[0][cc + 1];
+            corner = gn[0][0];
+#pragma unroll
+            for (int rr = 1; rr <= RR; ++rr) accL[rr] = gn[rr][0];
+        }
+        __device__ __forceinline__ void store(real* cp) const
+        {
+#pragma unroll
+            for (int i = 1; i <= RR; ++i) cp[(i - 1) * kWave] = accL[i];
+            cp[RR * kWave] = corner;
+#pragma unroll
+            for (int i = 0; i < C; ++i) cp[(RR + 1 + i) * kWave] = up[i];
+        }
+        __device__ __forceinline__ void load(const real* cp)
+        {
+#pragma unroll
+            for (int i = 1; i <= RR; ++i) accL[i] = cp[(i - 1) * kWave];
+            corner = cp[RR * kWave];
+#pragma unroll
+            for (int i = 0; i < C; ++i) up[i] = cp[(RR + 1 + i) * kWave];
+        }
+    };
+
     // ---------------- stencil wave, reverse ----------------
     struct Rev {
         real kR[RR + 1];     // forward values on the right edge of the block column to un-compute next

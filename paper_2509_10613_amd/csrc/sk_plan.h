@@ -80,6 +80,11 @@ struct Plan {
     int fv_bands = 0;     // bands of 16 lanes per pair
     int64_t fv_gx_slot = 0;
     size_t off_fvgx = 0;  // x-side sums of the strips of the pairs in work (several strips only)
+    // split mode: the forward and the adjoint sweep side by side, then independent tasks (sk_split_*.hip); lock or band says how
+    // the first of the two launches is laid out
+    int split = 0, sp_chunks = 0, sp_tasks = 0, sp_win = 0;
+    size_t sp_lds = 0, sp_off_gy = 0, sp_off_feed = 0, off_sp_arows = 0, off_sp_ackpt = 0;
+    int64_t sp_ackpt_slot = 0;
     int wide = 0;         // p of every block in scratch, any channel count and any number of strips (sk_wide.hip)
     int64_t wd_slot = 0;  // doubles of that scratch per workgroup
     size_t off_wd = 0;
@@ -238,6 +243,38 @@ constexpr int four_min_paths(int BL) { return BL == 0 ? 7 : (BL == 1 ? 5 : 6); }
 constexpr int kTileRowPad = 8;     // backward: node columns kept left of column 0 in the pair's bottom row (all 1)
 constexpr int kTileCkChunks = 8;   // backward: chunks of 8 macro-steps between two checkpoints (kept in LDS)
 
+// Split mode: waves of a workgroup of the second launch (two per SIMD, or one where what it keeps of eight macro-steps, all of it
+// in registers, and the lane's increments and sums need the whole register file), columns of a wave's window of y-side sums
+// for tasks of K chunks, and that launch's LDS: the y increments of the workgroup's tasks, the windows, two edge feeds per wave;
+// afterwards the waves' x-side sums.
+constexpr int split_seg_waves(int BL, int DT, int M) { return (M << BL) >= 4 || DT >= ((M << BL) == 2 ? 6 : 16) ? 4 : 8; }
+constexpr int split_window(int K, int rs2) { return ((K * kLockCH1 + kWave - 2) >> rs2) + 2; }
+inline size_t split_seg_lds(int BL, int DT, int M, int K, int rs2, size_t* off_gy = nullptr, size_t* off_feed = nullptr)
+{
+    const int W = split_seg_waves(BL, DT, M);
+    const size_t row = (size_t)(DT | 1) * 8;
+    const size_t y = align_up(split_window(W * K, rs2) * row, 256), gy = align_up(W * split_window(K, rs2) * row, 256);
+    if (off_gy) *off_gy = y;
+    if (off_feed) *off_feed = y + gy;
+    const size_t sweep = y + gy + (size_t)W * 2 * kLockCH1 * (1 << BL) * 8, sums = (size_t)W * kWave * M * row;
+    return sweep > sums ? sweep : sums;
+}
+// Chunks per task: a strip's tasks fill one workgroup, at most this many where that leaves other strips and pairs too little.
+constexpr int kSplitMaxChunks = 8, kSplitMaxChunks4 = 16;   // (workgroups of eight and of four waves)
+// Whether a forward and a backward call in that form, with the strips of a pair in one workgroup, are faster than the form they
+// replace (Plan p: a kept forward sweep where there is one).  Nearly always; us for both calls on the GPU, before and now
+// (476 shapes of 4 to 250 pairs, 16 to 400 points, orders 0 to 2; one / two / four strips 1.5 / 1.7 / 2.5 times faster in the mean):
+//   128 pairs, L = 256, d = 3 (1): 171 and 105;  4 pairs, L = 16, d = 3 (0): 54 and 25;  128 pairs, L = 400, d = 8 (0): 599 and 369;
+//   250 pairs, L = 128, d = 3 (0), two strips: 85 and 67
+// With so many strips that two workgroups share a compute unit, the lock-step kernels' kept form loses little to their fewer
+// sweeps: 250 pairs, two strips, lead-lag, L = 100, d = 8 (1): 164 and 190; L = 200, d = 3 (0): 158 and 182; sixteen channels,
+// L = 100 (0): 149 and 155; four strips, L = 200 (0): 403 and 414.
+inline bool split_pays(const Plan& p, int strips)
+{
+    if (p.npairs * strips <= 384 || p.gramM != 0 || p.io_elem != 8) return true;
+    return p.lock ? p.ll == 0 && p.DT <= 8 : p.ll != 0 || p.DT <= 8;
+}
+
 // Wide mode: waves per workgroup at most, doubles per block of the stored edges (right edge, and bottom edge without the
 // corner they share), macro-steps per chunk (what a wave holds of the coming chunk stays in registers), and the scratch that
 // its resident workgroups may take together.
@@ -269,7 +306,7 @@ constexpr int64_t kCoopMaxPairs = 1024;   // above this, one wave per pair alrea
 // L = 1500, d = 3 (1), backward: 5140 and 9668; forward with y in memory, 1500 pairs, L = 300, 700, d = 8 (0): 1468 and 2530.
 inline bool wide_pays(const Plan& p)
 {
-    if (p.lock || p.solo || p.tile || p.quad || p.four || p.band) return false;
+    if (p.lock || p.solo || p.tile || p.quad || p.four || p.band || p.split) return false;
     return p.DT == 0 || (p.backward && (!p.y_lds || (p.coop && p.DT == 16)));
 }
 
@@ -285,12 +322,15 @@ constexpr double kDriftTol = 1e-11;
 
 inline Plan make_plan(bool backward, bool gram, bool symmetric, int64_t nx, int64_t ny, int64_t L1, int64_t L2,
                       int64_t d, int lam1, int lam2, int io_elem, bool uncompute = true, bool keep = false,
-                      bool second_chance = false, bool lead_lag = false, bool may_four = true, bool may_wide = true)
+                      bool second_chance = false, bool lead_lag = false, bool may_four = true, bool may_wide = true,
+                      bool split = false)
 {
     // lead_lag: the sweep of two lead-lag paths (Section 4) on the grid of the original increments; lam1 and lam2 then
     // count the lead-lag level as one more dyadic level (the caller's orders plus one), L1, L2 and d are the caller's.
     // The level lies inside the blocks when these hold every refined cell of a pair of increments, above them
     // otherwise (Plan::ll); the tile kernels have no such form.
+    // split: a backward plan of the kernels that sweep forward and adjoint side by side; Plan::split says whether the shape has
+    // one.
     // second_chance: the plan of the launch that solves the listed pairs once more (wave-per-pair replay kernel,
     // a bounded number of waves, no increment and accumulator areas of its own: it works on the main plan's).
     // keep: a backward plan whose forward sweep may be a launch of its own (a forward call that keeps its sweep for
@@ -675,6 +715,56 @@ inline Plan make_plan(bool backward, bool gram, bool symmetric, int64_t nx, int6
         }
     }
 
+    // Split mode: few pairs, whose sweeps are chains that leave most of the chip idle.  In place of the lock-step kernels (up
+    // to four strips here: the sweeps alone need less LDS and fewer waves) and of the band kernels.
+    if (split && p.uncompute && !p.solo && !p.tile && !p.four && p.DT >= 2) {
+        int M = 1, lns = 0, NT = (int)align_up((size_t)p.nb + kWave - 1, 8), lrow = 0;
+        size_t used = 0, o_y = 0, o_cr = 0, o_kr = 0, o_dump = 0, cstride = 0;
+        auto lds_take = [&](size_t bytes) { size_t o = used; used = align_up(used + bytes, 256); return o; };
+        bool lock = lock_max_rows(true, p.BL, p.DT) > 0 && p.npairs <= kNumCU;
+        if (lock) {
+            const int maxM = lock_max_rows(true, p.BL, p.DT);
+            while (M < maxM && (p.mb + kWave * M - 1) / (kWave * M) > 2) M *= 2;
+            lns = (p.mb + kWave * M - 1) / (kWave * M);
+            lrow = (int)align_up((size_t)kWave * C + (size_t)NT * C + C + 2, 2);
+            o_y = lds_take((size_t)p.q * p.DP * elem);
+            cstride = (size_t)16384 * M;
+            o_cr = lds_take(cstride * lns);
+            o_kr = lds_take((size_t)(lns + 1) * lrow * elem);
+            o_dump = lds_take((size_t)(kWave + 8) * C * elem);
+            lock = lns <= kLockMaxStrips && used <= kLdsPerCU - 1024 && split_pays(p, lns);
+        }
+        if (lock) {
+            p.split = 1; p.lock = 1; p.band = 0; p.coop = 0;
+            p.lk_M = M; p.lk_ns = lns; p.lk_NT = NT; p.lk_rowlen = lrow; p.lk_padb = lns * kWave * M - p.mb;
+            p.lk_off_y = o_y; p.lk_off_cring = o_cr; p.lk_off_krows = o_kr; p.lk_off_dump = o_dump;
+            p.lk_cring_stride = cstride;
+            p.lds_bytes = used;
+            p.grid = (int)(2 * p.npairs);
+            p.nflags = 0;
+        } else if (p.band) {
+            p.split = 1;
+            used = 0;
+            p.bd_off_y = lds_take((size_t)kBandYRing * p.DP * elem);
+            p.bd_off_rings = lds_take((size_t)(kBandStrips + 1) * kBandRing * C * elem);
+            p.lds_bytes = used;
+            p.grid = (int)(2 * p.npairs * p.bd_nbands);
+        }
+        if (p.split) {
+            p.y_lds = 1; p.lds_wave = 0; p.nslots = p.npairs;
+            p.S = kLockS; p.nseg = NT / kLockS;
+            const int W = split_seg_waves(p.BL, p.DT, p.lk_M), most = W == 8 ? kSplitMaxChunks : kSplitMaxChunks4, nck = NT / kLockCH1;
+            int K = p.band ? 8 : (nck + W - 1) / W;
+            if (K > most) K = most;
+            while (K > 1 && split_seg_lds(p.BL, p.DT, p.lk_M, K, p.rs2) > kLdsPerCU - 1024) K /= 2;
+            p.sp_chunks = K;
+            p.sp_tasks = (nck + K - 1) / K;
+            p.sp_win = split_window(K, p.rs2);
+            p.sp_lds = split_seg_lds(p.BL, p.DT, p.lk_M, K, p.rs2, &p.sp_off_gy, &p.sp_off_feed);
+            p.sp_ackpt_slot = (int64_t)p.lk_ns * p.sp_tasks * (p.lk_M * R + 1 + C) * kWave;
+        }
+    }
+
     // Wide mode takes over what is left to the wave-per-pair and the cooperative kernels with more channels than those hold
     // in registers, or with y increments (and their sums) that do not fit in LDS.
     if (may_wide && wide_pays(p) && (!backward || p.uncompute) && !second_chance) {
@@ -718,14 +808,14 @@ inline Plan make_plan(bool backward, bool gram, bool symmetric, int64_t nx, int6
         p.off_dyT = symmetric ? p.off_dxT : take((size_t)ny * p.ystride * elem);
     }
     if (p.wide) p.off_wd = take((size_t)p.nslots * p.wd_slot * elem);
-    p.rows_slot = p.four ? (int64_t)p.fv_bands * kQuadPairs * p.rowlen : (int64_t)p.ns * p.rowlen;
+    p.rows_slot = p.four ? (int64_t)p.fv_bands * kQuadPairs * p.rowlen : (p.split && p.lock ? 0 : (int64_t)p.ns * p.rowlen);
     p.off_rows = take((size_t)p.nslots * p.rows_slot * elem);
     if (backward) {
         if (!second_chance) {
             p.off_gdxT = take((size_t)nx * p.xstride * elem);
             p.off_gdyT = symmetric ? p.off_gdxT : take((size_t)ny * p.ystride * elem);
         }
-        p.adj_slot = p.wide ? 0 : (p.band && p.bd_nbands > 4 ? p.bd_nbands : 4) * (int64_t)p.rowlen;   // two rows of 2C values per block column; band mode: one row per band
+        p.adj_slot = p.wide || p.split ? 0 : (p.band && p.bd_nbands > 4 ? p.bd_nbands : 4) * (int64_t)p.rowlen;   // two rows of 2C values per block column; band mode: one row per band
         p.off_adj = take((size_t)p.nslots * p.adj_slot * elem);
         // lane state kept per checkpoint: right edge, bottom edge, bottom-left corner
         const bool lean = p.lock || p.solo || p.tile || p.band || p.four;
@@ -746,12 +836,17 @@ inline Plan make_plan(bool backward, bool gram, bool symmetric, int64_t nx, int6
         if (p.lock) p.off_keep = take((size_t)p.npairs * (p.lk_ns + 1) * p.lk_rowlen * elem);
         else if (p.band) p.off_keep = take((size_t)p.kcount * elem);   // band mode: the kernel values of the kept sweep
         if (p.lock || p.band) p.off_keep_tag = take(256);   // which call's forward sweep the workspace holds
+        if (p.split) {
+            p.off_keep_tag = p.off_badcnt;   // (this mode counts no drifted pairs, and every other backward call clears that place)
+            p.off_sp_arows = take((size_t)p.npairs * (p.lock ? (p.lk_ns + 1) * p.lk_rowlen : p.lk_ns * p.rowlen) * elem);
+            p.off_sp_ackpt = take((size_t)p.npairs * p.sp_ackpt_slot * elem);
+        }
     }
     if (io_elem != elem) {
         p.off_kio = take((size_t)p.kcount * elem);
         if (backward) p.off_gkio = take((size_t)p.kcount * elem);
     }
-    if (backward && p.uncompute && !second_chance) p.off_badlist = take((size_t)p.kcount * sizeof(long long));
+    if (backward && p.uncompute && !second_chance && !p.split) p.off_badlist = take((size_t)p.kcount * sizeof(long long));
     p.total = off;
     p.valid = true;
     if (p.four && p.total > kFourScratch) {

@@ -50,7 +50,8 @@ void check(int rc)
 // Workspace sizes and whether the forward sweep is kept, by shape and flags: arithmetic on the host that the library would
 // repeat in every call.  The last few shapes of each thread.
 struct Need {
-    size_t forward, kept, backward;   // kept: the forward call that keeps its sweep (0: the shape has no such form)
+    size_t forward, kept, backward;   // kept: the forward call that keeps what it sweeps (0: the shape has no such form)
+    int keep, have;                   // the flags of that form, forward and backward
 };
 struct ShapeKey {
     int64_t v[8];
@@ -77,9 +78,16 @@ Need kernel_need(bool gram, bool symmetric, int64_t N, int64_t M, int64_t L1, in
 {
     const int fwd = gram ? SK_OP_GRAM : SK_OP_FWD, bwd = gram ? SK_OP_GRAM_BWD : SK_OP_BWD;
     auto size = [&](int op, int f) { return sigkernel_workspace_bytes(op, N, M, L1, L2, d, lam1, lam2, f, dt); };
-    Need n{size(fwd, flags), 0, size(bwd, flags)};
+    Need n{size(fwd, flags), 0, size(bwd, flags), SK_FLAG_KEEP_FORWARD, SK_FLAG_HAVE_FORWARD};
     if (N < 1 || L1 < 2 || L2 < 2 || (gram && M < 1)) return n;
     char text[1024];
+    if (sigkernel_describe(fwd, N, M, L1, L2, d, lam1, lam2, flags | SK_FLAG_KEEP_SWEEPS, dt, text, sizeof(text)) == SK_OK &&
+        std::strstr(text, " kept_sweeps=2")) {
+        n.keep = SK_FLAG_KEEP_SWEEPS;
+        n.have = SK_FLAG_HAVE_SWEEPS;
+        n.kept = size(fwd, flags | SK_FLAG_KEEP_SWEEPS);
+        return n;
+    }
     if (sigkernel_describe(fwd, N, M, L1, L2, d, lam1, lam2, flags | SK_FLAG_KEEP_FORWARD, dt, text, sizeof(text)) != SK_OK ||
         !std::strstr(text, " kept_sweep_half=1 "))
         return n;
@@ -96,9 +104,9 @@ Need kernel_need(bool gram, bool symmetric, int64_t N, int64_t M, int64_t L1, in
 struct KernelNode : public Node {
     SavedVariable x_, y_;
     bool gram = false, symmetric = false, want_x = false, want_y = false;
-    int lam1 = 0, lam2 = 0, flags = 0;
+    int lam1 = 0, lam2 = 0, flags = 0, have = 0;
     size_t need = 0;
-    Tensor ws;                       // the kept forward sweep
+    Tensor ws;                       // the kept sweeps
     std::vector<int64_t> out_sizes;
     at::TensorOptions options;
 
@@ -116,7 +124,7 @@ struct KernelNode : public Node {
         const Tensor x = x_.unpack(), y = symmetric ? x : y_.unpack();
         const Tensor g = grads[0].defined() ? grads[0].contiguous() : at::zeros(out_sizes, options);
         const Tensor w = ws.defined() ? ws : bytes(need, x);
-        const int f = flags | (ws.defined() ? SK_FLAG_HAVE_FORWARD : 0);
+        const int f = flags | (ws.defined() ? have : 0);
         const sk_dtype dt = dtype_of(x);
         const int64_t N = x.size(0), M = y.size(0), L1 = x.size(1), L2 = y.size(1), d = x.size(2);
         // (a Gram call computes both sides)
@@ -214,7 +222,7 @@ bool number(const py::object& o, int& v)
 }
 
 // flags of the wrappers (those that keep a forward sweep or take one over are theirs to set)
-bool flag_bits(const py::object& o, int& v) { return number(o, v) && (v & (SK_FLAG_KEEP_FORWARD | SK_FLAG_HAVE_FORWARD)) == 0; }
+bool flag_bits(const py::object& o, int& v) { return number(o, v) && (v & (SK_FLAG_KEEP_FORWARD | SK_FLAG_HAVE_FORWARD | SK_FLAG_KEEP_SWEEPS | SK_FLAG_HAVE_SWEEPS)) == 0; }
 
 // ---------------------------------------------------------------- the calls
 Tensor kernel_call(const Tensor& x0, const Tensor& y0, bool gram, bool symmetric, int lam1, int lam2, int flags, size_t keep_limit)
@@ -222,6 +230,7 @@ Tensor kernel_call(const Tensor& x0, const Tensor& y0, bool gram, bool symmetric
     const bool grad = at::GradMode::is_enabled() && (x0.requires_grad() || y0.requires_grad());
     Tensor x, y, k, ws;
     size_t need_bwd;
+    int have = 0;
     bool kept = false;
     {
         at::NoGradGuard no_grad;
@@ -234,6 +243,7 @@ Tensor kernel_call(const Tensor& x0, const Tensor& y0, bool gram, bool symmetric
         const Need need = need_of(key, [&] { return kernel_need(gram, symmetric, N, gram ? M : 0, L1, L2, d, lam1, lam2, flags, dt); });
         if (grad && need.kept > keep_limit) return {};
         need_bwd = need.backward;
+        have = need.have;
         if (grad && need.kept != 0) {
             try {
                 ws = bytes(need.kept, x);
@@ -242,7 +252,7 @@ Tensor kernel_call(const Tensor& x0, const Tensor& y0, bool gram, bool symmetric
             }
         }
         if (!kept) ws = bytes(need.forward, x);
-        const int f = flags | (kept ? SK_FLAG_KEEP_FORWARD : 0);
+        const int f = flags | (kept ? need.keep : 0);
         int rc;
         if (gram) {
             k = at::empty({N, M}, x.options());
@@ -268,6 +278,7 @@ Tensor kernel_call(const Tensor& x0, const Tensor& y0, bool gram, bool symmetric
         node->lam1 = lam1;
         node->lam2 = lam2;
         node->flags = flags;
+        node->have = have;
         node->need = need_bwd;
         if (kept) node->ws = ws;
         node->out_sizes = k.sizes().vec();
@@ -335,7 +346,7 @@ py::object mmd2(py::object xo, py::object yo, py::object l1, py::object l2, py::
             const int64_t N = x.size(0), M = y.size(0), L1 = x.size(1), L2 = y.size(1), d = x.size(2);
             const ShapeKey key{{8 | (int64_t)(want_x || want_y) << 1 | (int64_t)dt << 2, N, M, L1, L2, d, (int64_t)lam1 << 32 | (uint32_t)lam2, flags}};
             const Need need = need_of(key, [&] {
-                return Need{sigkernel_mmd2_workspace_bytes(N, M, L1, L2, d, lam1, lam2, flags, dt, want_x || want_y ? 1 : 0), 0, 0};
+                return Need{sigkernel_mmd2_workspace_bytes(N, M, L1, L2, d, lam1, lam2, flags, dt, want_x || want_y ? 1 : 0), 0, 0, 0, 0};
             });
             loss = at::empty({}, x.options());
             if (want_x) gx = at::empty_like(x, at::MemoryFormat::Contiguous);
@@ -375,7 +386,7 @@ py::object signature(py::object xo, py::object No, py::object fl)
             x = x0.contiguous();
             const ShapeKey key{{16 | (int64_t)dt << 2, B, 0, L, 0, d, N, flags}};
             need = need_of(key, [&] {
-                return Need{signature_workspace_bytes(B, L, d, N, flags, dt), 0, signature_bwd_workspace_bytes(B, L, d, N, flags, dt, 1)};
+                return Need{signature_workspace_bytes(B, L, d, N, flags, dt), 0, signature_bwd_workspace_bytes(B, L, d, N, flags, dt, 1), 0, 0};
             });
             out = at::empty({B, n}, x.options());
             const Tensor ws = bytes(need.forward, x);
