@@ -8,8 +8,9 @@
 namespace sg {
 
 struct Args {
-    const double* dz;   // [B][np][Dpad] increments of the transformed paths, rows n..np-1 zero
-    double* out;        // [B][sig_len]
+    const double* dz;   // [B][np][Dpad] increments of the transformed paths, rows n..np-1 zero (not read if PW > 1)
+    void* out;          // [B][sig_len], float if out_f32, else double
+    int out_f32;
     long B;
     long n;             // segments per path
     long np;            // stored rows per path: n rounded up to an odd number (0 if n = 0)
@@ -19,6 +20,13 @@ struct Args {
     int PW;             // paths per wave (1, or several short paths side by side in a wave: then WP = 1)
     long NW;            // waves of the launch
     int leadlag;        // rows alternate between moves of the lead and of the lag half of the channels (n is even)
+    // several paths per wave: the kernel reads the points themselves
+    const void* x;      // [B / P][L][d], float if x_f32, else double
+    int x_f32;
+    long L;
+    int d, time;        // channels of the points, 1 if the time channel follows
+    long total;         // segments of a whole path; piece p of its P pieces holds those from p n on
+    int P;              // a power of two
 };
 
 struct BwdArgs {
@@ -56,6 +64,7 @@ hipError_t launch_increments(const TI* x, double* dz, long B, long L, int d, int
                              long np, int time_aug, int lead_lag, hipStream_t st);
 
 // out[i] = in[2 i] (x) in[2 i + 1] for i < pairs, signatures of sig_len entries (levels 0..N over D channels)
-hipError_t launch_chen_pairs(const double* in, double* out, long pairs, int D, int N, long sig_len, hipStream_t st);
+template <typename TO>
+hipError_t launch_chen_pairs(const double* in, TO* out, long pairs, int D, int N, long sig_len, hipStream_t st);
 
 }  // namespace sg

@@ -99,6 +99,28 @@ inline bool matrix_pays(int64_t VB, int64_t D, int N, int64_t segments, bool lea
 // segments, 251 and 288.
 constexpr int64_t kMatrixLong = 768, kMatrixPiece = 120, kMatrixPieceEntries = 100000;
 
+// LDS of a wave that holds PW paths (forward): their points in chunks, `stride` doubles per path (odd: the paths of a wave
+// then start in different banks), and in their place, if it fits, the finished signatures.  At most kSharedLds doubles and
+// the few past the end that the last point's missing channels are read from: five workgroups per compute unit.  Signatures
+// are worth twice that, two workgroups: 300000 paths of 5 points in 2 channels to level 5, double, 64.6 us stored word by
+// word, 38.8 through LDS.
+constexpr int kSharedLds = 1024, kSharedStage = 2048;
+struct SharedLds { int points, stride, doubles; bool staged; };
+#ifdef __HIP__
+__host__ __device__
+#endif
+inline SharedLds shared_lds(int PW, int d, int L, int64_t sig_len)
+{
+    SharedLds s;
+    int points = (kSharedLds / PW - 1) / d;       // (at least 15: a path has at least d lanes)
+    s.points = points < L ? points : L;
+    s.stride = (s.points * d) | 1;
+    s.staged = sig_len <= kSharedStage / PW;
+    const int pts = PW * s.stride + kSharedMaxD, sig = s.staged ? PW * (int)sig_len : 0;
+    s.doubles = pts > sig ? pts : sig;
+    return s;
+}
+
 inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
 struct Plan {
@@ -275,6 +297,13 @@ inline Plan make_plan(int64_t B, int64_t L, int64_t d, int N, bool time_aug, boo
             p.VB = B * P;
             if (!choose(p.VB)) return p;
         }
+    }
+    // Forward, fewer paths than fill the chip: fewer in a wave, on more of its SIMDs, so that a wave copies less in a row.
+    // Waves full and spread: (B, L, d, N) = (1000, 100, 6, 2) 23.9 and 14.5 us, (20, 2000, 2, 2) 38.4 and 23.5,
+    // (5000, 64, 4, 3) with time 27.2 and 19.1.
+    if (!backward && p.PW > 2 && p.VB < (int64_t)p.PW * kSimds) {
+        const int64_t even = (p.VB + kSimds - 1) / kSimds;
+        p.PW = even > 2 ? (int)even : 2;
     }
     p.waves = p.PW > 1 ? (p.VB + p.PW - 1) / p.PW : p.VB * p.WP;
     p.grid = (p.waves + kWavesPerWG - 1) / kWavesPerWG;

@@ -902,10 +902,24 @@ int sig_validate(int64_t B, int64_t L, int64_t d, int N, int flags, int dt, sg::
     return SK_OK;
 }
 
+// the forward kernel's arguments: signatures of the plan's paths (or pieces) into out
+// (T: type of the points; the plan of a recomputed forward pass is that of double callers)
+template <typename T>
+sg::Args sig_args(const sg::Plan& p, const T* x, const double* dz, void* out, bool out_f32, int flags)
+{
+    sg::Args a;
+    a.dz = dz; a.out = out; a.out_f32 = out_f32;
+    a.B = p.VB; a.n = p.Lc; a.np = p.np; a.D = p.D; a.Dpad = p.Dpad; a.N = p.N; a.Q = p.Q; a.NB = p.NB;
+    a.LP = p.LP; a.WP = p.WP; a.sig_len = p.sig_len; a.PW = p.PW; a.NW = p.waves;
+    a.leadlag = (flags & SK_FLAG_LEAD_LAG) ? 1 : 0;
+    a.x = x; a.x_f32 = sizeof(T) == 4; a.L = p.L; a.d = p.d; a.time = (flags & SK_FLAG_TIME_AUG) ? 1 : 0;
+    a.total = p.n; a.P = p.P;
+    return a;
+}
+
 template <typename T>
 int run_signature(const sg::Plan& p, const void* x, void* out, int flags, void* ws, hipStream_t st)
 {
-    constexpr bool kIsDouble = sizeof(T) == 8;
     unsigned char* base = static_cast<unsigned char*>(ws);
     hipError_t e;
 #define SK_CHECK(call)                                                                         \
@@ -914,15 +928,12 @@ int run_signature(const sg::Plan& p, const void* x, void* out, int flags, void* 
         if (e != hipSuccess) return fail(SK_ERR_HIP, "%s: %s", #call, hipGetErrorString(e));   \
     } while (0)
     double* dz = reinterpret_cast<double*>(base + p.off_dz);
-    SK_CHECK(sg::launch_increments<T>(static_cast<const T*>(x), dz, p.B, p.L, p.d, p.D, p.Dpad, p.n, p.P, p.Lc, p.np,
-                                      (flags & SK_FLAG_TIME_AUG) ? 1 : 0, (flags & SK_FLAG_LEAD_LAG) ? 1 : 0, st));
-    double* result = kIsDouble ? static_cast<double*>(out) : reinterpret_cast<double*>(base + p.off_out);
-    sg::Args a;
-    a.dz = dz;
-    a.out = p.P > 1 ? reinterpret_cast<double*>(base + p.off_t0) : result;
-    a.B = p.VB; a.n = p.Lc; a.np = p.np; a.D = p.D; a.Dpad = p.Dpad; a.N = p.N; a.Q = p.Q; a.NB = p.NB;
-    a.LP = p.LP; a.WP = p.WP; a.sig_len = p.sig_len; a.PW = p.PW; a.NW = p.waves;
-    a.leadlag = (flags & SK_FLAG_LEAD_LAG) ? 1 : 0;
+    if (p.PW == 1)      // (kernels that hold several paths per wave read the points)
+        SK_CHECK(sg::launch_increments<T>(static_cast<const T*>(x), dz, p.B, p.L, p.d, p.D, p.Dpad, p.n, p.P, p.Lc, p.np,
+                                          (flags & SK_FLAG_TIME_AUG) ? 1 : 0, (flags & SK_FLAG_LEAD_LAG) ? 1 : 0, st));
+    // the kernel that finishes a signature writes the caller's type; pieces stay double
+    const sg::Args a = p.P > 1 ? sig_args(p, static_cast<const T*>(x), dz, base + p.off_t0, false, flags)
+                                : sig_args(p, static_cast<const T*>(x), dz, out, sizeof(T) == 4, flags);
     const int ttag = timing_tag();
     EventPair ev;
     if (ttag) SK_CHECK(ev.begin(0, ttag, st));
@@ -932,14 +943,14 @@ int run_signature(const sg::Plan& p, const void* x, void* out, int flags, void* 
         double* t0 = reinterpret_cast<double*>(base + p.off_t0);
         double* t1 = reinterpret_cast<double*>(base + p.off_t1);
         const double* src = t0;
-        for (int cur = p.P; cur > 1; cur /= 2) {
-            double* dst = cur == 2 ? result : (src == t0 ? t1 : t0);
+        for (int cur = p.P; cur > 2; cur /= 2) {
+            double* dst = src == t0 ? t1 : t0;
             SK_CHECK(sg::launch_chen_pairs(src, dst, p.B * (cur / 2), p.D, p.N, p.sig_len, st));
             src = dst;
         }
+        SK_CHECK(sg::launch_chen_pairs(src, static_cast<T*>(out), p.B, p.D, p.N, p.sig_len, st));
     }
     if (ttag) SK_CHECK(ev.end(st));
-    if (!kIsDouble) SK_CHECK((sk::launch_convert<double, T>(result, static_cast<T*>(out), p.B * p.sig_len, st)));
 #undef SK_CHECK
     return SK_OK;
 }
@@ -975,15 +986,6 @@ int run_signature_bwd(const sg::Plan& p, const sg::Plan& pf, const void* x, cons
     const int ttag = timing_tag();
     const bool timed = ttag != 0;
     EventPair ev;
-    auto forward_args = [&](double* out) {
-        sg::Args f;
-        f.dz = dz;
-        f.out = out;
-        f.B = pf.VB; f.n = pf.Lc; f.np = pf.np; f.D = pf.D; f.Dpad = pf.Dpad; f.N = pf.N; f.Q = pf.Q; f.NB = pf.NB;
-        f.LP = pf.LP; f.WP = pf.WP; f.sig_len = pf.sig_len; f.PW = pf.PW; f.NW = pf.waves;
-        f.leadlag = (flags & SK_FLAG_LEAD_LAG) ? 1 : 0;
-        return f;
-    };
     const double* sig64;
     if (p.P > 1) {
         // Paths cut into pieces: signatures of the pieces (level 0 of a tree), products of neighbouring pairs level by
@@ -992,7 +994,7 @@ int run_signature_bwd(const sg::Plan& p, const sg::Plan& pf, const void* x, cons
         if (timed) SK_CHECK(ev.begin(1, ttag, st));
         double* tv = reinterpret_cast<double*>(base + p.off_t0);
         double* ta = reinterpret_cast<double*>(base + p.off_t1);
-        sg::Args f = forward_args(tv);
+        const sg::Args f = sig_args(pf, static_cast<const T*>(x), dz, tv, false, flags);
         SK_CHECK(sg::launch_horner(pf.DT, pf.M, pf.S, f, pf.grid, st));
         // level j holds P >> j signatures per path, starting at lev[j] signatures into the tree buffers
         long lev[16];
@@ -1015,9 +1017,9 @@ int run_signature_bwd(const sg::Plan& p, const sg::Plan& pf, const void* x, cons
         sig64 = tv;
         gout64 = ta;
     } else if (!sig) {
-        sg::Args f = forward_args(reinterpret_cast<double*>(base + p.off_sig));
-        SK_CHECK(sg::launch_horner(pf.DT, pf.M, pf.S, f, pf.grid, st));
-        sig64 = f.out;
+        double* s64 = reinterpret_cast<double*>(base + p.off_sig);
+        SK_CHECK(sg::launch_horner(pf.DT, pf.M, pf.S, sig_args(pf, static_cast<const T*>(x), dz, s64, false, flags), pf.grid, st));
+        sig64 = s64;
     } else if (kIsDouble) {
         sig64 = static_cast<const double*>(sig);
     } else {
