@@ -11,7 +11,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libsigkernel.so")
 NATIVE = os.path.join(HERE, "_native.so")   # the autograd wrappers' host path (a Python module over the library)
-SOURCES = ["sk_api.hip", "sk_kernels.hip", "sk_lockstep.hip", "sk_solo.hip", "sk_solo_one.hip", "sk_tile.hip", "sk_tile_bwd.hip", "sk_quad.hip", "sk_four.hip", "sk_band.hip", "sk_wide.hip", "sk_split_lock.hip", "sk_split_band.hip", "sk_split_seg.hip", "sg_horner.hip", "sg_horner_bwd.hip", "sg_horner_bwd_matrix.hip"]
+SOURCES = ["sk_api.hip", "sk_kernels.hip", "sk_lockstep.hip", "sk_solo.hip", "sk_solo_one.hip", "sk_tile.hip", "sk_tile_bwd.hip", "sk_quad.hip", "sk_four.hip", "sk_band.hip", "sk_wide.hip", "sk_split_lock.hip", "sk_split_band.hip", "sk_split_seg.hip", "sg_horner.hip", "sg_horner_bwd.hip", "sg_horner_bwd_matrix.hip", "sg_pieces.hip"]
 HEADERS = ["sk_plan.h", "sk_band.h", "sk_kernels.h", "sk_dev.h", "sk_lane.h", "sk_solo_impl.h", "sk_tile.h", "sk_quad.h", "sg_plan.h", "sg_kernels.h", "sg_dev.h"]
 PUBLIC = ["sigkernel.h", "signature.h"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-munsafe-fp-atomics",

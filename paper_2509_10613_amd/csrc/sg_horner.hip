@@ -427,47 +427,6 @@ __global__ __launch_bounds__(256) void increments_kernel(const TI* __restrict__ 
     }
 }
 
-// Chen's identity (Proposition 2.2) for pairs of neighbouring pieces: out[i] = in[2 i] (x) in[2 i + 1], truncated at
-// level N; entry w of level k is sum_{j=0..k} A[first j letters of w] B[last k - j letters of w].  One thread per entry.
-template <typename TO>
-__global__ __launch_bounds__(256) void chen_pairs_kernel(const double* __restrict__ in, TO* __restrict__ out, long pairs,
-                                                         int D, int N, long sig_len)
-{
-    const unsigned Du = (unsigned)D;
-    for (long e = (long)blockIdx.x * blockDim.x + threadIdx.x; e < sig_len; e += (long)gridDim.x * blockDim.x) {
-        // level k and word number of entry e (32-bit arithmetic: a signature here has fewer than 2^31 entries)
-        int k = 0;
-        unsigned at = 0, pw = 1;            // start of level k, D^k
-        while ((unsigned)e >= at + pw) {
-            at += pw;
-            pw *= Du;
-            ++k;
-        }
-        for (long pr = blockIdx.y; pr < pairs; pr += gridDim.y) {
-            const double* A = in + 2 * pr * sig_len;
-            const double* Bm = A + sig_len;
-            // t = 0 .. k letters go to the second factor: the prefix of k - t letters has the number w / D^t, the
-            // suffix the number w % D^t; one letter moves over per term
-            unsigned pre = (unsigned)e - at, suf = 0, div = 1;
-            unsigned at_pre = at;      // start of level k - t
-            unsigned pw_pre = pw;      // D^(k - t)
-            unsigned at_suf = 0;       // start of level t
-            double acc = 0.0;
-            for (int t = 0; t <= k; ++t) {
-                acc = __builtin_fma(A[at_pre + pre], Bm[at_suf + suf], acc);
-                const unsigned q = pre / Du;
-                suf += (pre - q * Du) * div;
-                pre = q;
-                at_suf += div;
-                div *= Du;
-                pw_pre /= Du;
-                at_pre -= pw_pre;
-            }
-            out[pr * sig_len + e] = (TO)acc;
-        }
-    }
-}
-
 template <int DT, int M, int S, int QC, bool SHARED>
 hipError_t launch_one(const Args& a, long grid, hipStream_t st)
 {
@@ -536,21 +495,6 @@ hipError_t launch_horner(int DT, int M, int S, const Args& a, long grid, hipStre
 #undef SG_CASE
     return hipErrorInvalidValue;
 }
-
-template <typename TO>
-hipError_t launch_chen_pairs(const double* in, TO* out, long pairs, int D, int N, long sig_len, hipStream_t st)
-{
-    if (pairs <= 0 || sig_len <= 0) return hipSuccess;
-    if (sig_len >= (1L << 31) || D < 1) return hipErrorInvalidValue;
-    long gx = (sig_len + 255) / 256;
-    if (gx > 65536) gx = 65536;
-    const long gy = pairs < 65535 ? pairs : 65535;
-    hipLaunchKernelGGL(chen_pairs_kernel<TO>, dim3((unsigned)gx, (unsigned)gy), dim3(256), 0, st, in, out, pairs, D, N, sig_len);
-    return hipGetLastError();
-}
-
-template hipError_t launch_chen_pairs<float>(const double*, float*, long, int, int, long, hipStream_t);
-template hipError_t launch_chen_pairs<double>(const double*, double*, long, int, int, long, hipStream_t);
 
 template <typename TI>
 hipError_t launch_increments(const TI* x, double* dz, long B, long L, int d, int D, int Dpad, long n, int P, long Lc,

@@ -54,17 +54,19 @@ template <typename TO>
 hipError_t launch_point_gradients(const double* gz, TO* gx, long B, long L, int d, int Dpad, int P, long Lc, long np,
                                   int lead_lag, hipStream_t st);
 
-// adjoints of the two factors of each pair product: Gc[2 i] = adjoint of X[2 i], Gc[2 i + 1] = adjoint of X[2 i + 1],
-// given the adjoint Gp[i] of X[2 i] (x) X[2 i + 1]
-hipError_t launch_chen_pairs_adjoint(const double* X, const double* Gp, double* Gc, long pairs, int D, int N, long sig_len,
-                                     hipStream_t st);
-
 template <typename TI>
 hipError_t launch_increments(const TI* x, double* dz, long B, long L, int d, int D, int Dpad, long n, int P, long Lc,
                              long np, int time_aug, int lead_lag, hipStream_t st);
 
-// out[i] = in[2 i] (x) in[2 i + 1] for i < pairs, signatures of sig_len entries (levels 0..N over D channels)
-template <typename TO>
-hipError_t launch_chen_pairs(const double* in, TO* out, long pairs, int D, int N, long sig_len, hipStream_t st);
+// Signatures of P pieces per path, sig_len entries each (levels 0..N over D channels): their product, float or double;
+// or the products of the first p + 1 pieces and of the pieces after p (p < P - 1), for every p; and the adjoint of the
+// former from the upstream gradient of the whole (levels 1..N).
+hipError_t launch_piece_product(const double* pieces, void* out, bool out_f32, long B, int P, int D, int N, long sig_len,
+                                hipStream_t st);
+hipError_t launch_piece_scans(const double* pieces, double* prefix, double* suffix, long B, int P, int D, int N, long sig_len,
+                              hipStream_t st);
+template <typename TI>
+hipError_t launch_piece_adjoints(const TI* gout, const double* suffix, double* adj, long B, int P, int D, int N, long sig_len,
+                                 hipStream_t st);
 
 }  // namespace sg

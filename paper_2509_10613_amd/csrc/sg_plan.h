@@ -25,6 +25,7 @@ constexpr int kLongPrefixMaxD = 9;   // channel counts whose variants also exist
 constexpr int64_t kSimds = 1024;       // 256 compute units of 4 SIMDs
 constexpr int kMinPiece = 32;          // fewest segments a piece of a path is cut down to
 constexpr int kMaxPieces = 1024;
+constexpr int kPiecesMaxN = 14;        // deepest level with a kernel that multiplies pieces: kQMax letters, one, and five owned
 constexpr int kSharedMaxQ = 2;         // waves that hold several paths: longest prefix and most channels with such kernels
 constexpr int kSharedMaxD = 9;
 
@@ -146,7 +147,8 @@ struct Plan {
     int64_t sig_len = 0;  // entries per path, level 0 included
     int io_elem = 8;
     size_t off_dz = 0, off_out = 0, total = 0;
-    size_t off_t0 = 0, off_t1 = 0;   // signatures of the pieces and of their pairwise products (P > 1)
+    size_t off_t0 = 0;    // signatures of the pieces (P > 1); backward: then the adjoints at their ends
+    size_t off_t1 = 0;    // backward: signatures of the pieces up to each one and after it
     // backward
     bool backward = false;
     size_t lds_wave = 0;      // doubles of LDS per wave
@@ -259,9 +261,9 @@ inline Plan make_plan(int64_t B, int64_t L, int64_t d, int N, bool time_aug, boo
     if (!choose(B)) return p;
     const bool may_matrix = backward && force_M < 0 && force_S == 0 && force_W == 0;   // (no kernel of the others asked for)
     // Few long paths leave most SIMDs without a wave: cut every path into P pieces of Lc segments, let the Horner
-    // kernel treat the pieces as paths, and multiply the signatures of the pieces pairwise afterwards (Chen's identity,
-    // Proposition 2.2).  Backward: the same products, then their adjoints pair by pair back down to the pieces, then
-    // the backward kernel on the pieces.
+    // kernel treat the pieces as paths, and multiply the signatures of the pieces afterwards (Chen's identity,
+    // Proposition 2.2).  Backward: the products up to and after every piece give the signature and the adjoint that the
+    // backward kernel starts a piece from.
     if (p.n > 0) {
         int P = 1;
         if (force_P > 0) {
@@ -318,8 +320,6 @@ inline Plan make_plan(int64_t B, int64_t L, int64_t d, int N, bool time_aug, boo
         if (p.P > 1) {
             p.off_t0 = off;
             off = align_up(off + (size_t)p.VB * (size_t)p.sig_len * sizeof(double), 256);
-            p.off_t1 = off;
-            off = align_up(off + (size_t)(p.VB / 2) * (size_t)p.sig_len * sizeof(double), 256);
         }
     } else {
         if (p.DT == 0 && D > kBwdMaxRuntimeD) { p.why = "backward: more than 1024 channels"; return p; }
@@ -341,13 +341,11 @@ inline Plan make_plan(int64_t B, int64_t L, int64_t d, int N, bool time_aug, boo
         p.off_gout = off;    // float callers: the upstream gradient in double
         if (!io_double) off = align_up(off + (size_t)B * (size_t)p.sig_len * sizeof(double), 256);
         if (p.P > 1) {
-            // signatures of the pieces and of the products of 2, 4, ... neighbouring pieces (levels 0 .. log2 P - 1 of
-            // the product tree, P + P/2 + ... + 2 signatures per path), and the adjoints of the same
-            const size_t tree = (size_t)(2 * p.VB - 2 * B) * (size_t)p.sig_len * sizeof(double);
+            const size_t pieces = (size_t)p.VB * (size_t)p.sig_len * sizeof(double);
             p.off_t0 = off;
-            off = align_up(off + tree, 256);
+            off = align_up(off + pieces, 256);
             p.off_t1 = off;
-            off = align_up(off + tree, 256);
+            off = align_up(off + 2 * pieces, 256);
         }
     }
     p.total = off < 256 ? 256 : off;

@@ -939,16 +939,9 @@ int run_signature(const sg::Plan& p, const void* x, void* out, int flags, void* 
     if (ttag) SK_CHECK(ev.begin(0, ttag, st));
     SK_CHECK(sg::launch_horner(p.DT, p.M, p.S, a, p.grid, st));
     if (p.P > 1) {
-        // the signatures of the pieces, multiplied pairwise until one per path is left (Chen's identity)
-        double* t0 = reinterpret_cast<double*>(base + p.off_t0);
-        double* t1 = reinterpret_cast<double*>(base + p.off_t1);
-        const double* src = t0;
-        for (int cur = p.P; cur > 2; cur /= 2) {
-            double* dst = src == t0 ? t1 : t0;
-            SK_CHECK(sg::launch_chen_pairs(src, dst, p.B * (cur / 2), p.D, p.N, p.sig_len, st));
-            src = dst;
-        }
-        SK_CHECK(sg::launch_chen_pairs(src, static_cast<T*>(out), p.B, p.D, p.N, p.sig_len, st));
+        // the signature of the path from those of its pieces (Chen's identity)
+        SK_CHECK(sg::launch_piece_product(reinterpret_cast<double*>(base + p.off_t0), out, sizeof(T) == 4, p.B, p.P, p.D, p.N,
+                                          p.sig_len, st));
     }
     if (ttag) SK_CHECK(ev.end(st));
 #undef SK_CHECK
@@ -975,10 +968,10 @@ int run_signature_bwd(const sg::Plan& p, const sg::Plan& pf, const void* x, cons
     SK_CHECK(sg::launch_increments<T>(static_cast<const T*>(x), dz, p.B, p.L, p.d, p.D, p.Dpad, p.n, p.P, p.Lc, p.np,
                                       (flags & SK_FLAG_TIME_AUG) ? 1 : 0, (flags & SK_FLAG_LEAD_LAG) ? 1 : 0, st));
     SK_CHECK(sk::launch_fill<double>(gz, p.VB * p.np * p.Dpad, 0.0, st));
-    const double* gout64;
+    const double* gout64 = nullptr;
     if (kIsDouble) {
         gout64 = static_cast<const double*>(grad_out);
-    } else {
+    } else if (p.P == 1) {
         double* g64 = reinterpret_cast<double*>(base + p.off_gout);
         SK_CHECK((sk::launch_convert<T, double>(static_cast<const T*>(grad_out), g64, count, st)));
         gout64 = g64;
@@ -988,34 +981,18 @@ int run_signature_bwd(const sg::Plan& p, const sg::Plan& pf, const void* x, cons
     EventPair ev;
     const double* sig64;
     if (p.P > 1) {
-        // Paths cut into pieces: signatures of the pieces (level 0 of a tree), products of neighbouring pairs level by
-        // level up to the whole paths, then the adjoints back down; the backward kernel then sees the pieces as paths
-        // with their own signatures and upstream gradients.  Signatures the caller passed are not used.
+        // Paths cut into pieces: the backward kernel sees the pieces as paths that end in the signature up to there, with
+        // the adjoint of that.  Signatures the caller passed are not used.
         if (timed) SK_CHECK(ev.begin(1, ttag, st));
-        double* tv = reinterpret_cast<double*>(base + p.off_t0);
-        double* ta = reinterpret_cast<double*>(base + p.off_t1);
-        const sg::Args f = sig_args(pf, static_cast<const T*>(x), dz, tv, false, flags);
+        double* pieces = reinterpret_cast<double*>(base + p.off_t0);
+        double* prefix = reinterpret_cast<double*>(base + p.off_t1);
+        double* suffix = prefix + p.VB * p.sig_len;
+        const sg::Args f = sig_args(pf, static_cast<const T*>(x), dz, pieces, false, flags);
         SK_CHECK(sg::launch_horner(pf.DT, pf.M, pf.S, f, pf.grid, st));
-        // level j holds P >> j signatures per path, starting at lev[j] signatures into the tree buffers
-        long lev[16];
-        int nlev = 0;
-        {
-            long o = 0;
-            for (int cur = p.P; cur > 1; cur /= 2) {
-                lev[nlev++] = o;
-                o += p.B * cur;
-            }
-        }
-        for (int j = 0; j + 1 < nlev; ++j)      // the product of all pieces is not needed: its adjoint is grad_out
-            SK_CHECK(sg::launch_chen_pairs(tv + lev[j] * p.sig_len, tv + lev[j + 1] * p.sig_len, p.B * (p.P >> (j + 1)), p.D,
-                                           p.N, p.sig_len, st));
-        for (int j = nlev - 1; j >= 0; --j) {
-            const double* parent = j == nlev - 1 ? gout64 : ta + lev[j + 1] * p.sig_len;
-            SK_CHECK(sg::launch_chen_pairs_adjoint(tv + lev[j] * p.sig_len, parent, ta + lev[j] * p.sig_len,
-                                                   p.B * (p.P >> (j + 1)), p.D, p.N, p.sig_len, st));
-        }
-        sig64 = tv;
-        gout64 = ta;
+        SK_CHECK(sg::launch_piece_scans(pieces, prefix, suffix, p.B, p.P, p.D, p.N, p.sig_len, st));
+        SK_CHECK(sg::launch_piece_adjoints(static_cast<const T*>(grad_out), suffix, pieces, p.B, p.P, p.D, p.N, p.sig_len, st));
+        sig64 = prefix;
+        gout64 = pieces;
     } else if (!sig) {
         double* s64 = reinterpret_cast<double*>(base + p.off_sig);
         SK_CHECK(sg::launch_horner(pf.DT, pf.M, pf.S, sig_args(pf, static_cast<const T*>(x), dz, s64, false, flags), pf.grid, st));
