@@ -390,8 +390,10 @@ __global__ __launch_bounds__(kWave * kWavesPerWG) void horner_kernel(const Args 
 // holds the segments p Lc .. p Lc + Lc - 1 (those below n), then zero rows.
 // I: type of the entries' numbers.  Three divisions per entry are what the kernel is bound by: in 64 bits 13.0 us for
 // 100000 paths of 10 points, where the entries' numbers fit 32 bits and are divided as such 10.7 us.
+// zero: doubles to clear beside them (the backward pass's sums).
 template <typename TI, typename I>
-__global__ __launch_bounds__(256) void increments_kernel(const TI* __restrict__ x, double* __restrict__ dz, I total, long L,
+__global__ __launch_bounds__(256) void increments_kernel(const TI* __restrict__ x, double* __restrict__ dz,
+                                                         double* __restrict__ zero, I total, long L,
                                                          int d, int D, int Dpad, long n, int P, long Lc, long np,
                                                          int time_aug, int lead_lag)
 {
@@ -424,6 +426,7 @@ __global__ __launch_bounds__(256) void increments_kernel(const TI* __restrict__ 
             }
         }
         dz[i] = v;
+        if (zero) zero[i] = 0.0;
     }
 }
 
@@ -497,7 +500,7 @@ hipError_t launch_horner(int DT, int M, int S, const Args& a, long grid, hipStre
 }
 
 template <typename TI>
-hipError_t launch_increments(const TI* x, double* dz, long B, long L, int d, int D, int Dpad, long n, int P, long Lc,
+hipError_t launch_increments(const TI* x, double* dz, double* zero, long B, long L, int d, int D, int Dpad, long n, int P, long Lc,
                              long np, int time_aug, int lead_lag, hipStream_t st)
 {
     if (P < 1 || np < Lc || P * Lc < n || (np > 0 && !(np & 1))) return hipErrorInvalidValue;
@@ -506,15 +509,15 @@ hipError_t launch_increments(const TI* x, double* dz, long B, long L, int d, int
     long grid = (total + 255) / 256;
     if (grid > 65536) grid = 65536;
     if (total < (1L << 31))       // (a step of the loop adds at most 2^24)
-        hipLaunchKernelGGL((increments_kernel<TI, unsigned>), dim3((unsigned)grid), dim3(256), 0, st, x, dz, (unsigned)total, L, d,
+        hipLaunchKernelGGL((increments_kernel<TI, unsigned>), dim3((unsigned)grid), dim3(256), 0, st, x, dz, zero, (unsigned)total, L, d,
                            D, Dpad, n, P, Lc, np, time_aug, lead_lag);
     else
-        hipLaunchKernelGGL((increments_kernel<TI, unsigned long>), dim3((unsigned)grid), dim3(256), 0, st, x, dz,
+        hipLaunchKernelGGL((increments_kernel<TI, unsigned long>), dim3((unsigned)grid), dim3(256), 0, st, x, dz, zero,
                            (unsigned long)total, L, d, D, Dpad, n, P, Lc, np, time_aug, lead_lag);
     return hipGetLastError();
 }
 
-template hipError_t launch_increments<float>(const float*, double*, long, long, int, int, int, long, int, long, long, int, int, hipStream_t);
-template hipError_t launch_increments<double>(const double*, double*, long, long, int, int, int, long, int, long, long, int, int, hipStream_t);
+template hipError_t launch_increments<float>(const float*, double*, double*, long, long, int, int, int, long, int, long, long, int, int, hipStream_t);
+template hipError_t launch_increments<double>(const double*, double*, double*, long, long, int, int, int, long, int, long, long, int, int, hipStream_t);
 
 }  // namespace sg

@@ -20,17 +20,17 @@ namespace sg {
 
 namespace {
 
-template <int D, int M, int S, int TOT, int m = 0>
-__device__ __forceinline__ void load_owned(double (&A)[TOT], const double* src, const long (&at)[M + 1], int Dn,
+template <int D, int M, int S, int TOT, int m = 0, typename TI>
+__device__ __forceinline__ void load_owned(double (&A)[TOT], const TI* src, const long (&at)[M + 1], int Dn,
                                            long first, int c0, bool valid)
 {
     constexpr int pm = ipow(D, m);
 #pragma unroll
     for (int s = 0; s < S; ++s) {
         const bool ok = valid && c0 + s < Dn;
-        const double* o = src + at[m] + (first + s) * pm;
+        const TI* o = src + at[m] + (first + s) * pm;
 #pragma unroll
-        for (int v = 0; v < pm; ++v) A[Tree<D, M, S>::off(m) + s * pm + v] = ok ? o[v] : 0.0;
+        for (int v = 0; v < pm; ++v) A[Tree<D, M, S>::off(m) + s * pm + v] = ok ? (double)o[v] : 0.0;
     }
     if constexpr (m < M) load_owned<D, M, S, TOT, m + 1>(A, src, at, Dn, first, c0, valid);
 }
@@ -112,24 +112,31 @@ __device__ __forceinline__ void run_bwd(const BwdArgs& a, double* lds)
 
     // the signature of the whole path and the upstream gradient, each lane its own entries
     double A[T::TOT], Ab[T::TOT], preR[QA], prb[QA];
-    const double* sig = a.sig + b * a.sig_len;
-    const double* gout = a.gout + b * a.sig_len;
-    load_owned<DD, M, S, T::TOT>(A, sig, at, D, rest * D + blk * S, blk * S, true);
-    load_owned<DD, M, S, T::TOT>(Ab, gout, at, D, rest * D + blk * S, blk * S, valid);
-    {
+    auto load_sig = [&](const auto* sig) {
+        load_owned<DD, M, S, T::TOT>(A, sig, at, D, rest * D + blk * S, blk * S, true);
         long pw = 1;
 #pragma unroll
         for (int r = 0; r < QA; ++r) {
             preR[r] = 0.0;
-            prb[r] = 0.0;
-            if (r < QC && has<QC>(r, Q)) {
-                const long idx = lvl(Q - r) + rest / pw;
-                preR[r] = sig[idx];
-                if (valid && blk == 0 && rest % pw == 0) prb[r] = gout[idx];   // one lane starts with the upstream value
-            }
+            if (r < QC && has<QC>(r, Q)) preR[r] = (double)sig[lvl(Q - r) + rest / pw];
             pw *= D;
         }
-    }
+    };
+    auto load_gout = [&](const auto* gout) {
+        load_owned<DD, M, S, T::TOT>(Ab, gout, at, D, rest * D + blk * S, blk * S, valid);
+        long pw = 1;
+#pragma unroll
+        for (int r = 0; r < QA; ++r) {
+            prb[r] = 0.0;
+            // one lane starts with the upstream value
+            if (r < QC && has<QC>(r, Q) && valid && blk == 0 && rest % pw == 0) prb[r] = (double)gout[lvl(Q - r) + rest / pw];
+            pw *= D;
+        }
+    };
+    if (a.sig_f32) load_sig(static_cast<const float*>(a.sig) + b * a.sig_len);
+    else load_sig(static_cast<const double*>(a.sig) + b * a.sig_len);
+    if (a.gout_f32) load_gout(static_cast<const float*>(a.gout) + b * a.sig_len);
+    else load_gout(static_cast<const double*>(a.gout) + b * a.sig_len);
 
     const double* zrow = a.dz + b * a.np * a.Dpad;
     double* grow = a.gz + b * a.np * a.Dpad;
@@ -151,6 +158,7 @@ __device__ __forceinline__ void run_bwd(const BwdArgs& a, double* lds)
         for (int r = 0; r < QA; ++r) zu_[r] = (r < QC && has<QC>(r, Q)) ? zp[uR[r]] : 0.0;
     };
 
+    const bool alone = a.WP == 1;       // no other wave has a share of this path's sums
     // The sum of dF/dz[row] over the lanes of the wave takes three hops through LDS, and they are spread over three
     // segments so that no hop waits for the one before it: after segment i the lanes publish their shares of row i
     // (a row of DS doubles per lane: the shares that belong to the wave-uniform increments are written, the shares a
@@ -217,7 +225,8 @@ __device__ __forceinline__ void run_bwd(const BwdArgs& a, double* lds)
         }
         if (flush && lane < DD) {
             acc[lane] = 0.0;
-            atomicAdd(&grow[r2 * a.Dpad + lane], v);
+            if (alone) grow[r2 * a.Dpad + lane] = v;
+            else atomicAdd(&grow[r2 * a.Dpad + lane], v);
         }
         if (coll && lane < DD * P) atomicAdd(&acc[c], sum);
         if (row_new >= 0) publish(zzb, zcb, zub);
@@ -265,7 +274,8 @@ __device__ __forceinline__ void run_bwd(const BwdArgs& a, double* lds)
             for (int c = lane; c < D; c += kWave) {
                 const double v = acc[c];
                 acc[c] = 0.0;
-                atomicAdd(&grow[row * a.Dpad + c], v);
+                if (alone) grow[row * a.Dpad + c] = v;
+                else atomicAdd(&grow[row * a.Dpad + c], v);
             }
             __builtin_amdgcn_wave_barrier();
         }

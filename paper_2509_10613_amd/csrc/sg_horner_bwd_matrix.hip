@@ -81,46 +81,54 @@ __global__ __launch_bounds__(kWave * kWavesPerWG, 2) void horner_bwd_matrix_kern
         }
         return o;
     };
-    const double* sig = a.sig + b * a.sig_len;
-    const double* gout = a.gout + b * a.sig_len;
     // the adjoints of the top level: of the lane's own words, and of word s of lane 16 g + k at channel i
     double top[S][D], b2[S][16];
-    {
-        const double* gt = gout + lvl(Q + 2);
+    double A[S], Ab[S], preR[Q], prb[Q];
+    const long own = lvl(Q + 1) + (long)u * D;
+    auto load_sig = [&](const auto* sig) {
+#pragma unroll
+        for (int s = 0; s < S; ++s) A[s] = (double)sig[own + cs[s]];
+        int pw = 1;
+#pragma unroll
+        for (int r = 0; r < Q; ++r) {
+            preR[r] = (double)sig[lvl(Q - r) + u / pw];
+            pw *= D;
+        }
+    };
+    auto load_gout = [&](const auto* gout) {
+        const auto* gt = gout + lvl(Q + 2);
 #pragma unroll
         for (int s = 0; s < S; ++s) {
-            const double* o = gt + ((long)u * D + cs[s]) * D;
+            const auto* o = gt + ((long)u * D + cs[s]) * D;
 #pragma unroll
-            for (int c = 0; c < D; ++c) top[s][c] = o[c];
+            for (int c = 0; c < D; ++c) top[s][c] = (double)o[c];
 #pragma unroll
             for (int c = 0; c < D; ++c) top[s][c] = valid[s] ? top[s][c] : 0.0;
 #pragma unroll
             for (int k = 0; k < 16; ++k) {
                 const int uw = w0 + (16 * g + k) / DP, cw = k % DP * S + s;
                 const bool ok = uw < NU && cw < D && i < D;
-                const double v = gt[ok ? ((long)uw * D + cw) * D + i : 0];
+                const double v = (double)gt[ok ? ((long)uw * D + cw) * D + i : 0];
                 b2[s][k] = ok ? v : 0.0;
             }
         }
-    }
-    double A[S], Ab[S], preR[Q], prb[Q];
-    {
-        const long at = lvl(Q + 1) + (long)u * D;
 #pragma unroll
         for (int s = 0; s < S; ++s) {
-            A[s] = sig[at + cs[s]];
-            const double v = gout[at + cs[s]];
+            const double v = (double)gout[own + cs[s]];
             Ab[s] = valid[s] ? v : 0.0;
         }
         int pw = 1;
 #pragma unroll
         for (int r = 0; r < Q; ++r) {
-            const long idx = lvl(Q - r) + u / pw;
-            preR[r] = sig[idx];
-            prb[r] = (inside && blk == 0 && u % pw == 0) ? gout[idx] : 0.0;   // one lane starts with the upstream value
+            // one lane starts with the upstream value
+            prb[r] = (inside && blk == 0 && u % pw == 0) ? (double)gout[lvl(Q - r) + u / pw] : 0.0;
             pw *= D;
         }
-    }
+    };
+    if (a.sig_f32) load_sig(static_cast<const float*>(a.sig) + b * a.sig_len);
+    else load_sig(static_cast<const double*>(a.sig) + b * a.sig_len);
+    if (a.gout_f32) load_gout(static_cast<const float*>(a.gout) + b * a.sig_len);
+    else load_gout(static_cast<const double*>(a.gout) + b * a.sig_len);
     const double* zrow = a.dz + b * a.np * a.Dpad;
     double* grow = a.gz + b * a.np * a.Dpad;
     const long n = a.n;

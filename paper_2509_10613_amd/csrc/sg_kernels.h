@@ -31,9 +31,10 @@ struct Args {
 
 struct BwdArgs {
     const double* dz;    // [B][np][Dpad] increments of the transformed paths
-    double* gz;          // [B][np][Dpad] dF/dz, zero on entry, accumulated by atomics
-    const double* sig;   // [B][sig_len] signatures of the whole paths
-    const double* gout;  // [B][sig_len] upstream gradient
+    double* gz;          // [B][np][Dpad] dF/dz: zero on entry and accumulated by atomics, unless a path is one wave's
+    const void* sig;     // [B][sig_len] signatures of the whole paths, float if sig_f32, else double
+    const void* gout;    // [B][sig_len] upstream gradient, likewise
+    int sig_f32, gout_f32;
     long B;
     long n, np;
     int D, Dpad, N, Q, NB;
@@ -54,8 +55,9 @@ template <typename TO>
 hipError_t launch_point_gradients(const double* gz, TO* gx, long B, long L, int d, int Dpad, int P, long Lc, long np,
                                   int lead_lag, hipStream_t st);
 
+// zero: as many doubles to clear on the way, or nullptr
 template <typename TI>
-hipError_t launch_increments(const TI* x, double* dz, long B, long L, int d, int D, int Dpad, long n, int P, long Lc,
+hipError_t launch_increments(const TI* x, double* dz, double* zero, long B, long L, int d, int D, int Dpad, long n, int P, long Lc,
                              long np, int time_aug, int lead_lag, hipStream_t st);
 
 // Signatures of P pieces per path, sig_len entries each (levels 0..N over D channels): their product, float or double;

@@ -153,7 +153,7 @@ struct Plan {
     bool backward = false;
     size_t lds_wave = 0;      // doubles of LDS per wave
     size_t lds_bytes = 0;
-    size_t off_gz = 0, off_sig = 0, off_gout = 0;
+    size_t off_gz = 0, off_sig = 0;
     bool matrix = false;             // the top level on the matrix cores; launch shape of that kernel:
     int matrix_Q = 0, matrix_S = 1;
     int64_t matrix_WP = 0, matrix_waves = 0, matrix_grid = 0;
@@ -336,9 +336,10 @@ inline Plan make_plan(int64_t B, int64_t L, int64_t d, int N, bool time_aug, boo
         p.lds_bytes = (size_t)kWavesPerWG * p.lds_wave * sizeof(double);
         p.off_gz = off;      // dF/dz, one row per stored increment row
         off = align_up(off + (size_t)p.VB * (size_t)p.np * p.Dpad * sizeof(double), 256);
-        p.off_sig = off;     // signatures in double: computed here, or converted from a float caller's
+        p.off_sig = off;     // signatures in double, if the caller has none
+        // (room for float callers' signatures and upstream gradients in double, which the kernels now read as they are,
+        // stays part of the size)
         if (p.P == 1 && (!have_sig || !io_double)) off = align_up(off + (size_t)B * (size_t)p.sig_len * sizeof(double), 256);
-        p.off_gout = off;    // float callers: the upstream gradient in double
         if (!io_double) off = align_up(off + (size_t)B * (size_t)p.sig_len * sizeof(double), 256);
         if (p.P > 1) {
             const size_t pieces = (size_t)p.VB * (size_t)p.sig_len * sizeof(double);

@@ -929,7 +929,7 @@ int run_signature(const sg::Plan& p, const void* x, void* out, int flags, void* 
     } while (0)
     double* dz = reinterpret_cast<double*>(base + p.off_dz);
     if (p.PW == 1)      // (kernels that hold several paths per wave read the points)
-        SK_CHECK(sg::launch_increments<T>(static_cast<const T*>(x), dz, p.B, p.L, p.d, p.D, p.Dpad, p.n, p.P, p.Lc, p.np,
+        SK_CHECK(sg::launch_increments<T>(static_cast<const T*>(x), dz, nullptr, p.B, p.L, p.d, p.D, p.Dpad, p.n, p.P, p.Lc, p.np,
                                           (flags & SK_FLAG_TIME_AUG) ? 1 : 0, (flags & SK_FLAG_LEAD_LAG) ? 1 : 0, st));
     // the kernel that finishes a signature writes the caller's type; pieces stay double
     const sg::Args a = p.P > 1 ? sig_args(p, static_cast<const T*>(x), dz, base + p.off_t0, false, flags)
@@ -954,7 +954,6 @@ template <typename T>
 int run_signature_bwd(const sg::Plan& p, const sg::Plan& pf, const void* x, const void* sig, const void* grad_out,
                       void* grad_x, int flags, void* ws, hipStream_t st)
 {
-    constexpr bool kIsDouble = sizeof(T) == 8;
     unsigned char* base = static_cast<unsigned char*>(ws);
     hipError_t e;
 #define SK_CHECK(call)                                                                         \
@@ -964,22 +963,16 @@ int run_signature_bwd(const sg::Plan& p, const sg::Plan& pf, const void* x, cons
     } while (0)
     double* dz = reinterpret_cast<double*>(base + p.off_dz);
     double* gz = reinterpret_cast<double*>(base + p.off_gz);
-    const long count = p.B * p.sig_len;
-    SK_CHECK(sg::launch_increments<T>(static_cast<const T*>(x), dz, p.B, p.L, p.d, p.D, p.Dpad, p.n, p.P, p.Lc, p.np,
-                                      (flags & SK_FLAG_TIME_AUG) ? 1 : 0, (flags & SK_FLAG_LEAD_LAG) ? 1 : 0, st));
-    SK_CHECK(sk::launch_fill<double>(gz, p.VB * p.np * p.Dpad, 0.0, st));
-    const double* gout64 = nullptr;
-    if (kIsDouble) {
-        gout64 = static_cast<const double*>(grad_out);
-    } else if (p.P == 1) {
-        double* g64 = reinterpret_cast<double*>(base + p.off_gout);
-        SK_CHECK((sk::launch_convert<T, double>(static_cast<const T*>(grad_out), g64, count, st)));
-        gout64 = g64;
-    }
+    // (a wave that has a path to itself writes its sums, several waves add them to zeros)
+    const bool adds = p.matrix || p.WP > 1;
+    SK_CHECK(sg::launch_increments<T>(static_cast<const T*>(x), dz, adds ? gz : nullptr, p.B, p.L, p.d, p.D, p.Dpad, p.n, p.P, p.Lc,
+                                      p.np, (flags & SK_FLAG_TIME_AUG) ? 1 : 0, (flags & SK_FLAG_LEAD_LAG) ? 1 : 0, st));
     const int ttag = timing_tag();
     const bool timed = ttag != 0;
     EventPair ev;
-    const double* sig64;
+    sg::BwdArgs a;
+    a.sig = sig; a.sig_f32 = sizeof(T) == 4;
+    a.gout = grad_out; a.gout_f32 = sizeof(T) == 4;
     if (p.P > 1) {
         // Paths cut into pieces: the backward kernel sees the pieces as paths that end in the signature up to there, with
         // the adjoint of that.  Signatures the caller passed are not used.
@@ -991,21 +984,14 @@ int run_signature_bwd(const sg::Plan& p, const sg::Plan& pf, const void* x, cons
         SK_CHECK(sg::launch_horner(pf.DT, pf.M, pf.S, f, pf.grid, st));
         SK_CHECK(sg::launch_piece_scans(pieces, prefix, suffix, p.B, p.P, p.D, p.N, p.sig_len, st));
         SK_CHECK(sg::launch_piece_adjoints(static_cast<const T*>(grad_out), suffix, pieces, p.B, p.P, p.D, p.N, p.sig_len, st));
-        sig64 = prefix;
-        gout64 = pieces;
+        a.sig = prefix; a.gout = pieces;
+        a.sig_f32 = a.gout_f32 = 0;
     } else if (!sig) {
         double* s64 = reinterpret_cast<double*>(base + p.off_sig);
         SK_CHECK(sg::launch_horner(pf.DT, pf.M, pf.S, sig_args(pf, static_cast<const T*>(x), dz, s64, false, flags), pf.grid, st));
-        sig64 = s64;
-    } else if (kIsDouble) {
-        sig64 = static_cast<const double*>(sig);
-    } else {
-        double* s64 = reinterpret_cast<double*>(base + p.off_sig);
-        SK_CHECK((sk::launch_convert<T, double>(static_cast<const T*>(sig), s64, count, st)));
-        sig64 = s64;
+        a.sig = s64; a.sig_f32 = 0;
     }
-    sg::BwdArgs a;
-    a.dz = dz; a.gz = gz; a.sig = sig64; a.gout = gout64;
+    a.dz = dz; a.gz = gz;
     a.B = p.VB; a.n = p.Lc; a.np = p.np; a.D = p.D; a.Dpad = p.Dpad; a.N = p.N; a.Q = p.Q; a.NB = p.NB;
     a.LP = p.LP; a.WP = p.WP; a.sig_len = p.sig_len; a.lds_wave = p.lds_wave; a.PW = p.PW; a.NW = p.waves;
     a.leadlag = (flags & SK_FLAG_LEAD_LAG) ? 1 : 0;
