@@ -319,8 +319,18 @@ __device__ __forceinline__ void run_shared(const Args& a, double* lds)
                 for (int c = 0; c < DD; ++c) cur[c] = own[j * d + c];
             }
         };
+        int j = 0;
         read(0);
-        for (int j = 0; j < count; ++j) {
+        if (c0 == 0) {                                          // the path's first point
+#pragma unroll
+            for (int i = 0; i < NW; ++i) prevL[i] = curL[i];
+#pragma unroll
+            for (int c = 0; c < DD; ++c) prev[c] = kStatic ? cur[c] : 0.0;
+            j = 1;
+            read(count > 1 ? 1 : 0);
+        }
+#pragma unroll 2
+        for (; j < count; ++j) {
             double dl[NW], dp[DD];
 #pragma unroll
             for (int i = 0; i < NW; ++i) {
@@ -333,7 +343,6 @@ __device__ __forceinline__ void run_shared(const Args& a, double* lds)
                 prev[c] = kStatic ? cur[c] : 0.0;
             }
             read(j + 1 < count ? j + 1 : j);
-            if (c0 + j == 0) continue;                         // the first point
             const double t = c0 + j <= mine ? tick : 0.0;
             if constexpr (LEADLAG) {
                 row(std::integral_constant<int, 1>(), 1, dl, dp, t);

@@ -23,9 +23,6 @@ namespace {
 
 __host__ __device__ constexpr int tri(int n) { return n * (n + 1) / 2; }
 
-// What N allows to be requested before the arithmetic that reads it: pieces per batch.
-__host__ __device__ constexpr int batch(int N) { return N <= 3 ? 4 : (N <= 5 ? 2 : 1); }
-
 struct PieceArgs {
     const double* pieces;    // [B][P][sig_len]
     double* prefix;          // [B][P][sig_len] L_p, or nullptr
@@ -41,7 +38,7 @@ struct PieceArgs {
 template <int N, bool SUFFIX>
 __device__ __forceinline__ void scan(const PieceArgs& a, long b, unsigned w)
 {
-    constexpr int U = batch(N);
+    constexpr int U = pieces_batch(N);     // requested before the arithmetic that reads them
     // number of the word's first j letters
     unsigned pre[N + 1];
 #pragma unroll

@@ -23,7 +23,7 @@ constexpr int kQMax = 8;            // longest carried prefix
 constexpr int kQExact = 4;          // prefix lengths with code of their own
 constexpr int kLongPrefixMaxD = 9;   // channel counts whose variants also exist for prefixes longer than kQExact
 constexpr int64_t kSimds = 1024;       // 256 compute units of 4 SIMDs
-constexpr int kMinPiece = 32;          // fewest segments a piece of a path is cut down to
+constexpr int kMinPiece = 12;          // fewest segments a piece of a path is cut down to
 constexpr int kMaxPieces = 1024;
 constexpr int kPiecesMaxN = 14;        // deepest level with a kernel that multiplies pieces: kQMax letters, one, and five owned
 constexpr int kSharedMaxQ = 2;         // waves that hold several paths: longest prefix and most channels with such kernels
@@ -93,11 +93,12 @@ inline bool matrix_pays(int64_t VB, int64_t D, int N, int64_t segments, bool lea
     return VB * matrix_waves(D, N - 2, matrix_words(VB, D, N - 2)) <= most;
 }
 // Pieces of long paths for the matrix kernel (make_plan): segments from which a path is long, the least of a piece, and the
-// entries of a signature up to which more pieces are worth their products.  (B, L, D, N) by the matrix kernel's waves, and
-// as cut by this rule: (128, 1024, 5, 4) 350 and 196, (32, 1024, 10, 4) 367 and 297, (128, 1024, 10, 3) 236 and 194;
-// lead-lag, D channels in all: (16, 1024, 12, 4) 730 and 455, (32, 1024, 10, 4) 722 and 490, (8, 1024, 16, 4) 735 and 511;
-// but (1, 1024, 10, 5) lead-lag, 111111 entries, 411 and 455, (64, 300, 6, 5) 144 and 204, and lead-lag (450, 300, 10, 3), 598
-// segments, 251 and 288.
+// entries of a signature up to which more pieces are worth their products.  With more of the matrix kernel's waves than half
+// of the chip's SIMDs such paths go by the other kernel's: (B, L, D, N) = (128, 1024, 5, 4), 1 and 4 pieces, 350 and 171 us.
+constexpr int64_t kMatrixCut = 160;    // fewest segments of a path that is cut for the matrix kernel
+constexpr int pieces_batch(int N) { return N <= 3 ? 4 : (N <= 5 ? 2 : 1); }   // pieces a lane of the product asks for at once
+// Forward, estimated us: a segment's latency, the launch of the product, and in it the latency of a batch and a piece's word
+constexpr double kSegment = 0.2, kProduct = 4.0, kPieceLatency = 0.6, kPieceWord = 0.9e-5;
 constexpr int64_t kMatrixLong = 768, kMatrixPiece = 120, kMatrixPieceEntries = 100000;
 
 // LDS of a wave that holds PW paths (forward): their points in chunks, `stride` doubles per path (odd: the paths of a wave
@@ -212,6 +213,7 @@ inline Plan make_plan(int64_t B, int64_t L, int64_t d, int N, bool time_aug, boo
         }
         return true;
     };
+    double step_cycles = 0.0;     // estimate for a step of all paths, by choose
     auto choose = [&](int64_t Bsel) -> bool {
         // The variant with the least estimated time.  A lane executes about `instr` vector instructions per step: the
         // multiply-adds of its owned levels and their chains, the chains over the carried prefix for each owned level,
@@ -219,7 +221,7 @@ inline Plan make_plan(int64_t B, int64_t L, int64_t d, int N, bool time_aug, boo
         // instruction per 4 clocks when it has several waves and per about 5 clocks when it has a single one, and the
         // waves of the launch are spread over kSimds SIMDs.
         bool have = false;
-        double best = 0.0;
+        double best = 0.0;       // (0 without a variant: the run-time channel count)
         const Variant* list = backward ? kBwdVariants : kVariants;
         const size_t nlist = backward ? sizeof(kBwdVariants) / sizeof(Variant) : sizeof(kVariants) / sizeof(Variant);
         for (size_t vi = 0; vi < nlist; ++vi) {
@@ -256,6 +258,7 @@ inline Plan make_plan(int64_t B, int64_t L, int64_t d, int N, bool time_aug, boo
             p.PW = (!backward && LP <= kWave / 2 && Q <= kSharedMaxQ && force_W != 1) ? (int)(kWave / LP) : 1;
         }
         p.WP = (p.LP + kWave - 1) / kWave;
+        step_cycles = best;
         return true;
     };
     if (!choose(B)) return p;
@@ -268,24 +271,45 @@ inline Plan make_plan(int64_t B, int64_t L, int64_t d, int N, bool time_aug, boo
         int P = 1;
         if (force_P > 0) {
             P = force_P;
-        } else if (B > 0 && p.n >= 2 * kMinPiece && p.sig_len < ((int64_t)1 << 31)) {
-            // backward, the products and their adjoints cost several launches: only when the chip is mostly empty
-            const int64_t few = backward ? kSimds / 2 : kSimds, want = backward ? kSimds : 2 * kSimds;
-            auto pieces = [&](int64_t w1, int64_t least) {
+        } else if (B > 0 && p.sig_len < ((int64_t)1 << 31) && !backward) {
+            // The number with the least estimated time: a segment takes kSegment us, that long after the one before it
+            // has asked for its increments, or what all waves of a SIMD issue; a piece costs its latency and the
+            // multiply-adds of its words in the product, and the product a launch.  1, 2, 4, ... pieces, in us, (B, L, d, N)
+            // = (40, 2048, 7, 5): 565, 298, 174; (16, 1024, 16, 4), from 4: 110, 122, 173; (200, 100, 3, 3): 19.9, 14.2,
+            // 10.4, 8.8; (4, 1024, 8, 3), from 8: 30.9, 21.1, 16.7, 18.4; (128, 1024, 5, 4), from 4: 57.6, 42.8, 36.3, 39.2.
+            const double words = (double)B * ((double)(p.sig_len - 1) * (double)(D - 1) / (double)D + 1.0);
+            double best = 0.0;
+            for (int q = 1; q <= kMaxPieces && (q == 1 || p.n / q >= kMinPiece); q *= 2) {
+                if (q == 1 && p.n < 2 * kMinPiece) break;
+                if (p.sig_len > ((int64_t)1 << 44) / (B * q) || !choose(B * q)) break;
+                const double issue = step_cycles / 2400.0;
+                const double t = (double)p.n / q * (issue > kSegment ? issue : kSegment) +
+                                 (q > 1 ? kProduct + q * (kPieceLatency / pieces_batch(N) + words * kPieceWord) : 0.0);
+                if (q == 1 || t < best) {
+                    best = t;
+                    P = q;
+                }
+            }
+            if (!choose(B)) return p;
+        } else if (B > 0 && p.sig_len < ((int64_t)1 << 31)) {
+            // Backward: cut while that leaves at most four waves per SIMD, from half a wave per SIMD or less.  The matrix
+            // kernel has more waves for the same words and takes a third of the time of the other per segment, so it cuts
+            // later.  1, 2, 4, ... pieces, in us, (B, L, d, N) = (100, 200, 4, 3), from 2: 115, 69, 44, 34; (200, 100, 3, 3): 71,
+            // 58, 38, 30; (500, 500, 3, 4), from 4: 156, 113, 109, 131; matrix kernel: (64, 1024, 6, 4), from 2: 283, 165, 139,
+            // 128; (4, 1024, 8, 3), from 8: 72, 47, 36, 38; (64, 128, 12, 3): 44, 57, 46, 52.
+            auto pieces = [&](int64_t w1, int64_t few, int64_t want, int64_t least) {
                 int q = 1;
-                if (w1 < few)
-                    while (q < kMaxPieces && w1 * q < want && p.n / (2 * q) >= least) q *= 2;
+                if (w1 <= few)
+                    while (q < kMaxPieces && w1 * 2 * q <= want && p.n / (2 * q) >= least) q *= 2;
                 return q;
             };
             const int64_t w1 = p.PW > 1 ? (B + p.PW - 1) / p.PW : B * p.WP;
             if (may_matrix && matrix_pays(B, D, N, p.n, lead_lag)) {
-                // The matrix kernel has more waves for the same words, and cuts paths less.  Long paths go by the other
-                // kernel's waves down to pieces of kMatrixPiece segments: the time of a segment counts there, not the waves.
-                P = pieces(B * matrix_waves(D, N - 2, 1), kMinPiece);
-                const int q = p.n >= kMatrixLong && p.sig_len < kMatrixPieceEntries ? pieces(w1, kMatrixPiece) : 1;
+                if (p.n >= kMatrixCut) P = pieces(B * matrix_waves(D, N - 2, 1), kSimds / 2 - 1, 3 * kSimds, kMatrixSteps);
+                const int q = p.n >= kMatrixLong && p.sig_len < kMatrixPieceEntries ? pieces(w1, kSimds / 2 - 1, 2 * kSimds - 1, kMatrixPiece) : 1;
                 if (q > P) P = q;
-            } else {
-                P = pieces(w1, kMinPiece);
+            } else if (p.n >= 4 * kMinPiece) {
+                P = pieces(w1, kSimds / 2, 4 * kSimds, kMinPiece);
             }
         }
         if (P > 1) {
