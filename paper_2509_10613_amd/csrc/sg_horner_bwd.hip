@@ -158,7 +158,7 @@ __device__ __forceinline__ void run_bwd(const BwdArgs& a, double* lds)
         for (int r = 0; r < QA; ++r) zu_[r] = (r < QC && has<QC>(r, Q)) ? zp[uR[r]] : 0.0;
     };
 
-    const bool alone = a.WP == 1;       // no other wave has a share of this path's sums
+    constexpr bool alone = DT > 0 && lone_wave(DT, S, QC);     // no other wave has a share of this path's sums
     // The sum of dF/dz[row] over the lanes of the wave takes three hops through LDS, and they are spread over three
     // segments so that no hop waits for the one before it: after segment i the lanes publish their shares of row i
     // (a row of DS doubles per lane: the shares that belong to the wave-uniform increments are written, the shares a
@@ -225,7 +225,7 @@ __device__ __forceinline__ void run_bwd(const BwdArgs& a, double* lds)
         }
         if (flush && lane < DD) {
             acc[lane] = 0.0;
-            if (alone) grow[r2 * a.Dpad + lane] = v;
+            if constexpr (alone) grow[r2 * a.Dpad + lane] = v;
             else atomicAdd(&grow[r2 * a.Dpad + lane], v);
         }
         if (coll && lane < DD * P) atomicAdd(&acc[c], sum);
@@ -274,8 +274,7 @@ __device__ __forceinline__ void run_bwd(const BwdArgs& a, double* lds)
             for (int c = lane; c < D; c += kWave) {
                 const double v = acc[c];
                 acc[c] = 0.0;
-                if (alone) grow[row * a.Dpad + c] = v;
-                else atomicAdd(&grow[row * a.Dpad + c], v);
+                atomicAdd(&grow[row * a.Dpad + c], v);
             }
             __builtin_amdgcn_wave_barrier();
         }

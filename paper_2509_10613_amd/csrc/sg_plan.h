@@ -98,6 +98,8 @@ inline bool matrix_pays(int64_t VB, int64_t D, int N, int64_t segments, bool lea
 constexpr int64_t kMatrixCut = 160;    // fewest segments of a path that is cut for the matrix kernel
 constexpr int pieces_batch(int N) { return N <= 3 ? 4 : (N <= 5 ? 2 : 1); }   // pieces a lane of the product asks for at once
 // Forward, estimated us: a segment's latency, the launch of the product, and in it the latency of a batch and a piece's word
+constexpr int kSharedPiece = 40;
+constexpr double kSegmentBwd = 0.75, kSegmentMatrix = 0.35, kPieceWordBwd = 2.8e-5;   // backward, forward part included
 constexpr double kSegment = 0.2, kProduct = 4.0, kPieceLatency = 0.6, kPieceWord = 0.9e-5;
 constexpr int64_t kMatrixLong = 768, kMatrixPiece = 120, kMatrixPieceEntries = 100000;
 
@@ -121,6 +123,15 @@ inline SharedLds shared_lds(int PW, int d, int L, int64_t sig_len)
     const int pts = PW * s.stride + kSharedMaxD, sig = s.staged ? PW * (int)sig_len : 0;
     s.doubles = pts > sig ? pts : sig;
     return s;
+}
+
+// Backward, kernels for a channel count and a prefix length: whether a path's lanes are one wave's.
+constexpr bool lone_wave(int D, int S, int Q)
+{
+    if (Q > kQExact) return false;
+    int lanes = (D + S - 1) / S;
+    for (int i = 0; i < Q; ++i) lanes *= D;
+    return lanes <= kWave;
 }
 
 inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
@@ -292,24 +303,33 @@ inline Plan make_plan(int64_t B, int64_t L, int64_t d, int N, bool time_aug, boo
             }
             if (!choose(B)) return p;
         } else if (B > 0 && p.sig_len < ((int64_t)1 << 31)) {
-            // Backward: cut while that leaves at most four waves per SIMD, from half a wave per SIMD or less.  The matrix
+            // Backward: cut while that leaves at most four waves per SIMD, from less than half a wave per SIMD.  The matrix
             // kernel has more waves for the same words and takes a third of the time of the other per segment, so it cuts
-            // later.  1, 2, 4, ... pieces, in us, (B, L, d, N) = (100, 200, 4, 3), from 2: 115, 69, 44, 34; (200, 100, 3, 3): 71,
+            // later.  Waves of many paths have sums of as many paths per segment, and stop at one wave per SIMD, two with long pieces: (8000, 500, 2, 3),
+            // from 1: 285, 271, 221, 251; (3000, 200, 3, 2): 103, 101, 80, 82.  The others: 1, 2, 4, ... pieces, in us, (B, L, d, N) = (100, 200, 4, 3), from 2: 115, 69, 44, 34; (200, 100, 3, 3): 71,
             // 58, 38, 30; (500, 500, 3, 4), from 4: 156, 113, 109, 131; matrix kernel: (64, 1024, 6, 4), from 2: 283, 165, 139,
             // 128; (4, 1024, 8, 3), from 8: 72, 47, 36, 38; (64, 128, 12, 3): 44, 57, 46, 52.
-            auto pieces = [&](int64_t w1, int64_t few, int64_t want, int64_t least) {
+            // No further than twice as many save segments' time over what the words of their products take: (128, 256, 4, 6),
+            // whole and in 8 pieces, 170 and 274.
+            const double words = (double)B * ((double)(p.sig_len - 1) * (double)(D - 1) / (double)D + 1.0);
+            auto pieces = [&](int64_t w1, int64_t want, int64_t least, double segment) {
                 int q = 1;
-                if (w1 <= few)
-                    while (q < kMaxPieces && w1 * 2 * q <= want && p.n / (2 * q) >= least) q *= 2;
+                if (w1 < kSimds / 2)
+                    while (q < kMaxPieces && w1 * 2 * q <= want && p.n / (2 * q) >= least &&
+                           (double)p.n / (2 * q) * segment > q * words * kPieceWordBwd) q *= 2;
                 return q;
             };
             const int64_t w1 = p.PW > 1 ? (B + p.PW - 1) / p.PW : B * p.WP;
             if (may_matrix && matrix_pays(B, D, N, p.n, lead_lag)) {
-                if (p.n >= kMatrixCut) P = pieces(B * matrix_waves(D, N - 2, 1), kSimds / 2 - 1, 3 * kSimds, kMatrixSteps);
-                const int q = p.n >= kMatrixLong && p.sig_len < kMatrixPieceEntries ? pieces(w1, kSimds / 2 - 1, 2 * kSimds - 1, kMatrixPiece) : 1;
+                if (p.n >= kMatrixCut) P = pieces(B * matrix_waves(D, N - 2, 1), 3 * kSimds, kMatrixSteps, kSegmentMatrix);
+                const int q = p.n >= kMatrixLong && p.sig_len < kMatrixPieceEntries ? pieces(w1, 2 * kSimds - 1, kMatrixPiece, kSegmentMatrix) : 1;
                 if (q > P) P = q;
             } else if (p.n >= 4 * kMinPiece) {
-                P = pieces(w1, kSimds / 2, 4 * kSimds, kMinPiece);
+                P = pieces(w1, p.PW > 4 ? kSimds : 4 * kSimds, kMinPiece, kSegmentBwd);
+                if (p.PW > 4) {
+                    const int q = pieces(w1, 2 * kSimds, kSharedPiece, kSegmentBwd);
+                    if (q > P) P = q;
+                }
             }
         }
         if (P > 1) {

@@ -964,7 +964,7 @@ int run_signature_bwd(const sg::Plan& p, const sg::Plan& pf, const void* x, cons
     double* dz = reinterpret_cast<double*>(base + p.off_dz);
     double* gz = reinterpret_cast<double*>(base + p.off_gz);
     // (a wave that has a path to itself writes its sums, several waves add them to zeros)
-    const bool adds = p.matrix || p.WP > 1;
+    const bool adds = p.matrix || p.DT == 0 || !sg::lone_wave(p.DT, p.S, p.Q);
     SK_CHECK(sg::launch_increments<T>(static_cast<const T*>(x), dz, adds ? gz : nullptr, p.B, p.L, p.d, p.D, p.Dpad, p.n, p.P, p.Lc,
                                       p.np, (flags & SK_FLAG_TIME_AUG) ? 1 : 0, (flags & SK_FLAG_LEAD_LAG) ? 1 : 0, st));
     const int ttag = timing_tag();

@@ -13,7 +13,7 @@
 // What bounds it: the scratch, (1 + 2^(BL+1) - 1) doubles per block written and read once or twice each, and instruction
 // issue in the sweeps.  What it replaces looped over the channels of every block in memory, with an atomic addition per
 // block, channel and side (measured, both sides: in front of wide_pays in sk_plan.h).  At 59 x 106 pairs of 231 x 163 cells the
-// kernel moves about 24 GB through its scratch in 9.1 ms.
+// kernel moves about 24 GB through its scratch in 7.9 ms.
 //
 // Strips: strip s + 1 follows strip s at a fixed lag of macro-steps, one strip per wave, nw of them in a workgroup that
 // advances in chunks separated by barriers; strips beyond that take further rounds.  With enough pairs to fill the chip a
