@@ -77,13 +77,16 @@ _SWEEP = (sk.SK_FLAG_KEEP_FORWARD, sk.SK_FLAG_HAVE_FORWARD)
 _SWEEPS = (sk.SK_FLAG_KEEP_SWEEPS, sk.SK_FLAG_HAVE_SWEEPS)
 
 
-def _take_workspace(ctx):
+def _take_workspace(ctx, x, y):
     """The workspace the forward call kept, or None.  A large one is taken out of the graph: a further backward call through
-    it sweeps forward itself."""
+    it sweeps forward itself.  A call whose saved paths lie elsewhere than the forward call's (saved-tensor hooks and recomputed
+    checkpoints give equal tensors back) goes without: the library would take the sweeps for another call's."""
     ws = ctx.ws
-    if ws is not None and ws.numel() > _KEEP_LIMIT:
+    if ws is None:
+        return None
+    if ws.numel() > _KEEP_LIMIT:
         ctx.ws = None
-    return ws
+    return ws if ctx.at == (x.data_ptr(), y.data_ptr()) else None
 
 
 class _PairKernel(torch.autograd.Function):
@@ -93,6 +96,7 @@ class _PairKernel(torch.autograd.Function):
         y = y.contiguous()
         ctx.save_for_backward(x, y)
         ctx.args = (lam1, lam2, flags)
+        ctx.at = (x.data_ptr(), y.data_ptr())
         ctx.ws = None
         # Where the launch mode can hand its forward sweep to the backward call, this call keeps it in a workspace of
         # its own (the grid the paper's backward pass takes over from its forward pass, here as checkpoints).
@@ -116,7 +120,7 @@ class _PairKernel(torch.autograd.Function):
         want_x, want_y = ctx.needs_input_grad[0], ctx.needs_input_grad[1]
         if not (want_x or want_y):
             return None, None, None, None, None
-        ws = _take_workspace(ctx)
+        ws = _take_workspace(ctx, x, y)
         if ws is not None:
             _, gx, gy = sk.sigkernel_bwd(x, y, grad_k.contiguous(), lam1, lam2, flags | ctx.kept[1],
                                          want_x=want_x, want_y=want_y, ws=ws)
@@ -155,6 +159,7 @@ class _GramKernel(torch.autograd.Function):
         Y = Y.contiguous()
         ctx.save_for_backward(X, Y)
         ctx.args = (lam1, lam2, flags)
+        ctx.at = (X.data_ptr(), Y.data_ptr())
         ctx.ws = _gram_keep_workspace(ctx, X, Y, lam1, lam2, flags)
         if ctx.ws is not None:
             return sk.sigkernel_gram(X, Y, None, lam1, lam2, flags | ctx.kept[0], ws=ctx.ws)
@@ -164,7 +169,7 @@ class _GramKernel(torch.autograd.Function):
     def backward(ctx, grad_K):
         X, Y = ctx.saved_tensors
         lam1, lam2, flags = ctx.args
-        ws = _take_workspace(ctx)
+        ws = _take_workspace(ctx, X, Y)
         if ws is not None:
             _, gX, gY = sk.sigkernel_gram(X, Y, grad_K.contiguous(), lam1, lam2, flags | ctx.kept[1], ws=ws)
         else:
@@ -178,6 +183,7 @@ class _GramKernelSym(torch.autograd.Function):
         X = X.contiguous()
         ctx.save_for_backward(X)
         ctx.args = (lam1, lam2, flags)
+        ctx.at = (X.data_ptr(), X.data_ptr())
         ctx.ws = _gram_keep_workspace(ctx, X, X, lam1, lam2, flags, symmetric=True)
         if ctx.ws is not None:
             return sk.sigkernel_gram(X, X, None, lam1, lam2, flags | ctx.kept[0], ws=ctx.ws)
@@ -187,7 +193,7 @@ class _GramKernelSym(torch.autograd.Function):
     def backward(ctx, grad_K):
         (X,) = ctx.saved_tensors
         lam1, lam2, flags = ctx.args
-        ws = _take_workspace(ctx)
+        ws = _take_workspace(ctx, X, X)
         keep = ctx.kept[1] if ws is not None else 0
         _, gX, _ = sk.sigkernel_gram(X, X, grad_K.contiguous(), lam1, lam2, flags | keep, ws=ws)   # total derivative
         return gX, None, None, None

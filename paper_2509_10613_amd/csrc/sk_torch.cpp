@@ -107,6 +107,7 @@ struct KernelNode : public Node {
     int lam1 = 0, lam2 = 0, flags = 0, have = 0;
     size_t need = 0;
     Tensor ws;                       // the kept sweeps
+    const void *x_at = nullptr, *y_at = nullptr;   // the paths they belong to
     std::vector<int64_t> out_sizes;
     at::TensorOptions options;
 
@@ -123,8 +124,11 @@ struct KernelNode : public Node {
         if (!want_x && !want_y) return out;
         const Tensor x = x_.unpack(), y = symmetric ? x : y_.unpack();
         const Tensor g = grads[0].defined() ? grads[0].contiguous() : at::zeros(out_sizes, options);
-        const Tensor w = ws.defined() ? ws : bytes(need, x);
-        const int f = flags | (ws.defined() ? have : 0);
+        // (saved-tensor hooks and recomputed checkpoints give equal paths back at other addresses, which the library takes for
+        // another call's)
+        const bool kept = ws.defined() && x.data_ptr() == x_at && y.data_ptr() == y_at;
+        const Tensor w = kept ? ws : bytes(need, x);
+        const int f = flags | (kept ? have : 0);
         const sk_dtype dt = dtype_of(x);
         const int64_t N = x.size(0), M = y.size(0), L1 = x.size(1), L2 = y.size(1), d = x.size(2);
         // (a Gram call computes both sides)
@@ -281,6 +285,8 @@ Tensor kernel_call(const Tensor& x0, const Tensor& y0, bool gram, bool symmetric
         node->have = have;
         node->need = need_bwd;
         if (kept) node->ws = ws;
+        node->x_at = x.data_ptr();
+        node->y_at = y.data_ptr();
         node->out_sizes = k.sizes().vec();
         node->options = k.options();
         torch::autograd::set_history(k, node);

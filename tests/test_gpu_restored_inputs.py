@@ -1,0 +1,83 @@
+"""Backward calls whose saved inputs come back from elsewhere: autograd may hand a backward call equal tensors at other addresses
+(saved-tensor hooks that copy, recomputed checkpoints), and the sweeps a forward call has kept are then not taken over."""
+import pytest
+import torch
+from torch.utils.checkpoint import checkpoint
+
+from paper_2509_10613_amd import autograd as ska
+from paper_2509_10613_amd import binding as sk
+
+pytestmark = pytest.mark.gpu
+
+LL = sk.SK_FLAG_LEAD_LAG
+
+
+def paths(seed, n, L, d, dtype):
+    g = torch.Generator(device="cuda")
+    g.manual_seed(seed)
+    return ((torch.randn(n, L, d, generator=g, device="cuda", dtype=torch.float64) / (d * L) ** 0.5).cumsum(1)).to(dtype)
+
+
+def _pair(x, y, lam, flags):
+    return ska.sig_kernel(x, y, lam, lam, flags)
+
+
+def _gram(x, y, lam, flags):
+    return ska.sig_kernel_gram(x, y, lam, lam, flags)
+
+
+def _one_set(x, y, lam, flags):
+    return ska.sig_kernel_gram(x, None, lam, lam, flags)
+
+
+CLASSES = {_pair: lambda x, y, lam, flags: ska._PairKernel.apply(x, y, lam, lam, flags),
+           _gram: lambda x, y, lam, flags: ska._GramKernel.apply(x, y, lam, lam, flags),
+           _one_set: lambda x, y, lam, flags: ska._GramKernelSym.apply(x, lam, lam, flags)}
+
+# (wrapper, paths on either side, points, order, flags): few pairs keep both sweeps, the others the forward one (float: none)
+CALLS = {
+    "pairs": (_pair, 6, 6, 30, 1, 0),
+    "pairs, lead-lag": (_pair, 4, 4, 30, 0, LL | 1),
+    "pairs, bands": (_pair, 2, 2, 400, 0, 0),
+    "many pairs": (_pair, 300, 300, 70, 1, 0),
+    "gram": (_gram, 5, 7, 30, 1, 0),
+    "gram, lead-lag": (_gram, 40, 40, 60, 1, LL),
+    "gram of one set": (_one_set, 6, 6, 30, 1, 0),
+}
+HELD = []
+
+
+def _copying():
+    # (what the backward call gets lies elsewhere: the saved tensor itself is held)
+    return torch.autograd.graph.saved_tensors_hooks(lambda t: HELD.append(t) or t, lambda t: t.clone())
+
+
+@pytest.mark.parametrize("way", ["copies", "host", "checkpoint"])
+@pytest.mark.parametrize("native", [True, False], ids=["native", "classes"])
+@pytest.mark.parametrize("dtype", [torch.float64, torch.float32])
+@pytest.mark.parametrize("name", list(CALLS))
+def test_gradients_do_not_depend_on_where_saved_inputs_lie(name, dtype, native, way):
+    wrapper, n, m, L, lam, flags = CALLS[name]
+    call = wrapper if native else CLASSES[wrapper]
+    x, y = paths(11, n, L, 3, dtype).requires_grad_(), paths(12, m, L - 4, 3, dtype).requires_grad_()
+    wanted = (x,) if name == "gram of one set" else (x, y)
+
+    def loss(a, b):
+        k = call(a * 1.0, b * 1.0, lam, flags)          # (the saved inputs are the products)
+        return (k * torch.linspace(0.5, 1.5, k.numel(), device="cuda", dtype=dtype).reshape(k.shape)).sum()
+    ref = torch.autograd.grad(loss(x, y), wanted)
+    if way == "checkpoint":
+        out = checkpoint(loss, x, y, use_reentrant=False)
+    else:
+        with _copying() if way == "copies" else torch.autograd.graph.save_on_cpu():
+            out = loss(x, y)
+    block = [torch.full_like(t, 9.0) for t in (x, x, y, y)]     # (memory that the saved inputs may have lain in)
+    for again in (True, False):
+        got = torch.autograd.grad(out, wanted, retain_graph=again and way != "checkpoint")
+        tol = 1e-12 if dtype == torch.float64 else 1e-5
+        for g, r in zip(got, ref):
+            assert float((g - r).abs().max()) <= tol * max(1.0, float(r.abs().max()))
+        if way == "checkpoint":
+            break
+    HELD.clear()
+    del block
