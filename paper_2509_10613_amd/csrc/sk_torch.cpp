@@ -101,6 +101,15 @@ Need kernel_need(bool gram, bool symmetric, int64_t N, int64_t M, int64_t L1, in
 }
 
 // ---------------------------------------------------------------- graph nodes
+// A backward call's tensor (what a saved-tensor hook gave back, an upstream gradient) as the forward call knew it: the library
+// takes addresses.
+void expect(const Tensor& t, const char* name, at::IntArrayRef sizes, const at::TensorOptions& options)
+{
+    TORCH_CHECK_VALUE(t.is_cuda() && t.layout() == at::kStrided && t.is_contiguous(), name, " must be a contiguous device tensor");
+    TORCH_CHECK_VALUE(t.device() == options.device() && t.scalar_type() == c10::typeMetaToScalarType(options.dtype()) && t.sizes() == sizes,
+                      name, " is not what the forward call had: ", t.sizes(), " ", t.scalar_type(), " on ", t.device());
+}
+
 struct KernelNode : public Node {
     SavedVariable x_, y_;
     bool gram = false, symmetric = false, want_x = false, want_y = false;
@@ -108,7 +117,7 @@ struct KernelNode : public Node {
     size_t need = 0;
     Tensor ws;                       // the kept sweeps
     const void *x_at = nullptr, *y_at = nullptr;   // the paths they belong to
-    std::vector<int64_t> out_sizes;
+    std::vector<int64_t> x_sizes, y_sizes, out_sizes;
     at::TensorOptions options;
 
     std::string name() const override { return gram ? "SigKernelGramBackward" : "SigKernelPairBackward"; }
@@ -124,6 +133,9 @@ struct KernelNode : public Node {
         if (!want_x && !want_y) return out;
         const Tensor x = x_.unpack(), y = symmetric ? x : y_.unpack();
         const Tensor g = grads[0].defined() ? grads[0].contiguous() : at::zeros(out_sizes, options);
+        expect(x, "x", x_sizes, options);
+        if (!symmetric) expect(y, "y", y_sizes, options);
+        expect(g, "the upstream gradient", out_sizes, options);
         // (saved-tensor hooks and recomputed checkpoints give equal paths back at other addresses, which the library takes for
         // another call's)
         const bool kept = ws.defined() && x.data_ptr() == x_at && y.data_ptr() == y_at;
@@ -175,7 +187,7 @@ struct SignatureNode : public Node {
     SavedVariable x_, out_;
     int N = 0, flags = 0;
     size_t need = 0;
-    std::vector<int64_t> out_sizes;
+    std::vector<int64_t> x_sizes, out_sizes;
     at::TensorOptions options;
     std::string name() const override { return "SignatureBackward"; }
     void release_variables() override
@@ -187,6 +199,9 @@ struct SignatureNode : public Node {
     {
         const Tensor x = x_.unpack(), sig = out_.unpack(shared_from_this());
         const Tensor g = grads[0].defined() ? grads[0].contiguous() : at::zeros(out_sizes, options);
+        expect(x, "x", x_sizes, options);
+        expect(sig, "the signatures", out_sizes, options);
+        expect(g, "the upstream gradient", out_sizes, options);
         const Tensor gx = at::empty_like(x, at::MemoryFormat::Contiguous);
         const Tensor w = bytes(need, x);
         check(signature_bwd(x.data_ptr(), sig.data_ptr(), g.data_ptr(), gx.data_ptr(), x.size(0), x.size(1), x.size(2), N, flags,
@@ -287,6 +302,8 @@ Tensor kernel_call(const Tensor& x0, const Tensor& y0, bool gram, bool symmetric
         if (kept) node->ws = ws;
         node->x_at = x.data_ptr();
         node->y_at = y.data_ptr();
+        node->x_sizes = x.sizes().vec();
+        node->y_sizes = y.sizes().vec();
         node->out_sizes = k.sizes().vec();
         node->options = k.options();
         torch::autograd::set_history(k, node);
@@ -406,6 +423,7 @@ py::object signature(py::object xo, py::object No, py::object fl)
             node->N = N;
             node->flags = flags;
             node->need = need.backward;
+            node->x_sizes = x.sizes().vec();
             node->out_sizes = out.sizes().vec();
             node->options = out.options();
             torch::autograd::set_history(out, node);

@@ -81,3 +81,32 @@ def test_gradients_do_not_depend_on_where_saved_inputs_lie(name, dtype, native, 
             break
     HELD.clear()
     del block
+
+
+# what a hook may give back that is no place for a kernel to read the forward call's numbers from
+UNFIT = {"host": lambda t: t.cpu(), "strides": lambda t: t.transpose(0, -1).contiguous().transpose(0, -1), "type": lambda t: t.float(),
+         "points": lambda t: t[..., :-1].contiguous()}
+
+
+def _signature(x, y, lam, flags):
+    return ska.signature(x, 3)
+
+
+@pytest.mark.parametrize("unfit", list(UNFIT))
+@pytest.mark.parametrize("call", [_pair, _gram, _one_set, _signature])
+def test_saved_tensors_that_come_back_unfit_are_refused(call, unfit):
+    x, y = paths(13, 6, 30, 3, torch.float64).requires_grad_(), paths(14, 6, 30, 3, torch.float64)
+    with torch.autograd.graph.saved_tensors_hooks(lambda t: t, UNFIT[unfit]):
+        out = call(x, y, 1, 0)
+    with pytest.raises(ValueError):
+        out.sum().backward()
+    assert x.grad is None
+
+
+@pytest.mark.parametrize("call", [_pair, _gram, _one_set, _signature])
+def test_upstream_gradients_that_do_not_fit_are_refused(call):
+    x, y = paths(13, 6, 30, 3, torch.float64).requires_grad_(), paths(14, 6, 30, 3, torch.float64)
+    out = call(x, y, 1, 0)
+    for g in (torch.ones_like(out).cpu(), torch.ones_like(out).float(), torch.ones_like(out)[:-1]):
+        with pytest.raises(ValueError):
+            out.grad_fn(g)
