@@ -12,6 +12,7 @@
 #include <ATen/ATen.h>
 #include <c10/core/impl/LocalDispatchKeySet.h>
 #include <c10/hip/HIPStream.h>
+#include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/edge.h>
 #include <torch/csrc/autograd/function.h>
 #include <torch/csrc/autograd/functions/utils.h>
@@ -41,9 +42,16 @@ sk_dtype dtype_of(const Tensor& t) { return t.scalar_type() == at::kDouble ? SK_
 Tensor bytes(size_t n, const Tensor& like) { return at::empty({(int64_t)(n < 256 ? 256 : n)}, like.options().dtype(at::kByte)); }
 void* ptr(const Tensor& t) { return t.defined() ? t.data_ptr() : nullptr; }
 
+// (the exception that the classes raise)
 void check(int rc)
 {
-    if (rc != SK_OK) throw std::runtime_error(std::string("sigkernel error ") + std::to_string(rc) + ": " + sigkernel_last_error());
+    if (rc == SK_OK) return;
+    const std::string what = "sigkernel error " + std::to_string(rc) + ": " + sigkernel_last_error();
+    py::gil_scoped_acquire gil;
+    PyErr_SetString(py::module_::import("paper_2509_10613_amd.binding").attr("SigKernelError").ptr(), what.c_str());
+    python_error error;
+    error.persist();   // (it crosses from the engine's thread to the caller's)
+    throw error;
 }
 
 // ---------------------------------------------------------------- what a shape needs

@@ -110,3 +110,11 @@ def test_upstream_gradients_that_do_not_fit_are_refused(call):
     for g in (torch.ones_like(out).cpu(), torch.ones_like(out).float(), torch.ones_like(out)[:-1]):
         with pytest.raises(ValueError):
             out.grad_fn(g)
+
+
+def test_what_the_library_refuses_is_its_own_exception():
+    # 2000 channels have signatures but no gradients
+    x = paths(15, 2, 4, 2000, torch.float64).requires_grad_()
+    for out in (ska.signature(x, 1), ska._Signature.apply(x, 1, 0)):
+        with pytest.raises(sk.SigKernelError, match="1024 channels"):
+            out.sum().backward()
