@@ -25,6 +25,7 @@
 #include <array>
 #include <cstring>
 #include <memory>
+#include <mutex>
 #include <string>
 
 #include "sigkernel.h"
@@ -118,6 +119,9 @@ void expect(const Tensor& t, const char* name, at::IntArrayRef sizes, const at::
                       name, " is not what the forward call had: ", t.sizes(), " ", t.scalar_type(), " on ", t.device());
 }
 
+// (Threads may run backward calls through one node: what it holds is read and released under the node's lock.)
+using Lock = std::lock_guard<std::mutex>;
+
 struct KernelNode : public Node {
     SavedVariable x_, y_;
     bool gram = false, symmetric = false, want_x = false, want_y = false;
@@ -131,6 +135,7 @@ struct KernelNode : public Node {
     std::string name() const override { return gram ? "SigKernelGramBackward" : "SigKernelPairBackward"; }
     void release_variables() override
     {
+        const Lock lock(mutex_);
         x_.reset_data();
         y_.reset_data();
         ws.reset();
@@ -139,15 +144,21 @@ struct KernelNode : public Node {
     {
         variable_list out(symmetric ? 1 : 2);
         if (!want_x && !want_y) return out;
-        const Tensor x = x_.unpack(), y = symmetric ? x : y_.unpack();
+        Tensor x, y, held;
+        {
+            const Lock lock(mutex_);
+            x = x_.unpack();
+            y = symmetric ? x : y_.unpack();
+            held = ws;
+        }
         const Tensor g = grads[0].defined() ? grads[0].contiguous() : at::zeros(out_sizes, options);
         expect(x, "x", x_sizes, options);
         if (!symmetric) expect(y, "y", y_sizes, options);
         expect(g, "the upstream gradient", out_sizes, options);
         // (saved-tensor hooks and recomputed checkpoints give equal paths back at other addresses, which the library takes for
         // another call's)
-        const bool kept = ws.defined() && x.data_ptr() == x_at && y.data_ptr() == y_at;
-        const Tensor w = kept ? ws : bytes(need, x);
+        const bool kept = held.defined() && x.data_ptr() == x_at && y.data_ptr() == y_at;
+        const Tensor w = kept ? held : bytes(need, x);
         const int f = flags | (kept ? have : 0);
         const sk_dtype dt = dtype_of(x);
         const int64_t N = x.size(0), M = y.size(0), L1 = x.size(1), L2 = y.size(1), d = x.size(2);
@@ -174,6 +185,7 @@ struct MmdNode : public Node {
     std::string name() const override { return "SigMmd2Backward"; }
     void release_variables() override
     {
+        const Lock lock(mutex_);
         gx_.reset_data();
         gy_.reset_data();
     }
@@ -181,8 +193,11 @@ struct MmdNode : public Node {
     {
         variable_list out(2);
         Tensor gx, gy;
-        if (have_x) gx = gx_.unpack();
-        if (have_y) gy = gy_.unpack();
+        {
+            const Lock lock(mutex_);
+            if (have_x) gx = gx_.unpack();
+            if (have_y) gy = gy_.unpack();
+        }
         const Tensor& some = have_x ? gx : gy;
         const Tensor g = grads[0].defined() ? grads[0] : at::zeros({}, some.options());
         if (have_x) out[0] = gx * g;
@@ -200,12 +215,18 @@ struct SignatureNode : public Node {
     std::string name() const override { return "SignatureBackward"; }
     void release_variables() override
     {
+        const Lock lock(mutex_);
         x_.reset_data();
         out_.reset_data();
     }
     variable_list apply(variable_list&& grads) override
     {
-        const Tensor x = x_.unpack(), sig = out_.unpack(shared_from_this());
+        Tensor x, sig;
+        {
+            const Lock lock(mutex_);
+            x = x_.unpack();
+            sig = out_.unpack(shared_from_this());
+        }
         const Tensor g = grads[0].defined() ? grads[0].contiguous() : at::zeros(out_sizes, options);
         expect(x, "x", x_sizes, options);
         expect(sig, "the signatures", out_sizes, options);

@@ -1,5 +1,7 @@
 """The wrappers' native host path (csrc/sk_torch.cpp) against the torch.autograd.Function classes it stands for: the same values
 and gradients, the same calls taken and refused."""
+import threading
+
 import pytest
 import torch
 
@@ -107,3 +109,29 @@ def test_what_is_left_to_the_classes_or_refused():
     e = torch.empty((0, 5, 2), dtype=torch.float64, device="cuda", requires_grad=True)
     out = ska.sig_kernel(e, e.detach())
     assert out.shape == (0,) and torch.autograd.grad(out.sum(), e)[0].shape == (0, 5, 2)
+
+
+@pytest.mark.parametrize("call", [lambda x, y: ska.sig_kernel(x, y, 1, 1), lambda x, y: ska.sig_kernel_gram(x, y),
+                                  lambda x, y: ska.sig_mmd2(x, y), lambda x, y: ska.signature(x, 3)], ids=["pairs", "gram", "mmd", "signature"])
+def test_threads_that_run_backward_through_one_graph(call):
+    # each gets the gradient, or is told that another one has used the graph up
+    x, y = paths(7, 6, 24, 3).requires_grad_(), paths(8, 6, 24, 3)
+    ref = torch.autograd.grad(call(x, y).sum(), x)[0]
+
+    def one(loss, keep, got, gate):
+        gate.wait()
+        try:
+            got.append(torch.autograd.grad(loss, x, retain_graph=keep)[0])
+        except RuntimeError as e:
+            got.append(str(e))
+    for n in range(40):
+        loss, keep, got, gate = call(x, y).sum(), n % 2 == 0, [], threading.Barrier(4)
+        threads = [threading.Thread(target=one, args=(loss, keep, got, gate)) for _ in range(4)]
+        for t in threads:
+            t.start()
+        for t in threads:
+            t.join()
+        done = [g for g in got if not isinstance(g, str)]
+        assert len(got) == 4 and (len(done) == 4 if keep else len(done) >= 1)
+        assert all("second time" in g for g in got if isinstance(g, str))
+        assert all(float((g - ref).abs().max()) <= 1e-12 * float(ref.abs().max()) for g in done)
