@@ -97,8 +97,6 @@ int validate(int64_t nx, int64_t ny, int64_t L1, int64_t L2, int64_t d, int lam1
 }
 
 constexpr int kKeptFlags = SK_FLAG_KEEP_FORWARD | SK_FLAG_HAVE_FORWARD | SK_FLAG_KEEP_SWEEPS | SK_FLAG_HAVE_SWEEPS;
-// Internal bit beside the caller's flags: the plan whose scratch stays small (no wide mode).
-constexpr int kSmallScratch = 1 << 20;
 
 // The scratch of a call: the launch plan's, then (backward calls whose reverse sweep inverts Eq. (1)) that of the
 // launch that solves drifted pairs once more with the replay kernel.
@@ -113,15 +111,16 @@ struct Layout {
     bool ll = false;
 };
 
-// L1, L2, d, lam1, lam2 are the caller's.
+// L1, L2, d, lam1, lam2 are the caller's.  small: the plan whose scratch stays small (no wide mode).
 Layout make_layout(bool backward, bool gram, bool symmetric, int64_t nx, int64_t ny, int64_t L1, int64_t L2, int64_t d,
-                   int lam1, int lam2, int flags, int io_elem, bool uncompute, bool keep = false, bool split = false)
+                   int lam1, int lam2, int flags, int io_elem, bool uncompute, bool keep = false, bool split = false,
+                   bool small = false)
 {
     Layout l;
     l.ll = (flags & SK_FLAG_LEAD_LAG) != 0;
     if (l.ll) { lam1 += 1; lam2 += 1; }
     l.p = sk::make_plan(backward, gram, symmetric, nx, ny, L1, L2, d, lam1, lam2, io_elem, uncompute, keep, false, l.ll, true,
-                        !(flags & kSmallScratch), split);
+                        !small, split);
     l.total = l.p.total;
     if (l.p.valid && backward && l.p.uncompute && !l.p.wide && !l.p.split) {   // (those divide by nothing: no pair of theirs drifts)
         l.sc = sk::make_plan(true, gram, symmetric, nx, ny, L1, L2, d, lam1, lam2, io_elem, false, false, true, l.ll);
@@ -394,9 +393,9 @@ bool split_forward(const sk::Plan& pb, sk_dtype dt)
 
 int dispatch(bool backward, bool gram, const void* x, const void* y, void* k, const void* grad_k, void* grad_x,
              void* grad_y, int64_t nx, int64_t ny, int64_t L1, int64_t L2, int64_t d, int lam1, int lam2, int flags,
-             sk_dtype dt, void* ws, size_t ws_bytes, void* stream)
+             sk_dtype dt, void* ws, size_t ws_bytes, void* stream, bool small = false)
 {
-    int rc = validate(nx, ny, L1, L2, d, lam1, lam2, flags & ~kSmallScratch, (int)dt);
+    int rc = validate(nx, ny, L1, L2, d, lam1, lam2, flags, (int)dt);
     if (rc != SK_OK) return rc;
     const int64_t npairs = gram ? nx * ny : nx;
     if (npairs == 0 && !(gram && backward)) return SK_OK;
@@ -416,7 +415,7 @@ int dispatch(bool backward, bool gram, const void* x, const void* y, void* k, co
     rc = check_device();
     if (rc != SK_OK) return rc;
     Layout lay = make_layout(backward, gram, symmetric, nx, ny, L1, L2, d, lam1, lam2, flags, elem,
-                             !(flags & SK_FLAG_BWD_REPLAY));
+                             !(flags & SK_FLAG_BWD_REPLAY), false, false, small);
     if (!lay.p.valid) return fail(SK_ERR_SHAPE, "internal: plan invalid");
     if (!ws || (reinterpret_cast<uintptr_t>(ws) & 255) != 0)
         return fail(SK_ERR_WORKSPACE, "workspace pointer is NULL or not 256-byte aligned");
@@ -556,10 +555,10 @@ extern "C" int sigkernel_bwd_static(const void* x, const void* y, const void* gr
     int rc = validate(B, B, L1, L2, d, lam1, lam2, flags, (int)dt);
     if (rc != SK_OK) return rc;
     size_t need = B > 0 ? sigkernel_workspace_bytes(SK_OP_BWD, B, 0, L1, L2, d, lam1, lam2, flags, dt) : 0;
-    if (need > kStaticScratchBytes) {
-        flags |= kSmallScratch;
-        need = make_layout(true, false, false, B, B, L1, L2, d, lam1, lam2, flags, dt == SK_F64 ? 8 : 4, !(flags & SK_FLAG_BWD_REPLAY)).total;
-    }
+    const bool small = need > kStaticScratchBytes;
+    if (small)
+        need = make_layout(true, false, false, B, B, L1, L2, d, lam1, lam2, flags, dt == SK_F64 ? 8 : 4, !(flags & SK_FLAG_BWD_REPLAY),
+                           false, false, true).total;
     if (need > kStaticScratchBytes)
         return fail(SK_ERR_WORKSPACE, "this shape needs %zu bytes of scratch, sigkernel_bwd_static holds %zu per device; "
                     "use sigkernel_bwd with a workspace of the caller's", need, kStaticScratchBytes);
@@ -570,7 +569,7 @@ extern "C" int sigkernel_bwd_static(const void* x, const void* y, const void* gr
     // call that sweeps forward itself erases the signature of a kept sweep: nothing of the previous call's contents
     // is read before it is written.
     return dispatch(true, false, x, y, k_out, grad_k, grad_x, grad_y, B, B, L1, L2, d, lam1, lam2, flags, dt, ptr,
-                    kStaticScratchBytes, stream);
+                    kStaticScratchBytes, stream, small);
 }
 
 // Layout of the scratch of sigkernel_mmd2: the three Gram matrices, their constant upstream weights, the second

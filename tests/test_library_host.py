@@ -55,6 +55,20 @@ def test_argument_validation_needs_no_gpu(lib):
     assert f(None, None, None, 0, 8, 8, 2, 0, 0, 0, 1, None, 0, None) == 0
 
 
+def test_flag_bits_without_a_meaning_are_refused_by_every_entry_point(lib):
+    one, f64 = C.c_void_p(256), binding.SK_F64
+    known = {v for k, v in vars(binding).items() if k.startswith("SK_FLAG_")}
+    for bit in (1 << n for n in range(31)):
+        if bit in known:
+            continue
+        assert lib.sigkernel_workspace_bytes(binding.SK_OP_BWD, 4, 0, 8, 8, 2, 0, 0, bit, f64) == 0, hex(bit)
+        assert lib.sigkernel_fwd(one, one, one, 4, 8, 8, 2, 0, 0, bit, f64, one, 1 << 30, None) == -4, hex(bit)
+        assert lib.sigkernel_bwd(one, one, one, one, one, one, 4, 8, 8, 2, 0, 0, bit, f64, one, 1 << 30, None) == -4, hex(bit)
+        assert lib.sigkernel_bwd_static(one, one, one, one, one, one, 4, 8, 8, 2, 0, 0, bit, f64, None) == -4, hex(bit)
+        assert lib.sigkernel_gram(one, one, one, None, None, None, 4, 4, 8, 8, 2, 0, 0, bit, f64, one, 1 << 30, None) == -4, hex(bit)
+        assert lib.sigkernel_mmd2(one, C.c_void_p(512), one, None, None, 4, 4, 8, 8, 2, 0, 0, bit, f64, one, 1 << 30, None) == -4, hex(bit)
+
+
 def test_workspace_query(lib):
     q = binding.sigkernel_workspace_bytes
     f64 = binding.SK_F64
