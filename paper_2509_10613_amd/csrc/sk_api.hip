@@ -617,10 +617,8 @@ LaunchNames launch_names(const sk::Plan& p, bool backward, int phase, bool time)
         else std::snprintf(l.kernel, sizeof(l.kernel), "tile_fwd_kernel<%d>", p.DT / 4);
         l.threads = sk::kWavesPerWG * sk::kWave;
     } else if (p.wide) {
-        l.mode = p.nw > 1 ? "cooperative" : "wave-per-pair";
-        if (backward) std::snprintf(l.kernel, sizeof(l.kernel), "wide_bwd_kernel<%d, %d>", p.BL, p.ll == 1 ? 1 : 0);
-        else if (p.ll == 1) std::snprintf(l.kernel, sizeof(l.kernel), "wide_ll_fwd_kernel<%d>", p.BL);
-        else std::snprintf(l.kernel, sizeof(l.kernel), "sweep_fwd_kernel<%d, 0, false>", p.BL);
+        l.mode = "wide";
+        std::snprintf(l.kernel, sizeof(l.kernel), "wide_%s_kernel<%d, %d>", backward ? "bwd" : "fwd", p.BL, p.ll == 1 ? 1 : 0);
         l.threads = p.nw * sk::kWave;
     } else if (p.four) {
         l.mode = "four";
@@ -645,7 +643,7 @@ LaunchNames launch_names(const sk::Plan& p, bool backward, int phase, bool time)
     } else {
         const char* base = !backward ? "sweep_fwd" : (p.uncompute ? "sweep_bwdu" : "sweep_bwd");
         l.mode = p.coop ? "cooperative" : "wave-per-pair";
-        std::snprintf(l.kernel, sizeof(l.kernel), "%s%s_kernel<%d, %d, %s>", base, p.coop ? "_coop" : "", p.BL, p.DT ? p.DT : -1,
+        std::snprintf(l.kernel, sizeof(l.kernel), "%s%s_kernel<%d, %d, %s>", base, p.coop ? "_coop" : "", p.BL, p.DT,
                       (p.y_lds && p.DT) ? "true" : "false");
         l.threads = (p.coop ? p.nw : sk::kWavesPerWG) * sk::kWave;
     }

@@ -2147,7 +2147,7 @@ hipError_t launch_sweep_bl(bool backward, int DT, bool ylds, const SweepArgs& a,
 {
     switch (DT) {
 #ifndef SK_ONLY_C2   /* development builds instantiate a single shape */
-        case 0: return launch_sweep_y<BL, -1>(backward, ylds, a, grid, lds, st);
+        case 0: return launch_sweep_y<BL, 0>(backward, ylds, a, grid, lds, st);
         case 2: return launch_sweep_y<BL, 2>(backward, ylds, a, grid, lds, st);
         case 3: return launch_sweep_y<BL, 3>(backward, ylds, a, grid, lds, st);
         case 4: return launch_sweep_y<BL, 4>(backward, ylds, a, grid, lds, st);

@@ -19,7 +19,7 @@ constexpr int kNumCU = 256;
 constexpr int kMaxBL = 2;
 
 // Channel counts with a dedicated kernel instantiation (increments kept in registers).  (More: the wide kernels, or, where
-// their scratch is too much, the sweep kernels with a run-time loop over the channels, template argument -1.)
+// their scratch is too much, the sweep kernels with a run-time loop over the channels, template argument 0.)
 constexpr int kTemplD[] = {2, 3, 4, 5, 6, 8, 16};
 
 inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }

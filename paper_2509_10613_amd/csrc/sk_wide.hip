@@ -217,18 +217,8 @@ __device__ __forceinline__ void wide_fwd(const SweepArgs& a)
     }
 }
 
-// The forward kernels are the run-time channel count of the sweep kernels' template (a lead-lag level inside the blocks has
-// kernels of its own).
-template <int BL, int D, bool YLDS>
-__global__ void sweep_fwd_kernel(SweepArgs a);
-template <>
-__global__ __launch_bounds__(kWideMaxWaves* kWave, 2) void sweep_fwd_kernel<0, 0, false>(SweepArgs a) { wide_fwd<0, 0>(a); }
-template <>
-__global__ __launch_bounds__(kWideMaxWaves* kWave, 2) void sweep_fwd_kernel<1, 0, false>(SweepArgs a) { wide_fwd<1, 0>(a); }
-template <>
-__global__ __launch_bounds__(kWideMaxWaves* kWave, 2) void sweep_fwd_kernel<2, 0, false>(SweepArgs a) { wide_fwd<2, 0>(a); }
-template <int BL>
-__global__ __launch_bounds__(kWideMaxWaves* kWave, 2) void wide_ll_fwd_kernel(SweepArgs a) { wide_fwd<BL, 1>(a); }
+template <int BL, int LL>
+__global__ __launch_bounds__(kWideMaxWaves* kWave, 2) void wide_fwd_kernel(SweepArgs a) { wide_fwd<BL, LL>(a); }
 
 // ------------------------------------------------------------------------------------------------
 // backward: forward sweep with the blocks' edges stored, reverse sweep, linear map
@@ -546,8 +536,7 @@ static hipError_t launch_wide_t(bool backward, const SweepArgs& a, int grid, hip
 {
     const dim3 block((unsigned)a.nw * kWave);
     if (backward) hipLaunchKernelGGL((wide_bwd_kernel<BL, LL>), dim3((unsigned)grid), block, 0, st, a);
-    else if constexpr (LL == 1) hipLaunchKernelGGL((wide_ll_fwd_kernel<BL>), dim3((unsigned)grid), block, 0, st, a);
-    else hipLaunchKernelGGL((sweep_fwd_kernel<BL, 0, false>), dim3((unsigned)grid), block, 0, st, a);
+    else hipLaunchKernelGGL((wide_fwd_kernel<BL, LL>), dim3((unsigned)grid), block, 0, st, a);
     return hipGetLastError();
 }
 

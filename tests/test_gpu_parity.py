@@ -532,9 +532,12 @@ def test_lead_lag_checkerboard_form_with_large_increments(lam, flags):
     (1100, 140, 20, 3, 0, LL | 1, torch.float64, "wave-per-pair"),
     (1100, 70, 20, 5, 1, LL, torch.float64, "wave-per-pair"),
     (1100, 40, 12, 5, 2, LL | 1, torch.float32, "wave-per-pair"),
-    (40, 200, 40, 20, 0, LL | 1, torch.float64, "cooperative"),     # more than 16 channels: the run-time channel loop
-    (40, 100, 40, 16, 1, LL, torch.float64, "cooperative"),
-    (40, 100, 40, 16, 2, LL | 1, torch.float64, "cooperative"),
+    (600, 200, 40, 5, 0, LL | 1, torch.float64, "cooperative"),
+    (600, 70, 20, 5, 1, LL, torch.float64, "cooperative"),
+    (600, 40, 12, 5, 2, LL | 1, torch.float64, "cooperative"),
+    (40, 200, 40, 20, 0, LL | 1, torch.float64, "wide"),            # more than 16 channels
+    (40, 100, 40, 16, 1, LL, torch.float64, "wide"),
+    (40, 100, 40, 16, 2, LL | 1, torch.float64, "wide"),
 ])
 @pytest.mark.parametrize("big", [0.0, 2.2])
 def test_lead_lag_checkerboard_form_few_pairs(B, L1, L2, d, lam, flags, dtype, mode, big):
@@ -1356,7 +1359,8 @@ def test_default_backward_is_exact_for_large_increments(scale):
                                                   (1300, 40, 44, 16, 0, "tile"),
                                                   (3, 400, 330, 3, 0, "band"),
                                                   (1100, 140, 20, 3, 0, "wave-per-pair"),
-                                                  (40, 200, 40, 20, 0, "cooperative")])
+                                                  (300, 140, 20, 3, 0, "cooperative"),
+                                                  (40, 200, 40, 20, 0, "wide")])
 @pytest.mark.parametrize("where", ["first columns", "last rows", "one pair"])
 def test_large_increments_in_every_launch_mode(B, L1, L2, d, lam, mode, where):
     # Increments of order one in a few places of otherwise benign paths: in the first columns (the stretch left of the

@@ -190,9 +190,16 @@ def test_launch_plan_of_the_five_configurations(lib):
     # many pairs of longer paths (more than 128 block rows): strips chained through global rows
     p = _plan(binding.SK_OP_BWD, 4096, 0, 300, 300, 4, 0, 0, 0, f64)
     assert p["mode"] == "wave-per-pair" and p["kernel"].startswith("sweep_bwdu_kernel<0, 4,") and p["strips"] == "5"
-    # more than 16 channels: runtime channel loop, y increments in global memory
+    # more than 16 channels: p of every block by matrix instructions into scratch; a workgroup is one wave where the pairs
+    # fill the chip, and its strips' waves where they do not
     p = _plan(binding.SK_OP_FWD, 4096, 0, 40, 40, 20, 1, 1, 0, f64)
-    assert p["mode"] == "wave-per-pair" and p["kernel"] == "sweep_fwd_kernel<1, 0, false>"
+    assert p["mode"] == "wide" and p["kernel"] == "wide_fwd_kernel<1, 0>" and p["threads"] == "64" and p["grid"] == "4096"
+    p = _plan(binding.SK_OP_BWD, 40, 0, 200, 40, 20, 0, 0, 0, f64)
+    assert p["mode"] == "wide" and p["kernel"] == "wide_bwd_kernel<0, 0>" and p["threads"] == "256" and p["grid"] == "40"
+    assert _plan(binding.SK_OP_FWD, 40, 0, 200, 40, 20, 0, 0, binding.SK_FLAG_LEAD_LAG, f64)["kernel"] == "wide_fwd_kernel<1, 1>"
+    # the variant that replays has the run-time channel loop
+    p = _plan(binding.SK_OP_BWD, 40, 0, 200, 40, 20, 0, 0, binding.SK_FLAG_BWD_REPLAY, f64)
+    assert p["mode"] == "cooperative" and p["kernel"] == "sweep_bwd_coop_kernel<0, 0, false>"
     # c4 (32 pairs, 2047 block rows = 32 strips each): bands of four strips on different compute units, eight
     # bands per pair, all 256 workgroups resident at once; four strip waves and a data-moving wave each
     p = _plan(binding.SK_OP_BWD, 32, 0, 2048, 2048, 8, 2, 2, 0, f64)
