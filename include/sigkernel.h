@@ -77,7 +77,7 @@ enum {
     SK_ERR_SHAPE = -2,     /* L < 1, d < 1, negative batch, or (L-1) << lam does not fit in 31 bits */
     SK_ERR_DYADIC = -3,    /* lam1 or lam2 negative or above 20 */
     SK_ERR_DTYPE = -4,     /* dt is neither SK_F32 nor SK_F64; unknown flag bits */
-    SK_ERR_WORKSPACE = -5, /* ws is NULL, misaligned or smaller than the query says */
+    SK_ERR_WORKSPACE = -5, /* ws is NULL, misaligned or smaller than the least the query says */
     SK_ERR_HIP = -6        /* a HIP runtime call failed (message has the HIP error string) */
 };
 
@@ -91,6 +91,14 @@ enum { SK_OP_FWD = 0, SK_OP_BWD = 1, SK_OP_GRAM = 2, SK_OP_GRAM_BWD = 3 };
  */
 size_t sigkernel_workspace_bytes(int op, int64_t B_or_N, int64_t M, int64_t L1, int64_t L2, int64_t d,
                                  int lam1, int lam2, int flags, sk_dtype dt);
+
+/*
+ * The least the operation takes: no more than the above, and less where its scratch grows with the workgroups at work (more
+ * than sixteen channels, and backward calls for long paths: up to 8 GiB).  With a workspace in between, the call launches as many
+ * workgroups as that has room for, or other kernels; with less it returns SK_ERR_WORKSPACE.
+ */
+size_t sigkernel_workspace_least_bytes(int op, int64_t B_or_N, int64_t M, int64_t L1, int64_t L2, int64_t d,
+                                       int lam1, int lam2, int flags, sk_dtype dt);
 
 /*
  * Forward over a batch of pairs (Algorithm "CPU Algorithm for Signature Kernels", Eq. (1)):
@@ -150,7 +158,7 @@ int sigkernel_bwd(const void* x, const void* y, const void* grad_k, void* grad_x
  * harnesses that forbid hipMalloc) and have no workspace to hand in: the same operation, arguments and results as
  * sigkernel_bwd, with the scratch taken from an array of SK_STATIC_SCRATCH_BYTES bytes that is part of the library
  * (one copy per GPU, held until the process ends).  The call allocates and frees nothing.
- *  - Shapes whose sigkernel_workspace_bytes(SK_OP_BWD, ...) exceeds SK_STATIC_SCRATCH_BYTES are refused with
+ *  - Shapes whose sigkernel_workspace_least_bytes(SK_OP_BWD, ...) exceeds SK_STATIC_SCRATCH_BYTES are refused with
  *    SK_ERR_WORKSPACE (configuration-2-sized batches fit: 128 pairs of 256 points at dyadic order 1).
  *  - The flags of kept sweeps are refused (SK_ERR_DTYPE): the scratch belongs to no caller.
  *  - Every call on a GPU uses that GPU's one array: calls that overlap on one GPU (two streams, two threads) race.
@@ -189,6 +197,8 @@ int sigkernel_gram(const void* X, const void* Y, void* K, const void* grad_K, vo
  */
 size_t sigkernel_mmd2_workspace_bytes(int64_t N, int64_t M, int64_t L1, int64_t L2, int64_t d, int lam1, int lam2,
                                       int flags, sk_dtype dt, int with_grads);
+size_t sigkernel_mmd2_workspace_least_bytes(int64_t N, int64_t M, int64_t L1, int64_t L2, int64_t d, int lam1, int lam2,
+                                            int flags, sk_dtype dt, int with_grads);   /* as sigkernel_workspace_least_bytes */
 int sigkernel_mmd2(const void* X, const void* Y, void* loss, void* grad_X, void* grad_Y, int64_t N, int64_t M,
                    int64_t L1, int64_t L2, int64_t d, int lam1, int lam2, int flags, sk_dtype dt, void* ws,
                    size_t ws_bytes, void* stream);

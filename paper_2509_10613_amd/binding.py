@@ -41,9 +41,9 @@ def SK_SIG_DEPTH(m):
     return (m + 1) << 8
 
 
-EXPORTS = ["sigkernel_workspace_bytes", "sigkernel_fwd", "sigkernel_bwd", "sigkernel_bwd_static", "sigkernel_gram",
-           "sigkernel_describe",
-           "sigkernel_mmd2", "sigkernel_mmd2_workspace_bytes",
+EXPORTS = ["sigkernel_workspace_bytes", "sigkernel_workspace_least_bytes", "sigkernel_fwd", "sigkernel_bwd",
+           "sigkernel_bwd_static", "sigkernel_gram", "sigkernel_describe",
+           "sigkernel_mmd2", "sigkernel_mmd2_workspace_bytes", "sigkernel_mmd2_workspace_least_bytes",
            "sigkernel_event_timing", "sigkernel_event_timing_read", "sigkernel_event_timing_read_tag", "sigkernel_last_error", "sigkernel_version",
            "signature_length", "signature_workspace_bytes", "signature_fwd", "signature_describe",
            "signature_bwd_workspace_bytes", "signature_bwd", "signature_bwd_describe"]
@@ -66,8 +66,9 @@ def load():
                              % LIB_PATH)
     lib = C.CDLL(LIB_PATH)
     i64, vp, ci = C.c_int64, C.c_void_p, C.c_int
-    lib.sigkernel_workspace_bytes.restype = C.c_size_t
-    lib.sigkernel_workspace_bytes.argtypes = [ci, i64, i64, i64, i64, i64, ci, ci, ci, ci]
+    for f in (lib.sigkernel_workspace_bytes, lib.sigkernel_workspace_least_bytes):
+        f.restype = C.c_size_t
+        f.argtypes = [ci, i64, i64, i64, i64, i64, ci, ci, ci, ci]
     lib.sigkernel_describe.restype = ci
     lib.sigkernel_describe.argtypes = [ci, i64, i64, i64, i64, i64, ci, ci, ci, ci, C.c_char_p, C.c_size_t]
     lib.sigkernel_fwd.restype = ci
@@ -79,8 +80,9 @@ def load():
     lib.sigkernel_gram.restype = ci
     lib.sigkernel_gram.argtypes = [vp, vp, vp, vp, vp, vp, i64, i64, i64, i64, i64, ci, ci, ci, ci, vp, C.c_size_t,
                                    vp]
-    lib.sigkernel_mmd2_workspace_bytes.restype = C.c_size_t
-    lib.sigkernel_mmd2_workspace_bytes.argtypes = [i64, i64, i64, i64, i64, ci, ci, ci, ci, ci]
+    for f in (lib.sigkernel_mmd2_workspace_bytes, lib.sigkernel_mmd2_workspace_least_bytes):
+        f.restype = C.c_size_t
+        f.argtypes = [i64, i64, i64, i64, i64, ci, ci, ci, ci, ci]
     lib.sigkernel_mmd2.restype = ci
     lib.sigkernel_mmd2.argtypes = [vp, vp, vp, vp, vp, i64, i64, i64, i64, i64, ci, ci, ci, ci, vp, C.c_size_t, vp]
     lib.sigkernel_event_timing.restype = ci
@@ -142,6 +144,10 @@ def sigkernel_workspace_bytes(op, B_or_N, M, L1, L2, d, lam1, lam2, flags, dt):
     return int(load().sigkernel_workspace_bytes(op, B_or_N, M, L1, L2, d, lam1, lam2, flags, dt))
 
 
+def sigkernel_workspace_least_bytes(op, B_or_N, M, L1, L2, d, lam1, lam2, flags, dt):
+    return int(load().sigkernel_workspace_least_bytes(op, B_or_N, M, L1, L2, d, lam1, lam2, flags, dt))
+
+
 def sigkernel_describe(op, B_or_N, M, L1, L2, d, lam1, lam2, flags, dt):
     """The launch the library would make for this operation and shape, as 'key=value' text (no GPU call)."""
     buf = C.create_string_buffer(1024)
@@ -166,15 +172,31 @@ def sigkernel_event_timing_read(tag=0):
 _ws_cache = {}
 
 
-def workspace(nbytes, device):
+def workspace(nbytes, device, least=None):
     """A cached, 256-byte aligned scratch tensor of at least nbytes on `device` for calls on the current stream
-    (grown on demand; one per device and stream: calls that share a workspace must be ordered)."""
+    (grown on demand; one per device and stream: calls that share a workspace must be ordered).  Where the device has no
+    room for it, half of it and so on down to least(), the least the call takes."""
     key = (str(device), torch.cuda.current_stream(device).cuda_stream)
     t = _ws_cache.get(key)
-    if t is None or t.numel() < nbytes:
-        t = torch.empty(max(int(nbytes), 256), dtype=torch.uint8, device=device)
-        _ws_cache[key] = t
-    return t
+    if t is not None and t.numel() >= nbytes:
+        return t
+    size, few = max(int(nbytes), 256), None
+    while True:
+        try:
+            _ws_cache[key] = torch.empty(size, dtype=torch.uint8, device=device)
+            return _ws_cache[key]
+        except torch.OutOfMemoryError:
+            if few is None:
+                few = max(least(), 256) if least else size
+            if t is not None:
+                if t.numel() >= max(size // 2, few):
+                    return t
+                t = None                # (gives the smaller one back)
+                del _ws_cache[key]
+            elif size <= few:
+                raise
+            else:
+                size = max(size // 2, few)
 
 
 def keeps_forward(B, L1, L2, d, lam1, lam2, flags, dt, gram_M=None):
@@ -208,9 +230,9 @@ def sigkernel_fwd(x, y, lam1=0, lam2=0, flags=0, k=None, ws=None):
     dt = _dt(x)
     if k is None:
         k = torch.empty((B,), dtype=x.dtype, device=x.device)
-    need = sigkernel_workspace_bytes(SK_OP_FWD, B, 0, L1, L2, d, lam1, lam2, flags, dt)
+    shape = (SK_OP_FWD, B, 0, L1, L2, d, lam1, lam2, flags, dt)
     if ws is None:
-        ws = workspace(need, x.device)
+        ws = workspace(sigkernel_workspace_bytes(*shape), x.device, lambda: sigkernel_workspace_least_bytes(*shape))
     _check(load().sigkernel_fwd(_ptr(x), _ptr(y), _ptr(k), B, L1, L2, d, lam1, lam2, flags, dt, _ptr(ws),
                                 ws.numel(), _stream()))
     return k
@@ -230,9 +252,9 @@ def sigkernel_bwd(x, y, grad_k, lam1=0, lam2=0, flags=0, grad_x=None, grad_y=Non
         grad_y = torch.empty_like(y)
     if k_out is None:
         k_out = torch.empty((B,), dtype=x.dtype, device=x.device)
-    need = sigkernel_workspace_bytes(SK_OP_BWD, B, 0, L1, L2, d, lam1, lam2, flags, dt)
+    shape = (SK_OP_BWD, B, 0, L1, L2, d, lam1, lam2, flags, dt)
     if ws is None:
-        ws = workspace(need, x.device)
+        ws = workspace(sigkernel_workspace_bytes(*shape), x.device, lambda: sigkernel_workspace_least_bytes(*shape))
     _check(load().sigkernel_bwd(_ptr(x), _ptr(y), _ptr(grad_k), _ptr(grad_x), _ptr(grad_y), _ptr(k_out), B, L1, L2,
                                 d, lam1, lam2, flags, dt, _ptr(ws), ws.numel(), _stream()))
     return k_out, grad_x, grad_y
@@ -271,10 +293,9 @@ def sigkernel_gram(X, Y, grad_K=None, lam1=0, lam2=0, flags=0, K=None, grad_X=No
             grad_X = torch.empty_like(X)
         if grad_Y is None and not sym:
             grad_Y = torch.empty_like(Y)
-    need = sigkernel_workspace_bytes(SK_OP_GRAM_BWD if backward else SK_OP_GRAM, N, M, L1, L2, d, lam1, lam2, flags,
-                                     dt)
+    shape = (SK_OP_GRAM_BWD if backward else SK_OP_GRAM, N, M, L1, L2, d, lam1, lam2, flags, dt)
     if ws is None:
-        ws = workspace(need, X.device)
+        ws = workspace(sigkernel_workspace_bytes(*shape), X.device, lambda: sigkernel_workspace_least_bytes(*shape))
     _check(load().sigkernel_gram(_ptr(X), _ptr(Y), _ptr(K), _ptr(grad_K), _ptr(grad_X), _ptr(grad_Y), N, M, L1, L2,
                                  d, lam1, lam2, flags, dt, _ptr(ws), ws.numel(), _stream()))
     if backward:
@@ -293,9 +314,10 @@ def sigkernel_mmd2(X, Y, lam1=0, lam2=0, flags=0, want_x=True, want_y=True, ws=N
     loss = torch.empty((1,), dtype=X.dtype, device=X.device)
     gX = torch.empty_like(X) if want_x else None
     gY = torch.empty_like(Y) if want_y else None
-    need = int(load().sigkernel_mmd2_workspace_bytes(N, M, L1, L2, d, lam1, lam2, flags, dt, 1 if (want_x or want_y) else 0))
+    shape = (N, M, L1, L2, d, lam1, lam2, flags, dt, 1 if (want_x or want_y) else 0)
     if ws is None:
-        ws = workspace(need, X.device)
+        ws = workspace(int(load().sigkernel_mmd2_workspace_bytes(*shape)), X.device,
+                       lambda: int(load().sigkernel_mmd2_workspace_least_bytes(*shape)))
     _check(load().sigkernel_mmd2(_ptr(X), _ptr(Y), _ptr(loss), _ptr(gX), _ptr(gY), N, M, L1, L2, d, lam1, lam2, flags,
                                  dt, _ptr(ws), ws.numel(), _stream()))
     return loss, gX, gY

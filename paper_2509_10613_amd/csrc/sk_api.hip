@@ -111,16 +111,16 @@ struct Layout {
     bool ll = false;
 };
 
-// L1, L2, d, lam1, lam2 are the caller's.  small: the plan whose scratch stays small (no wide mode).
+// L1, L2, d, lam1, lam2 are the caller's.  wide_scratch: as in make_plan.
 Layout make_layout(bool backward, bool gram, bool symmetric, int64_t nx, int64_t ny, int64_t L1, int64_t L2, int64_t d,
                    int lam1, int lam2, int flags, int io_elem, bool uncompute, bool keep = false, bool split = false,
-                   bool small = false)
+                   size_t wide_scratch = sk::kWideScratch)
 {
     Layout l;
     l.ll = (flags & SK_FLAG_LEAD_LAG) != 0;
     if (l.ll) { lam1 += 1; lam2 += 1; }
     l.p = sk::make_plan(backward, gram, symmetric, nx, ny, L1, L2, d, lam1, lam2, io_elem, uncompute, keep, false, l.ll, true,
-                        !small, split);
+                        wide_scratch, split);
     l.total = l.p.total;
     if (l.p.valid && backward && l.p.uncompute && !l.p.wide && !l.p.split) {   // (those divide by nothing: no pair of theirs drifts)
         l.sc = sk::make_plan(true, gram, symmetric, nx, ny, L1, L2, d, lam1, lam2, io_elem, false, false, true, l.ll);
@@ -391,9 +391,62 @@ bool split_forward(const sk::Plan& pb, sk_dtype dt)
     return pb.band || (pb.lock && dt == SK_F64);
 }
 
+// Layout of a call (without kept sweeps) in a workspace of ws_bytes: wide mode takes fewer workgroups, or leaves the call to
+// the kernels that need less, where the workspace has no room for all of its scratch.  Every other plan needs what it needs.
+Layout fit_layout(bool backward, bool gram, bool symmetric, int64_t nx, int64_t ny, int64_t L1, int64_t L2, int64_t d, int lam1,
+                  int lam2, int flags, int io_elem, size_t ws_bytes)
+{
+    size_t scratch = sk::kWideScratch;
+    for (;;) {
+        const Layout l = make_layout(backward, gram, symmetric, nx, ny, L1, L2, d, lam1, lam2, flags, io_elem,
+                                     !(flags & SK_FLAG_BWD_REPLAY), false, false, scratch);
+        if (!l.p.valid || !l.p.wide || l.total <= ws_bytes) return l;
+        const size_t slot = (size_t)l.p.wd_slot * l.p.elem, per = slot + (size_t)l.p.rows_slot * l.p.elem;
+        const int64_t fewer = (int64_t)((l.total - ws_bytes + per - 1) / per);
+        scratch = fewer < l.p.grid ? (size_t)(l.p.grid - fewer) * slot : 0;
+    }
+}
+
+// Bytes of an operation's workspace; least: the least that fit_layout finds a plan for.
+size_t op_bytes(int op, int64_t B_or_N, int64_t M, int64_t L1, int64_t L2, int64_t d, int lam1, int lam2, int flags, sk_dtype dt,
+                bool least)
+{
+    const bool gram = op == SK_OP_GRAM || op == SK_OP_GRAM_BWD;
+    // a forward call that keeps its sweep works in the backward call's workspace
+    const bool fwd_op = op == SK_OP_FWD || op == SK_OP_GRAM;
+    const bool kept = (flags & (fwd_op ? SK_FLAG_KEEP_FORWARD : SK_FLAG_HAVE_FORWARD)) != 0;
+    const bool both = (flags & (fwd_op ? SK_FLAG_KEEP_SWEEPS : SK_FLAG_HAVE_SWEEPS)) != 0;
+    const bool backward = !fwd_op || kept;
+    if (op < SK_OP_FWD || op > SK_OP_GRAM_BWD) return 0;
+    const int64_t ny = gram ? M : B_or_N;
+    if (validate(B_or_N, ny, L1, L2, d, lam1, lam2, flags, (int)dt) != SK_OK) return 0;
+    auto total = [&](bool symmetric) {
+        auto layout = [&](bool split, size_t wide_scratch) {
+            return make_layout(split || backward, gram, symmetric, B_or_N, ny, L1, L2, d, lam1, lam2, flags, dt == SK_F64 ? 8 : 4,
+                               !(flags & SK_FLAG_BWD_REPLAY), !split && kept, split, wide_scratch);
+        };
+        if (both) {
+            const Layout l = layout(true, sk::kWideScratch);
+            if (l.p.valid && l.p.split) return l.total;
+        }
+        const Layout l = layout(false, sk::kWideScratch);
+        size_t bytes = l.p.valid ? l.total : (size_t)0;
+        if (least && !kept && l.p.valid && l.p.wide)      // one workgroup, or the kernels without that scratch
+            for (const size_t scratch : {(size_t)l.p.wd_slot * l.p.elem, (size_t)0}) {
+                const size_t t = layout(false, scratch).total;
+                if (t < bytes) bytes = t;
+            }
+        return bytes;
+    };
+    const size_t need = total(false);
+    // K(X, X) is the same query.  It needs no more, unless the two take different launch modes.
+    const size_t sym = gram && (backward || both) && B_or_N == ny && L1 == L2 ? total(true) : 0;
+    return need > sym ? need : sym;
+}
+
 int dispatch(bool backward, bool gram, const void* x, const void* y, void* k, const void* grad_k, void* grad_x,
              void* grad_y, int64_t nx, int64_t ny, int64_t L1, int64_t L2, int64_t d, int lam1, int lam2, int flags,
-             sk_dtype dt, void* ws, size_t ws_bytes, void* stream, bool small = false)
+             sk_dtype dt, void* ws, size_t ws_bytes, void* stream)
 {
     int rc = validate(nx, ny, L1, L2, d, lam1, lam2, flags, (int)dt);
     if (rc != SK_OK) return rc;
@@ -414,8 +467,7 @@ int dispatch(bool backward, bool gram, const void* x, const void* y, void* k, co
     }
     rc = check_device();
     if (rc != SK_OK) return rc;
-    Layout lay = make_layout(backward, gram, symmetric, nx, ny, L1, L2, d, lam1, lam2, flags, elem,
-                             !(flags & SK_FLAG_BWD_REPLAY), false, false, small);
+    Layout lay = fit_layout(backward, gram, symmetric, nx, ny, L1, L2, d, lam1, lam2, flags, elem, ws_bytes);
     if (!lay.p.valid) return fail(SK_ERR_SHAPE, "internal: plan invalid");
     if (!ws || (reinterpret_cast<uintptr_t>(ws) & 255) != 0)
         return fail(SK_ERR_WORKSPACE, "workspace pointer is NULL or not 256-byte aligned");
@@ -463,29 +515,13 @@ extern "C" {
 size_t sigkernel_workspace_bytes(int op, int64_t B_or_N, int64_t M, int64_t L1, int64_t L2, int64_t d, int lam1,
                                  int lam2, int flags, sk_dtype dt)
 {
-    const bool gram = op == SK_OP_GRAM || op == SK_OP_GRAM_BWD;
-    // a forward call that keeps its sweep works in the backward call's workspace
-    const bool fwd_op = op == SK_OP_FWD || op == SK_OP_GRAM;
-    const bool kept = (flags & (fwd_op ? SK_FLAG_KEEP_FORWARD : SK_FLAG_HAVE_FORWARD)) != 0;
-    const bool backward = !fwd_op || kept;
-    if (op < SK_OP_FWD || op > SK_OP_GRAM_BWD) return 0;
-    const int64_t ny = gram ? M : B_or_N;
-    if (validate(B_or_N, ny, L1, L2, d, lam1, lam2, flags, (int)dt) != SK_OK) return 0;
-    auto total = [&](bool symmetric) {
-        if (flags & (fwd_op ? SK_FLAG_KEEP_SWEEPS : SK_FLAG_HAVE_SWEEPS)) {
-            const Layout l = make_layout(true, gram, symmetric, B_or_N, ny, L1, L2, d, lam1, lam2, flags, dt == SK_F64 ? 8 : 4,
-                                         !(flags & SK_FLAG_BWD_REPLAY), false, true);
-            if (l.p.valid && l.p.split) return l.total;
-        }
-        const Layout l = make_layout(backward, gram, symmetric, B_or_N, ny, L1, L2, d, lam1, lam2, flags, dt == SK_F64 ? 8 : 4,
-                                     !(flags & SK_FLAG_BWD_REPLAY), kept);
-        return l.p.valid ? l.total : (size_t)0;
-    };
-    const size_t need = total(false);
-    // K(X, X) is the same query.  It needs no more, unless the two take different launch modes.
-    const bool both = (flags & (fwd_op ? SK_FLAG_KEEP_SWEEPS : SK_FLAG_HAVE_SWEEPS)) != 0;
-    const size_t sym = gram && (backward || both) && B_or_N == ny && L1 == L2 ? total(true) : 0;
-    return need > sym ? need : sym;
+    return op_bytes(op, B_or_N, M, L1, L2, d, lam1, lam2, flags, dt, false);
+}
+
+size_t sigkernel_workspace_least_bytes(int op, int64_t B_or_N, int64_t M, int64_t L1, int64_t L2, int64_t d, int lam1,
+                                       int lam2, int flags, sk_dtype dt)
+{
+    return op_bytes(op, B_or_N, M, L1, L2, d, lam1, lam2, flags, dt, true);
 }
 
 int sigkernel_fwd(const void* x, const void* y, void* k, int64_t B, int64_t L1, int64_t L2, int64_t d, int lam1,
@@ -554,11 +590,7 @@ extern "C" int sigkernel_bwd_static(const void* x, const void* y, const void* gr
                     "(its scratch is shared by every call on the device)");
     int rc = validate(B, B, L1, L2, d, lam1, lam2, flags, (int)dt);
     if (rc != SK_OK) return rc;
-    size_t need = B > 0 ? sigkernel_workspace_bytes(SK_OP_BWD, B, 0, L1, L2, d, lam1, lam2, flags, dt) : 0;
-    const bool small = need > kStaticScratchBytes;
-    if (small)
-        need = make_layout(true, false, false, B, B, L1, L2, d, lam1, lam2, flags, dt == SK_F64 ? 8 : 4, !(flags & SK_FLAG_BWD_REPLAY),
-                           false, false, true).total;
+    const size_t need = B > 0 ? sigkernel_workspace_least_bytes(SK_OP_BWD, B, 0, L1, L2, d, lam1, lam2, flags, dt) : 0;
     if (need > kStaticScratchBytes)
         return fail(SK_ERR_WORKSPACE, "this shape needs %zu bytes of scratch, sigkernel_bwd_static holds %zu per device; "
                     "use sigkernel_bwd with a workspace of the caller's", need, kStaticScratchBytes);
@@ -569,7 +601,7 @@ extern "C" int sigkernel_bwd_static(const void* x, const void* y, const void* gr
     // call that sweeps forward itself erases the signature of a kept sweep: nothing of the previous call's contents
     // is read before it is written.
     return dispatch(true, false, x, y, k_out, grad_k, grad_x, grad_y, B, B, L1, L2, d, lam1, lam2, flags, dt, ptr,
-                    kStaticScratchBytes, stream, small);
+                    kStaticScratchBytes, stream);
 }
 
 // Layout of the scratch of sigkernel_mmd2: the three Gram matrices, their constant upstream weights, the second
@@ -654,7 +686,7 @@ struct MmdLayout {
     size_t kxx, kxy, kyy, wxx, wxy, wyy, gx2, gy2, sub, sub_bytes, total;
 };
 MmdLayout mmd_layout(int64_t N, int64_t M, int64_t L1, int64_t L2, int64_t d, int lam1, int lam2, int flags,
-                     sk_dtype dt, bool grads)
+                     sk_dtype dt, bool grads, bool least = false)
 {
     MmdLayout l{};
     const size_t e = dt == SK_F64 ? 8 : 4;
@@ -671,10 +703,11 @@ MmdLayout mmd_layout(int64_t N, int64_t M, int64_t L1, int64_t L2, int64_t d, in
         l.gy2 = take((size_t)M * L2 * d * e);
     }
     const int op = grads ? SK_OP_GRAM_BWD : SK_OP_GRAM;
-    size_t s = sigkernel_workspace_bytes(op, N, N, L1, L1, d, lam1, lam1, flags, dt);
-    size_t t = sigkernel_workspace_bytes(op, N, M, L1, L2, d, lam1, lam2, flags, dt);
+    const auto bytes = least ? sigkernel_workspace_least_bytes : sigkernel_workspace_bytes;
+    size_t s = bytes(op, N, N, L1, L1, d, lam1, lam1, flags, dt);
+    size_t t = bytes(op, N, M, L1, L2, d, lam1, lam2, flags, dt);
     if (t > s) s = t;
-    t = sigkernel_workspace_bytes(op, M, M, L2, L2, d, lam2, lam2, flags, dt);
+    t = bytes(op, M, M, L2, L2, d, lam2, lam2, flags, dt);
     if (t > s) s = t;
     l.sub_bytes = s;
     l.sub = take(s);
@@ -742,6 +775,13 @@ size_t sigkernel_mmd2_workspace_bytes(int64_t N, int64_t M, int64_t L1, int64_t 
     return mmd_layout(N, M, L1, L2, d, lam1, lam2, flags, dt, with_grads != 0).total;
 }
 
+size_t sigkernel_mmd2_workspace_least_bytes(int64_t N, int64_t M, int64_t L1, int64_t L2, int64_t d, int lam1, int lam2,
+                                            int flags, sk_dtype dt, int with_grads)
+{
+    if (sigkernel_mmd2_workspace_bytes(N, M, L1, L2, d, lam1, lam2, flags, dt, with_grads) == 0) return 0;
+    return mmd_layout(N, M, L1, L2, d, lam1, lam2, flags, dt, with_grads != 0, true).total;
+}
+
 int sigkernel_mmd2(const void* X, const void* Y, void* loss, void* grad_X, void* grad_Y, int64_t N, int64_t M,
                    int64_t L1, int64_t L2, int64_t d, int lam1, int lam2, int flags, sk_dtype dt, void* ws,
                    size_t ws_bytes, void* stream)
@@ -754,10 +794,12 @@ int sigkernel_mmd2(const void* X, const void* Y, void* loss, void* grad_X, void*
     if (!X || !Y || !loss) return fail(SK_ERR_NULL, "X / Y / loss is NULL");
     if (X == Y) return fail(SK_ERR_SHAPE, "mmd2 of a set with itself is zero; pass two arrays");
     const bool grads = grad_X != nullptr || grad_Y != nullptr;
-    const MmdLayout l = mmd_layout(N, M, L1, L2, d, lam1, lam2, flags, dt, grads);
+    MmdLayout l = mmd_layout(N, M, L1, L2, d, lam1, lam2, flags, dt, grads);
+    if (ws_bytes < l.total) l = mmd_layout(N, M, L1, L2, d, lam1, lam2, flags, dt, grads, true);
     if (!ws || (reinterpret_cast<uintptr_t>(ws) & 255) != 0)
         return fail(SK_ERR_WORKSPACE, "workspace pointer is NULL or not 256-byte aligned");
     if (ws_bytes < l.total) return fail(SK_ERR_WORKSPACE, "workspace has %zu bytes, %zu needed", ws_bytes, l.total);
+    l.sub_bytes = ws_bytes - l.sub;
     if (dt == SK_F64)
         return run_mmd2<double>(l, X, Y, loss, grad_X, grad_Y, N, M, L1, L2, d, lam1, lam2, flags, dt, ws, stream);
     return run_mmd2<float>(l, X, Y, loss, grad_X, grad_Y, N, M, L1, L2, d, lam1, lam2, flags, dt, ws, stream);

@@ -277,11 +277,12 @@ inline bool split_pays(const Plan& p, int strips)
 
 // Wide mode: waves per workgroup at most, doubles per block of the stored edges (right edge, and bottom edge without the
 // corner they share), macro-steps per chunk (what a wave holds of the coming chunk stays in registers), and the scratch that
-// its resident workgroups may take together.
+// its resident workgroups may take together: forward no more than kWideForward once it keeps the chip busy with the waves of
+// that many workgroups.  Gram 64 x 64, L = 600, d = 20 (0), forward, with 6.6, 4 and 2 GiB: 13.5, 13.1 and 12.7 ms.
 constexpr int kWideMaxWaves = 8;
 constexpr int wide_edge_values(int BL) { return 2 * (1 << BL) - 1; }
 constexpr int wide_chunk(int BL) { return BL == 2 ? 4 : 8; }
-constexpr size_t kWideScratch = (size_t)8 << 30;
+constexpr size_t kWideScratch = (size_t)8 << 30, kWideForward = (size_t)2 << 30;
 
 // Band mode: strips per workgroup, block columns per hand-over ring, coarse y columns per y ring (powers of
 // two), chunks the data-moving wave works ahead, and the bound on its polls of another workgroup's counter.
@@ -301,6 +302,10 @@ constexpr int64_t kCoopMaxPairs = 1024;   // above this, one wave per pair alrea
 //   memory, d = 5 (0) / (1): 49543 / 49937 and 7085 / 9599;  d = 8: 119663 / 121405 and 7265 / 9784
 //   backward with sixteen channels, cooperative, (0) / (1) / (2): 8 pairs, L = 150: 279 / 416 / 500 and 168 / 217 / 357; 64 pairs,
 //   L = 300: 586 / 959 / 1420 and 393 / 485 / 835; 300 pairs, L = 200, 250: 873 / 905 / 1531 and 575 / 785 / 1306
+// Also with less scratch than they would fill, down to one workgroup's (the figures: those kernels, these with all of their
+// scratch, and with no more than those need).  ms, backward: 32 pairs, L = 2048, d = 17 (2): 551, 48 and 159; 64 pairs, d = 8 (2):
+// 112, 69 and 133; 256 pairs, L = 2048, 1500, d = 17 (0): 1281, 25 and 46; Gram 100 x 100, L = 128, d = 20 (1): 310, 6.0 and 6.1;
+// forward: Gram 64 x 64, L = 600, d = 20 (0): 167, 12.7 and 40; Gram 256 x 256, L = 128, d = 20 (0): 111, 10.3 and 50.6.
 // Not elsewhere: forward with sixteen channels, 300 pairs, L = 200, 250: 150 / 180 / 248 and 195 / 206 / 288; backward, sixteen
 // channels, wave per pair, 1500 pairs, L = 90 (1) / (2): 624 / 894 and 763 / 1250; up to eight channels with y in LDS, 64 pairs,
 // L = 1500, d = 3 (1), backward: 5140 and 9668; forward with y in memory, 1500 pairs, L = 300, 700, d = 8 (0): 1468 and 2530.
@@ -322,13 +327,14 @@ constexpr double kDriftTol = 1e-11;
 
 inline Plan make_plan(bool backward, bool gram, bool symmetric, int64_t nx, int64_t ny, int64_t L1, int64_t L2,
                       int64_t d, int lam1, int lam2, int io_elem, bool uncompute = true, bool keep = false,
-                      bool second_chance = false, bool lead_lag = false, bool may_four = true, bool may_wide = true,
+                      bool second_chance = false, bool lead_lag = false, bool may_four = true, size_t wide_scratch = kWideScratch,
                       bool split = false)
 {
     // lead_lag: the sweep of two lead-lag paths (Section 4) on the grid of the original increments; lam1 and lam2 then
     // count the lead-lag level as one more dyadic level (the caller's orders plus one), L1, L2 and d are the caller's.
     // The level lies inside the blocks when these hold every refined cell of a pair of increments, above them
     // otherwise (Plan::ll); the tile kernels have no such form.
+    // wide_scratch: what the resident workgroups of a wide launch may take together (0: no wide mode).
     // split: a backward plan of the kernels that sweep forward and adjoint side by side; Plan::split says whether the shape has
     // one.
     // second_chance: the plan of the launch that solves the listed pairs once more (wave-per-pair replay kernel,
@@ -767,21 +773,25 @@ inline Plan make_plan(bool backward, bool gram, bool symmetric, int64_t nx, int6
 
     // Wide mode takes over what is left to the wave-per-pair and the cooperative kernels with more channels than those hold
     // in registers, or with y increments (and their sums) that do not fit in LDS.
-    if (may_wide && wide_pays(p) && (!backward || p.uncompute) && !second_chance) {
+    if (wide_scratch != 0 && wide_pays(p) && (!backward || p.uncompute) && !second_chance) {
         const int NT = (int)align_up((size_t)p.nb + kWave - 1, 8);
         const int64_t pairs = may_tri ? nx * (nx + 1) / 2 : p.npairs;
         const int64_t slot = (int64_t)p.ns * kWave * (NT + (backward ? (int64_t)(NT + 2) * wide_edge_values(p.BL) : 0));
-        // as many waves per pair as fill the chip: two wavefronts per SIMD by registers, forward four
-        const int64_t resident = (backward ? 8 : 16) * kNumCU;
-        int64_t nw = (resident + pairs - 1) / pairs;
-        if (nw > p.ns) nw = p.ns;
-        if (nw > kWideMaxWaves) nw = kWideMaxWaves;
-        int64_t grid = resident / nw;
-        if (grid > pairs) grid = pairs;
-        grid = (pairs + (pairs + grid - 1) / grid - 1) / ((pairs + grid - 1) / grid);   // the same rounds, evenly filled
-        const int64_t fit = (int64_t)(kWideScratch / ((size_t)slot * elem));
-        if (grid > fit) grid = fit;
-        if (grid >= (pairs < kNumCU / 8 ? pairs : kNumCU / 8)) {
+        // As many waves per pair as fill the chip: two wavefronts per SIMD by registers, forward four.  Where the scratch
+        // leaves room for fewer workgroups, they have more waves, up to one per strip.
+        const int64_t resident = (backward ? 8 : 16) * kNumCU, waves = p.ns < kWideMaxWaves ? p.ns : kWideMaxWaves;
+        int64_t most = (int64_t)(wide_scratch / ((size_t)slot * elem));   // workgroups
+        if (!backward && most > resident / waves) {
+            const int64_t enough = (int64_t)(kWideForward / ((size_t)slot * elem));
+            if (most > enough) most = enough > resident / waves ? enough : resident / waves;
+        }
+        if (most > pairs) most = pairs;
+        if (most >= 1) {
+            int64_t nw = (resident + most - 1) / most;
+            if (nw > waves) nw = waves;
+            if (most > resident / nw) most = resident / nw;
+            const int64_t rounds = (pairs + most - 1) / most;
+            const int64_t grid = (pairs + rounds - 1) / rounds;   // the same rounds, evenly filled
             p.wide = 1; p.coop = 0;
             p.nw = (int)nw;
             p.tri = may_tri ? 1 : 0;
@@ -851,7 +861,7 @@ inline Plan make_plan(bool backward, bool gram, bool symmetric, int64_t nx, int6
     p.valid = true;
     if (p.four && p.total > kFourScratch) {
         const Plan one = make_plan(backward, gram, symmetric, nx, ny, L1, L2, d, lam1, lam2, io_elem, uncompute, keep,
-                                   second_chance, lead_lag, false, may_wide);
+                                   second_chance, lead_lag, false, wide_scratch);
         if (one.total < p.total) return one;
     }
     return p;

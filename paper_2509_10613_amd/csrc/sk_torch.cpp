@@ -41,6 +41,21 @@ using torch::autograd::variable_list;
 void* current_stream() { return static_cast<void*>(c10::hip::getCurrentHIPStream().stream()); }
 sk_dtype dtype_of(const Tensor& t) { return t.scalar_type() == at::kDouble ? SK_F64 : SK_F32; }
 Tensor bytes(size_t n, const Tensor& like) { return at::empty({(int64_t)(n < 256 ? 256 : n)}, like.options().dtype(at::kByte)); }
+// The workspace a call is fastest with or, where the device has no room for it, half of that and so on down to the least the
+// call takes.
+template <class F>
+Tensor workspace(size_t n, const Tensor& like, F&& least)
+{
+    for (size_t few = 0;;) {
+        try {
+            return bytes(n, like);
+        } catch (const c10::OutOfMemoryError&) {
+            if (few == 0) few = least();
+            if (n <= few) throw;
+        }
+        n = n / 2 > few ? n / 2 : few;
+    }
+}
 void* ptr(const Tensor& t) { return t.defined() ? t.data_ptr() : nullptr; }
 
 // (the exception that the classes raise)
@@ -158,10 +173,12 @@ struct KernelNode : public Node {
         // (saved-tensor hooks and recomputed checkpoints give equal paths back at other addresses, which the library takes for
         // another call's)
         const bool kept = held.defined() && x.data_ptr() == x_at && y.data_ptr() == y_at;
-        const Tensor w = kept ? held : bytes(need, x);
         const int f = flags | (kept ? have : 0);
         const sk_dtype dt = dtype_of(x);
         const int64_t N = x.size(0), M = y.size(0), L1 = x.size(1), L2 = y.size(1), d = x.size(2);
+        const Tensor w = kept ? held : workspace(need, x, [&] {
+            return sigkernel_workspace_least_bytes(gram ? SK_OP_GRAM_BWD : SK_OP_BWD, N, M, L1, L2, d, lam1, lam2, f, dt);
+        });
         // (a Gram call computes both sides)
         Tensor gx, gy;
         if (want_x || gram) gx = at::empty_like(x, at::MemoryFormat::Contiguous);
@@ -299,7 +316,10 @@ Tensor kernel_call(const Tensor& x0, const Tensor& y0, bool gram, bool symmetric
             } catch (const c10::OutOfMemoryError&) {   // the calls go on without one
             }
         }
-        if (!kept) ws = bytes(need.forward, x);
+        if (!kept)
+            ws = workspace(need.forward, x, [&] {
+                return sigkernel_workspace_least_bytes(gram ? SK_OP_GRAM : SK_OP_FWD, N, M, L1, L2, d, lam1, lam2, flags, dt);
+            });
         const int f = flags | (kept ? need.keep : 0);
         int rc;
         if (gram) {
@@ -403,7 +423,9 @@ py::object mmd2(py::object xo, py::object yo, py::object l1, py::object l2, py::
             loss = at::empty({}, x.options());
             if (want_x) gx = at::empty_like(x, at::MemoryFormat::Contiguous);
             if (want_y) gy = at::empty_like(y, at::MemoryFormat::Contiguous);
-            const Tensor ws = bytes(need.forward, x);
+            const Tensor ws = workspace(need.forward, x, [&] {
+                return sigkernel_mmd2_workspace_least_bytes(N, M, L1, L2, d, lam1, lam2, flags, dt, want_x || want_y ? 1 : 0);
+            });
             if (sigkernel_mmd2(x.data_ptr(), y.data_ptr(), loss.data_ptr(), ptr(gx), ptr(gy), N, M, L1, L2, d, lam1, lam2, flags, dt,
                                ws.data_ptr(), (size_t)ws.numel(), current_stream()) != SK_OK)
                 loss.reset();

@@ -7,6 +7,7 @@ import pytest
 import torch
 
 import oracle
+from paper_2509_10613_amd import autograd as ska
 from paper_2509_10613_amd import binding as sk
 from paper_2509_10613_amd import workloads
 from tests.test_gpu_parity import check_grads, check_values, dev, host, rounded
@@ -107,3 +108,105 @@ def test_small_scratch_entry_point_still_takes_what_it_took():
     check_values(host(k1), host(k), torch.float64, "k")
     check_grads(host(gx1), host(gx), torch.float64, "grad_x")
     check_grads(host(gy1), host(gy), torch.float64, "grad_y")
+
+
+def sizes(op, n, m, L1, L2, d, lam, flags, sdt):
+    shape = (op, n, m, L1, L2, d, lam, lam, flags, sdt)
+    return sk.sigkernel_workspace_least_bytes(*shape), sk.sigkernel_workspace_bytes(*shape)
+
+
+@pytest.mark.parametrize("n,m,L1,L2,d,lam,flags,dtype", [
+    (300, None, 70, 40, 18, 1, 0, torch.float64),      # pairs: a wave or several per pair, by the workgroups there is room for
+    (40, None, 520, 30, 17, 0, 1, torch.float64),      # nine strips
+    (3, None, 300, 280, 20, 0, 0, torch.float64),      # the channel loops, where there is room for no wide workgroup
+    (2, None, 90, 90, 18, 0, LL, torch.float32),
+    (30, 41, 70, 66, 20, 0, 0, torch.float64),
+    (25, 0, 70, 70, 17, 1, 1, torch.float32),          # K(X, X)
+    (7, 9, 150, 230, 12, 0, 0, torch.float64),         # backward: y side too long for LDS
+])
+def test_workspaces_between_the_least_and_the_best(n, m, L1, L2, d, lam, flags, dtype):
+    gram, sym = m is not None, m == 0
+    X, Y = paths(2001, n, L1, d, 1.0), paths(2002, m or n, L2, d, 1.0)
+    W = workloads.upstream_weights(98, (n, m or n) if gram else (n,))
+    x = dev(X, dtype)
+    y = x if sym else dev(Y, dtype)
+    Xr = rounded(X, dtype)
+    Yr = Xr if sym else rounded(Y, dtype)
+    w, sdt = dev(W, dtype), sk.SK_F64 if dtype == torch.float64 else sk.SK_F32
+    ref = (oracle.gram if gram else oracle.bwd)(Xr, Yr, rounded(W, dtype), lam, lam, flags)
+    for back in (False, True):
+        op = (sk.SK_OP_GRAM_BWD if back else sk.SK_OP_GRAM) if gram else (sk.SK_OP_BWD if back else sk.SK_OP_FWD)
+        least, best = sizes(op, n, (m or n) if gram else 0, L1, L2, d, lam, flags, sdt)
+        assert 0 < least <= best and (best > least or d <= 16)
+        for size in sorted({least, least + 256, least + (best - least) // 3 // 256 * 256, best - 256 if best > least else best, best}):
+            print("%s %d of %d" % ("backward" if back else "forward", size, best), flush=True)
+            ws = torch.full((size,), 0xa5, dtype=torch.uint8, device="cuda")
+            if not back:
+                k = sk.sigkernel_gram(x, y, None, lam, lam, flags, ws=ws) if gram else sk.sigkernel_fwd(x, y, lam, lam, flags, ws=ws)
+                check_values(host(k), ref[0], dtype, "K")
+                continue
+            k, gx, gy = sk.sigkernel_gram(x, y, w, lam, lam, flags, ws=ws) if gram else sk.sigkernel_bwd(x, y, w, lam, lam, flags, ws=ws)
+            check_values(host(k), ref[0], dtype, "K")
+            check_grads(host(gx), ref[1], dtype, "grad_X")
+            if not sym:
+                check_grads(host(gy), ref[2], dtype, "grad_Y")
+        if sym:      # (needs less than the query says, which is K(X, Y)'s)
+            continue
+        with pytest.raises(sk.SigKernelError, match="workspace"):
+            small = torch.empty(least - 256, dtype=torch.uint8, device="cuda")
+            if gram:
+                sk.sigkernel_gram(x, y, w if back else None, lam, lam, flags, ws=small)
+            elif back:
+                sk.sigkernel_bwd(x, y, w, lam, lam, flags, ws=small)
+            else:
+                sk.sigkernel_fwd(x, y, lam, lam, flags, ws=small)
+
+
+def test_mmd_in_the_least_workspace():
+    X, Y = dev(paths(2003, 12, 60, 18, 1.0)), dev(paths(2004, 9, 50, 18, 1.0))
+    ref = sk.sigkernel_mmd2(X, Y)
+    shape = (12, 9, 60, 50, 18, 0, 0, 0, sk.SK_F64)
+    for want in (True, False):
+        least = sk.load().sigkernel_mmd2_workspace_least_bytes(*shape, int(want))
+        assert least < sk.load().sigkernel_mmd2_workspace_bytes(*shape, int(want))
+        got = sk.sigkernel_mmd2(X, Y, want_x=want, want_y=want, ws=torch.full((least,), 0xa5, dtype=torch.uint8, device="cuda"))
+        for g, r in zip(got, ref):
+            assert g is None or float((g - r).abs().max()) <= 1e-12 * float(r.abs().max())
+        with pytest.raises(sk.SigKernelError, match="workspace"):
+            sk.sigkernel_mmd2(X, Y, want_x=want, want_y=want, ws=torch.empty(least - 256, dtype=torch.uint8, device="cuda"))
+
+
+@pytest.mark.parametrize("what", ["pairs", "gram", "mmd"])
+@pytest.mark.parametrize("through", ["wrappers", "classes", "binding"])
+def test_calls_go_on_where_the_device_has_no_room(through, what):
+    # 1 GiB of memory for calls that are fastest with more (the allocator's own limit; nothing else is refused)
+    n, L, d = {"pairs": (200, 600, 17), "gram": (40, 300, 20), "mmd": (40, 300, 20)}[what]
+    x, y = (dev(paths(s, n, L, d, 1.0)).requires_grad_() for s in (2005, 2006))
+    call = {"pairs": {"wrappers": lambda: ska.sig_kernel(x, y), "classes": lambda: ska._PairKernel.apply(x, y, 0, 0, 0)},
+            "gram": {"wrappers": lambda: ska.sig_kernel_gram(x, y), "classes": lambda: ska._GramKernel.apply(x, y, 0, 0, 0)},
+            "mmd": {"wrappers": lambda: ska.sig_mmd2(x, y), "classes": lambda: ska._Mmd2.apply(x, y, 0, 0, 0)}}[what]
+
+    def step():
+        if through != "binding":
+            k = call[through]()
+            return (k.detach(), *torch.autograd.grad(k.sum(), (x, y)))
+        a, b = x.detach(), y.detach()
+        if what == "mmd":
+            return sk.sigkernel_mmd2(a, b)
+        k = sk.sigkernel_gram(a, b) if what == "gram" else sk.sigkernel_fwd(a, b)
+        return (k, *((sk.sigkernel_gram if what == "gram" else sk.sigkernel_bwd)(a, b, torch.ones_like(k))[1:]))
+    ref = step()
+    op = sk.SK_OP_BWD if what == "pairs" else sk.SK_OP_GRAM_BWD
+    need = sizes(op, n, 0 if what == "pairs" else n, L, L, d, 0, 0, sk.SK_F64)
+    assert need[0] < 1 << 30 < need[1]
+    total = torch.cuda.get_device_properties(0).total_memory
+    sk._ws_cache.clear()
+    torch.cuda.empty_cache()
+    torch.cuda.set_per_process_memory_fraction((torch.cuda.memory_reserved() + (1 << 30)) / total)
+    try:
+        got = step()
+    finally:
+        torch.cuda.set_per_process_memory_fraction(1.0)
+        sk._ws_cache.clear()
+    for g, r in zip(got, ref):
+        assert float((g - r).abs().max()) <= 1e-11 * float(r.abs().max())

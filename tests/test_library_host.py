@@ -207,9 +207,13 @@ def test_launch_plan_of_the_five_configurations(lib):
     assert p["threads"] == "320" and p["strips"] == "32" and int(p["lds_bytes"]) <= 160 * 1024
     p = _plan(binding.SK_OP_FWD, 32, 0, 2048, 2048, 8, 2, 2, 0, f64)
     assert p["mode"] == "band" and p["kernel"] == "band_fwd_kernel<2, 8, false, 0>" and p["grid"] == "256"
-    # more long pairs than the chip has room for bands: one workgroup per pair, its strips in rounds
-    p = _plan(binding.SK_OP_BWD, 64, 0, 2048, 2048, 8, 2, 2, 0, f64)
+    # more long pairs than the chip has room for bands: one workgroup per pair, its strips in rounds; backward, where the y
+    # side does not fit in LDS, as many workgroups as 8 GiB of scratch hold, the same rounds evenly filled
+    p = _plan(binding.SK_OP_FWD, 64, 0, 2048, 2048, 8, 2, 2, 0, f64)
     assert p["mode"] == "cooperative" and p["grid"] == "64"
+    for pairs, grid in ((31, 31), (32, 16), (64, 22)):
+        p = _plan(binding.SK_OP_BWD, pairs, 0, 2048, 2048, 17, 2, 2, 0, f64)
+        assert p["mode"] == "wide" and p["grid"] == str(grid) and p["threads"] == "512", pairs
     # 16 channels have no band kernel
     assert _plan(binding.SK_OP_FWD, 8, 0, 2048, 2048, 16, 2, 2, 0, f64)["mode"] == "cooperative"
     # the replay variant of the backward pass never runs in lock step
