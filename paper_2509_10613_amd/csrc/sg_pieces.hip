@@ -26,7 +26,7 @@ __host__ __device__ constexpr int tri(int n) { return n * (n + 1) / 2; }
 struct PieceArgs {
     const double* pieces;    // [B][P][sig_len]
     double* prefix;          // [B][P][sig_len] L_p, or nullptr
-    double* suffix;          // [B][P][sig_len] R_p, p < P - 1, or nullptr
+    double* suffix;          // [B][P - 1][sig_len] R_p, or nullptr
     void* whole;             // [B][sig_len] L_{P-1}, float or double, or nullptr
     int whole_f32;
     long B, sig_len;
@@ -70,7 +70,7 @@ __device__ __forceinline__ void scan(const PieceArgs& a, long b, unsigned w, uns
     double* dst = SUFFIX ? a.suffix : a.prefix;
     // after q + 1 pieces from the end: what follows piece P - 2 - q
     auto keep = [&](int q) {
-        if (dst) put(dst + (b * a.P + (SUFFIX ? a.P - 2 - q : q)) * a.sig_len);
+        if (dst) put(dst + (SUFFIX ? b * (a.P - 1) + a.P - 2 - q : b * a.P + q) * a.sig_len);
     };
     {
         const double* s = src + (SUFFIX ? a.P - 1 : 0) * a.sig_len;
@@ -153,7 +153,7 @@ __global__ __launch_bounds__(kWave) void scan_pieces_kernel(const PieceArgs a)
 // follow each other: with workgroups of their own per piece and level, two pieces each of 5000 paths of 100 points in
 // two channels, level 3, took signature_bwd 73.5 us, so 63.5; in four 73.7 and 50.9.
 struct AdjointArgs {
-    const double* suffix;    // [B][P][sig_len]
+    const double* suffix;    // [B][P - 1][sig_len]
     double* adj;             // [B][P][sig_len]
     long pieces, sig_len, slots;
     int P, N;
@@ -175,7 +175,7 @@ __global__ __launch_bounds__(256) void piece_adjoints_kernel(const TI* __restric
         const TI* g = gout + (long)b * a.sig_len;
         double acc = lane == 0 ? (double)g[a.lv[k] + u] : 0.0;         // the empty word
         if (bp - b * (I)a.P != (I)a.P - 1) {
-            const double* r = a.suffix + (long)bp * a.sig_len;
+            const double* r = a.suffix + (long)(bp - b) * a.sig_len;
             for (int j = 1; j <= a.N - k; ++j) {
                 const unsigned cnt = a.pw[j];
                 const TI* gj = g + a.lv[k + j] + u * cnt;

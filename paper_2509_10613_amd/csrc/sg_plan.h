@@ -158,7 +158,7 @@ struct Plan {
     int Dpad = 0;         // doubles per stored increment row
     int64_t sig_len = 0;  // entries per path, level 0 included
     int io_elem = 8;
-    size_t off_dz = 0, off_out = 0, total = 0;
+    size_t off_dz = 0, total = 0;
     size_t off_t0 = 0;    // signatures of the pieces (P > 1); backward: then the adjoints at their ends
     size_t off_t1 = 0;    // backward: signatures of the pieces up to each one and after it
     // backward
@@ -356,11 +356,9 @@ inline Plan make_plan(int64_t B, int64_t L, int64_t d, int N, bool time_aug, boo
     if (p.grid > 0x7fffffffLL) { p.why = "too many workgroups"; return p; }
     p.Dpad = (int)align_up((size_t)D, 2);
     size_t off = 0;
-    p.off_dz = off;
-    off = align_up(off + (size_t)p.VB * (size_t)p.np * p.Dpad * sizeof(double), 256);
-    p.off_out = off;
+    p.off_dz = off;      // (kernels that hold several paths per wave read the points; the backward ones read increments always)
+    if (backward || p.PW == 1) off = align_up(off + (size_t)p.VB * (size_t)p.np * p.Dpad * sizeof(double), 256);
     if (!backward) {
-        if (!io_double) off = align_up(off + (size_t)B * (size_t)p.sig_len * sizeof(double), 256);
         if (p.P > 1) {
             p.off_t0 = off;
             off = align_up(off + (size_t)p.VB * (size_t)p.sig_len * sizeof(double), 256);
@@ -381,16 +379,13 @@ inline Plan make_plan(int64_t B, int64_t L, int64_t d, int N, bool time_aug, boo
         p.off_gz = off;      // dF/dz, one row per stored increment row
         off = align_up(off + (size_t)p.VB * (size_t)p.np * p.Dpad * sizeof(double), 256);
         p.off_sig = off;     // signatures in double, if the caller has none
-        // (room for float callers' signatures and upstream gradients in double, which the kernels now read as they are,
-        // stays part of the size)
-        if (p.P == 1 && (!have_sig || !io_double)) off = align_up(off + (size_t)B * (size_t)p.sig_len * sizeof(double), 256);
-        if (!io_double) off = align_up(off + (size_t)B * (size_t)p.sig_len * sizeof(double), 256);
+        if (p.P == 1 && !have_sig) off = align_up(off + (size_t)B * (size_t)p.sig_len * sizeof(double), 256);
         if (p.P > 1) {
             const size_t pieces = (size_t)p.VB * (size_t)p.sig_len * sizeof(double);
             p.off_t0 = off;
             off = align_up(off + pieces, 256);
-            p.off_t1 = off;
-            off = align_up(off + 2 * pieces, 256);
+            p.off_t1 = off;      // (nothing follows a path's last piece)
+            off = align_up(off + 2 * pieces - (size_t)B * (size_t)p.sig_len * sizeof(double), 256);
         }
     }
     p.total = off < 256 ? 256 : off;

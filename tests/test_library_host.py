@@ -322,12 +322,15 @@ def test_signature_host_side(lib):
     assert f(one, one, 4, 8, 3, 3, 0, 1, one, 16, None) == -5
     assert f(one, one, 4, 8, 3, 3, 0, 1, C.c_void_p(264), 1 << 20, None) == -5
     assert f(None, None, 0, 8, 3, 3, 0, 1, None, 0, None) == 0           # empty batch
-    # workspace: increments of the (transformed) paths in double, rows padded to an even count, plus the double
-    # staging of the result for float callers
+    # workspace: increments of the (transformed) paths in double, rows padded to an even count, whatever the caller's type;
+    # none for kernels that hold several paths per wave and read the points
     assert binding.signature_workspace_bytes(128, 1024, 16, 4, 0, binding.SK_F64) >= 128 * 1023 * 16 * 8
     assert binding.signature_workspace_bytes(128, 1024, 16, 4, 0, binding.SK_F64) < 128 * 1023 * 16 * 8 + 512
     w32 = binding.signature_workspace_bytes(10, 20, 3, 3, binding.SK_FLAG_LEAD_LAG, binding.SK_F32)
-    assert w32 >= 10 * 38 * 6 * 8 + 10 * (1 + 6 + 36 + 216) * 8
+    assert 10 * 38 * 6 * 8 <= w32 < 10 * 39 * 6 * 8 + 512
+    assert "paths_per_wave=1 " in binding.signature_describe(10, 20, 3, 3, binding.SK_FLAG_LEAD_LAG, binding.SK_F32)
+    assert "paths_per_wave=32 " in binding.signature_describe(100000, 10, 2, 3, 0, binding.SK_F32)
+    assert binding.signature_workspace_bytes(100000, 10, 2, 3, 0, binding.SK_F32) == 256
     assert binding.signature_workspace_bytes(0, 20, 3, 3, 0, binding.SK_F64) == 0
 
 
@@ -383,14 +386,17 @@ def test_signature_backward_host_side(lib):
     assert f(one, None, None, one, 4, 8, 3, 3, 0, 1, one, 1 << 20, None) == -1
     assert f(one, None, one, one, 4, 8, 3, 3, 0, 1, one, 16, None) == -5
     assert f(None, None, None, None, 0, 8, 3, 3, 0, 1, None, 0, None) == 0
-    # workspace: increments and their gradients (rows rounded up to an odd count), the signatures when the caller
-    # does not pass them, double copies for float callers
+    # workspace: increments and their gradients (rows rounded up to an odd count), and the signatures when the caller
+    # does not pass them; float callers' are read as they are
     n = 1 + 3 + 9 + 27
     base = 2 * 4 * 7 * 4 * 8
     w0 = lib.signature_bwd_workspace_bytes(4, 8, 3, 3, 0, 1, 1)
     w1 = lib.signature_bwd_workspace_bytes(4, 8, 3, 3, 0, 1, 0)
     w2 = lib.signature_bwd_workspace_bytes(4, 8, 3, 3, 0, 0, 1)
-    assert base <= w0 < base + 1024 and w1 >= w0 + 4 * n * 8 and w2 >= w0 + 2 * 4 * n * 8
+    assert base <= w0 < base + 1024 and w1 >= w0 + 4 * n * 8 and w2 == w0
+    # paths in pieces: a signature of every piece, one up to it, and one after all but the last
+    sigs = lambda P: lib.signature_bwd_workspace_bytes(100, 65, 3, 4, binding.SK_SIG_PIECES(P), 1, 1) // (100 * 121 * 8)  # noqa: E731
+    assert [sigs(1), sigs(2), sigs(3)] == [5 + sigs(0), 11 + sigs(0), 23 + sigs(0)]
     # launch plans: the backward variants hold entries and adjoints, so the subtrees are smaller than the forward's
     other = binding.SK_SIG_ONE_PATH_PER_WAVE       # a form of the kernel that sums over the words lane by lane
     text = binding.signature_bwd_describe(128, 1024, 16, 4, other, binding.SK_F64)
