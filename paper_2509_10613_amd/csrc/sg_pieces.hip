@@ -148,9 +148,7 @@ __global__ __launch_bounds__(kWave) void scan_pieces_kernel(const PieceArgs a)
     }
 }
 
-// Words of k letters sum over 1 + D + ... + D^(N - k) terms: a wave, eight lanes or one lane per word (shift[k] = 6, 3, 0,
-// falling with k), slots start[k] .. start[k + 1] - 1 of a piece's `slots`, a multiple of the largest group.  The slots of all pieces
-// follow each other: with workgroups of their own per piece and level, two pieces each of 5000 paths of 100 points in
+// start, shift and slots as in adjoint_slots.  The slots of all pieces follow each other: with workgroups of their own per piece and level, two pieces each of 5000 paths of 100 points in
 // two channels, level 3, took signature_bwd 73.5 us, so 63.5; in four 73.7 and 50.9.
 struct AdjointArgs {
     const double* suffix;    // [B][P - 1][sig_len]
@@ -276,16 +274,7 @@ hipError_t launch_piece_adjoints(const TI* gout, const double* suffix, double* a
     AdjointArgs a = {};
     if (P < 2 || !levels(D, N, a.lv, a.pw) || sig_len != (long)a.lv[N] + a.pw[N]) return hipErrorInvalidValue;
     a.suffix = suffix; a.adj = adj; a.pieces = B * P; a.sig_len = sig_len; a.P = P; a.N = N;
-    unsigned long slots = 0;
-    for (int k = 1; k <= N; ++k) {
-        const unsigned terms = a.lv[N - k] + a.pw[N - k];
-        a.shift[k] = terms <= 8 ? 0 : (terms <= 64 ? 3 : 6);
-        a.start[k] = (unsigned)slots;
-        slots += (unsigned long)a.pw[k] << a.shift[k];
-    }
-    if (slots >= (1UL << 31)) return hipErrorInvalidValue;
-    a.start[N + 1] = (unsigned)slots;
-    a.slots = (long)align_up(slots, (size_t)1 << a.shift[1]);
+    a.slots = (long)adjoint_slots(D, N, a.start, a.shift);
     const long total = a.pieces * a.slots;
     long grid = (total + 255) / 256;
     if (grid > (1L << 20)) grid = 1L << 20;

@@ -103,6 +103,8 @@ constexpr double kSegmentBwd = 0.75, kSegmentMatrix = 0.35, kPieceWordBwd = 2.8e
 constexpr double kSegment = 0.2, kProduct = 4.0, kPieceLatency = 0.6, kPieceWord = 0.9e-5;
 constexpr int64_t kMatrixLong = 768, kMatrixPiece = 120, kMatrixPieceEntries = 100000;
 
+inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
+
 // LDS of a wave that holds PW paths (forward): their points in chunks, `stride` doubles per path (odd: the paths of a wave
 // then start in different banks), and in their place, if it fits, the finished signatures.  At most kSharedLds doubles and
 // the few past the end that the last point's missing channels are read from: five workgroups per compute unit.  Signatures
@@ -125,6 +127,27 @@ inline SharedLds shared_lds(int PW, int d, int L, int64_t sig_len)
     return s;
 }
 
+// Adjoints of the pieces: words of k letters sum over 1 + D + ... + D^(N - k) terms, with a wave, eight lanes or one lane per
+// word (shift[k] = 6, 3, 0, falling with k), slots start[k] .. start[k + 1] - 1.  Returns the slots of a piece, a multiple of the
+// largest group and fewer than 2^31: so many words have fewer lanes each.  (Signatures of fewer than 2^31 entries.)
+inline uint64_t adjoint_slots(int D, int N, unsigned (&start)[16], unsigned (&shift)[16])
+{
+    for (unsigned most = 6;; most -= 3) {
+        uint64_t slots = 0, words = 1, terms[16], t = 0, pw = 1;
+        for (int j = 0; j < N; ++j, pw *= (uint64_t)D) terms[N - j] = t += pw;
+        for (int k = 1; k <= N; ++k) {
+            const unsigned lanes = terms[k] <= 8 ? 0 : (terms[k] <= 64 ? 3 : 6);
+            shift[k] = lanes < most ? lanes : most;
+            start[k] = (unsigned)slots;
+            words *= (uint64_t)D;
+            slots += words << shift[k];
+        }
+        start[N + 1] = (unsigned)slots;
+        slots = align_up(slots, (size_t)1 << shift[1]);
+        if (slots < ((uint64_t)1 << 31) || most == 0) return slots;
+    }
+}
+
 // Backward, kernels for a channel count and a prefix length: whether a path's lanes are one wave's.
 constexpr bool lone_wave(int D, int S, int Q)
 {
@@ -133,8 +156,6 @@ constexpr bool lone_wave(int D, int S, int Q)
     for (int i = 0; i < Q; ++i) lanes *= D;
     return lanes <= kWave;
 }
-
-inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
 struct Plan {
     bool valid = false;
