@@ -72,9 +72,20 @@ def _keep_workspace(nbytes, device):
     return ws
 
 
-# Flags of the two forms in which a forward call leaves its sweeps for the backward call: forward and backward.
-_SWEEP = (sk.SK_FLAG_KEEP_FORWARD, sk.SK_FLAG_HAVE_FORWARD)
-_SWEEPS = (sk.SK_FLAG_KEEP_SWEEPS, sk.SK_FLAG_HAVE_SWEEPS)
+def _kept(ctx, x, y, lam1, lam2, flags, gram=False, symmetric=False):
+    """A workspace of this call's own if it wants gradients, the launch mode hands what it sweeps to the backward call (the grid
+    the paper's backward pass takes over from its forward pass, here as checkpoints), and that much may be kept; else None.
+    ctx.kept: the flags of that form, forward and backward."""
+    ctx.at = (x.data_ptr(), y.data_ptr())
+    if not any(ctx.needs_input_grad[:1 if symmetric else 2]):
+        return None
+    N, L1, d = x.shape
+    M, L2 = y.shape[:2]
+    try:
+        nbytes, *ctx.kept = _native.kept_form(gram, symmetric, N, M if gram else 0, L1, L2, d, lam1, lam2, flags, sk._dt(x))
+    except TypeError:       # (orders or flags that are no integers: the call itself says so)
+        return None
+    return _keep_workspace(nbytes, x.device) if nbytes else None
 
 
 def _take_workspace(ctx, x, y):
@@ -96,21 +107,9 @@ class _PairKernel(torch.autograd.Function):
         y = y.contiguous()
         ctx.save_for_backward(x, y)
         ctx.args = (lam1, lam2, flags)
-        ctx.at = (x.data_ptr(), y.data_ptr())
-        ctx.ws = None
-        # Where the launch mode can hand its forward sweep to the backward call, this call keeps it in a workspace of
-        # its own (the grid the paper's backward pass takes over from its forward pass, here as checkpoints).
-        B, L1, d = x.shape
-        if ctx.needs_input_grad[0] or ctx.needs_input_grad[1]:
-            shape = (B, L1, y.shape[1], d, lam1, lam2, flags, sk._dt(x))
-            ctx.kept = _SWEEPS if sk.keeps_sweeps(*shape) else (_SWEEP if sk.keeps_forward(*shape) else None)
-            if ctx.kept is not None:
-                # (room for either form)
-                need = max(sk.sigkernel_workspace_bytes(sk.SK_OP_FWD, B, 0, L1, y.shape[1], d, lam1, lam2, flags | form, sk._dt(x))
-                           for form in (ctx.kept[0], sk.SK_FLAG_KEEP_FORWARD))
-                ctx.ws = _keep_workspace(need, x.device)
-            if ctx.ws is not None:
-                return sk.sigkernel_fwd(x, y, lam1, lam2, flags | ctx.kept[0], ws=ctx.ws)
+        ctx.ws = _kept(ctx, x, y, lam1, lam2, flags)
+        if ctx.ws is not None:
+            return sk.sigkernel_fwd(x, y, lam1, lam2, flags | ctx.kept[0], ws=ctx.ws)
         return sk.sigkernel_fwd(x, y, lam1, lam2, flags)
 
     @staticmethod
@@ -129,29 +128,6 @@ class _PairKernel(torch.autograd.Function):
         return gx, gy, None, None, None
 
 
-def _gram_keep_workspace(ctx, X, Y, lam1, lam2, flags, symmetric=False):
-    """A workspace of this call's own if it wants gradients, the launch mode can keep the sweeps of a Gram matrix
-    for its backward call, and that much may be kept; else None."""
-    if not any(ctx.needs_input_grad[:2]):
-        return None
-    N, L1, d = X.shape
-    M, L2 = Y.shape[0], Y.shape[1]
-    if sk.keeps_sweeps(N, L1, L2, d, lam1, lam2, flags, sk._dt(X), gram_M=M):
-        ctx.kept = _SWEEPS
-        need = sk.sigkernel_workspace_bytes(sk.SK_OP_GRAM, N, M, L1, L2, d, lam1, lam2, flags | ctx.kept[0], sk._dt(X))
-        return _keep_workspace(need, X.device)
-    ctx.kept = _SWEEP
-    if not sk.keeps_forward(N, L1, L2, d, lam1, lam2, flags, sk._dt(X), gram_M=M):
-        return None
-    # (the backward sweep with four pairs per wavefront makes its own forward sweep, and is mostly faster than the kept form)
-    desc = sk.sigkernel_describe(sk.SK_OP_GRAM_BWD, N, M, L1, L2, d, lam1, lam2, flags, sk._dt(X))
-    if (" symmetric_over_kept_sweep=1" if symmetric else " over_kept_sweep=1") in desc:
-        return None
-    need = sk.sigkernel_workspace_bytes(sk.SK_OP_GRAM, N, M, L1, L2, d, lam1, lam2, flags | sk.SK_FLAG_KEEP_FORWARD,
-                                        sk._dt(X))
-    return _keep_workspace(need, X.device)
-
-
 class _GramKernel(torch.autograd.Function):
     @staticmethod
     def forward(ctx, X, Y, lam1, lam2, flags):
@@ -159,8 +135,7 @@ class _GramKernel(torch.autograd.Function):
         Y = Y.contiguous()
         ctx.save_for_backward(X, Y)
         ctx.args = (lam1, lam2, flags)
-        ctx.at = (X.data_ptr(), Y.data_ptr())
-        ctx.ws = _gram_keep_workspace(ctx, X, Y, lam1, lam2, flags)
+        ctx.ws = _kept(ctx, X, Y, lam1, lam2, flags, gram=True)
         if ctx.ws is not None:
             return sk.sigkernel_gram(X, Y, None, lam1, lam2, flags | ctx.kept[0], ws=ctx.ws)
         return sk.sigkernel_gram(X, Y, None, lam1, lam2, flags)
@@ -183,8 +158,7 @@ class _GramKernelSym(torch.autograd.Function):
         X = X.contiguous()
         ctx.save_for_backward(X)
         ctx.args = (lam1, lam2, flags)
-        ctx.at = (X.data_ptr(), X.data_ptr())
-        ctx.ws = _gram_keep_workspace(ctx, X, X, lam1, lam2, flags, symmetric=True)
+        ctx.ws = _kept(ctx, X, X, lam1, lam2, flags, gram=True, symmetric=True)
         if ctx.ws is not None:
             return sk.sigkernel_gram(X, X, None, lam1, lam2, flags | ctx.kept[0], ws=ctx.ws)
         return sk.sigkernel_gram(X, X, None, lam1, lam2, flags)

@@ -484,10 +484,20 @@ py::object signature(py::object xo, py::object No, py::object fl)
     return wrap(out);
 }
 
+// The rule for the classes: what a forward call of this shape keeps for its backward call, in bytes (0: nothing), and the flags
+// of that form, forward and backward.
+py::tuple kept_form(bool gram, bool symmetric, int64_t N, int64_t M, int64_t L1, int64_t L2, int64_t d, int lam1, int lam2, int flags,
+                    int dt)
+{
+    const Need n = kernel_need(gram, symmetric, N, M, L1, L2, d, lam1, lam2, flags, (sk_dtype)dt);
+    return py::make_tuple(n.kept, n.keep, n.have);
+}
+
 }  // namespace
 
 PYBIND11_MODULE(_native, m)
 {
+    m.def("kept_form", &kept_form);
     m.def("pair", &pair);
     m.def("gram", &gram);
     m.def("mmd2", &mmd2);

@@ -6,6 +6,7 @@ import numpy as np
 import pytest
 import torch
 
+from paper_2509_10613_amd import _native
 from paper_2509_10613_amd import autograd as ska
 from paper_2509_10613_amd import binding as sk
 
@@ -41,12 +42,32 @@ def test_no_room_for_a_workspace(small_limits):
     assert ska._keep_workspace(1 << 20, "cpu") is None and ska._large_held == {"cpu": 0}
 
 
+@pytest.mark.parametrize("gram,symmetric,N,M,L,d,lam,flags,dt,form", [
+    (False, False, 8, 0, 120, 3, 1, 0, sk.SK_F64, "sweeps"), (False, False, 64, 0, 101, 4, 0, 9, sk.SK_F32, "sweeps"),
+    (False, False, 300, 0, 70, 3, 1, 0, sk.SK_F64, "forward"), (False, False, 300, 0, 70, 3, 1, 0, sk.SK_F32, None),
+    (True, False, 5, 7, 30, 3, 1, 0, sk.SK_F64, "sweeps"), (True, True, 6, 6, 30, 3, 1, 0, sk.SK_F32, "sweeps"),
+    (True, False, 40, 40, 60, 3, 1, 8, sk.SK_F64, "forward"),
+    (True, False, 92, 92, 128, 3, 1, 0, sk.SK_F64, "forward"), (True, True, 92, 92, 64, 4, 0, 0, sk.SK_F64, None),    # four pairs a wave: none
+    (False, False, 0, 0, 30, 3, 1, 0, sk.SK_F64, None), (False, False, 8, 0, 1, 3, 1, 0, sk.SK_F64, None),
+])
+def test_what_forward_calls_keep(gram, symmetric, N, M, L, d, lam, flags, dt, form):
+    nbytes, *bits = _native.kept_form(gram, symmetric, N, M, L, L, d, lam, lam, flags, dt)
+    if form is None:
+        assert nbytes == 0
+        return
+    keep, have = {"sweeps": (sk.SK_FLAG_KEEP_SWEEPS, sk.SK_FLAG_HAVE_SWEEPS), "forward": (sk.SK_FLAG_KEEP_FORWARD, sk.SK_FLAG_HAVE_FORWARD)}[form]
+    assert bits == [keep, have]
+    assert nbytes == sk.sigkernel_workspace_bytes(sk.SK_OP_GRAM if gram else sk.SK_OP_FWD, N, M, L, L, d, lam, lam, flags | keep, dt) > 0
+    assert nbytes == sk.sigkernel_workspace_bytes(sk.SK_OP_GRAM_BWD if gram else sk.SK_OP_BWD, N, M, L, L, d, lam, lam, flags | have, dt)
+
+
 def _pairs(B=8, L=120, d=3):
     rng = np.random.default_rng(95)
     inc = rng.normal(0.0, (2.0 / (d * L)) ** 0.5, (2, B, L, d))
     x, y = (torch.tensor(np.cumsum(v, axis=1), device="cuda", requires_grad=True) for v in inc)
-    need = sk.sigkernel_workspace_bytes(sk.SK_OP_FWD, B, 0, L, L, d, 1, 1, sk.SK_FLAG_KEEP_FORWARD, sk.SK_F64)
-    assert sk.keeps_forward(B, L, L, d, 1, 1, 0, sk.SK_F64) and need > 1 << 16
+    need = sk.sigkernel_workspace_bytes(sk.SK_OP_FWD, B, 0, L, L, d, 1, 1, sk.SK_FLAG_KEEP_SWEEPS, sk.SK_F64)
+    assert sk.keeps_sweeps(B, L, L, d, 1, 1, 0, sk.SK_F64) and need > 1 << 16
+    assert _native.kept_form(False, False, B, 0, L, L, d, 1, 1, 0, sk.SK_F64) == (need, sk.SK_FLAG_KEEP_SWEEPS, sk.SK_FLAG_HAVE_SWEEPS)
     return x, y, need
 
 
@@ -101,3 +122,34 @@ def test_calls_go_on_where_a_workspace_does_not_fit(small_limits):
         finally:
             small_limits.setattr(torch, "empty", empty)
         assert _close(torch.autograd.grad(loss, w), ref)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("B,L,call", [(250, 256, lambda x, y: ska.sig_kernel(x, y, 1, 1)),
+                                      (15, 200, lambda x, y: ska.sig_kernel_gram(x, y, 1, 1, sk.SK_FLAG_LEAD_LAG)),
+                                      (48, 100, lambda x, y: ska.sig_kernel_gram(x + y, None, 1, 1))], ids=["pairs", "gram", "gram of one set"])
+def test_native_calls_go_on_where_a_workspace_does_not_fit(B, L, call):
+    # the allocator's own limit during the forward call: below what that call would keep, above what it needs
+    gc.collect()
+    sk._ws_cache.clear()
+    torch.cuda.empty_cache()
+    x, y, _ = _pairs(B, L, 3)
+    before = torch.cuda.memory_allocated()
+    k = call(x, y)
+    held = torch.cuda.memory_allocated() - before
+    assert held > 64 << 20
+    ref = torch.autograd.grad(k.sum(), (x, y))
+    del k
+    gc.collect()
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    print("kept %d, allocated %d, reserved %d" % (held, torch.cuda.memory_allocated(), torch.cuda.memory_reserved()), flush=True)
+    room = torch.cuda.memory_reserved() + held // 4 * 3
+    torch.cuda.set_per_process_memory_fraction(room / torch.cuda.get_device_properties(0).total_memory)
+    try:
+        before = torch.cuda.memory_allocated()
+        k = call(x, y)
+        assert k.grad_fn.name().startswith("SigKernel") and torch.cuda.memory_allocated() - before < 32 << 20
+    finally:
+        torch.cuda.set_per_process_memory_fraction(1.0)
+    assert _close(torch.autograd.grad(k.sum(), (x, y)), ref)
