@@ -158,7 +158,7 @@ class Part:
         """Pairs the last backward call handed to the replay kernel because the inverse recurrence drifted (the
         launch description says where in the workspace the call counts them): 0 means the timed path was the fast one."""
         import torch
-        if not self.bwd or "drifted_pairs_counter_at=" not in self.desc_bwd:
+        if not self.bwd or "drifted_pairs_counter_at=" not in self.desc_bwd or "drifted_pairs_counter_at=0 " in self.desc_bwd:
             return None
         at = int(self.desc_bwd.split("drifted_pairs_counter_at=", 1)[1].split()[0])
         torch.cuda.synchronize()
@@ -262,13 +262,15 @@ def make_case(name, io, args, sk, workloads, torch, dev):
         gx = torch.empty_like(x)
         gy = torch.empty_like(y)
         # A step is a forward call followed by a backward call on the same paths and workspace, so the forward call
-        # keeps its sweep for the backward call (launch modes without that form ignore the two flags).
-        keep = sk.SK_FLAG_KEEP_FORWARD if keep_ok else 0
+        # keeps its sweep for the backward call, or (few pairs) makes both sweeps and keeps them, as the autograd wrappers
+        # have it (launch modes without such a form ignore the flags).
+        both = keep_ok and not args.no_keep_sweeps and sk.keeps_sweeps(B, w.L, w.L, w.d, lam, lam, flags, sdt)
+        keep = (sk.SK_FLAG_KEEP_SWEEPS if both else sk.SK_FLAG_KEEP_FORWARD) if keep_ok else 0
         if keep and not args.keep_forward_any_size and sk.sigkernel_workspace_bytes(
                 sk.SK_OP_FWD, B, 0, w.L, w.L, w.d, lam, lam, flags | keep, sdt) > KEEP_LIMIT + sk.sigkernel_workspace_bytes(
                 sk.SK_OP_BWD, B, 0, w.L, w.L, w.d, lam, lam, flags, sdt):
             keep = 0
-        have = sk.SK_FLAG_HAVE_FORWARD if keep else 0
+        have = (sk.SK_FLAG_HAVE_SWEEPS if both else sk.SK_FLAG_HAVE_FORWARD) if keep else 0
         need = max(sk.sigkernel_workspace_bytes(sk.SK_OP_FWD, B, 0, w.L, w.L, w.d, lam, lam, flags | keep, sdt),
                    sk.sigkernel_workspace_bytes(sk.SK_OP_BWD, B, 0, w.L, w.L, w.d, lam, lam, flags, sdt))
         ws = torch.empty(need, dtype=torch.uint8, device=dev)
@@ -354,10 +356,13 @@ def run_case(case, args, sk, torch):
         rec = {"part": p.label, "pairs": p.pairs, "pairs_solved": p.pairs_solved,
                "fwd_kernel": kernel_name(p.desc_fwd), "fwd_kernel_ms": f_ms / max(nf, 1),
                "fwd_flops": cells_launch * algorithmic_flops_per_cell(d_eff, ta, w.lam, False)}
+        # (both sweeps in the forward call: the adjoint recurrence, 6 flops per cell, is its launch's)
+        moved = 6.0 * cells_launch if p.bwd and " kept_sweeps=2" in p.desc_fwd else 0.0
+        rec["fwd_flops"] += moved
         if p.bwd:
             rec.update({"pairs_solved_twice": p.pairs_solved_twice(),
                         "bwd_kernel": kernel_name(p.desc_bwd), "bwd_kernel_ms": b_ms / max(nb, 1),
-                        "bwd_flops": cells_launch * algorithmic_flops_per_cell(d_eff, ta, w.lam, True)})
+                        "bwd_flops": cells_launch * algorithmic_flops_per_cell(d_eff, ta, w.lam, True) - moved})
         launches.append(rec)
     # roofline of the dominant kernel (the backward sweep when there is one), over all its launches of a step:
     # algorithmic flops per launch (the average launch) / average launch duration
@@ -468,6 +473,9 @@ def main():
     ap.add_argument("--no-keep-forward", action="store_true",
                     help="the backward call sweeps forward again instead of taking over the sweep of the forward call "
                          "before it (SK_FLAG_KEEP_FORWARD / SK_FLAG_HAVE_FORWARD)")
+    ap.add_argument("--no-keep-sweeps", action="store_true",
+                    help="few pairs: the forward call keeps its own sweep alone, not the adjoint sweep beside it "
+                         "(SK_FLAG_KEEP_SWEEPS / SK_FLAG_HAVE_SWEEPS)")
     ap.add_argument("--keep-forward-any-size", action="store_true",
                     help="keep the forward sweep whatever workspace that takes (c3: 7 GB of checkpoints in the one-pair "
                          "kernels); by default only if it adds at most 1 GiB to the backward call's workspace")
