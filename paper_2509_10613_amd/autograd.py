@@ -16,6 +16,10 @@ library's flag takes t_i = i/(L-1)) is an ordinary channel: ``with_times(x, t)``
 
 The gradients are first-order only (the backward pass is not itself differentiable).
 
+A forward call on inputs that require gradients keeps what it sweeps for its backward call where the launch mode has such a
+form, and for few pairs also makes the adjoint sweep, beside its own.  It does so whether or not a backward call follows:
+evaluate under ``torch.no_grad()``.
+
 Each call goes to the same wrapper in native code first (csrc/sk_torch.cpp: the same library calls as nodes of PyTorch's
 graph; the classes below cost a short training pass 20 to 90 us of host time).  It leaves to the classes what is not the
 ordinary case: tracers and function transforms, forward gradients, kept workspaces above _KEEP_LIMIT, and everything that

@@ -298,7 +298,7 @@ constexpr int64_t kCoopMaxPairs = 1024;   // above this, one wave per pair alrea
 // (d channels, order in brackets):
 //   Gram 66 x 593, L = 124, 76, d = 19 (1), forward: 39185 and 4711;  31 x 917, L = 16, d = 19 (1), step: 24879 and 2976
 //   64 pairs, L = 889, 460, d = 19 (0), step: 74602 and 2411;  96 pairs, L = 38, 68, d = 17 (1), forward: 215 and 39
-//   Gram 59 x 106, L = 232, 164, d = 10 (0), step: 185727 and 9105 (y in memory);  1500 pairs, L = 300, 700, backward, y in
+//   Gram 59 x 106, L = 232, 164, d = 10 (0), step: 185727 and 7894 (y in memory);  1500 pairs, L = 300, 700, backward, y in
 //   memory, d = 5 (0) / (1): 49543 / 49937 and 7085 / 9599;  d = 8: 119663 / 121405 and 7265 / 9784
 //   backward with sixteen channels, cooperative, (0) / (1) / (2): 8 pairs, L = 150: 279 / 416 / 500 and 168 / 217 / 357; 64 pairs,
 //   L = 300: 586 / 959 / 1420 and 393 / 485 / 835; 300 pairs, L = 200, 250: 873 / 905 / 1531 and 575 / 785 / 1306

@@ -5,13 +5,14 @@
 // forward values from the checkpoint in front of it, keeping each macro-step's left edge and the edge from the lane above in
 // registers (the eight steps are unrolled), then walks the chunk back with the adjoint, which it carries from the checkpoint
 // behind the task.  x-side sums stay in registers, y-side sums in a window of LDS of the wave's own; the waves of a
-// workgroup take neighbouring tasks of one strip and add both up, in a fixed order, before they go to memory.  (Up to 64 chunks
-// a strip is one workgroup's, and two strips at most add to one place: such gradients are the same bits in every call.)
+// workgroup take neighbouring tasks of one strip and add both up, in a fixed order, before they go to memory.  (A strip of up to
+// 64 chunks is one workgroup's: the gradients of pairs of at most two such strips are the same bits in every call.  More strips or
+// workgroups, and the pairs of a Gram matrix, add in the order in which they arrive.)
 //
-// What bounds it: instruction issue, half of it the forward values (replayed once to keep the edges, formed once more block by
-// block); where a lane's state takes the whole register file, of a wave alone on its SIMD, whose LDS instructions nothing hides
-// (4 x 4 cells, eight channels: 1930 vector and 160 LDS instructions per chunk).  128 pairs of 256 points, d = 5, order 1: 54 us,
-// where the reverse sweep took 135; 32 pairs of 2048 points, d = 8, order 2: 2.0 ms for 3.65.
+// What bounds it: instruction issue of a wave alone on its SIMD, half of it the forward values (replayed once to keep the edges,
+// formed once more block by block), and its LDS instructions, which nothing hides.  Counters: 128 pairs of 256 points, d = 5, order
+// 1: 14100 vector and 1150 LDS instructions per wave, 8.0 clocks per vector instruction (4 to issue it), 54 us, where the
+// reverse sweep took 135; 32 pairs of 2048 points, d = 8, order 2: 15700 and 1230, 7.9 clocks, 2.0 ms for 3.65.
 #include <hip/hip_runtime.h>
 
 #include <type_traits>

@@ -1,5 +1,6 @@
 // Wide kernels (gfx950): any channel count, any number of strips.  For paths of more channels than the other kernels hold
-// in registers (above 16), and for nine to sixteen channels where a pair has more block rows than those kernels have lanes.
+// in registers (above 16), and backward, whatever the channel count, where the y increments and their sums do not fit in LDS
+// or the cooperative kernels would hold sixteen channels (wide_pays).
 //
 // The contraction over the channels is taken out of the sweeps altogether: the wave that owns a strip of 64 block rows
 // first writes p of Eq. (1) for every block of the strip into its scratch, formed on the matrix cores
@@ -10,10 +11,11 @@
 // division, no checkpoint and no second try; dF/dp replaces p in place, and the linear map of Section 3.4 is two more
 // contractions on the matrix cores.
 //
-// What bounds it: the scratch, (1 + 2^(BL+1) - 1) doubles per block written and read once or twice each, and instruction
-// issue in the sweeps.  What it replaces looped over the channels of every block in memory, with an atomic addition per
-// block, channel and side (measured, both sides: in front of wide_pays in sk_plan.h).  At 59 x 106 pairs of 231 x 163 cells the
-// kernel moves about 24 GB through its scratch in 7.9 ms.
+// What bounds it: the scratch, (1 + 2^(BL+1) - 1) doubles per block written and read once or twice each.  Counters, backward, 59 x
+// 106 pairs of 231 x 163 cells, d = 10: 25.4 GB in 6.8 ms, 3.7 TB/s where a copy reads and writes 4.6; vector instructions take a
+// tenth of the issue slots.  Forward, 66 x 593 pairs, d = 19, order 1: 14.0 GB in 4.85 ms.  What it replaces looped over the
+// channels of every block in memory, with an atomic addition per block, channel and side (measured, both sides: in front of
+// wide_pays in sk_plan.h).
 //
 // Strips: strip s + 1 follows strip s at a fixed lag of macro-steps, one strip per wave, nw of them in a workgroup that
 // advances in chunks separated by barriers; strips beyond that take further rounds.  With enough pairs to fill the chip a
