@@ -41,8 +41,11 @@ from . import _native  # noqa: E402  (needs the library, and raises if it has no
 # workspace is given back by the first backward call.  Training steps without and with it: 32 pairs of 2048 points, order 2
 # (1.6 GiB) 6.54 and 5.20 ms; lead-lag Grams of 128 x 128 paths of 101 points, d = 4 (1.5 GiB) 1.77 and 1.61 ms, K(X, X) of the
 # same 0.99 and 0.92 ms.
+# Smaller ones of the native calls come to at most _KEEP_ALL together, an eighth of a device's memory: a program that holds
+# thousands of graphs before it calls backward would otherwise run out of memory for workspaces it can do without.
 _KEEP_LIMIT = 1 << 30
 _KEEP_LARGE = 1 << 32
+_KEEP_ALL = 36 << 30
 
 _large_lock = threading.RLock()   # (taken again if a tensor is collected while it is held)
 _large_held = {}                  # device: bytes of the live workspaces above _KEEP_LIMIT
@@ -243,7 +246,7 @@ def sig_kernel(x, y, lam1=0, lam2=0, flags=0, times_x=None, times_y=None):
         raise ValueError("give time grids for both sides or for neither")
     if times_x is not None:
         x, y = with_times(x, times_x), with_times(y, times_y)
-    out = _native.pair(x, y, lam1, lam2, flags, _KEEP_LIMIT)
+    out = _native.pair(x, y, lam1, lam2, flags, _KEEP_LIMIT, _KEEP_ALL)
     return _PairKernel.apply(x, y, lam1, lam2, flags) if out is None else out
 
 
@@ -258,7 +261,7 @@ def sig_kernel_gram(X, Y=None, lam1=0, lam2=0, flags=0, times_x=None, times_y=No
             Y = with_times(Y, times_y)
     elif times_y is not None:
         raise ValueError("give time grids for both sides or for neither")
-    out = _native.gram(X, Y, lam1, lam2, flags, _KEEP_LIMIT)
+    out = _native.gram(X, Y, lam1, lam2, flags, _KEEP_LIMIT, _KEEP_ALL)
     if out is not None:
         return out
     if Y is None:

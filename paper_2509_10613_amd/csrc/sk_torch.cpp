@@ -23,7 +23,9 @@
 #include <torch/csrc/utils/pybind.h>
 
 #include <array>
+#include <atomic>
 #include <cstring>
+#include <limits>
 #include <memory>
 #include <mutex>
 #include <string>
@@ -134,6 +136,44 @@ void expect(const Tensor& t, const char* name, at::IntArrayRef sizes, const at::
                       name, " is not what the forward call had: ", t.sizes(), " ", t.scalar_type(), " on ", t.device());
 }
 
+// Bytes of kept sweeps that the live graphs hold on a device: a share of it, given back with the graph.
+class Share {
+public:
+    // false: all shares would come to more than `most`
+    bool take(const Tensor& like, size_t bytes, size_t most)
+    {
+        static std::array<std::atomic<int64_t>, 64> held;
+        auto& all = held[(size_t)like.device().index() % held.size()];
+        if (all.fetch_add((int64_t)bytes) + (int64_t)bytes > (int64_t)most) {
+            all.fetch_sub((int64_t)bytes);
+            return false;
+        }
+        all_ = &all;
+        bytes_ = (int64_t)bytes;
+        return true;
+    }
+    void give_back()
+    {
+        if (all_) all_->fetch_sub(bytes_);
+        all_ = nullptr;
+    }
+    Share() = default;
+    Share(Share&& o) noexcept : all_(o.all_), bytes_(o.bytes_) { o.all_ = nullptr; }
+    Share& operator=(Share&& o) noexcept
+    {
+        give_back();
+        all_ = o.all_;
+        bytes_ = o.bytes_;
+        o.all_ = nullptr;
+        return *this;
+    }
+    ~Share() { give_back(); }
+
+private:
+    std::atomic<int64_t>* all_ = nullptr;
+    int64_t bytes_ = 0;
+};
+
 // (Threads may run backward calls through one node: what it holds is read and released under the node's lock.)
 using Lock = std::lock_guard<std::mutex>;
 
@@ -143,6 +183,7 @@ struct KernelNode : public Node {
     int lam1 = 0, lam2 = 0, flags = 0, have = 0;
     size_t need = 0;
     Tensor ws;                       // the kept sweeps
+    Share share;                     // ... and what of all kept sweeps they are
     const void *x_at = nullptr, *y_at = nullptr;   // the paths they belong to
     std::vector<int64_t> x_sizes, y_sizes, out_sizes;
     at::TensorOptions options;
@@ -154,6 +195,7 @@ struct KernelNode : public Node {
         x_.reset_data();
         y_.reset_data();
         ws.reset();
+        share.give_back();
     }
     variable_list apply(variable_list&& grads) override
     {
@@ -290,13 +332,15 @@ bool number(const py::object& o, int& v)
 bool flag_bits(const py::object& o, int& v) { return number(o, v) && (v & (SK_FLAG_KEEP_FORWARD | SK_FLAG_HAVE_FORWARD | SK_FLAG_KEEP_SWEEPS | SK_FLAG_HAVE_SWEEPS)) == 0; }
 
 // ---------------------------------------------------------------- the calls
-Tensor kernel_call(const Tensor& x0, const Tensor& y0, bool gram, bool symmetric, int lam1, int lam2, int flags, size_t keep_limit)
+Tensor kernel_call(const Tensor& x0, const Tensor& y0, bool gram, bool symmetric, int lam1, int lam2, int flags, size_t keep_limit,
+                   size_t keep_all)
 {
     const bool grad = at::GradMode::is_enabled() && (x0.requires_grad() || y0.requires_grad());
     Tensor x, y, k, ws;
     size_t need_bwd;
     int have = 0;
     bool kept = false;
+    Share share;
     {
         at::NoGradGuard no_grad;
         x = x0.contiguous();
@@ -309,11 +353,12 @@ Tensor kernel_call(const Tensor& x0, const Tensor& y0, bool gram, bool symmetric
         if (grad && need.kept > keep_limit) return {};
         need_bwd = need.backward;
         have = need.have;
-        if (grad && need.kept != 0) {
+        if (grad && need.kept != 0 && share.take(x, need.kept, keep_all)) {
             try {
                 ws = bytes(need.kept, x);
                 kept = true;
             } catch (const c10::OutOfMemoryError&) {   // the calls go on without one
+                share.give_back();
             }
         }
         if (!kept)
@@ -348,7 +393,10 @@ Tensor kernel_call(const Tensor& x0, const Tensor& y0, bool gram, bool symmetric
         node->flags = flags;
         node->have = have;
         node->need = need_bwd;
-        if (kept) node->ws = ws;
+        if (kept) {
+            node->ws = ws;
+            node->share = std::move(share);
+        }
         node->x_at = x.data_ptr();
         node->y_at = y.data_ptr();
         node->x_sizes = x.sizes().vec();
@@ -366,7 +414,7 @@ py::object wrap(const Tensor& t)
     return py::reinterpret_steal<py::object>(THPVariable_Wrap(t));
 }
 
-py::object pair(py::object xo, py::object yo, py::object l1, py::object l2, py::object fl, size_t keep_limit)
+py::object pair(py::object xo, py::object yo, py::object l1, py::object l2, py::object fl, size_t keep_limit, size_t keep_all)
 {
     Tensor x, y, k;
     int lam1, lam2, flags;
@@ -375,13 +423,13 @@ py::object pair(py::object xo, py::object yo, py::object l1, py::object l2, py::
         return py::none();
     {
         py::gil_scoped_release release;
-        k = kernel_call(x, y, false, false, lam1, lam2, flags, keep_limit);
+        k = kernel_call(x, y, false, false, lam1, lam2, flags, keep_limit, keep_all);
     }
     return wrap(k);
 }
 
 // Y None: K(X, X)
-py::object gram(py::object xo, py::object yo, py::object l1, py::object l2, py::object fl, size_t keep_limit)
+py::object gram(py::object xo, py::object yo, py::object l1, py::object l2, py::object fl, size_t keep_limit, size_t keep_all)
 {
     Tensor x, y, k;
     int lam1, lam2, flags;
@@ -394,7 +442,7 @@ py::object gram(py::object xo, py::object yo, py::object l1, py::object l2, py::
     if (!symmetric && x.data_ptr() == y.data_ptr()) return py::none();
     {
         py::gil_scoped_release release;
-        k = kernel_call(x, y, true, symmetric, lam1, lam2, flags, keep_limit);
+        k = kernel_call(x, y, true, symmetric, lam1, lam2, flags, keep_limit, keep_all);
     }
     return wrap(k);
 }
@@ -498,8 +546,10 @@ py::tuple kept_form(bool gram, bool symmetric, int64_t N, int64_t M, int64_t L1,
 PYBIND11_MODULE(_native, m)
 {
     m.def("kept_form", &kept_form);
-    m.def("pair", &pair);
-    m.def("gram", &gram);
+    // keep_limit: bytes that one call may keep (more is the classes' business); keep_all: that all live graphs may, on a device
+    const auto all = py::arg("keep_all") = std::numeric_limits<int64_t>::max();
+    m.def("pair", &pair, py::arg("x"), py::arg("y"), py::arg("lam1"), py::arg("lam2"), py::arg("flags"), py::arg("keep_limit"), all);
+    m.def("gram", &gram, py::arg("x"), py::arg("y"), py::arg("lam1"), py::arg("lam2"), py::arg("flags"), py::arg("keep_limit"), all);
     m.def("mmd2", &mmd2);
     m.def("signature", &signature);
 }

@@ -153,3 +153,30 @@ def test_native_calls_go_on_where_a_workspace_does_not_fit(B, L, call):
     finally:
         torch.cuda.set_per_process_memory_fraction(1.0)
     assert _close(torch.autograd.grad(k.sum(), (x, y)), ref)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("call", [lambda x, y: ska.sig_kernel(x, y, 1, 1), lambda x, y: ska.sig_kernel_gram(x, y, 1, 1)], ids=["pairs", "gram"])
+def test_small_workspaces_of_all_live_graphs_have_a_bound_too(monkeypatch, call):
+    gc.collect()
+    x, y, _ = _pairs(12, 100, 3)
+    ref = torch.autograd.grad(call(x, y).sum(), (x, y))
+
+    def held(n):
+        torch.cuda.synchronize()
+        before = torch.cuda.memory_allocated()
+        ks = [call(x, y) for _ in range(n)]
+        return ks, (torch.cuda.memory_allocated() - before)
+    ks, one = held(1)
+    assert one > 1 << 20
+    del ks
+    monkeypatch.setattr(ska, "_KEEP_ALL", 3 * one)
+    for _ in range(2):                            # what a graph held is given back with it
+        ks, all_of_them = held(9)
+        assert 2 * one <= all_of_them <= 3 * one + (1 << 16)
+        for k in ks:
+            assert _close(torch.autograd.grad(k.sum(), (x, y), retain_graph=True), ref)
+        torch.autograd.grad(ks[0].sum(), (x, y))  # ... or with the backward call that uses it up
+        more, rest = held(2)
+        assert one // 2 <= rest <= one + (1 << 16)
+        del ks, more, k
