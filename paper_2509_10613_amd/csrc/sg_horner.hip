@@ -224,6 +224,8 @@ __device__ __forceinline__ void run_shared(const Args& a, double* lds)
     const int shift = __builtin_ctz((unsigned)a.P);
     const long first = ((b0 + g) & (a.P - 1)) * step;           // first segment of this lane's piece
     const long mine = min(step, max(0L, a.total / per - first));// its segments
+    // ... and those that every piece of the wave has: the last pieces of a path may have fewer
+    const long least = max(0L, min(step, a.total / per - min((long)a.P - 1, (b0 & (a.P - 1)) + here - 1) * step));
     // number e of the chunk of path gg, 64 apart: q paths and `rem` numbers on; between the chunks of two whole paths lie
     // `skip` numbers of x
     auto stage = [&](auto* x, long c0, int count) {
@@ -329,36 +331,43 @@ __device__ __forceinline__ void run_shared(const Args& a, double* lds)
             j = 1;
             read(count > 1 ? 1 : 0);
         }
-#pragma unroll 2
-        for (; j < count; ++j) {
-            double dl[NW], dp[DD];
+        // (segments past a piece's end do not move: by a difference of equal points they would where those are infinite)
+        auto segments = [&](auto all, int end) {
+            constexpr bool ALL = decltype(all)::value;
+#pragma unroll(ALL ? 2 : 1)
+            for (; j < end; ++j) {
+                const bool inside = ALL || c0 + j <= mine;
+                double dl[NW], dp[DD];
 #pragma unroll
-            for (int i = 0; i < NW; ++i) {
-                dl[i] = curL[i] - prevL[i];
-                prevL[i] = curL[i];
-            }
-#pragma unroll
-            for (int c = 0; c < DD; ++c) {
-                dp[c] = kStatic ? cur[c] - prev[c] : 0.0;
-                prev[c] = kStatic ? cur[c] : 0.0;
-            }
-            read(j + 1 < count ? j + 1 : j);
-            const double t = c0 + j <= mine ? tick : 0.0;
-            if constexpr (LEADLAG) {
-                row(std::integral_constant<int, 1>(), 1, dl, dp, t);
-                row(std::integral_constant<int, 2>(), 2, dl, dp, t);
-            } else {
-                bool both = true;
-                if constexpr (DT < 4) {
-                    if (a.leadlag) {
-                        row(std::integral_constant<int, 0>(), 1, dl, dp, t);
-                        row(std::integral_constant<int, 0>(), 2, dl, dp, t);
-                        both = false;
-                    }
+                for (int i = 0; i < NW; ++i) {
+                    dl[i] = inside ? curL[i] - prevL[i] : 0.0;
+                    prevL[i] = curL[i];
                 }
-                if (both) row(std::integral_constant<int, 0>(), 0, dl, dp, t);
+#pragma unroll
+                for (int c = 0; c < DD; ++c) {
+                    dp[c] = kStatic && inside ? cur[c] - prev[c] : 0.0;
+                    prev[c] = kStatic ? cur[c] : 0.0;
+                }
+                read(j + 1 < count ? j + 1 : j);
+                const double t = inside ? tick : 0.0;
+                if constexpr (LEADLAG) {
+                    row(std::integral_constant<int, 1>(), 1, dl, dp, t);
+                    row(std::integral_constant<int, 2>(), 2, dl, dp, t);
+                } else {
+                    bool both = true;
+                    if constexpr (DT < 4) {
+                        if (a.leadlag) {
+                            row(std::integral_constant<int, 0>(), 1, dl, dp, t);
+                            row(std::integral_constant<int, 0>(), 2, dl, dp, t);
+                            both = false;
+                        }
+                    }
+                    if (both) row(std::integral_constant<int, 0>(), 0, dl, dp, t);
+                }
             }
-        }
+        };
+        segments(std::true_type(), (int)min((long)count, least - c0 + 1));
+        segments(std::false_type(), count);
     }
 
     const long lenS = a.sig_len, base = b0 * lenS;

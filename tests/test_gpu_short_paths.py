@@ -49,3 +49,21 @@ def test_several_paths_per_wave(B, L, d, N, flags, dtype):
         bound = bound + 2.0 ** -24 * np.abs(got) * (1 + 2.0 ** -20) + 2.0 ** -150
     assert np.all(np.abs(got[some] - ref) <= 2 * bound[some])       # (the oracle's own roundings)
     assert np.all(np.abs(got - one) <= 2 * bound)
+
+
+# (a piece of ten segments in eight has at most two, and the last ones none)
+@pytest.mark.parametrize("P,flags", [(0, 0), (1, T), (3, 0), (3, T), (3, LL), (4, LL | T)])
+@pytest.mark.parametrize("d,N", [(2, 2), (3, 1), (5, 2), (20, 1)])
+def test_a_path_that_ends_in_infinity_has_moved_that_far(P, flags, d, N):
+    # level 1 is where a path ends less where it starts; pieces that reach past the end don't move there
+    rng = np.random.default_rng(P + d)
+    x = np.cumsum(rng.normal(0, 0.3, size=(4, 11, d)), axis=1)
+    x[1, -1, 0], x[2, -1, d - 1] = np.inf, -np.inf
+    f = flags | sk.SK_SIG_PIECES(P)
+    desc = sk.signature_describe(4, 11, d, N, f, sk.SK_F64)
+    print(desc, flush=True)
+    assert "pieces_per_path=%d " % 2 ** P in desc and (d >= 5 and flags & LL or ", true, " in desc and "paths_per_wave=1 " not in desc)
+    got = sk.signature_fwd(torch.tensor(x).cuda(), N, f).cpu().numpy()
+    move = x[:, -1] - x[:, 0]
+    move = np.concatenate([move] + [move] * bool(flags & LL) + [np.ones((4, 1))] * bool(flags & T), axis=1)
+    assert np.allclose(got[:, 1:1 + move.shape[1]], move, rtol=0, atol=1e-12) and np.isfinite(got[[0, 3]]).all()
