@@ -13,6 +13,7 @@
 #include <c10/core/impl/LocalDispatchKeySet.h>
 #include <c10/hip/HIPStream.h>
 #include <torch/csrc/Exceptions.h>
+#include <torch/csrc/autograd/custom_function.h>
 #include <torch/csrc/autograd/edge.h>
 #include <torch/csrc/autograd/function.h>
 #include <torch/csrc/autograd/functions/utils.h>
@@ -238,29 +239,29 @@ struct KernelNode : public Node {
     }
 };
 
-struct MmdNode : public Node {
-    SavedVariable gx_, gy_;
-    bool have_x = false, have_y = false;
-    std::string name() const override { return "SigMmd2Backward"; }
-    void release_variables() override
+// The gradients are the forward call's, and the backward call is tensor arithmetic: a function of PyTorch's own kind, whose
+// nodes compiled autograd takes as well.
+struct MmdParts {
+    Tensor loss, gx, gy;   // gx, gy: undefined where not wanted
+};
+struct SigMmd2 : public torch::autograd::Function<SigMmd2> {
+    static Tensor forward(torch::autograd::AutogradContext* ctx, const Tensor&, const Tensor&, const MmdParts& parts)
     {
-        const Lock lock(mutex_);
-        gx_.reset_data();
-        gy_.reset_data();
+        variable_list grads;
+        for (const Tensor& g : {parts.gx, parts.gy})
+            if (g.defined()) grads.push_back(g);
+        ctx->save_for_backward(grads);
+        ctx->saved_data["have_x"] = parts.gx.defined();
+        ctx->saved_data["have_y"] = parts.gy.defined();
+        return parts.loss;
     }
-    variable_list apply(variable_list&& grads) override
+    static variable_list backward(torch::autograd::AutogradContext* ctx, const variable_list& grads)
     {
-        variable_list out(2);
-        Tensor gx, gy;
-        {
-            const Lock lock(mutex_);
-            if (have_x) gx = gx_.unpack();
-            if (have_y) gy = gy_.unpack();
-        }
-        const Tensor& some = have_x ? gx : gy;
-        const Tensor g = grads[0].defined() ? grads[0] : at::zeros({}, some.options());
-        if (have_x) out[0] = gx * g;
-        if (have_y) out[1] = gy * g;
+        variable_list out(3);
+        const variable_list saved = ctx->get_saved_variables();
+        const bool have_x = ctx->saved_data["have_x"].toBool(), have_y = ctx->saved_data["have_y"].toBool();
+        if (have_x) out[0] = saved[0] * grads[0];
+        if (have_y) out[1] = saved[have_x ? 1 : 0] * grads[0];
         return out;
     }
 };
@@ -478,15 +479,7 @@ py::object mmd2(py::object xo, py::object yo, py::object l1, py::object l2, py::
                                ws.data_ptr(), (size_t)ws.numel(), current_stream()) != SK_OK)
                 loss.reset();
         }
-        if (loss.defined() && (want_x || want_y)) {
-            auto node = make_node<MmdNode>();
-            node->set_next_edges(torch::autograd::collect_next_edges(x0, y0));
-            if (want_x) node->gx_ = SavedVariable(gx, false);
-            if (want_y) node->gy_ = SavedVariable(gy, false);
-            node->have_x = want_x;
-            node->have_y = want_y;
-            torch::autograd::set_history(loss, node);
-        }
+        if (loss.defined() && (want_x || want_y)) loss = SigMmd2::apply(x0, y0, MmdParts{loss, gx, gy});
     }
     return wrap(loss);
 }

@@ -135,3 +135,20 @@ def test_threads_that_run_backward_through_one_graph(call):
         assert len(got) == 4 and (len(done) == 4 if keep else len(done) >= 1)
         assert all("second time" in g for g in got if isinstance(g, str))
         assert all(float((g - ref).abs().max()) <= 1e-12 * float(ref.abs().max()) for g in done)
+
+
+@pytest.mark.parametrize("wanted", ["both", "x", "y"])
+def test_compiled_autograd_takes_the_mmd_backward(wanted):
+    # tensor arithmetic alone, which it has always traced (the others call the library, and are refused)
+    from torch._dynamo import compiled_autograd
+    x, y = paths(9, 6, 20, 3), paths(10, 5, 24, 3)
+    leaves = [t.requires_grad_() for t, n in ((x, "x"), (y, "y")) if wanted in ("both", n)]
+    ref = torch.autograd.grad(ska.sig_mmd2(x, y, 1, 1) * 3.0, leaves)
+    for _ in range(2):
+        loss = ska.sig_mmd2(x, y, 1, 1) * 3.0
+        for t in leaves:
+            t.grad = None
+        with compiled_autograd._enable(torch.compile(backend="eager")):
+            loss.backward()
+        for t, r in zip(leaves, ref):
+            assert float((t.grad - r).abs().max()) <= 1e-12 * float(r.abs().max())
