@@ -18,7 +18,7 @@ The gradients are first-order only (the backward pass is not itself differentiab
 
 A forward call on inputs that require gradients keeps what it sweeps for its backward call where the launch mode has such a
 form, and for few pairs also makes the adjoint sweep, beside its own.  It does so whether or not a backward call follows:
-evaluate under ``torch.no_grad()``.
+evaluate under ``torch.no_grad()``.  Under saved-tensor hooks (checkpoints, ``save_on_cpu``) it keeps nothing.
 
 Each call goes to the same wrapper in native code first (csrc/sk_torch.cpp: the same library calls as nodes of PyTorch's
 graph; the classes below cost a short training pass 20 to 90 us of host time).  It leaves to the classes what is not the
@@ -84,7 +84,8 @@ def _kept(ctx, x, y, lam1, lam2, flags, gram=False, symmetric=False):
     the paper's backward pass takes over from its forward pass, here as checkpoints), and that much may be kept; else None.
     ctx.kept: the flags of that form, forward and backward."""
     ctx.at = (x.data_ptr(), y.data_ptr())
-    if not any(ctx.needs_input_grad[:1 if symmetric else 2]):
+    # (through saved-tensor hooks, checkpoints among them, the backward call may get other paths)
+    if not any(ctx.needs_input_grad[:1 if symmetric else 2]) or _native.saving_through_hooks():
         return None
     N, L1, d = x.shape
     M, L2 = y.shape[:2]
@@ -97,8 +98,8 @@ def _kept(ctx, x, y, lam1, lam2, flags, gram=False, symmetric=False):
 
 def _take_workspace(ctx, x, y):
     """The workspace the forward call kept, or None.  A large one is taken out of the graph: a further backward call through
-    it sweeps forward itself.  A call whose saved paths lie elsewhere than the forward call's (saved-tensor hooks and recomputed
-    checkpoints give equal tensors back) goes without: the library would take the sweeps for another call's."""
+    it sweeps forward itself.  A call whose saved paths lie elsewhere than the forward call's (their data have been set) goes
+    without: the library would take the sweeps for another call's."""
     ws = ctx.ws
     if ws is None:
         return None

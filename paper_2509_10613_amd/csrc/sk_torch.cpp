@@ -10,6 +10,7 @@
 // floating type and consistent shapes and int arguments, calls under a tracer or a function transform, kept workspaces
 // above the given limit (their accounting lives there), and whatever the library refuses (the classes then raise).
 #include <ATen/ATen.h>
+#include <ATen/SavedTensorHooks.h>
 #include <c10/core/impl/LocalDispatchKeySet.h>
 #include <c10/hip/HIPStream.h>
 #include <torch/csrc/Exceptions.h>
@@ -213,8 +214,7 @@ struct KernelNode : public Node {
         expect(x, "x", x_sizes, options);
         if (!symmetric) expect(y, "y", y_sizes, options);
         expect(g, "the upstream gradient", out_sizes, options);
-        // (saved-tensor hooks and recomputed checkpoints give equal paths back at other addresses, which the library takes for
-        // another call's)
+        // (paths whose data have been set elsewhere are another call's to the library)
         const bool kept = held.defined() && x.data_ptr() == x_at && y.data_ptr() == y_at;
         const int f = flags | (kept ? have : 0);
         const sk_dtype dt = dtype_of(x);
@@ -332,6 +332,10 @@ bool number(const py::object& o, int& v)
 // flags of the wrappers (those that keep a forward sweep or take one over are theirs to set)
 bool flag_bits(const py::object& o, int& v) { return number(o, v) && (v & (SK_FLAG_KEEP_FORWARD | SK_FLAG_HAVE_FORWARD | SK_FLAG_KEEP_SWEEPS | SK_FLAG_HAVE_SWEEPS)) == 0; }
 
+// Whether what a call saves goes through hooks.  Its backward call may then get anything back, recomputed or rounded, at any
+// address, and what the forward call would keep would mostly lie there unused: a checkpointed segment is run again.
+bool saving_through_hooks() { return at::SavedTensorDefaultHooks::get_hooks().has_value(); }
+
 // ---------------------------------------------------------------- the calls
 Tensor kernel_call(const Tensor& x0, const Tensor& y0, bool gram, bool symmetric, int lam1, int lam2, int flags, size_t keep_limit,
                    size_t keep_all)
@@ -351,10 +355,11 @@ Tensor kernel_call(const Tensor& x0, const Tensor& y0, bool gram, bool symmetric
         const ShapeKey key{{(int64_t)gram | (int64_t)symmetric << 1 | (int64_t)dt << 2, N, M, L1, L2, d, (int64_t)lam1 << 32 | (uint32_t)lam2,
                             flags}};
         const Need need = need_of(key, [&] { return kernel_need(gram, symmetric, N, gram ? M : 0, L1, L2, d, lam1, lam2, flags, dt); });
-        if (grad && need.kept > keep_limit) return {};
+        const bool keep = grad && need.kept != 0 && !saving_through_hooks();
+        if (keep && need.kept > keep_limit) return {};
         need_bwd = need.backward;
         have = need.have;
-        if (grad && need.kept != 0 && share.take(x, need.kept, keep_all)) {
+        if (keep && share.take(x, need.kept, keep_all)) {
             try {
                 ws = bytes(need.kept, x);
                 kept = true;
@@ -539,6 +544,7 @@ py::tuple kept_form(bool gram, bool symmetric, int64_t N, int64_t M, int64_t L1,
 PYBIND11_MODULE(_native, m)
 {
     m.def("kept_form", &kept_form);
+    m.def("saving_through_hooks", &saving_through_hooks);
     // keep_limit: bytes that one call may keep (more is the classes' business); keep_all: that all live graphs may, on a device
     const auto all = py::arg("keep_all") = std::numeric_limits<int64_t>::max();
     m.def("pair", &pair, py::arg("x"), py::arg("y"), py::arg("lam1"), py::arg("lam2"), py::arg("flags"), py::arg("keep_limit"), all);

@@ -1,5 +1,6 @@
 """Backward calls whose saved inputs come back from elsewhere: autograd may hand a backward call equal tensors at other addresses
-(saved-tensor hooks that copy, recomputed checkpoints), and the sweeps a forward call has kept are then not taken over."""
+(saved-tensor hooks that copy, recomputed checkpoints, data that have been set) or other tensors, and no sweeps of the forward
+call are then taken over."""
 import pytest
 import torch
 from torch.utils.checkpoint import checkpoint
@@ -52,7 +53,7 @@ def _copying():
     return torch.autograd.graph.saved_tensors_hooks(lambda t: HELD.append(t) or t, lambda t: t.clone())
 
 
-@pytest.mark.parametrize("way", ["copies", "host", "checkpoint"])
+@pytest.mark.parametrize("way", ["copies", "host", "checkpoint", "set"])
 @pytest.mark.parametrize("native", [True, False], ids=["native", "classes"])
 @pytest.mark.parametrize("dtype", [torch.float64, torch.float32])
 @pytest.mark.parametrize("name", list(CALLS))
@@ -62,15 +63,24 @@ def test_gradients_do_not_depend_on_where_saved_inputs_lie(name, dtype, native, 
     x, y = paths(11, n, L, 3, dtype).requires_grad_(), paths(12, m, L - 4, 3, dtype).requires_grad_()
     wanted = (x,) if name == "gram of one set" else (x, y)
 
+    saved = []
+
     def loss(a, b):
-        k = call(a * 1.0, b * 1.0, lam, flags)          # (the saved inputs are the products)
+        saved[:] = a * 1.0, b * 1.0                     # (the saved inputs are the products)
+        k = call(*saved, lam, flags)
         return (k * torch.linspace(0.5, 1.5, k.numel(), device="cuda", dtype=dtype).reshape(k.shape)).sum()
     ref = torch.autograd.grad(loss(x, y), wanted)
     if way == "checkpoint":
         out = checkpoint(loss, x, y, use_reentrant=False)
+    elif way == "set":
+        out = loss(x, y)
+        for t in saved:
+            HELD.append(t.data)
+            t.data = t.data.clone()
     else:
         with _copying() if way == "copies" else torch.autograd.graph.save_on_cpu():
             out = loss(x, y)
+    saved.clear()
     block = [torch.full_like(t, 9.0) for t in (x, x, y, y)]     # (memory that the saved inputs may have lain in)
     for again in (True, False):
         got = torch.autograd.grad(out, wanted, retain_graph=again and way != "checkpoint")
@@ -81,6 +91,29 @@ def test_gradients_do_not_depend_on_where_saved_inputs_lie(name, dtype, native, 
             break
     HELD.clear()
     del block
+
+
+@pytest.mark.parametrize("native", [True, False], ids=["native", "classes"])
+@pytest.mark.parametrize("dtype", [torch.float64, torch.float32])
+@pytest.mark.parametrize("name", list(CALLS))
+def test_hooks_may_give_back_other_paths(name, dtype, native):
+    # half of what was saved, in the same memory: gradients are those at the paths that came back, and no workspace is held for them
+    wrapper, n, m, L, lam, flags = CALLS[name]
+    call = wrapper if native else CLASSES[wrapper]
+    x, y = paths(11, n, L, 3, dtype).requires_grad_(), paths(12, m, L - 4, 3, dtype).requires_grad_()
+    wanted = (x,) if name == "gram of one set" else (x, y)
+    halves = [(t.detach() * 0.5).requires_grad_() for t in (x, y)]
+    ref = torch.autograd.grad(call(*halves, lam, flags).sum(), halves[:len(wanted)])
+    call(x.detach(), y.detach(), lam, flags)
+    saved = x * 1.0, y * 1.0
+    before = torch.cuda.memory_allocated()
+    with torch.autograd.graph.saved_tensors_hooks(lambda t: t.detach(), lambda t: t.mul_(0.5)):
+        k = call(*saved, lam, flags)
+    assert torch.cuda.memory_allocated() - before <= k.numel() * k.element_size() + 1024
+    got = torch.autograd.grad(k.sum(), wanted)
+    tol = 1e-12 if dtype == torch.float64 else 1e-5
+    for g, r in zip(got, ref):
+        assert float((g - r).abs().max()) <= tol * max(1.0, float(r.abs().max()))
 
 
 # what a hook may give back that is no place for a kernel to read the forward call's numbers from
